@@ -19,6 +19,22 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// One 64-byte step of the contraction: 16 rows of A against 16 rows of B, 16 bytes of each per lane
+// (lane l: row l%16, piece l/16).  16-bit types: one 16x16x32 instruction.  fp32: four 16x16x4 ones; the
+// order in which they take the channels is the same for both operands, which is all a sum needs.
+enum { DT_BF16 = 0, DT_F16 = 1, DT_F32 = 2 };
+template <int DT>
+__device__ __forceinline__ f32x4 mfma_64b(bf16x8 a, bf16x8 b, f32x4 c) {
+  if constexpr (DT == DT_F32) {
+    const f32x4 av = __builtin_bit_cast(f32x4, a), bv = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[i], c, 0, 0, 0);
+    return c;
+  } else {
+    return mfma_16x16x32<DT == DT_F16>(a, b, c);
+  }
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
@@ -58,17 +74,17 @@ __device__ __forceinline__ float fold_partials(const float2 *__restrict__ part, 
   return m + fast_log2(z);
 }
 
-// ---- MFMA building blocks (bf16, v_mfma_f32_16x16x32_bf16) ----------------------------------
+// ---- MFMA building blocks ----------------------------------
 constexpr int MF_THREADS = 256;           // per row half (see score_mfma_kernel)
 constexpr int MF_WAVES = 4;              // waves that share the key tiles of an iteration
 constexpr int MF_KT = 2;                 // key tiles of 16 per wave iteration (share each B fragment)
 constexpr float MF_BIG = 1.0e30f;        // a tile sum above this re-references the row (2^100)
 
 // Arrange the M query rows of KV head h as MFMA B fragments in LDS.
-// Fragment (mt, ks) is 64 x 16 bytes: lane l holds row 16*mt + l%16, channels 32*ks + 8*(l/16)..+7.
-template <int D, int MT, int NT>                          // NT threads stage MT row tiles
+// Fragment (mt, ks) is 64 x 16 bytes: lane l holds row 16*mt + l%16, bytes 64*ks + 16*(l/16)..+15 of it.
+template <int D, int MT, int NT, int ES = 2>              // NT threads stage MT row tiles of ES-byte elements
 struct QStage {
-  static constexpr int KS = D / 32;
+  static constexpr int KS = D * ES / 64;
   static constexpr int TOTAL = MT * KS * 64;               // 16-byte pieces of the fragments
   static constexpr int N = (TOTAL + NT - 1) / NT;          // per thread
   uint4 v[N];
@@ -83,8 +99,8 @@ struct QStage {
       v[k] = make_uint4(0u, 0u, 0u, 0u);
       if (i < TOTAL && r < s.M) {
         const int hq = h * s.G + r / s.w_obs, io = r % s.w_obs;
-        const int64_t off = (int64_t)b * s.q_sb + (int64_t)hq * s.q_sh + (int64_t)io * s.q_st + ks * 32 + (l >> 4) * 8;
-        v[k] = *(const uint4 *)((const uint16_t *)qbase + off);
+        const int64_t off = (int64_t)b * s.q_sb + (int64_t)hq * s.q_sh + (int64_t)io * s.q_st;
+        v[k] = *(const uint4 *)((const char *)qbase + off * ES + ks * 64 + (l >> 4) * 16);
       }
     }
   }
@@ -110,15 +126,15 @@ struct KFrags {
 };
 
 // Loads the A fragments of MF_KT key tiles starting at key j0 (rows clamped into [0, L-1];
-// callers pass L >= 1).
+// callers pass L >= 1).  kbase: the lane's 16-byte piece of key row 0; st: bytes between key rows.
 template <int KS>
-__device__ __forceinline__ void load_k(KFrags<KS> &kf, const uint16_t *kbase, int64_t st, int j0, int col, int L) {
+__device__ __forceinline__ void load_k(KFrags<KS> &kf, const char *kbase, int64_t st, int j0, int col, int L) {
 #pragma unroll
   for (int n = 0; n < MF_KT; ++n) {
     const int j = min(j0 + n * 16 + col, L - 1);
-    const uint16_t *kp = kbase + (int64_t)j * st;
+    const char *kp = kbase + (int64_t)j * st;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kf.f[n][ks] = *(const bf16x8 *)(kp + ks * 32);
+    for (int ks = 0; ks < KS; ++ks) kf.f[n][ks] = *(const bf16x8 *)(kp + ks * 64);
   }
 }
 

@@ -160,19 +160,19 @@ static int32_t pick_chunk(const BatchParams &bp, int32_t B, int64_t rows_per_seq
 ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   ScorePlan pl;
   pl.m_pad = (s.M + 15) / 16 * 16;
-  pl.mfma = s.dtype != WKV_F32;      // 16-bit inputs: matrix-pipe kernels (m_pad <= 256 always holds)
+  const bool f32 = s.dtype == WKV_F32;
   const int64_t rows_per_seq = (int64_t)s.Hkv * n_groups;
   const int32_t Lmax = s.t_stride + s.w_obs;
-  const int64_t slots = pl.m_pad <= 128 ? 768 : 256;
+  const int64_t slots = pl.m_pad > 128 ? 256 : (f32 ? 512 : 768);
   pl.chunk1 = pick_chunk(bp, s.B, rows_per_seq, 0, 256, MAX_CHUNK1, slots);
   pl.n_chunks1 = (int32_t)ceil_div(Lmax, pl.chunk1);
-  pl.chunk2 = pick_chunk(bp, s.B, rows_per_seq, s.w_obs, 256, MAX_CHUNK2, slots);
+  pl.chunk2 = pick_chunk(bp, s.B, rows_per_seq, s.w_obs, 256, max_chunk2(f32), slots);
   pl.n_chunks2 = (int32_t)ceil_div(s.t_stride > 0 ? s.t_stride : 1, pl.chunk2);
   // every pass-2 workgroup re-reads rows * n_chunks1 partials when it folds them itself: worth
   // it (one launch less) only while that stays a few KB
-  pl.fold_in_pass2 = pl.mfma && pl.n_chunks1 <= 16;
+  pl.fold_in_pass2 = pl.n_chunks1 <= 16;
   // chunks are multiples of 128 keys: windows never straddle two workgroups when win divides 128
-  pl.pool_in_pass2 = pl.mfma;
+  pl.pool_in_pass2 = true;
   for (int32_t b = 0; b < s.B; ++b) pl.pool_in_pass2 = pl.pool_in_pass2 && (128 % bp.seq[b].win == 0);
   return pl;
 }
@@ -197,7 +197,7 @@ ResidentPlan plan_resident(const Shape &s, const BatchParams &bp, const ScorePla
   rp.n_items = (int32_t)items;
   // a wait that is still unanswered after this many polls (tens of milliseconds) gives up
   rp.spin_limit = (flags & WKV_DEBUG_WAIT_GIVES_UP) ? 0 : (1 << 16);
-  const bool can = plan.mfma && plan.m_pad <= 128 && s.t_stride > 0 && items < (int64_t)1 << 30;
+  const bool can = s.dtype != WKV_F32 && plan.m_pad <= 128 && s.t_stride > 0 && items < (int64_t)1 << 30;
   rp.use = can && (flags & WKV_SCORE_SINGLE_READ);
   return rp;
 }

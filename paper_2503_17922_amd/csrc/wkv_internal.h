@@ -67,14 +67,15 @@ struct Shape {
 // token scores in LDS (4 bytes per key).
 constexpr int32_t MAX_CHUNK1 = 8192;
 constexpr int32_t MAX_CHUNK2 = 4096;
+// fp32 query fragments take 64 KB of LDS per 128 softmax rows, which leaves less for the staging.
+constexpr int32_t max_chunk2(bool f32) { return f32 ? 2048 : MAX_CHUNK2; }
 
 struct ScorePlan {
   int32_t chunk1, n_chunks1;   // stats pass
   int32_t chunk2, n_chunks2;   // score pass (over t_stride)
   int32_t m_pad;               // rows padded to a multiple of 16
-  bool mfma;                   // bf16 MFMA kernels (else the generic ones)
-  bool fold_in_pass2;          // MFMA path: pass 2 folds the pass-1 partials itself (few chunks per row)
-  bool pool_in_pass2;          // MFMA path: pass 2 can pool its chunk's windows (every window size divides 128)
+  bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
+  bool pool_in_pass2;          // pass 2 can pool its chunk's windows (every window size divides 128)
 };
 
 // ---- single-read score kernel ("resident keys") ----------------------------------------------------

@@ -120,11 +120,11 @@ __global__ __launch_bounds__(MF_THREADS, 3) void score_resident_kernel(Shape s, 
     __syncthreads();                                   // the previous slice's readers of qfrag / t_s / lse_s are done
     QStage<D, MT, NT> qstage;
     qstage.load(s, gp.q[g], b, h, tid);
-    const uint16_t *kbase = (const uint16_t *)gp.k[g] + (int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh + quad * 8;
+    const char *kbase = (const char *)((const uint16_t *)gp.k[g] + (int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) + quad * 16;
     const int ja = c0 + wave * STEP, jb = ja + MF_WAVES * STEP;
     KFrags<KS> ka, kb;                                 // resident for both phases
-    load_k<KS>(ka, kbase, s.kv_st, ja, col, cend);
-    load_k<KS>(kb, kbase, s.kv_st, jb, col, cend);
+    load_k<KS>(ka, kbase, s.kv_st * 2, ja, col, cend);
+    load_k<KS>(kb, kbase, s.kv_st * 2, jb, col, cend);
     qstage.store(qfrag, tid);
     __syncthreads();
     RK_T(0);

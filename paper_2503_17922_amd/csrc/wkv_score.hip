@@ -16,22 +16,14 @@
 // A caller whose prefill attention kept the normalisers of the observation rows hands them
 // over; pass 1 and the fold are then skipped and the keys are read once.
 //
-// Two kernel families implement the passes:
-//   * MFMA (bf16 or fp16 inputs): v_mfma_f32_16x16x32_bf16 / _f16 with the keys as the A operand,
-//     loaded straight from global memory into registers in operand layout, so K never passes
-//     through LDS and the four waves of a workgroup never synchronise in the loop; the
-//     query rows are the B operand, read as pre-arranged fragments from LDS.
-//   * generic (fp32 inputs): plain fp32 FMAs, thread-per-row for the stats,
-//     thread-per-key for the scores, the other operand broadcast from LDS.
+// Both passes run on the matrix pipe: v_mfma_f32_16x16x32_bf16 / _f16 for 16-bit inputs, v_mfma_f32_16x16x4_f32
+// for fp32 inputs, with the keys as the A operand, loaded straight from global memory into registers in
+// operand layout, so K never passes through LDS and the waves of a workgroup never synchronise in the
+// loop; the query rows are the B operand, read as pre-arranged fragments from LDS.
 #include "wkv_device.h"
 #include "wkv_pool.h"
 
 namespace wkv {
-
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-  static __device__ __forceinline__ float load(const void *p, int64_t i) { return ((const float *)p)[i]; }
-};
 
 // =========================================================================================
 // fold: per-chunk (m, z) partials of pass 1 -> one lse2 per row, once per (group, sequence, KV head)
@@ -74,118 +66,10 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 }
 
 // =========================================================================================
-// generic kernels
-// =========================================================================================
-constexpr int GEN_THREADS = 256;
-constexpr int GEN_KT = 32;   // keys staged per LDS tile in the stats kernel
-
-// Pass 1, generic.  Thread (row r = tid % R, key lane kl = tid / R); R = rows rounded up to a
-// power of two <= 256, KL = 256 / R.  Each thread keeps its query row in registers and walks
-// the staged key tile with broadcast LDS reads.
-template <typename T, int D>
-__global__ __launch_bounds__(GEN_THREADS) void stats_generic_kernel(Shape s, BatchParams bp, GroupPtrs gp,
-                                                                    ScorePlan pl, float2 *__restrict__ partials,
-                                                                    int R) {
-  __shared__ float ktile[GEN_KT][D + 1];
-  __shared__ float2 red[GEN_THREADS];
-  const int bh = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv, g = blockIdx.z;
-  const int L = bp.seq[b].L;
-  const int c0 = blockIdx.x * pl.chunk1;
-  const int64_t prow = (((int64_t)g * s.B * s.Hkv + bh) * pl.m_pad) * pl.n_chunks1 + blockIdx.x;
-  const int r = threadIdx.x % R, kl = threadIdx.x / R, KL = GEN_THREADS / R;
-  const bool row_ok = r < s.M;
-  // query row r: head h*G + r / w_obs, observation index r % w_obs
-  float q[D];
-  const int io = r % s.w_obs;
-  if (row_ok) {
-    const int hq = h * s.G + r / s.w_obs;
-    const int64_t qoff = (int64_t)b * s.q_sb + (int64_t)hq * s.q_sh + (int64_t)io * s.q_st;
-#pragma unroll
-    for (int c = 0; c < D; ++c) q[c] = Elem<T>::load(gp.q[g], qoff + c);
-  } else {
-#pragma unroll
-    for (int c = 0; c < D; ++c) q[c] = 0.0f;
-  }
-  const int last_visible = L - s.w_obs + io;   // causal: key j visible iff j <= last_visible
-  const int c1 = min(c0 + pl.chunk1, L);
-  float m = -INFINITY, z = 0.0f;
-  const int64_t koff = (int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh;
-  for (int j0 = c0; j0 < c1; j0 += GEN_KT) {
-    __syncthreads();
-    for (int i = threadIdx.x; i < GEN_KT * D; i += GEN_THREADS) {
-      const int jj = i / D, c = i % D;
-      const int j = j0 + jj;
-      ktile[jj][c] = j < c1 ? Elem<T>::load(gp.k[g], koff + (int64_t)j * s.kv_st + c) : 0.0f;
-    }
-    __syncthreads();
-    for (int jj = kl; jj < GEN_KT; jj += KL) {
-      const int j = j0 + jj;
-      if (j < c1 && j <= last_visible && row_ok) {
-        float dot = 0.0f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) dot = fmaf(q[c], ktile[jj][c], dot);
-        merge_stats(m, z, dot * s.c1, 1.0f);
-      }
-    }
-  }
-  red[threadIdx.x] = make_float2(m, z);
-  __syncthreads();
-  if (kl == 0 && r < pl.m_pad) {
-    for (int i = 1; i < KL; ++i) merge_stats(m, z, red[i * R + r].x, red[i * R + r].y);
-    partials[prow + (int64_t)r * pl.n_chunks1] = make_float2(m, z);
-  }
-}
-
-// Pass 2, generic.  One thread per key of the chunk; query rows and their lse2 are broadcast
-// from LDS; the key row lives in registers.
-template <typename T, int D>
-__global__ __launch_bounds__(GEN_THREADS) void score_generic_kernel(Shape s, BatchParams bp, GroupPtrs gp,
-                                                                    ScorePlan pl,
-                                                                    const float *__restrict__ lse_g,
-                                                                    float *__restrict__ t_out) {
-  extern __shared__ float smem[];            // q [M][D], then lse2 [M]
-  float *qs = smem;
-  float *lse = smem + (size_t)s.M * D;
-  const int bh = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv, g = blockIdx.z;
-  const int n_review = bp.seq[b].L - s.w_obs;
-  const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
-  float *trow = t_out + row * s.t_stride;
-  const int c0 = blockIdx.x * pl.chunk2;
-  const int cend = min(c0 + pl.chunk2, s.t_stride);
-  if (c0 >= n_review) {                      // nothing to score here: only the zero fill
-    for (int j = c0 + threadIdx.x; j < cend; j += GEN_THREADS) trow[j] = 0.0f;
-    return;
-  }
-  for (int i = threadIdx.x; i < s.M * D; i += GEN_THREADS) {
-    const int r = i / D, c = i % D;
-    const int hq = h * s.G + r / s.w_obs, io = r % s.w_obs;
-    qs[i] = Elem<T>::load(gp.q[g], (int64_t)b * s.q_sb + (int64_t)hq * s.q_sh + (int64_t)io * s.q_st + c);
-  }
-  for (int r = threadIdx.x; r < s.M; r += GEN_THREADS) lse[r] = row_lse2(s, pl, gp, lse_g, g, b, h, row, r);
-  __syncthreads();
-  const int64_t koff = (int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh;
-  for (int j = c0 + threadIdx.x; j < cend; j += GEN_THREADS) {
-    float tj = 0.0f;
-    if (j < n_review) {
-      float kr[D];
-#pragma unroll
-      for (int c = 0; c < D; ++c) kr[c] = Elem<T>::load(gp.k[g], koff + (int64_t)j * s.kv_st + c);
-      for (int r = 0; r < s.M; ++r) {
-        float dot = 0.0f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) dot = fmaf(qs[r * D + c], kr[c], dot);
-        tj += fast_exp2(fmaf(dot, s.c1, -lse[r]));
-      }
-    }
-    trow[j] = tj;
-  }
-}
-
-// =========================================================================================
-// MFMA kernels (bf16)
+// MFMA kernels
 // =========================================================================================
 // Orientation: D[key, query row] = sum_c K[key, c] * Q[row, c].  The keys are the A operand (16
-// keys x 32 channels per instruction, loaded straight from global memory: lane l holds key
+// keys x 64 bytes of each per step, loaded straight from global memory: lane l holds key
 // l%16, the 16-byte piece l/16 of a 64-byte run, so the four lanes of a key read 64 contiguous
 // bytes), the stacked query rows are the B operand (fragments pre-arranged in LDS, one
 // conflict-free ds_read_b128 each).  In the 16x16 result a lane holds 4 consecutive keys of
@@ -200,21 +84,28 @@ __global__ __launch_bounds__(GEN_THREADS) void score_generic_kernel(Shape s, Bat
 // row tiles 0..MT-1 and waves 4-7 on row tiles MT..2MT-1 of the same key tiles (the second
 // read of a key tile hits the CU's vector cache), the 64 KB of query fragments allow one
 // workgroup per CU, and pass 2 adds the column sums of the two halves in its epilogue.
-template <int D, int MT, int HV, int PASS, bool F16>
-__global__ __launch_bounds__(MF_THREADS * HV, HV == 1 ? 3 : 2) void score_mfma_kernel(Shape s, BatchParams bp, GroupPtrs gp,
+//
+// fp32 inputs take the same kernels with v_mfma_f32_16x16x4_f32 (fp32 products and sums): their passes are
+// bound by that instruction (32 cycles for 2 KFLOP), their query fragments are twice as large (64 KB per 128
+// rows: two workgroups per CU, half the chunk).  Eq. 1-2 of one 4096-token group (32q/8kv heads, d = 128):
+// 263 us with one vector FMA per product, thread per row / thread per key, 51 us here.
+template <int D, int MT, int HV, int PASS, int DT>
+__global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) void score_mfma_kernel(Shape s, BatchParams bp, GroupPtrs gp,
                                                                    ScorePlan pl, float2 *__restrict__ partials,
                                                                    const float *__restrict__ lse_g,
                                                                    float *__restrict__ t_out,
                                                                    float *__restrict__ s_pool,
                                                                    const uint32_t *__restrict__ only_if) {
-  constexpr int KS = D / 32;
+  constexpr int ES = DT == DT_F32 ? 4 : 2;             // bytes per element
+  constexpr int KS = D * ES / 64;
   constexpr int STEP = 16 * MF_KT;                    // keys per wave iteration
   constexpr int NT = MF_THREADS * HV;                 // threads of the workgroup
   // Launched behind the single-read kernel as its fall-back: nothing to do unless that kernel
   // raised the word (uniform over the grid).
   if (only_if && *only_if == 0u) return;
   constexpr int MTT = MT * HV;                        // row tiles of the workgroup
-  constexpr int TS_LEN = MAX_CHUNK2 + 256;            // token scores of a chunk + the scrap area
+  constexpr int TS_MAX = max_chunk2(DT == DT_F32);
+  constexpr int TS_LEN = TS_MAX + 256;            // token scores of a chunk + the scrap area
   __shared__ uint4 qfrag[MTT * KS * 64];
   __shared__ float2 wave_part[PASS == 1 ? MF_WAVES * HV : 1][MT * 16];
   // Pass 2 collects the chunk's token scores here and writes them out once at the end: global
@@ -257,13 +148,14 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 ? 3 : 2) void score_mfma_k
   }
   // Loads that depend on nothing staged below go out first, so that their latencies overlap: the
   // query fragments of this workgroup and the first key tile of every wave.
-  QStage<D, MTT, NT> qstage;
+  QStage<D, MTT, NT, ES> qstage;
   qstage.load(s, gp.q[g], b, h);
   const int cend = min(c0 + chunk, limit);
-  const uint16_t *kbase = (const uint16_t *)gp.k[g] + (int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh + quad * 8;
+  const char *kbase = (const char *)gp.k[g] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * ES + quad * 16;
+  const int64_t kstride = s.kv_st * ES;
   int j0 = c0 + kw * STEP;
   KFrags<KS> ka, kb;
-  load_k<KS>(ka, kbase, s.kv_st, j0, col, max(cend, 1));
+  load_k<KS>(ka, kbase, kstride, j0, col, max(cend, 1));
 
   if (PASS == 2) {
     // The base-2 log-sum-exp of the MT*16 rows, into LDS.  With few chunks per row the workgroup
@@ -308,7 +200,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 ? 3 : 2) void score_mfma_k
     // ---- prefetch the next iteration's keys while this one is computed --------------------
     // Unconditional: a prefetch behind a branch makes every wait for `kf` also wait for it.
     // Past the end of the chunk the row index clamps to the chunk's last key (a cache hit).
-    load_k<KS>(kn, kbase, s.kv_st, j0 + MF_WAVES * STEP, col, cend);
+    load_k<KS>(kn, kbase, kstride, j0 + MF_WAVES * STEP, col, cend);
 
     // ---- logits acc[n][mt][e] = k_{j0+16n+4*quad+e} . q_{16*mt+col}, and their exponentials --------
     // Written so that the MFMAs of row tile mt and the exponentials of row tile mt-1 alternate
@@ -328,7 +220,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 ? 3 : 2) void score_mfma_k
           const bf16x8 qb = *(const bf16x8 *)&qraw;
 #pragma unroll
           for (int n = 0; n < MF_KT; ++n)
-            acc[n][mt] = mfma_16x16x32<F16>(kf.f[n][ks], qb, ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[n][mt]);
+            acc[n][mt] = mfma_64b<DT>(kf.f[n][ks], qb, ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[n][mt]);
         }
       }
       if (mt > 0) {
@@ -404,7 +296,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 ? 3 : 2) void score_mfma_k
       // Every lane stores (lanes other than the first of each 16 into a scrap area past the
       // chunk): a store under a lane predicate would put a branch into the middle of the block.
       float *ts = t_s + half * TS_LEN;
-      float *dst = col == 0 ? ts + (j0 - c0) + quad * 4 : ts + MAX_CHUNK2 + lane * 4;
+      float *dst = col == 0 ? ts + (j0 - c0) + quad * 4 : ts + TS_MAX + lane * 4;
 #pragma unroll
       for (int n = 0; n < MF_KT; ++n) {
 #pragma unroll
@@ -466,7 +358,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 ? 3 : 2) void score_mfma_k
 // =========================================================================================
 // launch
 // =========================================================================================
-template <int D, int MT, int HV, bool F16>
+template <int D, int MT, int HV, int DT>
 static hipError_t launch_mfma(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp,
                               int32_t n_groups, bool have_lse, float2 *partials, float *lse, float *t_out,
                               float *s_pool, hipStream_t stream, hipEvent_t mid, const uint32_t *only_if) {
@@ -477,7 +369,7 @@ static hipError_t launch_mfma(const Shape &s, const BatchParams &bp, const Score
     if (s.t_stride <= 0) return hipSuccess;
   } else {
     dim3 g1(pl.n_chunks1, s.B * s.Hkv, n_groups);
-    hipLaunchKernelGGL((score_mfma_kernel<D, MT, HV, 1, F16>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
+    hipLaunchKernelGGL((score_mfma_kernel<D, MT, HV, 1, DT>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
@@ -489,59 +381,28 @@ static hipError_t launch_mfma(const Shape &s, const BatchParams &bp, const Score
   ScorePlan pl2 = pl;
   if (have_lse) pl2.fold_in_pass2 = false;
   dim3 g2(pl.n_chunks2, s.B * s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_mfma_kernel<D, MT, HV, 2, F16>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
-  return hipGetLastError();
-}
-
-template <typename T, int D>
-static hipError_t launch_generic(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp,
-                                 int32_t n_groups, bool have_lse, float2 *partials, float *lse, float *t_out,
-                                 hipStream_t stream, hipEvent_t mid) {
-  int R = 1;
-  while (R < pl.m_pad) R <<= 1;
-  dim3 block(GEN_THREADS);
-  hipError_t e;
-  if (have_lse) {                                      // no statistics pass: pass 2 reads the caller's normalisers
-    if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
-    if (s.t_stride <= 0) return hipSuccess;
-  } else {
-    dim3 g1(pl.n_chunks1, s.B * s.Hkv, n_groups);
-    hipLaunchKernelGGL((stats_generic_kernel<T, D>), g1, block, 0, stream, s, bp, gp, pl, partials, R);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
-    if (s.t_stride <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fold_kernel, dim3(s.B * s.Hkv, n_groups), dim3(FOLD_THREADS), 0, stream, s, pl, partials, lse, (const uint32_t *)nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  const size_t lds = ((size_t)s.M * D + s.M) * sizeof(float);
-  if (lds > 48 * 1024) {     // beyond the default dynamic-LDS limit: raise it (per device, any thread)
-    e = hipFuncSetAttribute((const void *)score_generic_kernel<T, D>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (WKV_MAX_OBS_ROWS * D + WKV_MAX_OBS_ROWS) * (int)sizeof(float));
-    if (e != hipSuccess) return e;
-  }
-  dim3 g2(pl.n_chunks2, s.B * s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_generic_kernel<T, D>), g2, block, lds, stream, s, bp, gp, pl, lse, t_out);
+  hipLaunchKernelGGL((score_mfma_kernel<D, MT, HV, 2, DT>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
   return hipGetLastError();
 }
 
 hipError_t launch_score(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp,
                         int32_t n_groups, bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool,
                         hipStream_t stream, hipEvent_t mid, const uint32_t *only_if) {
-  if (pl.mfma) {
-    const int mt = pl.m_pad / 16;
-    const bool f16 = s.dtype == WKV_F16;
-#define WKV_MFMA_CASE(DD, MM, HH)                                                                              \
-  if (s.d == DD && mt <= MM * HH)                                                                              \
-    return f16 ? launch_mfma<DD, MM, HH, true>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if) \
-               : launch_mfma<DD, MM, HH, false>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
-    WKV_MFMA_CASE(128, 1, 1) WKV_MFMA_CASE(128, 2, 1) WKV_MFMA_CASE(128, 4, 1) WKV_MFMA_CASE(128, 8, 1)
-    WKV_MFMA_CASE(64, 1, 1) WKV_MFMA_CASE(64, 2, 1) WKV_MFMA_CASE(64, 4, 1) WKV_MFMA_CASE(64, 8, 1)
-    WKV_MFMA_CASE(128, 8, 2) WKV_MFMA_CASE(64, 8, 2)      // 129..256 rows: two halves of 8 row tiles
-#undef WKV_MFMA_CASE
-    return hipErrorInvalidValue;
+  const int mt = pl.m_pad / 16;
+#define WKV_MFMA_TYPE(DD, MM, HH, TT) \
+  return launch_mfma<DD, MM, HH, TT>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
+#define WKV_MFMA_CASE(DD, MM, HH)                                     \
+  if (s.d == DD && mt <= MM * HH) {                                   \
+    if (s.dtype == WKV_BF16) WKV_MFMA_TYPE(DD, MM, HH, DT_BF16)       \
+    if (s.dtype == WKV_F16) WKV_MFMA_TYPE(DD, MM, HH, DT_F16)         \
+    WKV_MFMA_TYPE(DD, MM, HH, DT_F32)                                 \
   }
-  if (s.d == 128) return launch_generic<float, 128>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, stream, mid);
-  return launch_generic<float, 64>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, stream, mid);
+  WKV_MFMA_CASE(128, 1, 1) WKV_MFMA_CASE(128, 2, 1) WKV_MFMA_CASE(128, 4, 1) WKV_MFMA_CASE(128, 8, 1)
+  WKV_MFMA_CASE(64, 1, 1) WKV_MFMA_CASE(64, 2, 1) WKV_MFMA_CASE(64, 4, 1) WKV_MFMA_CASE(64, 8, 1)
+  WKV_MFMA_CASE(128, 8, 2) WKV_MFMA_CASE(64, 8, 2)      // 129..256 rows: two halves of 8 row tiles
+#undef WKV_MFMA_CASE
+#undef WKV_MFMA_TYPE
+  return hipErrorInvalidValue;
 }
 
 }  // namespace wkv
