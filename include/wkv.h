@@ -135,11 +135,10 @@ size_t wkv_workspace_bytes(const wkv_problem *problem, int32_t n_groups);
  *   t_offset   byte offset of the token scores  float32 [n_groups, batch, n_kv_heads, t_stride]
  *   s_offset   byte offset of the window scores float32 [n_groups, batch, n_kv_heads, nw_max]
  *   t_written  1 if the batched call writes the token scores to memory for this problem; 0 when
- *              its score kernel pools them on chip (every window size divides 128, 16-bit
- *              inputs) and they never leave the compute unit
- *   s_written  1 if the batched call writes the window scores to memory (entries w < NW_b of
- *              each row; the rest of a row is unspecified); 0 when pooling happens inside its
- *              selection kernel
+ *              its score kernel pools them on chip and they never leave the compute unit (always,
+ *              except with WKV_SCORE_SINGLE_READ and a window size that does not divide 256)
+ *   s_written  1 if the score kernel of the batched call writes the window scores to memory (entries
+ *              w < NW_b of each row; the rest of a row is unspecified); else they are a launch of their own
  * Exactly one of t_written / s_written is 1.  The stage calls do not use these regions.
  */
 typedef struct {
@@ -271,7 +270,7 @@ wkv_status wkv_compress_groups(const wkv_problem *problem, int32_t n_groups, int
  *   stage_ms_out  host float [WKV_N_STAGES]: milliseconds of, in order, the softmax-statistics
  *                 pass (Eq. 1; 0 with lse_obs_groups; with WKV_SCORE_SINGLE_READ the single-read
  *                 kernel, which then covers Eq. 1-2), the score pass (Eq. 1-2, and Eq. 3-4 where it
- *                 pools its own windows), the selection kernel (2.2.1, and Eq. 3-4 otherwise) and
+ *                 pools its own windows), the selection (2.2.1, and Eq. 3-4 otherwise) and
  *                 the shared-index gather (2.2.2).
  */
 #define WKV_N_STAGES 4

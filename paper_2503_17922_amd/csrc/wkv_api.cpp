@@ -196,9 +196,9 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
   hipError_t e;
 #define WKV_MARK(i) if (ev && (e = hipEventRecord(ev[i], stream)) != hipSuccess) return hip_fail(e, "event record");
   WKV_MARK(0)
-  // With window sizes that divide the chunk length the score kernel pools its own windows
-  // (Eq. 3-4 on the scores still in LDS) and only the window scores reach memory.
-  float *s_pool = pl.pool_in_pass2 ? ws.s : nullptr;
+  // The score kernel pools its own windows (Eq. 3-4 on the scores still in LDS) and only the window
+  // scores reach memory.
+  float *s_pool = rp.pools ? ws.s : nullptr;
   const uint32_t *only_if = nullptr;
   if (rp.use && !lse_obs_groups) {
     // one read of the keys; the two-pass kernels behind it run only if a wait of it gave up
@@ -210,8 +210,8 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
                    stream, ev ? ev[1] : nullptr, only_if);
   if (e != hipSuccess) return hip_fail(e, "score launch");
   WKV_MARK(2)
-  if (s_pool) e = launch_topk(pr.shape, pr.bp, gk, n_groups, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);
-  else e = launch_select(pr.shape, pr.bp, gk, n_groups, ws.t, win_idx_out, tok_idx_out, n_keep_out, stream);
+  if (!s_pool && (e = launch_pool(pr.shape, pr.bp, n_groups, ws.t, ws.s, stream)) != hipSuccess) return hip_fail(e, "pool launch");
+  e = launch_topk(pr.shape, pr.bp, gk, n_groups, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);
   if (e != hipSuccess) return hip_fail(e, "select launch");
   WKV_MARK(3)
   e = launch_gather(pr.shape, lp, n_layers, gamma, tok_idx_out, n_keep_out, stream);

@@ -171,9 +171,6 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   // every pass-2 workgroup re-reads rows * n_chunks1 partials when it folds them itself: worth
   // it (one launch less) only while that stays a few KB
   pl.fold_in_pass2 = pl.n_chunks1 <= 16;
-  // chunks are multiples of 128 keys: windows never straddle two workgroups when win divides 128
-  pl.pool_in_pass2 = true;
-  for (int32_t b = 0; b < s.B; ++b) pl.pool_in_pass2 = pl.pool_in_pass2 && (128 % bp.seq[b].win == 0);
   return pl;
 }
 
@@ -199,6 +196,8 @@ ResidentPlan plan_resident(const Shape &s, const BatchParams &bp, const ScorePla
   rp.spin_limit = (flags & WKV_DEBUG_WAIT_GIVES_UP) ? 0 : (1 << 16);
   const bool can = s.dtype != WKV_F32 && plan.m_pad <= 128 && s.t_stride > 0 && items < (int64_t)1 << 30;
   rp.use = can && (flags & WKV_SCORE_SINGLE_READ);
+  rp.pools = 1;
+  for (int32_t b = 0; rp.use && b < s.B; ++b) rp.pools = rp.pools && RK_SLICE % bp.seq[b].win == 0;
   return rp;
 }
 
@@ -306,11 +305,12 @@ wkv_status wkv_get_workspace_layout(const wkv_problem *problem, int32_t n_groups
   Shape s; BatchParams bp;
   fill_shape(problem, dm, &s, &bp);
   const ScorePlan pl = plan_score(s, bp, n_groups);
-  const Workspace w = carve_workspace(s, pl, plan_resident(s, bp, pl, n_groups, problem->flags), n_groups, nullptr);
+  const ResidentPlan rp = plan_resident(s, bp, pl, n_groups, problem->flags);
+  const Workspace w = carve_workspace(s, pl, rp, n_groups, nullptr);
   layout->t_offset = w.t_offset;
   layout->s_offset = w.s_offset;
-  layout->s_written = pl.pool_in_pass2 ? 1 : 0;
-  layout->t_written = pl.pool_in_pass2 ? 0 : 1;
+  layout->s_written = rp.pools ? 1 : 0;
+  layout->t_written = rp.pools ? 0 : 1;
   return WKV_OK;
 }
 

@@ -75,7 +75,6 @@ struct ScorePlan {
   int32_t chunk2, n_chunks2;   // score pass (over t_stride)
   int32_t m_pad;               // rows padded to a multiple of 16
   bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
-  bool pool_in_pass2;          // pass 2 can pool its chunk's windows (every window size divides 128)
 };
 
 // ---- single-read score kernel ("resident keys") ----------------------------------------------------
@@ -94,6 +93,9 @@ struct ResidentPlan {
   int32_t nsl_max;                       // most slices of any row
   int32_t m_pad;
   int32_t spin_limit;                    // polls before a waiting workgroup gives up
+  // The batched call's score kernel pools (Eq. 3-4).  The two-pass kernels always can; slices of the
+  // single-read kernel hold whole windows only if every window size divides their length.
+  int32_t pools;
 };
 
 struct Workspace {
@@ -131,9 +133,6 @@ hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, 
                        float *s_out, hipStream_t stream);
 hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
                        int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream);
-// Pooling and selection in one launch (same results as launch_pool followed by launch_topk).
-hipError_t launch_select(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *t,
-                         int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream);
 hipError_t launch_gather(const Shape &s, const LayerPtrs &lp, int32_t n_layers, int32_t gamma,
                          const int32_t *tok_idx, const int32_t *n_keep, hipStream_t stream);
 

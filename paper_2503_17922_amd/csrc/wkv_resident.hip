@@ -332,9 +332,7 @@ __global__ __launch_bounds__(MF_THREADS, 3) void score_resident_kernel(Shape s, 
       // Eq. 3-4 on the slice's token scores while they are in LDS: the slice starts on a window
       // boundary and no window but the sequence's last (partial) one ends outside it
       const SeqParam sp = bp.seq[b];
-      const int w0 = c0 / sp.win, w1 = (cend2 + sp.win - 1) / sp.win;
-      float *srow = s_pool + row * s.nw_max;
-      for (int w = w0 + tid; w < w1; w += NT) srow[w] = pool_window(t_s - c0, w, sp.win, n_review, sp.p);
+      pool_windows<NT>(t_s, c0 / sp.win, (cend2 + sp.win - 1) / sp.win, sp.win, sp.p, n_review, s_pool + row * s.nw_max);
     } else {
       float *trow = t_out + row * s.t_stride;
       const int cfill = c0 + RK_SLICE >= n_review ? s.t_stride : c0 + RK_SLICE;   // the row's padding is zeroed by its last scoring slice

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
   if (only_if && *only_if == 0u) return;
   constexpr int MTT = MT * HV;                        // row tiles of the workgroup
   constexpr int TS_MAX = max_chunk2(DT == DT_F32);
-  constexpr int TS_LEN = TS_MAX + 256;            // token scores of a chunk + the scrap area
+  constexpr int TS_LEN = TS_MAX + WKV_MAX_WIN + 256;  // token scores of a chunk, the rest of its last window, the scrap area
   __shared__ uint4 qfrag[MTT * KS * 64];
   __shared__ float2 wave_part[PASS == 1 ? MF_WAVES * HV : 1][MT * 16];
   // Pass 2 collects the chunk's token scores here and writes them out once at the end: global
@@ -129,15 +129,24 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
   const int col = lane & 15, quad = lane >> 4;
 
   const int chunk = PASS == 1 ? pl.chunk1 : pl.chunk2;
-  const int c0 = bx * chunk;
   const int limit = PASS == 1 ? L : n_review;         // keys that matter to this pass
+  int c0 = bx * chunk, c1 = min(c0 + chunk, limit);   // keys c0 .. c1-1 of the row
+  int w0 = 0, w1 = 0;
+  if (PASS == 2 && s_pool) {
+    // A window belongs to the chunk that holds its first token: the workgroup scores and pools whole
+    // windows, whatever their size, and no token is scored twice.
+    const int win = bp.seq[b].win;
+    w0 = (c0 + win - 1) / win;
+    w1 = (c1 + win - 1) / win;
+    c0 = w0 * win;
+    c1 = min(w1 * win, limit);
+  }
   float *trow = PASS == 2 ? t_out + row * s.t_stride : nullptr;
 
   if (PASS == 2) {
-    const int cend_fill = min(c0 + chunk, s.t_stride);
-    if (c0 >= n_review) {
+    if (c0 >= n_review || c0 >= c1) {
       if (!s_pool)
-        for (int j = c0 + threadIdx.x; j < cend_fill; j += NT) trow[j] = 0.0f;
+        for (int j = c0 + threadIdx.x; j < min(c0 + chunk, s.t_stride); j += NT) trow[j] = 0.0f;
       return;
     }
   }
@@ -150,7 +159,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
   // query fragments of this workgroup and the first key tile of every wave.
   QStage<D, MTT, NT, ES> qstage;
   qstage.load(s, gp.q[g], b, h);
-  const int cend = min(c0 + chunk, limit);
+  const int cend = c1;
   const char *kbase = (const char *)gp.k[g] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * ES + quad * 16;
   const int64_t kstride = s.kv_st * ES;
   int j0 = c0 + kw * STEP;
@@ -188,7 +197,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
     zsum[mt] = 0.0f;
   }
 
-  const float c1 = s.c1;
+  const float sc = s.c1;
 
   // One wave iteration: prefetch the keys of the next iteration into `kn`, compute on `kf`.
   // The loop below calls it with the two buffers swapped in turn, so no register copies are
@@ -230,13 +239,13 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
 #pragma unroll
           for (int n = 0; n < MF_KT; ++n)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a += fast_exp2(fmaf(acc[n][m1][e], c1, -mref[m1]));
+            for (int e = 0; e < 4; ++e) a += fast_exp2(fmaf(acc[n][m1][e], sc, -mref[m1]));
           psum[m1] = a;
         } else {
 #pragma unroll
           for (int n = 0; n < MF_KT; ++n)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tq[n][e] += fast_exp2(fmaf(acc[n][m1][e], c1, -lse_r[m1]));
+            for (int e = 0; e < 4; ++e) tq[n][e] += fast_exp2(fmaf(acc[n][m1][e], sc, -lse_r[m1]));
         }
       }
     }
@@ -256,7 +265,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
             for (int e = 0; e < 4; ++e) {
               const int j = j0 + n * 16 + quad * 4 + e;
               if (j > last_vis || j >= cend) acc[n][mt][e] = -INFINITY;
-              a += fast_exp2(fmaf(acc[n][mt][e], c1, -mref[mt]));
+              a += fast_exp2(fmaf(acc[n][mt][e], sc, -mref[mt]));
             }
           psum[mt] = a;
         }
@@ -275,7 +284,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
             for (int n = 0; n < MF_KT; ++n)
 #pragma unroll
               for (int e = 0; e < 4; ++e) vmax = fmaxf(vmax, acc[n][mt][e]);
-            const float nref = fmaxf(mref[mt], vmax * c1);
+            const float nref = fmaxf(mref[mt], vmax * sc);
             float a = 0.0f;
             if (nref != -INFINITY) {
               zsum[mt] *= fast_exp2(mref[mt] - nref);      // mref = -inf: 2^-inf = 0 and zsum is 0
@@ -283,7 +292,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
 #pragma unroll
               for (int n = 0; n < MF_KT; ++n)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a += fast_exp2(fmaf(acc[n][mt][e], c1, -nref));
+                for (int e = 0; e < 4; ++e) a += fast_exp2(fmaf(acc[n][mt][e], sc, -nref));
             }
             psum[mt] = a;
           }
@@ -296,7 +305,7 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
       // Every lane stores (lanes other than the first of each 16 into a scrap area past the
       // chunk): a store under a lane predicate would put a branch into the middle of the block.
       float *ts = t_s + half * TS_LEN;
-      float *dst = col == 0 ? ts + (j0 - c0) + quad * 4 : ts + TS_MAX + lane * 4;
+      float *dst = col == 0 ? ts + (j0 - c0) + quad * 4 : ts + TS_MAX + WKV_MAX_WIN + lane * 4;
 #pragma unroll
       for (int n = 0; n < MF_KT; ++n) {
 #pragma unroll
@@ -321,13 +330,8 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
       __syncthreads();
     }
     if (s_pool) {
-      // Eq. 3-4 on the chunk's token scores while they are in LDS: the chunk starts on a window
-      // boundary and no window but the sequence's last (partial) one ends outside it
-      const SeqParam sp = bp.seq[b];
-      const int w0 = c0 / sp.win, w1 = (cend + sp.win - 1) / sp.win;
-      float *srow = s_pool + row * s.nw_max;
-      for (int w = w0 + threadIdx.x; w < w1; w += NT)
-        srow[w] = pool_window(t_s - c0, w, sp.win, n_review, sp.p);
+      // Eq. 3-4 on the chunk's token scores while they are in LDS
+      pool_windows<NT>(t_s, w0, w1, bp.seq[b].win, bp.seq[b].p, n_review, s_pool + row * s.nw_max);
     } else {
       const int cend_fill = min(c0 + chunk, s.t_stride);
       for (int j = c0 + threadIdx.x; j < cend_fill; j += NT) trow[j] = j < cend ? t_s[j - c0] : 0.0f;

@@ -9,24 +9,43 @@
 namespace wkv {
 
 constexpr int POOL_THREADS = 256;
+constexpr int POOL_TOKENS = 2048;      // tokens a workgroup stages
 
-// One thread per window.
+// Windows that a workgroup pools: as many as fit its staging area.
+__host__ __device__ __forceinline__ int pool_windows_per_block(int win) { return POOL_TOKENS / win; }
+
 __global__ __launch_bounds__(POOL_THREADS) void pool_kernel(Shape s, BatchParams bp, const float *__restrict__ t,
                                                                  float *__restrict__ s_out) {
+  __shared__ __attribute__((aligned(16))) float t_s[POOL_TOKENS];
   const int bh = blockIdx.y, b = bh / s.Hkv, g = blockIdx.z;
   const SeqParam sp = bp.seq[b];
   const int n_review = sp.L - s.w_obs;
   const int nw = (n_review + sp.win - 1) / sp.win;
   const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
-  const int w = blockIdx.x * POOL_THREADS + threadIdx.x;
-  if (w >= s.nw_max) return;
-  s_out[row * s.nw_max + w] = w < nw ? pool_window(t + row * s.t_stride, w, sp.win, n_review, sp.p) : -INFINITY;
+  const float *trow = t + row * s.t_stride;
+  float *srow = s_out + row * s.nw_max;
+  const int per = pool_windows_per_block(sp.win);
+  // sequences with small windows need fewer workgroups than the grid has per row; the last one fills up
+  const int w0 = blockIdx.x * per, w1 = min(w0 + per, nw);
+  if (w0 < w1) {
+    const int tok0 = w0 * sp.win, n = min(w1 * sp.win, n_review) - tok0;
+    for (int i = threadIdx.x; i < n; i += POOL_THREADS) t_s[i] = trow[tok0 + i];
+    __syncthreads();
+    pool_windows<POOL_THREADS>(t_s, w0, w1, sp.win, sp.p, n_review, srow);
+  }
+  for (int w = max(w0, nw) + threadIdx.x; w < (blockIdx.x == gridDim.x - 1 ? s.nw_max : min(w0 + per, s.nw_max)); w += POOL_THREADS)
+    srow[w] = -INFINITY;
 }
 
 hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, const float *t,
                        float *s_out, hipStream_t stream) {
   if (s.nw_max <= 0) return hipSuccess;
-  dim3 grid((s.nw_max + POOL_THREADS - 1) / POOL_THREADS, s.B * s.Hkv, n_groups);
+  int blocks = 1;
+  for (int b = 0; b < s.B; ++b) {
+    const int nw = (bp.seq[b].L - s.w_obs + bp.seq[b].win - 1) / bp.seq[b].win, per = pool_windows_per_block(bp.seq[b].win);
+    blocks = max(blocks, (nw + per - 1) / per);
+  }
+  dim3 grid(blocks, s.B * s.Hkv, n_groups);
   hipLaunchKernelGGL(pool_kernel, grid, dim3(POOL_THREADS), 0, stream, s, bp, t, s_out);
   return hipGetLastError();
 }
@@ -183,26 +202,6 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams
   topk_body(s, sp, keys, row, win_idx, tok_idx, n_keep);
 }
 
-// Pooling and selection in one launch (the path wkv_compress_groups takes): the window scores
-// go straight from registers into the LDS key array and never touch global memory.
-__global__ __launch_bounds__(TOPK_THREADS) void select_kernel(Shape s, BatchParams bp, GroupK gk,
-                                                              const float *__restrict__ t,
-                                                              int32_t *__restrict__ win_idx,
-                                                              int32_t *__restrict__ tok_idx,
-                                                              int32_t *__restrict__ n_keep) {
-  extern __shared__ uint32_t keys[];
-  const int bh = blockIdx.x, b = bh / s.Hkv, g = blockIdx.y;
-  SeqParam sp = bp.seq[b];
-  if (gk.in_use) sp.k = gk.k[g * s.B + b];      // the group's own budget
-  const int n_review = sp.L - s.w_obs;
-  const int nw = (n_review + sp.win - 1) / sp.win;
-  const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
-  const float *trow = t + row * s.t_stride;
-  for (int w = threadIdx.x; w < nw; w += TOPK_THREADS)
-    keys[w] = float_to_key(pool_window(trow, w, sp.win, n_review, sp.p));
-  topk_body(s, sp, keys, row, win_idx, tok_idx, n_keep);
-}
-
 hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
                        int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
   const size_t lds = (size_t)(s.nw_max > 0 ? s.nw_max : 1) * sizeof(uint32_t);
@@ -213,19 +212,6 @@ hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, 
   }
   dim3 grid(s.B * s.Hkv, n_groups);
   hipLaunchKernelGGL(topk_kernel, grid, dim3(TOPK_THREADS), lds, stream, s, bp, gk, sc, win_idx, tok_idx, n_keep);
-  return hipGetLastError();
-}
-
-hipError_t launch_select(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *t,
-                         int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
-  const size_t lds = (size_t)(s.nw_max > 0 ? s.nw_max : 1) * sizeof(uint32_t);
-  if (lds > 48 * 1024) {     // beyond the default dynamic-LDS limit: raise it (per device, any thread)
-    hipError_t e = hipFuncSetAttribute((const void *)select_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       WKV_MAX_WINDOWS * (int)sizeof(uint32_t));
-    if (e != hipSuccess) return e;
-  }
-  dim3 grid(s.B * s.Hkv, n_groups);
-  hipLaunchKernelGGL(select_kernel, grid, dim3(TOPK_THREADS), lds, stream, s, bp, gk, t, win_idx, tok_idx, n_keep);
   return hipGetLastError();
 }
 
