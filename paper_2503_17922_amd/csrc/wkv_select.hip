@@ -51,127 +51,166 @@ hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, 
 }
 
 // ------------------------------------------------------------------------------------------
-// Top-k windows.  One 1024-thread workgroup per (group, sequence, KV head).
-//   1. window scores -> order-preserving uint32 keys in LDS
-//   2. radix select (4 passes of 8 bits, LDS histogram) for the k-th largest key T and the
-//      number `take_eq` of windows equal to T that still fit
-//   3. one ordered sweep: window w is kept iff key > T, or key == T and fewer than take_eq
-//      equal windows precede it (=> lower index wins ties).  Its output slot is
-//      (#greater before w) + min(#equal before w, take_eq), found with ballot/popcount
-//      prefix sums, so the list comes out ascending without a sort.
+// Top-k windows.  One 1024-thread workgroup per (group, sequence, KV head).  Bound by its chain of
+// synchronised steps, not by data (a row is a few KB), so every step is one that needs few of them:
+//   1. window scores -> order-preserving uint32 keys in LDS, their smallest and largest on the way
+//   2. the k-th largest key T by digits of the range the keys really span: 2048 bins over [lo, hi],
+//      descend into the bin that holds the k-th, until the windows that still fit are exactly a bin
+//      or a bin is one key wide (11 bits a pass: at most three passes, two for ordinary scores.
+//      Window scores differ in their low bits only, so digits taken from the top of the word put
+//      nearly all of them into one bin and serialise the LDS counters)
+//   3. window w is kept iff key > T, or key == T and fewer than take_eq equal windows precede it
+//      (=> lower index wins ties).  Its output slot is (#greater before w) + min(#equal before w,
+//      take_eq): ballots per wave and 1024 windows, one scan over all their counts, so the list comes
+//      out ascending without a sort
 //   4. expansion to token positions, the observation window appended, -1 padding.
+// The 32K-token configuration (64 rows of 2046 windows, k = 256): 12.2 us with 8-bit digits from the
+// top and three synchronisations per 1024 windows in step 3, 9.2 us so.
 // ------------------------------------------------------------------------------------------
 constexpr int TOPK_THREADS = 1024;
 constexpr int TOPK_WAVES = TOPK_THREADS / 64;
+constexpr int TOPK_BINS = 2048;
+constexpr int TOPK_ITERS = WKV_MAX_WINDOWS / TOPK_THREADS;
+static_assert(TOPK_ITERS <= 32 && TOPK_BINS == 2 * TOPK_THREADS, "one mask bit per 1024 windows, two bins a thread");
 
 __device__ __forceinline__ uint32_t float_to_key(float f) {
   const uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Steps 2-4 on the keys already in LDS; `row` is the (group, sequence, KV head) index.
-__device__ __forceinline__ void topk_body(const Shape &s, const SeqParam sp, uint32_t *keys, int64_t row,
-                                          int32_t *__restrict__ win_idx, int32_t *__restrict__ tok_idx,
-                                          int32_t *__restrict__ n_keep) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t sh_prefix, sh_remaining;
-  __shared__ int wave_gt[TOPK_WAVES], wave_eq[TOPK_WAVES];
-  __shared__ int run_gt, run_eq;
-
+__global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams bp, GroupK gk,
+                                                            const float *__restrict__ sc,
+                                                            int32_t *__restrict__ win_idx,
+                                                            int32_t *__restrict__ tok_idx,
+                                                            int32_t *__restrict__ n_keep) {
+  extern __shared__ uint32_t keys[];            // [nw_max], later reused for the selected list
+  __shared__ uint32_t hist[TOPK_BINS];
+  __shared__ uint32_t wave_a[TOPK_WAVES], wave_b[TOPK_WAVES];
+  __shared__ uint32_t counts[TOPK_ITERS * TOPK_WAVES];      // windows per wave and 1024: greater | equal << 16
+  __shared__ uint32_t sh_bin, sh_above, sh_count;
+  const int bh = blockIdx.x, b = bh / s.Hkv, g = blockIdx.y;
+  SeqParam sp = bp.seq[b];
+  if (gk.in_use) sp.k = gk.k[g * s.B + b];      // the group's own budget
   const int n_review = sp.L - s.w_obs;
   const int nw = (n_review + sp.win - 1) / sp.win;
   const int k = sp.k;
+  const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
   int32_t *wrow = win_idx + row * s.k_max;
   int32_t *trow = tok_idx + row * s.nkeep_max;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int n_rev_kept = 0;
 
-  if (tid == 0) { sh_prefix = 0u; sh_remaining = (uint32_t)k; }
-  __syncthreads();
-  // ---- 2. radix select -------------------------------------------------------------------
-  uint32_t T = 0u, take_eq = 0u;
   if (k > 0) {
-    uint32_t mask = 0u;
-    for (int pass = 3; pass >= 0; --pass) {
-      const int shift = pass * 8;
-      if (tid < 256) hist[tid] = 0u;
-      __syncthreads();
-      const uint32_t prefix = sh_prefix;
+    // ---- 1. keys and their range ------------------------------------------------------------
+    const float *srow = sc + row * s.nw_max;
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    for (int w = tid; w < nw; w += TOPK_THREADS) {
+      const uint32_t key = float_to_key(srow[w]);
+      keys[w] = key;
+      kmin = min(kmin, key);
+      kmax = max(kmax, key);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
+      kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
+    }
+    if (lane == 0) { wave_a[wave] = kmin; wave_b[wave] = kmax; }
+    hist[tid] = 0u; hist[tid + TOPK_THREADS] = 0u;
+    __syncthreads();
+    uint32_t lo = wave_a[0], hi = wave_b[0];
+#pragma unroll
+    for (int i = 1; i < TOPK_WAVES; ++i) { lo = min(lo, wave_a[i]); hi = max(hi, wave_b[i]); }
+
+    // ---- 2. the k-th largest key ----------------------------------------------------------------
+    uint32_t remaining = (uint32_t)k, take_eq, T;
+    for (;;) {
+      const int bits = 32 - __clz((int)((hi - lo) | 1u));
+      const int shift = max(bits - 11, 0);
       for (int w = tid; w < nw; w += TOPK_THREADS) {
         const uint32_t key = keys[w];
-        if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+        if (key >= lo && key <= hi) atomicAdd(&hist[(key - lo) >> shift], 1u);
       }
       __syncthreads();
-      if (wave == 0) {
-        // suffix sums over the 256 bins, 4 bins per lane, highest bins first
-        const uint32_t remaining = sh_remaining;
-        uint32_t c[4];
-        uint32_t local = 0u;
+      // windows in strictly higher bins: thread tid looks at bins 2047 - 2*tid and 2046 - 2*tid
+      const uint32_t c0 = hist[TOPK_BINS - 1 - 2 * tid], c1 = hist[TOPK_BINS - 2 - 2 * tid];
+      uint32_t incl = c0 + c1;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { c[i] = hist[255 - (lane * 4 + i)]; local += c[i]; }
-        uint32_t incl = local;                     // inclusive scan over lanes
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = (uint32_t)__shfl_up((int)incl, off);
+        if (lane >= off) incl += o;
+      }
+      if (lane == 63) wave_a[wave] = incl;
+      __syncthreads();
+      uint32_t above = incl - c0 - c1;
+#pragma unroll
+      for (int i = 0; i < TOPK_WAVES; ++i) above += i < wave ? wave_a[i] : 0u;
+      if (above < remaining && above + c0 >= remaining) { sh_bin = TOPK_BINS - 1 - 2 * tid; sh_above = above; sh_count = c0; }
+      above += c0;
+      if (above < remaining && above + c1 >= remaining) { sh_bin = TOPK_BINS - 2 - 2 * tid; sh_above = above; sh_count = c1; }
+      hist[TOPK_BINS - 1 - 2 * tid] = 0u; hist[TOPK_BINS - 2 - 2 * tid] = 0u;
+      __syncthreads();
+      const uint32_t bin_lo = lo + (sh_bin << shift);
+      remaining -= sh_above;
+      if (shift == 0) { T = bin_lo; take_eq = remaining; break; }              // one key wide: ties by index
+      const uint32_t bin_hi = bin_lo + min((1u << shift) - 1u, hi - bin_lo);
+      if (sh_count == remaining) {                      // the whole bin fits: everything from its lower edge on
+        if (bin_lo != 0u) { T = bin_lo - 1u; take_eq = 0u; break; }
+      }
+      lo = bin_lo;
+      hi = bin_hi;
+    }
+
+    // ---- 3. ordered compaction -------------------------------------------------------------
+    uint32_t gt_bits = 0u, eq_bits = 0u;          // this thread's windows, one bit per 1024
+    const int iters = (nw + TOPK_THREADS - 1) / TOPK_THREADS;
+    for (int i = 0; i < iters; ++i) {
+      const int w = i * TOPK_THREADS + tid;
+      const uint32_t key = w < nw ? keys[w] : 0u;
+      const bool gt = w < nw && key > T, eq = w < nw && key == T;
+      gt_bits |= (uint32_t)gt << i;
+      eq_bits |= (uint32_t)eq << i;
+      const int n_gt = __popcll(__ballot(gt)), n_eq = __popcll(__ballot(eq));
+      if (lane == 0) counts[i * TOPK_WAVES + wave] = (uint32_t)n_gt | (uint32_t)n_eq << 16;
+    }
+    __syncthreads();                              // every key has been read: the array is free
+    if (wave == 0) {                              // exclusive scan of the counts, in window order
+      uint32_t base = 0u;
+      for (int c = 0; c < iters * TOPK_WAVES; c += 64) {
+        const uint32_t v = c + lane < iters * TOPK_WAVES ? counts[c + lane] : 0u;
+        uint32_t incl = v;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
-          const uint32_t o = __shfl_up(incl, off);
+          const uint32_t o = (uint32_t)__shfl_up((int)incl, off);
           if (lane >= off) incl += o;
         }
-        uint32_t above = incl - local;             // windows in strictly higher bins
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (above < remaining && above + c[i] >= remaining) {
-            sh_prefix = prefix | ((uint32_t)(255 - (lane * 4 + i)) << shift);
-            sh_remaining = remaining - above;
-          }
-          above += c[i];
-        }
+        if (c + lane < iters * TOPK_WAVES) counts[c + lane] = base + incl - v;
+        base += (uint32_t)__shfl((int)incl, 63);
       }
-      mask |= 255u << shift;
-      __syncthreads();
     }
-    T = sh_prefix;
-    take_eq = sh_remaining;
-  }
-
-  // ---- 3. ordered compaction -------------------------------------------------------------
-  if (tid == 0) { run_gt = 0; run_eq = 0; }
-  __syncthreads();
-  for (int base = 0; base < nw; base += TOPK_THREADS) {
-    const int w = base + tid;
-    const bool valid = w < nw && k > 0;
-    const uint32_t key = valid ? keys[w] : 0u;
-    const bool gt = valid && key > T;
-    const bool eq = valid && key == T;
-    const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
+    __syncthreads();
     const unsigned long long below = (1ull << lane) - 1ull;
-    const int gt_in_wave = __popcll(bgt & below), eq_in_wave = __popcll(beq & below);
-    if (lane == 0) { wave_gt[wave] = __popcll(bgt); wave_eq[wave] = __popcll(beq); }
-    __syncthreads();                              // also orders the key reads before the writes below
-    int gt_before = run_gt + gt_in_wave, eq_before = run_eq + eq_in_wave;
-    for (int i = 0; i < wave; ++i) { gt_before += wave_gt[i]; eq_before += wave_eq[i]; }
-    const bool keep = gt || (eq && (uint32_t)eq_before < take_eq);
-    if (keep) {
-      const int slot = gt_before + min(eq_before, (int)take_eq);
-      keys[slot] = (uint32_t)w;                   // slot <= w < base + TOPK_THREADS: already consumed
-      wrow[slot] = w;
+    for (int i = 0; i < iters; ++i) {
+      const bool gt = gt_bits >> i & 1u, eq = eq_bits >> i & 1u;
+      const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
+      const uint32_t before = counts[i * TOPK_WAVES + wave];
+      const uint32_t gt_before = (before & 0xffffu) + __popcll(bgt & below), eq_before = (before >> 16) + __popcll(beq & below);
+      if (gt || (eq && eq_before < take_eq)) {
+        const uint32_t slot = gt_before + min(eq_before, take_eq);
+        keys[slot] = (uint32_t)(i * TOPK_THREADS + tid);
+        wrow[slot] = i * TOPK_THREADS + tid;
+      }
     }
     __syncthreads();
-    if (tid == 0) {
-      int a = 0, e = 0;
-      for (int i = 0; i < TOPK_WAVES; ++i) { a += wave_gt[i]; e += wave_eq[i]; }
-      run_gt += a; run_eq += e;
-    }
-    __syncthreads();
+    // Only the last window of the sequence can be partial, and if selected it is the last of
+    // the ascending list, so slot m < k starts at m*win.
+    n_rev_kept = k * sp.win;
+    const int missing = ((int)keys[k - 1] + 1) * sp.win - n_review;
+    if (missing > 0) n_rev_kept -= missing;
   }
   for (int i = k + tid; i < s.k_max; i += TOPK_THREADS) wrow[i] = -1;
 
   // ---- 4. token positions ------------------------------------------------------------------
-  // Only the last window of the sequence can be partial, and if selected it is the last of
-  // the ascending list, so slot m < k starts at m*win.
-  int n_rev_kept = k * sp.win;
-  if (k > 0) {
-    const int last = (int)keys[k - 1];
-    const int missing = (last + 1) * sp.win - n_review;
-    if (missing > 0) n_rev_kept -= missing;
-  }
   const int nk = n_rev_kept + s.w_obs;
   for (int r = tid; r < s.nkeep_max; r += TOPK_THREADS) {
     int tok = -1;
@@ -184,22 +223,6 @@ __device__ __forceinline__ void topk_body(const Shape &s, const SeqParam sp, uin
     trow[r] = tok;
   }
   if (tid == 0) n_keep[row] = nk;
-}
-
-__global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams bp, GroupK gk,
-                                                            const float *__restrict__ sc,
-                                                            int32_t *__restrict__ win_idx,
-                                                            int32_t *__restrict__ tok_idx,
-                                                            int32_t *__restrict__ n_keep) {
-  extern __shared__ uint32_t keys[];            // [nw_max], later reused for the selected list
-  const int bh = blockIdx.x, b = bh / s.Hkv, g = blockIdx.y;
-  SeqParam sp = bp.seq[b];
-  if (gk.in_use) sp.k = gk.k[g * s.B + b];      // the group's own budget
-  const int nw = (sp.L - s.w_obs + sp.win - 1) / sp.win;
-  const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
-  const float *srow = sc + row * s.nw_max;
-  for (int w = threadIdx.x; w < nw; w += TOPK_THREADS) keys[w] = float_to_key(srow[w]);
-  topk_body(s, sp, keys, row, win_idx, tok_idx, n_keep);
 }
 
 hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
