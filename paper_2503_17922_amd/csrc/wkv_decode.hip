@@ -5,7 +5,8 @@
 // is read once and used for G = Hq/Hkv dot products, so the step is bound by the HBM stream of
 // the two caches; what matters is that the arithmetic per row stays well below the memory rate.
 //
-//   partial kernel  grid (splits, B*Hkv): a workgroup walks one key range of one KV head.
+//   partial kernel  grid (splits, B*Hkv): a workgroup walks one key range of one KV head, over the rows
+//                   that are in the cache already.
 //                   fp32 inputs: everything on the vector ALU, as follows.  16-bit inputs: the
 //                   scores come from the matrix pipe (decode_partial_mfma_kernel below), the
 //                   value side keeps this layout.  A
@@ -15,10 +16,12 @@
 //                   piece) per query head, so nothing crosses lanes inside the loop except the
 //                   dot-product reduction within a row's lanes; lane groups, then waves, merge
 //                   once at the end and the workgroup writes (m, l, o) to the workspace.
-//   combine kernel  grid (B*Hkv): merges the splits, normalises, writes fp32 output, bumps the
-//                   row count.
+//   combine kernel  grid (B*Hkv, G): merges the key ranges of one query head and the new token (one dot
+//                   product; its row is appended to the caches here), normalises, writes fp32 output, bumps
+//                   the row count.
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "wkv_device.h"
 
@@ -43,6 +46,7 @@ template <> struct Piece<half_t> {
 #pragma unroll
     for (int i = 0; i < 8; ++i) f[i] = (float)h[i];
   }
+  static __device__ __forceinline__ float value(const half_t *p) { return (float)__builtin_bit_cast(_Float16, p->bits); }
 };
 template <> struct Piece<uint16_t> {
   static constexpr int E = 8;
@@ -54,12 +58,14 @@ template <> struct Piece<uint16_t> {
       f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
   }
+  static __device__ __forceinline__ float value(const uint16_t *p) { return bf16_to_float(*p); }
 };
 template <> struct Piece<float> {
   static constexpr int E = 4;
   static __device__ __forceinline__ void unpack(const uint4 &r, float (&f)[4]) {
     f[0] = __uint_as_float(r.x); f[1] = __uint_as_float(r.y); f[2] = __uint_as_float(r.z); f[3] = __uint_as_float(r.w);
   }
+  static __device__ __forceinline__ float value(const float *p) { return *p; }
 };
 
 // Sum over the LPK (8, 16 or 32) adjacent lanes that hold one row; every lane gets the total.
@@ -86,9 +92,17 @@ __device__ __forceinline__ void merge_state(float &m, float &l, float (&o)[E], f
   m = mn;
 }
 
-// Partial result of one (row of the grid, split): per query head g, D output channels then m, l.
-__device__ __forceinline__ int64_t part_offset(const DecodeShape &s, int bh, int split, int g) {
-  return (((int64_t)bh * s.n_splits + split) * s.G + g) * (s.d + 2);
+// Partial results in the workspace: the outputs [B*Hkv][splits][G][D] of every key range (only of ranges that
+// hold rows), then their (m, l) [B*Hkv][splits][G].  A range past the end of a row has m = -inf; m of range 0
+// is NaN where the cache cannot take the new row.
+__device__ __forceinline__ int64_t part_index(const DecodeShape &s, int bh, int split, int g) {
+  return ((int64_t)bh * s.n_splits + split) * s.G + g;
+}
+__device__ __forceinline__ float2 *part_stats(const DecodeShape &s, float *part) {
+  return (float2 *)(part + (int64_t)s.B * s.Hkv * s.n_splits * s.G * s.d);
+}
+__device__ __forceinline__ const float2 *part_stats(const DecodeShape &s, const float *part) {
+  return (const float2 *)(part + (int64_t)s.B * s.Hkv * s.n_splits * s.G * s.d);
 }
 
 // Merge the per-wave states in LDS ([wave][head][D outputs, m, l]) and store the workgroup's
@@ -111,16 +125,27 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeShape &s, floa
         oo += wave_state[w][g][c] * a;
       }
     }
-    float *dst = part + part_offset(s, bh, split, g);
-    dst[c] = oo;
-    if (c == 0) { dst[D] = mm; dst[D + 1] = ll; }
+    const int64_t at = part_index(s, bh, split, g);
+    part[at * D + c] = oo;
+    if (c == 0) part_stats(s, part)[at] = make_float2(mm, ll);
   }
+}
+
+// A key range without rows says so in its statistics; so does range 0 of a row that cannot take another token.
+template <int G>
+__device__ __forceinline__ bool nothing_to_do(const DecodeShape &s, int bh, int split, int n, int c0, int cend,
+                                              float *__restrict__ part) {
+  if (c0 < cend) return false;
+  if (threadIdx.x < G)
+    part_stats(s, part)[part_index(s, bh, split, threadIdx.x)] =
+        make_float2(split == 0 && (n < 0 || n >= s.capacity) ? __uint_as_float(0x7fc00000u) : -INFINITY, 0.0f);
+  return true;
 }
 
 template <typename T, int D, int G>
 __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape s, const T *__restrict__ q_new,
-                                                                     const T *__restrict__ k_new,
-                                                                     const T *__restrict__ v_new, T *k_cache, T *v_cache,
+                                                                     const T *__restrict__ k_cache,
+                                                                     const T *__restrict__ v_cache,
                                                                      const int32_t *__restrict__ n_valid,
                                                                      float *__restrict__ part) {
   constexpr int E = Piece<T>::E;
@@ -132,21 +157,11 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / LPK, piece = lane % LPK;
   const int n = n_valid[bh];
-  const bool usable = n >= 0 && n < s.capacity;       // room for the new row
-  const int n_total = usable ? n + 1 : 0;             // rows attended to, the new one last
+  const int c0 = split * s.chunk, cend = min(c0 + s.chunk, n < s.capacity ? n : 0);
+  if (nothing_to_do<G>(s, bh, split, n, c0, cend, part)) return;
 
-  T *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh;
-  T *vc = v_cache + (int64_t)b * s.sb + (int64_t)h * s.sh;
-  const T *kn = k_new + ((int64_t)b * s.Hkv + h) * D;
-  const T *vn = v_new + ((int64_t)b * s.Hkv + h) * D;
-
-  // append: the first workgroup of the row copies the new K/V row into the caches.  Nobody
-  // reads it from there in this launch (the new row is always taken from k_new / v_new).
-  if (split == 0 && usable && threadIdx.x < 2 * LPK) {
-    const int pc = threadIdx.x % LPK;
-    if (threadIdx.x < LPK) *(uint4 *)(kc + (int64_t)n * s.st + pc * E) = *(const uint4 *)(kn + pc * E);
-    else *(uint4 *)(vc + (int64_t)n * s.st + pc * E) = *(const uint4 *)(vn + pc * E);
-  }
+  const T *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh;
+  const T *vc = v_cache + (int64_t)b * s.sb + (int64_t)h * s.sh;
 
   // this lane's piece of the G query rows, pre-multiplied by scale * log2(e)
   float qv[G][E];
@@ -166,28 +181,23 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
     for (int c = 0; c < E; ++c) o[g][c] = 0.0f;
   }
 
-  const int c0 = split * s.chunk, cend = min(c0 + s.chunk, n_total);
   // rows of this wave: tiles of KPT rows, tile index wave, wave + DEC_WAVES, ...; DEC_U tiles per batch
-  auto row_ptr = [&](const T *cache, const T *fresh, int j) -> const uint4 * {
-    // rows below n live in the cache; row n (and anything clamped past the end) is the new one
-    return (const uint4 *)(j < n ? cache + (int64_t)j * s.st + piece * E : fresh + piece * E);
-  };
   uint4 kr[DEC_U], vr[DEC_U];
   auto load_batch = [&](int t0) {
 #pragma unroll
     for (int u = 0; u < DEC_U; ++u) {
-      const int j = c0 + (t0 + u * DEC_WAVES) * KPT + slot;
-      kr[u] = *row_ptr(kc, kn, j);
-      vr[u] = *row_ptr(vc, vn, j);
+      const int64_t off = (int64_t)min(c0 + (t0 + u * DEC_WAVES) * KPT + slot, cend - 1) * s.st + piece * E;
+      kr[u] = *(const uint4 *)(kc + off);
+      vr[u] = *(const uint4 *)(vc + off);
     }
   };
   int t0 = wave;
-  if (c0 < cend) load_batch(t0);
+  load_batch(t0);
   for (; c0 + t0 * KPT < cend; t0 += DEC_U * DEC_WAVES) {
     uint4 kcur[DEC_U], vcur[DEC_U];
 #pragma unroll
     for (int u = 0; u < DEC_U; ++u) { kcur[u] = kr[u]; vcur[u] = vr[u]; }
-    load_batch(t0 + DEC_U * DEC_WAVES);          // next batch (addresses clamp to the new row past the end)
+    load_batch(t0 + DEC_U * DEC_WAVES);          // next batch (past the end: the last row again)
 
     float sc[DEC_U][G];
 #pragma unroll
@@ -256,43 +266,72 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
 // The G query rows (padded to 16) are the B operand of v_mfma_f32_16x16x32_bf16 (_f16) and 16 cache rows
 // the A operand, loaded in operand layout as in the score kernels, so a block of 16 rows costs
 // D/32 MFMAs instead of 16 * G dot-product reductions, and each lane takes the exponent of 4
-// scores instead of G per row.  The probabilities go through a small per-wave LDS tile to the
-// value side, which keeps the row-piece layout above (V is contracted over rows, the wrong way
-// round for an MFMA operand).  Every lane of a wave uses the same running maximum per head, so
-// the lane groups' outputs simply add up at the end.
+// scores instead of G per row.  V is contracted over rows, the wrong way round for an MFMA operand, and
+// stays on the vector ALU in the row-piece layout above.  In the 16x16 result the lanes of one quad (16
+// lanes) hold rows 4*quad .. 4*quad+3, lane g of the quad those of head g; a quad's lanes take these very
+// rows on the value side, so the probability of a row and head is a broadcast inside a DPP row and
+// nothing goes through LDS in the loop.  Every lane of a wave uses the same running maximum per head, so
+// the lane groups' outputs simply add up at the end: permlane swaps, which halve the number of values
+// at each step.
+// A long cache is bound by the stream of its rows.  A single sequence (a block or two per wave) is bound by
+// the length of the code itself, fetched anew in every launch, and by LDS round trips: hence no
+// LDS in the loop and no shuffles through it at the end.  One 32q/8kv-head layer with 4128 rows in ranges of
+// 64, bf16: 10.6 us with probabilities through LDS and ds_bpermute reductions, 8.6 us so.
+// The value of lane N of each 16-lane DPP row, in all its lanes.
+template <int N>
+__device__ __forceinline__ float row_bcast(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + N, 0xF, 0xF, true));   // row_newbcast
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
+}
+// (A swap's two results are read as integers first: bit-casting an element of the returned vector in place gives
+// element 0 for both.)
+struct Pair { float a, b; };
+__device__ __forceinline__ Pair swap_halves(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const unsigned a = r[0], b = r[1];
+  return {__uint_as_float(a), __uint_as_float(b)};
+}
+__device__ __forceinline__ Pair swap_rows(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const unsigned a = r[0], b = r[1];
+  return {__uint_as_float(a), __uint_as_float(b)};
+}
+// Sums over the halves of the wave (the rows of each half): the lower lanes get that of x, the upper ones that of y.
+__device__ __forceinline__ float add_halves(float x, float y) { const Pair p = swap_halves(x, y); return p.a + p.b; }
+__device__ __forceinline__ float add_rows(float x, float y) { const Pair p = swap_rows(x, y); return p.a + p.b; }
+// With one value: the sum / maximum over the lanes with equal lane % 16, in all of them.
+__device__ __forceinline__ float quads_sum(float x) { x = add_halves(x, x); return add_rows(x, x); }
+__device__ __forceinline__ float quads_max(float x) {
+  Pair p = swap_halves(x, x);
+  x = fmaxf(p.a, p.b);
+  p = swap_rows(x, x);
+  return fmaxf(p.a, p.b);
+}
+
 template <int D, int G, bool F16>
-__global__ __launch_bounds__(DEC_THREADS) void decode_partial_mfma_kernel(
-    DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *__restrict__ k_new,
-    const uint16_t *__restrict__ v_new, uint16_t *k_cache, uint16_t *v_cache, const int32_t *__restrict__ n_valid,
-    float *__restrict__ part) {
+__global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mfma_kernel(
+    DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *__restrict__ k_cache,
+    const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ n_valid, float *__restrict__ part) {
   constexpr int E = 8;
-  constexpr int LPK = D / E;                 // lanes per row (value side)
-  constexpr int KPT = 64 / LPK;              // rows per wave load instruction (value side)
-  constexpr int VT = 16 / KPT;               // value loads per block of 16 rows
+  constexpr int LPK = D / E;                 // lanes per row (value side): 16 or 8
+  constexpr int VT = D / 32;                 // value loads per block of 16 rows: rows of a quad / rows it reads at once
   constexpr int KS = D / 32;                 // MFMA steps over the channels
-  constexpr int GP = G <= 4 ? 4 : 8;         // heads padded to whole float4s in LDS
-  __shared__ float wave_state[DEC_WAVES][G][D + 2];
-  __shared__ __attribute__((aligned(16))) float p_s[DEC_WAVES][16][GP];     // probabilities of the wave's block, [row][head]
-  __shared__ __attribute__((aligned(16))) float corr_s[DEC_WAVES][GP];      // rescale factor of the outputs, per head
+  __shared__ __attribute__((aligned(16))) float o_s[DEC_WAVES][G][D];
+  __shared__ float2 ml_s[DEC_WAVES][G];
 
   const int bh = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv, split = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, quad = lane >> 4;            // score side: head, 4 rows
-  const int slot = lane / LPK, piece = lane % LPK;        // value side: row of the tile, 16-byte piece
+  const int piece = lane % LPK, sub = col / LPK;          // value side: 16-byte piece, which of the quad's rows in flight
   const int n = n_valid[bh];
-  const bool usable = n >= 0 && n < s.capacity;
-  const int n_total = usable ? n + 1 : 0;
+  const int c0 = split * s.chunk, cend = min(c0 + s.chunk, n < s.capacity ? n : 0);
+  if (nothing_to_do<G>(s, bh, split, n, c0, cend, part)) return;
 
-  uint16_t *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh;
-  uint16_t *vc = v_cache + (int64_t)b * s.sb + (int64_t)h * s.sh;
-  const uint16_t *kn = k_new + ((int64_t)b * s.Hkv + h) * D;
-  const uint16_t *vn = v_new + ((int64_t)b * s.Hkv + h) * D;
-
-  if (split == 0 && usable && threadIdx.x < 2 * LPK) {     // append (see the kernel above)
-    const int pc = threadIdx.x % LPK;
-    if (threadIdx.x < LPK) *(uint4 *)(kc + (int64_t)n * s.st + pc * E) = *(const uint4 *)(kn + pc * E);
-    else *(uint4 *)(vc + (int64_t)n * s.st + pc * E) = *(const uint4 *)(vn + pc * E);
-  }
+  const uint16_t *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh + quad * 8;
+  const uint16_t *vc = v_cache + (int64_t)b * s.sb + (int64_t)h * s.sh + piece * E;
 
   // query rows as B fragments: lane (head col, quad) holds channels 32*ks + 8*quad .. +7; heads >= G are zero
   bf16x8 qb[KS];
@@ -304,207 +343,254 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_mfma_kernel(
   }
 
   float m = -INFINITY, l = 0.0f;             // of head `col` (lanes with col < G), l over this lane's rows only
-  float o[G][E];
+  float o[G * E];                            // [head][channel of the piece]
 #pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int c = 0; c < E; ++c) o[g][c] = 0.0f;
+  for (int i = 0; i < G * E; ++i) o[i] = 0.0f;
 
-  const int c0 = split * s.chunk, cend = min(c0 + s.chunk, n_total);
-  auto k_ptr = [&](int j, int ks) -> const uint4 * {      // rows below n live in the cache, the rest is the new row
-    return (const uint4 *)((j < n ? kc + (int64_t)j * s.st : kn) + ks * 32 + quad * 8);
-  };
-  auto v_ptr = [&](int j) -> const uint4 * {
-    return (const uint4 *)((j < n ? vc + (int64_t)j * s.st : vn) + piece * E);
-  };
   uint4 kr[KS], vr[VT];
   auto load_block = [&](int blk) {
     const int r0 = c0 + blk * 16;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kr[ks] = *k_ptr(r0 + col, ks);
+    for (int ks = 0; ks < KS; ++ks) kr[ks] = *(const uint4 *)(kc + (int64_t)min(r0 + col, cend - 1) * s.st + ks * 32);
 #pragma unroll
-    for (int t = 0; t < VT; ++t) vr[t] = *v_ptr(r0 + t * KPT + slot);
+    for (int t = 0; t < VT; ++t) vr[t] = *(const uint4 *)(vc + (int64_t)min(r0 + quad * 4 + t * (4 / VT) + sub, cend - 1) * s.st);
   };
   int blk = wave;
-  if (c0 < cend) load_block(blk);
+  load_block(blk);
   for (; c0 + blk * 16 < cend; blk += DEC_WAVES) {
     uint4 kcur[KS], vcur[VT];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) kcur[ks] = kr[ks];
 #pragma unroll
     for (int t = 0; t < VT; ++t) vcur[t] = vr[t];
-    load_block(blk + DEC_WAVES);               // next block (addresses clamp to the new row past the end)
+    load_block(blk + DEC_WAVES);               // next block (past the end: the last row again)
 
     // scores of 16 rows x 16 (padded) heads
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       acc = mfma_16x16x32<F16>(*(const bf16x8 *)&kcur[ks], qb[ks], acc);
-    const int r0 = c0 + blk * 16;
-    float sc[4];
+    const int r0 = c0 + blk * 16 + quad * 4;
+    float sc[4], pr[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) sc[e] = r0 + quad * 4 + e < cend ? acc[e] * s.c1 : -INFINITY;
-    float bm = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-    bm = fmaxf(bm, __shfl_xor(bm, 16));
-    bm = fmaxf(bm, __shfl_xor(bm, 32));          // the same in the 4 lanes of a head
-    const float mn = fmaxf(m, bm);
-    float corr = 1.0f, pr[4] = {0.f, 0.f, 0.f, 0.f};
-    if (mn != -INFINITY) {
-      corr = fast_exp2(m - mn);                  // m = -inf: 0
-      m = mn;
-      float ps = 0.0f;
+    for (int e = 0; e < 4; ++e) sc[e] = r0 + e < cend ? acc[e] * s.c1 : -INFINITY;
+    const float mn = fmaxf(m, quads_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]))));   // finite: the block has a row
+    const float corr = fast_exp2(m - mn);        // m = -inf: 0
+    m = mn;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { pr[e] = fast_exp2(sc[e] - mn); ps += pr[e]; }
-      l = l * corr + ps;
-    }
-    if (col < G) {
+    for (int e = 0; e < 4; ++e) pr[e] = fast_exp2(sc[e] - mn);
+    l = l * corr + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
+    if (__any(corr != 1.0f && col < G))
+      static_for<G>([&](auto g) {
+        const float c = row_bcast<g>(corr);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) p_s[wave][quad * 4 + e][col] = pr[e];
-      if (quad == 0) corr_s[wave][col] = corr;
-    }
-    // the wave's own LDS writes above are read back below: LDS serves a wave's requests in order
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-
-    float cr[GP];
-#pragma unroll
-    for (int i = 0; i < GP; i += 4) *(float4 *)&cr[i] = *(const float4 *)&corr_s[wave][i];
-    bool rescale = false;
-#pragma unroll
-    for (int g = 0; g < G; ++g) rescale |= cr[g] != 1.0f;
-    if (__any(rescale)) {
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int c = 0; c < E; ++c) o[g][c] *= cr[g];
-    }
+        for (int i = 0; i < E; ++i) o[g * E + i] *= c;
+      });
 #pragma unroll
     for (int t = 0; t < VT; ++t) {
-      float pg[GP], vf[E];
-#pragma unroll
-      for (int i = 0; i < GP; i += 4) *(float4 *)&pg[i] = *(const float4 *)&p_s[wave][t * KPT + slot][i];
+      float vf[E];
       if constexpr (F16) Piece<half_t>::unpack(vcur[t], vf); else Piece<uint16_t>::unpack(vcur[t], vf);
+      static_for<G>([&](auto g) {
+        float p = row_bcast<g>(pr[t * (4 / VT)]);
+        if constexpr (LPK == 8) {                // two rows of the quad at once: its upper 8 lanes take the second
+          const float p1 = row_bcast<g>(pr[t * 2 + 1]);
+          p = sub ? p1 : p;
+        }
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int c = 0; c < E; ++c) o[g][c] = fmaf(pg[g], vf[c], o[g][c]);
+        for (int i = 0; i < E; ++i) o[g * E + i] = fmaf(p, vf[i], o[g * E + i]);
+      });
     }
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
   }
 
-  // the wave's totals: outputs over the lane groups (lanes with equal piece), l over the 4 lanes of a head
+  // The wave's totals.  After the two swap steps lane (quad, piece) holds 2*G of a piece's sums: those of
+  // values quad * 2*G .. +2*G-1 of [head][channel] (quad 0: the first quarter, 1: the second, ...).
+  constexpr int N = G * E;
 #pragma unroll
-  for (int g = 0; g < G; ++g)
+  for (int i = 0; i < N / 2; ++i) o[i] = add_halves(o[i], o[i + N / 2]);
 #pragma unroll
-    for (int c = 0; c < E; ++c) {
-      float x = o[g][c];
-#pragma unroll
-      for (int off = LPK; off < 64; off <<= 1) x += __shfl_xor(x, off);
-      o[g][c] = x;
-    }
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
-  if (slot == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int c = 0; c < E; ++c) wave_state[wave][g][piece * E + c] = o[g][c];
+  for (int i = 0; i < N / 4; ++i) {
+    o[i] = add_rows(o[i], o[i + N / 4]);
+    if constexpr (LPK == 8)
+      o[i] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, o[i]), 0x128, 0xF, 0xF, false));   // row_ror:8
   }
-  if (lane < G) { wave_state[wave][lane][D] = m; wave_state[wave][lane][D + 1] = l; }    // lane = head (quad 0)
-  merge_waves_and_store<D, G>(s, wave_state, bh, split, part);
+  l = quads_sum(l);
+  if (sub == 0) {
+#pragma unroll
+    for (int i = 0; i < N / 4; i += 2) {
+      const int at = quad * (N / 4) + i;         // value `at` is channel at % 8 of head at / 8; pairs never cross a head
+      *(float2 *)&o_s[wave][at / E][piece * E + at % E] = make_float2(o[i], o[i + 1]);
+    }
+  }
+  if (lane < G) ml_s[wave][lane] = make_float2(m, l);        // lane = head (quad 0)
+  __syncthreads();
+
+  // merge the waves: a thread takes four channels of one head
+  for (int i = threadIdx.x; i < G * (D / 4); i += DEC_THREADS) {
+    const int g = i / (D / 4), c = i % (D / 4) * 4;
+    float mm = -INFINITY, ll = 0.0f;
+#pragma unroll
+    for (int w = 0; w < DEC_WAVES; ++w) mm = fmaxf(mm, ml_s[w][g].x);
+    float4 oo = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < DEC_WAVES; ++w) {
+      const float a = fast_exp2(ml_s[w][g].x - mm);          // wave 0 has at least one row: mm is finite
+      const float4 x = *(const float4 *)&o_s[w][g][c];
+      ll = fmaf(ml_s[w][g].y, a, ll);
+      oo.x = fmaf(x.x, a, oo.x); oo.y = fmaf(x.y, a, oo.y); oo.z = fmaf(x.z, a, oo.z); oo.w = fmaf(x.w, a, oo.w);
+    }
+    const int64_t at = part_index(s, bh, split, g);
+    *(float4 *)(part + at * D + c) = oo;
+    if (c == 0) part_stats(s, part)[at] = make_float2(mm, ll);
+  }
 }
 
-constexpr int DEC_MAX_SPLITS = 64;
-
-__global__ __launch_bounds__(DEC_THREADS) void decode_combine_kernel(DecodeShape s, const float *__restrict__ part,
+// One workgroup per (sequence, KV head, query head): D/4 lanes hold a row of outputs, so GROUPS key ranges
+// are summed side by side.  Bound by its chain of round trips to memory (the data is a few KB a head), hence
+// the outputs of the first ranges are requested together with the statistics that weigh them.  At 8 KV heads and
+// 33 ranges 4.9 us; 7.2 us for 18 ranges by one workgroup per KV head that summed them one after the other.
+template <typename T, int D, int NT>
+__global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const T *__restrict__ q_new,
+                                                                     const T *__restrict__ k_new, const T *__restrict__ v_new,
+                                                                     T *k_cache, T *v_cache, const float *__restrict__ part,
                                                                      int32_t *n_valid, float *__restrict__ out) {
-  // weight of every (head, split) in the merged result: 2^(m_split - m) / l, or 0
-  __shared__ float wgt[8][DEC_MAX_SPLITS];
-  __shared__ float m_s[8][DEC_MAX_SPLITS], l_s[8][DEC_MAX_SPLITS];
-  const int bh = blockIdx.x, b = bh / s.Hkv, h = bh % s.Hkv;
-  const int D = s.d;
-  for (int i = threadIdx.x; i < s.G * s.n_splits; i += DEC_THREADS) {      // all (m, l) pairs at once
-    const int g = i / s.n_splits, sp = i % s.n_splits;
-    const float *p = part + part_offset(s, bh, sp, g);
-    m_s[g][sp] = p[D];
-    l_s[g][sp] = p[D + 1];
+  constexpr int COLS = D / 4, GROUPS = NT / COLS, AHEAD = 4, WAVES = NT / 64;
+  constexpr int E = Piece<T>::E, LPK = D / E;
+  __shared__ float wgt[NT];
+  __shared__ __attribute__((aligned(16))) float acc_s[GROUPS][D];
+  __shared__ float q_k[2];
+  __shared__ float wave_m[WAVES], wave_l[WAVES];
+  const int bh = blockIdx.x, g = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int grp = tid / COLS, col = tid % COLS;
+  const int64_t hq = (int64_t)b * s.Hq + (int64_t)h * s.G + g;
+
+  // statistics of this head's ranges (one per thread), outputs of the first ranges, the new token
+  const float2 none = make_float2(-INFINITY, 0.0f);
+  const float2 ml = tid < s.n_splits ? part_stats(s, part)[part_index(s, bh, tid, g)] : none;
+  const float4 *po = (const float4 *)(part + part_index(s, bh, 0, g) * D) + col;     // range sp: sp * G * COLS further on
+  float4 pre[AHEAD];
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(grp + u * GROUPS, s.n_splits - 1) * s.G * COLS];
+  const bool last_wave = wave == WAVES - 1;       // this wave also takes q . k_new
+  float dot = 0.0f;
+  if (last_wave && lane < LPK) {
+    float qf[E], kf[E];
+    Piece<T>::unpack(*(const uint4 *)(q_new + hq * D + lane * E), qf);
+    Piece<T>::unpack(*(const uint4 *)(k_new + (int64_t)bh * D + lane * E), kf);
+#pragma unroll
+    for (int c = 0; c < E; ++c) dot = fmaf(qf[c], kf[c], dot);
   }
-  __syncthreads();
-  if (threadIdx.x < s.G) {
-    const int g = threadIdx.x;
-    float mm = -INFINITY, ll = 0.0f;
-    for (int sp = 0; sp < s.n_splits; ++sp) mm = fmaxf(mm, m_s[g][sp]);
-    for (int sp = 0; sp < s.n_splits; ++sp) {
-      const float a = mm == -INFINITY ? 0.0f : fast_exp2(m_s[g][sp] - mm);
-      wgt[g][sp] = a;
-      ll += l_s[g][sp] * a;
-    }
-    // no row could be attended to (the cache is full or its count is invalid): NaN marks it
-    const float inv = ll > 0.0f ? 1.0f / ll : __uint_as_float(0x7fc00000u);
-    for (int sp = 0; sp < s.n_splits; ++sp) wgt[g][sp] *= inv;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < s.G * D; i += DEC_THREADS) {
-    const int g = i / D, c = i % D;
-    const float *p = part + part_offset(s, bh, 0, g) + c;
-    const int64_t stride = (int64_t)s.G * (D + 2);                         // between the splits of one head
-    float oo = 0.0f;
-    int sp = 0;
-    for (; sp + 4 <= s.n_splits; sp += 4) {                                 // four independent loads in flight
-      const float a0 = p[sp * stride], a1 = p[(sp + 1) * stride], a2 = p[(sp + 2) * stride], a3 = p[(sp + 3) * stride];
-      oo += a0 * wgt[g][sp] + a1 * wgt[g][sp + 1] + a2 * wgt[g][sp + 2] + a3 * wgt[g][sp + 3];
-    }
-    for (; sp < s.n_splits; ++sp) oo += p[sp * stride] * wgt[g][sp];
-    out[((int64_t)b * s.Hq + (int64_t)h * s.G + g) * D + c] = oo;
-  }
-  if (threadIdx.x == 0) {
+  // append (by head 0's workgroup); nobody reads the row from the caches in this launch
+  if (g == 0 && tid < 2 * LPK) {
     const int n = n_valid[bh];
-    if (n >= 0 && n < s.capacity && !s.keep_count) n_valid[bh] = n + 1;
+    if (n >= 0 && n < s.capacity) {
+      const int pc = tid % LPK;
+      const int64_t off = (int64_t)b * s.sb + (int64_t)h * s.sh + (int64_t)n * s.st + pc * E;
+      if (tid < LPK) *(uint4 *)(k_cache + off) = *(const uint4 *)(k_new + (int64_t)bh * D + pc * E);
+      else *(uint4 *)(v_cache + off) = *(const uint4 *)(v_new + (int64_t)bh * D + pc * E);
+    }
+  }
+  if (last_wave) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off);
+    if (lane == 0) q_k[0] = dot * s.c1;
+  }
+  float m = ml.x;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  if (lane == 0) wave_m[wave] = m;
+  if (tid == 0) q_k[1] = ml.x;                          // NaN: the cache is full or its count is invalid
+  __syncthreads();
+  const float logit = q_k[0];
+  m = logit;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) m = fmaxf(m, wave_m[w]);
+  const float a = fast_exp2(ml.x - m);                  // a range without rows: 0
+  float l = ml.x == -INFINITY ? 0.0f : ml.y * a;
+  if (tid < s.n_splits) wgt[tid] = a;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+  if (lane == 0) wave_l[wave] = l;
+  __syncthreads();
+  const float w_new = fast_exp2(logit - m);
+  l = w_new;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) l += wave_l[w];
+
+  // (outputs of a range without rows are whatever memory held: skipped, not multiplied by zero)
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int sp = grp; sp < s.n_splits; sp += AHEAD * GROUPS) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const float w = sp + u * GROUPS < s.n_splits ? wgt[sp + u * GROUPS] : 0.0f;
+      if (w != 0.0f) { o.x = fmaf(pre[u].x, w, o.x); o.y = fmaf(pre[u].y, w, o.y); o.z = fmaf(pre[u].z, w, o.z); o.w = fmaf(pre[u].w, w, o.w); }
+    }
+    if (sp + AHEAD * GROUPS < s.n_splits)
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(sp + (AHEAD + u) * GROUPS, s.n_splits - 1) * s.G * COLS];
+  }
+  *(float4 *)&acc_s[grp][col * 4] = o;
+  __syncthreads();
+  for (int c = tid; c < D; c += NT) {
+    float x = 0.0f;
+#pragma unroll
+    for (int i = 0; i < GROUPS; ++i) x += acc_s[i][c];
+    const float v = Piece<T>::value(v_new + (int64_t)bh * D + c);
+    x = fmaf(w_new, v, x) / l;
+    out[hq * D + c] = q_k[1] != q_k[1] ? q_k[1] : x;
+  }
+  if (g == 0 && tid == 0 && !s.keep_count) {
+    const int n = n_valid[bh];
+    if (n >= 0 && n < s.capacity) n_valid[bh] = n + 1;
   }
 }
 
 template <typename T, int D, int G>
-static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, const void *kn, const void *vn, void *kc,
-                             void *vc, const int32_t *n_valid, float *part, hipStream_t stream) {
+static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, const void *kc, const void *vc,
+                             const int32_t *n_valid, float *part, hipStream_t stream) {
   if constexpr (sizeof(T) == 2)     // bf16 / fp16: scores on the matrix pipe
-    hipLaunchKernelGGL((decode_partial_mfma_kernel<D, G, sizeof(T) == 2 && !__is_same(T, uint16_t)>), grid, dim3(DEC_THREADS), 0, stream, s, (const uint16_t *)q,
-                       (const uint16_t *)kn, (const uint16_t *)vn, (uint16_t *)kc, (uint16_t *)vc, n_valid, part);
+    hipLaunchKernelGGL((decode_partial_mfma_kernel<D, G, !__is_same(T, uint16_t)>), grid, dim3(DEC_THREADS), 0, stream, s,
+                       (const uint16_t *)q, (const uint16_t *)kc, (const uint16_t *)vc, n_valid, part);
   else
-    hipLaunchKernelGGL((decode_partial_kernel<T, D, G>), grid, dim3(DEC_THREADS), 0, stream, s, (const T *)q,
-                       (const T *)kn, (const T *)vn, (T *)kc, (T *)vc, n_valid, part);
+    hipLaunchKernelGGL((decode_partial_kernel<T, D, G>), grid, dim3(DEC_THREADS), 0, stream, s, (const T *)q, (const T *)kc,
+                       (const T *)vc, n_valid, part);
 }
 
 template <typename T, int D>
-static hipError_t launch_partial(const DecodeShape &s, const void *q, const void *kn, const void *vn, void *kc,
-                                 void *vc, const int32_t *n_valid, float *part, hipStream_t stream) {
+static hipError_t launch_decode_t(const DecodeShape &s, const void *q, const void *kn, const void *vn, void *kc, void *vc,
+                                  int32_t *n_valid, float *out, float *part, hipStream_t stream) {
   dim3 grid(s.n_splits, s.B * s.Hkv);
 #define WKV_DEC_CASE(GG) \
-  case GG: launch_partial_g<T, D, GG>(s, grid, q, kn, vn, kc, vc, n_valid, part, stream); break;
+  case GG: launch_partial_g<T, D, GG>(s, grid, q, kc, vc, n_valid, part, stream); break;
   switch (s.G) {
     WKV_DEC_CASE(1) WKV_DEC_CASE(2) WKV_DEC_CASE(3) WKV_DEC_CASE(4) WKV_DEC_CASE(5) WKV_DEC_CASE(6)
     WKV_DEC_CASE(7) WKV_DEC_CASE(8)
     default: return hipErrorInvalidValue;
   }
 #undef WKV_DEC_CASE
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // a wave reads eight ranges (16 at 64 channels) in its first round trip: with no more than that, one wave a head
+  static_assert(DEC_MAX_SPLITS <= DEC_THREADS, "one thread per range");
+  const dim3 heads(s.B * s.Hkv, s.G);
+  if (s.n_splits <= 1024 / D)
+    hipLaunchKernelGGL((decode_combine_kernel<T, D, 64>), heads, dim3(64), 0, stream, s, (const T *)q, (const T *)kn, (const T *)vn,
+                       (T *)kc, (T *)vc, (const float *)part, n_valid, out);
+  else
+    hipLaunchKernelGGL((decode_combine_kernel<T, D, DEC_THREADS>), heads, dim3(DEC_THREADS), 0, stream, s, (const T *)q,
+                       (const T *)kn, (const T *)vn, (T *)kc, (T *)vc, (const float *)part, n_valid, out);
   return hipGetLastError();
 }
 
 hipError_t launch_decode(const DecodeShape &s, const void *q_new, const void *k_new, const void *v_new, void *k_cache,
                          void *v_cache, int32_t *n_valid, float *out, float *part, hipStream_t stream) {
-  hipError_t e;
-  if (s.dtype == WKV_BF16)
-    e = s.d == 128 ? launch_partial<uint16_t, 128>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, part, stream)
-                   : launch_partial<uint16_t, 64>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, part, stream);
-  else if (s.dtype == WKV_F16)
-    e = s.d == 128 ? launch_partial<half_t, 128>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, part, stream)
-                   : launch_partial<half_t, 64>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, part, stream);
-  else
-    e = s.d == 128 ? launch_partial<float, 128>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, part, stream)
-                   : launch_partial<float, 64>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, part, stream);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(decode_combine_kernel, dim3(s.B * s.Hkv), dim3(DEC_THREADS), 0, stream, s, part, n_valid, out);
-  return hipGetLastError();
+#define WKV_DEC_TYPE(TT) \
+  return s.d == 128 ? launch_decode_t<TT, 128>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, part, stream) \
+                    : launch_decode_t<TT, 64>(s, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, part, stream);
+  if (s.dtype == WKV_BF16) WKV_DEC_TYPE(uint16_t)
+  if (s.dtype == WKV_F16) WKV_DEC_TYPE(half_t)
+  WKV_DEC_TYPE(float)
+#undef WKV_DEC_TYPE
 }
 
 constexpr int MAX_DEVICES = 64;

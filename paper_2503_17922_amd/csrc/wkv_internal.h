@@ -140,6 +140,8 @@ hipError_t launch_jaccard(const Shape &s, int32_t n_sets, const int32_t *tok_idx
                           hipStream_t stream);
 
 // ---- decode over the compact cache --------------------------------------------------------
+constexpr int32_t DEC_MAX_SPLITS = 256;   // key ranges per (sequence, KV head): one per thread of the combine kernel
+
 struct DecodeShape {
   int32_t B, Hq, Hkv, d, G, dtype;
   int32_t capacity;          // token rows per (sequence, KV head) in the caches
@@ -150,7 +152,7 @@ struct DecodeShape {
 };
 struct Decode {
   DecodeShape shape;
-  size_t ws_bytes;           // partial results: [B*Hkv][n_splits][G][d + 2] floats
+  size_t ws_bytes;           // partial results: [B*Hkv][n_splits][G] times d + 2 floats
 };
 wkv_status validate_decode(const wkv_decode_shape *p, Decode *out);
 hipError_t launch_decode(const DecodeShape &s, const void *q_new, const void *k_new, const void *v_new, void *k_cache,

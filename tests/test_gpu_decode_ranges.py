@@ -1,0 +1,40 @@
+"""GPU parity of the decode step where its key ranges can go wrong: row counts around the edges of blocks (16
+rows), waves and ranges, mixed with empty caches, every head layout of the value side (64 and 128 channels)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_17922_amd as W
+from oracle import wkv_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,G,d", [("bf16", 4, 128), ("f16", 7, 128), ("bf16", 1, 64), ("f16", 5, 64), ("f32", 3, 128)])
+@pytest.mark.parametrize("rows", [[0, 1, 15, 16, 17, 63, 64, 65], [127, 128, 129, 255, 256, 257, 0, 2047], [4000, 5, 0, 700, 4095, 4096, 1, 129]])
+def test_row_counts_around_range_edges(dtype, G, d, rows, device):
+    B, H = len(rows), 2
+    cap = max(rows) + 1
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
+    gen = torch.Generator(device=device).manual_seed(17 + G)
+    mk = lambda *shape: torch.randn(shape, device=device, dtype=torch.float32, generator=gen).to(tdt)
+    kc, vc, q, kn, vn = mk(B, H, cap, d), mk(B, H, cap, d), 2 * mk(B, G * H, d), mk(B, H, d), mk(B, H, d)
+    for b, n in enumerate(rows):                    # what lies past the retained rows must not matter
+        kc[b, :, n:] = float("nan")
+        vc[b, :, n:] = float("nan")
+    n_valid = torch.tensor(rows, dtype=torch.int32, device=device)[:, None].repeat(1, H).contiguous()
+    shape = W.DecodeShape(batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=d, capacity=cap,
+                          dtype={"bf16": W.WKV_BF16, "f16": W.WKV_F16, "f32": W.WKV_F32}[dtype])
+    ws = torch.full((W.wkv_decode_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device=device)     # NaNs
+    out = torch.zeros((B, G * H, d), dtype=torch.float32, device=device)
+    f64 = lambda t: t.to("cpu").to(torch.float64).numpy()
+    k0, v0 = f64(kc), f64(vc)
+    W.wkv_decode_step(shape, q, kn, vn, kc, vc, n_valid, out, ws)
+    torch.cuda.synchronize()
+    got = f64(out)
+    for b, n in enumerate(rows):
+        for h in range(H):
+            want, *_ = O.decode_step(f64(q[b, h * G:(h + 1) * G]), k0[b, h, :n], v0[b, h, :n], f64(kn[b, h]), f64(vn[b, h]))
+            np.testing.assert_allclose(got[b, h * G:(h + 1) * G], want, rtol=1e-3, atol=2e-5, err_msg=f"rows {n} h{h}")
+            assert torch.equal(kc[b, h, n], kn[b, h]) and torch.equal(vc[b, h, n], vn[b, h])
+    assert n_valid.cpu().tolist() == [[n + 1] * H for n in rows]
