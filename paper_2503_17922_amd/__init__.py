@@ -2,12 +2,14 @@
 
 Argument marshalling only: every function below has the name and the arguments of the C entry
 point it calls (see ``include/wkv.h``); tensors are handed over as raw device pointers and the
-current torch stream as the HIP stream.  Nothing is computed here, and there is no fallback:
+current torch stream as the HIP stream.  The calls made per layer or per token go through the compiled
+module ``_native`` (``csrc/wkv_python.cpp``), the others through ctypes.  Nothing is computed here, and there is no fallback:
 if the HIP library is missing, every call raises.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
 from typing import List, Optional, Sequence
 
@@ -68,6 +70,23 @@ class WorkspaceLayout(C.Structure):
 
 
 _lib = None
+_calls = None
+
+
+def native():
+    """The compiled marshalling module.  Raises if it has not been built (there is no fallback)."""
+    global _calls
+    if _calls is None:
+        lib()
+        module = importlib.import_module("._native", __name__)
+        module.set_slow_stream(_current_stream)
+        _calls = module
+    return _calls
+
+
+def _current_stream() -> int:
+    import torch
+    return torch.cuda.current_stream().cuda_stream
 
 
 def lib() -> C.CDLL:
@@ -151,6 +170,7 @@ class Problem:
                     nkeep_max = dims.nkeep_max
             if nkeep_max is not None:      # an invalid problem keeps the placeholder; every call rejects it anyway
                 self.c.out_stride_b, self.c.out_stride_h, self.c.out_stride_t = n_kv_heads * nkeep_max * d, nkeep_max * d, d
+        self._addr = C.addressof(self.c)
 
     def ref(self):
         return C.byref(self.c)
@@ -166,8 +186,7 @@ def _ptr_array(ts):
 
 def _stream(stream=None) -> C.c_void_p:
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     return C.c_void_p(int(stream))
 
 
@@ -192,26 +211,20 @@ def wkv_get_workspace_layout(problem: Problem, n_groups: int = 1) -> WorkspaceLa
 
 def wkv_score(problem, q_obs, k_first, lse_obs, t_out, workspace, stream=None) -> None:
     """``lse_obs``: float32 [batch, n_q_heads, w_obs] natural-log softmax normalisers, or None."""
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(lib().wkv_score(problem.ref(), _ptr(q_obs), _ptr(k_first), _ptr(lse_obs), _ptr(t_out), _ptr(workspace),
-                           ws_bytes, _stream(stream)))
+    _check((_calls or native()).score(problem, q_obs, k_first, lse_obs, t_out, workspace, stream))
 
 
 def wkv_window_pool(problem, t, s_out, stream=None) -> None:
-    _check(lib().wkv_window_pool(problem.ref(), _ptr(t), _ptr(s_out), _stream(stream)))
+    _check((_calls or native()).window_pool(problem, t, s_out, stream))
 
 
 def wkv_topk_windows(problem, s, win_idx_out, tok_idx_out, n_keep_out, stream=None) -> None:
-    _check(lib().wkv_topk_windows(problem.ref(), _ptr(s), _ptr(win_idx_out), _ptr(tok_idx_out),
-                                  _ptr(n_keep_out), _stream(stream)))
+    _check((_calls or native()).topk_windows(problem, s, win_idx_out, tok_idx_out, n_keep_out, stream))
 
 
 def wkv_gather_group(problem, k_layers, v_layers, tok_idx, n_keep, k_out_layers, v_out_layers,
                      stream=None) -> None:
-    n = len(k_layers)
-    _check(lib().wkv_gather_group(problem.ref(), n, _ptr_array(k_layers), _ptr_array(v_layers), _ptr(tok_idx),
-                                  _ptr(n_keep), _ptr_array(k_out_layers), _ptr_array(v_out_layers),
-                                  _stream(stream)))
+    _check((_calls or native()).gather_group(problem, k_layers, v_layers, tok_idx, n_keep, k_out_layers, v_out_layers, stream))
 
 
 class CompressCall:
@@ -248,17 +261,15 @@ def wkv_compress_groups(problem, n_groups, gamma, q_obs_groups, lse_obs_groups, 
                         k_windows_groups=None) -> None:
     """The C entry point's ``k_windows_groups`` (between ``lse_obs_groups`` and ``k_layers`` there)
     is the trailing keyword here: a nested [n_groups][batch] sequence of ints, or None."""
-    CompressCall(problem, n_groups, gamma, q_obs_groups, lse_obs_groups, k_layers, v_layers, k_out_layers,
-                 v_out_layers, win_idx_out, tok_idx_out, n_keep_out, workspace, k_windows_groups)(stream)
+    _check((_calls or native()).compress_groups(problem, n_groups, gamma, q_obs_groups, lse_obs_groups, k_windows_groups, k_layers,
+                                                v_layers, k_out_layers, v_out_layers, win_idx_out, tok_idx_out, n_keep_out,
+                                                workspace, stream))
 
 
 def wkv_compress_group(problem, gamma, q_obs, lse_obs, k_layers, v_layers, k_out_layers, v_out_layers, win_idx_out,
                        tok_idx_out, n_keep_out, workspace, stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(lib().wkv_compress_group(problem.ref(), gamma, _ptr(q_obs), _ptr(lse_obs), _ptr_array(k_layers),
-                                    _ptr_array(v_layers), _ptr_array(k_out_layers), _ptr_array(v_out_layers),
-                                    _ptr(win_idx_out), _ptr(tok_idx_out), _ptr(n_keep_out), _ptr(workspace), ws_bytes,
-                                    _stream(stream)))
+    _check((_calls or native()).compress_group(problem, gamma, q_obs, lse_obs, k_layers, v_layers, k_out_layers, v_out_layers,
+                                                win_idx_out, tok_idx_out, n_keep_out, workspace, stream))
 
 
 def wkv_index_jaccard(problem, n_sets, tok_idx, n_keep, jaccard_out, stream=None) -> None:
@@ -273,6 +284,7 @@ class DecodeShape:
                  scale: float = 0.0, cache_strides=None, flags: int = 0):
         cache_strides = cache_strides or (n_kv_heads * capacity * head_dim, capacity * head_dim, head_dim)
         self.c = _DecodeShape(batch, n_q_heads, n_kv_heads, head_dim, dtype, scale, capacity, *cache_strides, flags)
+        self._addr = C.addressof(self.c)
 
     def ref(self):
         return C.byref(self.c)
@@ -287,14 +299,11 @@ def wkv_decode_workspace_bytes(shape: DecodeShape) -> int:
 
 def wkv_decode_step(shape: DecodeShape, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, workspace,
                     stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(lib().wkv_decode_step(shape.ref(), _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
-                                 _ptr(n_valid), _ptr(out), _ptr(workspace), ws_bytes, _stream(stream)))
+    _check((_calls or native()).decode_step(shape, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, workspace, stream))
 
 
 def wkv_decode_step_static(shape: DecodeShape, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, stream=None) -> None:
-    _check(lib().wkv_decode_step_static(shape.ref(), _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
-                                        _ptr(n_valid), _ptr(out), _stream(stream)))
+    _check((_calls or native()).decode_step_static(shape, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, stream))
 
 
 def wkv_group_budgets(b_total: float, n_groups: int, lam: float) -> List[float]:

@@ -1,7 +1,8 @@
-"""Builds libwkv.so (gfx950) in-tree with hipcc.  Run as ``python -m paper_2503_17922_amd.build``."""
+"""Builds libwkv.so (gfx950) and its CPython entry in-tree.  Run as ``python -m paper_2503_17922_amd.build``."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -9,6 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libwkv.so")
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))     # the CPython entry to it
 SOURCES = ["wkv_host.cpp", "wkv_api.cpp", "wkv_score.hip", "wkv_resident.hip", "wkv_select.hip", "wkv_gather.hip",
            "wkv_decode.hip"]
 HOST_SOURCES = ["wkv_host.cpp", "wkv_api.cpp"]          # no device code: also built for the CPU-only sanitizer test
@@ -45,6 +47,10 @@ def build(verbose: bool = True) -> str:
         list(pool.map(lambda so: _run([hipcc(), *flags, "-c", os.path.join(CSRC, so[0]), "-o", so[1]], verbose),
                       zip(SOURCES, objs)))
     _run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
+    # host code only: no device, no torch headers; finds libwkv.so beside itself
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+          "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "wkv_python.cpp"), "-L", HERE, "-lwkv",
+          "-Wl,-rpath,$ORIGIN", "-o", NATIVE], verbose)
     return LIB
 
 
