@@ -286,31 +286,6 @@ template <int N, class F>
 __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
 }
-// (A swap's two results are read as integers first: bit-casting an element of the returned vector in place gives
-// element 0 for both.)
-struct Pair { float a, b; };
-__device__ __forceinline__ Pair swap_halves(float x, float y) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  const unsigned a = r[0], b = r[1];
-  return {__uint_as_float(a), __uint_as_float(b)};
-}
-__device__ __forceinline__ Pair swap_rows(float x, float y) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  const unsigned a = r[0], b = r[1];
-  return {__uint_as_float(a), __uint_as_float(b)};
-}
-// Sums over the halves of the wave (the rows of each half): the lower lanes get that of x, the upper ones that of y.
-__device__ __forceinline__ float add_halves(float x, float y) { const Pair p = swap_halves(x, y); return p.a + p.b; }
-__device__ __forceinline__ float add_rows(float x, float y) { const Pair p = swap_rows(x, y); return p.a + p.b; }
-// With one value: the sum / maximum over the lanes with equal lane % 16, in all of them.
-__device__ __forceinline__ float quads_sum(float x) { x = add_halves(x, x); return add_rows(x, x); }
-__device__ __forceinline__ float quads_max(float x) {
-  Pair p = swap_halves(x, x);
-  x = fmaxf(p.a, p.b);
-  p = swap_rows(x, x);
-  return fmaxf(p.a, p.b);
-}
-
 template <int D, int G, bool F16>
 __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mfma_kernel(
     DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *__restrict__ k_cache,

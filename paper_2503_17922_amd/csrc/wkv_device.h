@@ -48,30 +48,30 @@ __device__ __forceinline__ void merge_stats(float &m, float &z, float m2, float 
   m = mn;
 }
 
-// (m, z) of one row over the partials c = first, first + step, ... < n_chunks.  Loads are
-// issued four at a time so that their latencies overlap.
-__device__ __forceinline__ void fold_partials_strided(const float2 *__restrict__ part, int n_chunks, int first,
-                                                      int step, float &m, float &z) {
-  m = -INFINITY;
-  z = 0.0f;
-  int c = first;
-  for (; c + 3 * step < n_chunks; c += 4 * step) {
-    const float2 p0 = part[c], p1 = part[c + step], p2 = part[c + 2 * step], p3 = part[c + 3 * step];
-    const float mn = fmaxf(fmaxf(fmaxf(p0.x, p1.x), fmaxf(p2.x, p3.x)), m);
-    if (mn != -INFINITY) {
-      z = z * fast_exp2(m - mn) + p0.y * fast_exp2(p0.x - mn) + p1.y * fast_exp2(p1.x - mn) +
-          p2.y * fast_exp2(p2.x - mn) + p3.y * fast_exp2(p3.x - mn);
-      m = mn;
-    }
-  }
-  for (; c < n_chunks; c += step) merge_stats(m, z, part[c].x, part[c].y);
+// ---- exchange between the four quads of a wave (lanes l, l+16, l+32, l+48) ------------------------
+// (A swap's two results are read as integers first: bit-casting an element of the returned vector in place gives
+// element 0 for both.)
+struct Pair { float a, b; };
+__device__ __forceinline__ Pair swap_halves(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const unsigned a = r[0], b = r[1];
+  return {__uint_as_float(a), __uint_as_float(b)};
 }
-
-// lse2 of one row from its per-chunk partials (single thread).
-__device__ __forceinline__ float fold_partials(const float2 *__restrict__ part, int n_chunks) {
-  float m, z;
-  fold_partials_strided(part, n_chunks, 0, 1, m, z);
-  return m + fast_log2(z);
+__device__ __forceinline__ Pair swap_rows(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const unsigned a = r[0], b = r[1];
+  return {__uint_as_float(a), __uint_as_float(b)};
+}
+// Sums over the halves of the wave (the rows of each half): the lower lanes get that of x, the upper ones that of y.
+__device__ __forceinline__ float add_halves(float x, float y) { const Pair p = swap_halves(x, y); return p.a + p.b; }
+__device__ __forceinline__ float add_rows(float x, float y) { const Pair p = swap_rows(x, y); return p.a + p.b; }
+// With one value: the sum / maximum over the lanes with equal lane % 16, in all of them.
+__device__ __forceinline__ float quads_sum(float x) { x = add_halves(x, x); return add_rows(x, x); }
+__device__ __forceinline__ float quads_max(float x) {
+  Pair p = swap_halves(x, x);
+  x = fmaxf(p.a, p.b);
+  p = swap_rows(x, x);
+  return fmaxf(p.a, p.b);
 }
 
 // ---- MFMA building blocks ----------------------------------
@@ -79,12 +79,13 @@ constexpr int MF_THREADS = 256;           // per row half (see score_mfma_kernel
 constexpr int MF_WAVES = 4;              // waves that share the key tiles of an iteration
 constexpr int MF_KT = 2;                 // key tiles of 16 per wave iteration (share each B fragment)
 constexpr float MF_BIG = 1.0e30f;        // a tile sum above this re-references the row (2^100)
+constexpr float MF_LOW = 1.0e-12f;       // so does a running sum below this (2^-40): terms that underflow are 2^-86 of it
 
 // Arrange the M query rows of KV head h as MFMA B fragments in LDS.
 // Fragment (mt, ks) is 64 x 16 bytes: lane l holds row 16*mt + l%16, bytes 64*ks + 16*(l/16)..+15 of it.
-template <int D, int MT, int NT, int ES = 2>              // NT threads stage MT row tiles of ES-byte elements
+template <int D, int MT, int NT>                          // NT threads stage MT row tiles (16-bit elements)
 struct QStage {
-  static constexpr int KS = D * ES / 64;
+  static constexpr int KS = D / 32;
   static constexpr int TOTAL = MT * KS * 64;               // 16-byte pieces of the fragments
   static constexpr int N = (TOTAL + NT - 1) / NT;          // per thread
   uint4 v[N];
@@ -100,7 +101,7 @@ struct QStage {
       if (i < TOTAL && r < s.M) {
         const int hq = h * s.G + r / s.w_obs, io = r % s.w_obs;
         const int64_t off = (int64_t)b * s.q_sb + (int64_t)hq * s.q_sh + (int64_t)io * s.q_st;
-        v[k] = *(const uint4 *)((const char *)qbase + off * ES + ks * 64 + (l >> 4) * 16);
+        v[k] = *(const uint4 *)((const char *)qbase + off * 2 + ks * 64 + (l >> 4) * 16);
       }
     }
   }

@@ -113,6 +113,7 @@ void fill_shape(const wkv_problem *p, const wkv_dims &dims, Shape *s, BatchParam
   s->nkeep_max = dims.nkeep_max; s->dtype = p->dtype;
   s->fill_padding = (p->flags & WKV_KEEP_PADDING) ? 0 : 1;
   const double scale = p->scale > 0.0f ? (double)p->scale : 1.0 / std::sqrt((double)p->head_dim);
+  s->w_magic = 65536u / (uint32_t)p->w_obs + 1u;
   s->c1 = (float)(scale * 1.4426950408889634074);
   s->q_sb = p->q_stride_b; s->q_sh = p->q_stride_h; s->q_st = p->q_stride_t;
   s->kv_sb = p->kv_stride_b; s->kv_sh = p->kv_stride_h; s->kv_st = p->kv_stride_t;
@@ -124,9 +125,6 @@ void fill_shape(const wkv_problem *p, const wkv_dims &dims, Shape *s, BatchParam
     bp->seq[b].p = p->top_p[b] < p->win[b] ? p->top_p[b] : p->win[b];
     bp->seq[b].k = p->k_windows[b];
   }
-  for (int b = 0; b < WKV_MAX_BATCH; ++b) bp->by_length[b] = (uint8_t)b;
-  std::stable_sort(bp->by_length, bp->by_length + p->batch,
-                   [&](uint8_t a, uint8_t c) { return p->seq_len[a] < p->seq_len[c]; });
 }
 
 // Number of (row, chunk) work items that hold at least one key, for chunks of `chunk` keys.
@@ -136,41 +134,57 @@ static int64_t count_items(const BatchParams &bp, int32_t B, int64_t rows_per_se
   return n;
 }
 
-// Keys per workgroup.  The score kernels keep three workgroups resident on each of the 256
-// compute units (one, with more than 128 softmax rows), and a workgroup's fixed cost (staging
-// the query fragments, the first key load, the epilogue) is several microseconds: the launch is
-// fastest when its non-empty work items fill those `slots` a whole number of times with chunks
-// as long as the kernels allow.
-// Chunks are multiples of 128 keys (one iteration of a workgroup); `drop` keys at the end of
-// every sequence are not part of the pass.
+// Keys per workgroup.  A workgroup's fixed cost (its query fragments, the first key tiles, the
+// epilogue) is several microseconds: the launch is fastest when its non-empty work items fill the
+// `slots` that the device holds at a time a whole number of times, with chunks as long as that allows.
+// Chunks are multiples of CHUNK_UNIT keys; `drop` keys at the end of every sequence are not part of the pass.
 static int32_t pick_chunk(const BatchParams &bp, int32_t B, int64_t rows_per_seq, int32_t drop, int32_t lo, int32_t hi,
                           int64_t slots) {
   int64_t total = 0;
   for (int32_t b = 0; b < B; ++b) total += (int64_t)std::max(bp.seq[b].L - drop, 0) * rows_per_seq;
   if (total <= 0) return lo;
   for (int64_t rounds = 1; rounds <= 64; ++rounds) {
-    int64_t c = ceil_div(ceil_div(total, slots * rounds), 128) * 128;
+    int64_t c = ceil_div(ceil_div(total, slots * rounds), CHUNK_UNIT) * CHUNK_UNIT;
     if (c < lo) return lo;
-    while (c <= hi && count_items(bp, B, rows_per_seq, drop, (int32_t)c) > slots * rounds) c += 128;
+    while (c <= hi && count_items(bp, B, rows_per_seq, drop, (int32_t)c) > slots * rounds) c += CHUNK_UNIT;
     if (c <= hi) return (int32_t)c;
   }
   return hi;
 }
 
+// Chunks of at most c keys per sequence, equal among themselves.  Only what holds keys becomes a workgroup: the
+// dispatcher deals workgroup numbers round-robin to the 8 XCDs, and numbers without work would leave some
+// of them more of the rest than others.
+static void plan_pass(const BatchParams &bp, int32_t B, int32_t drop, int32_t c, PassPlan *pp) {
+  std::memset(pp, 0, sizeof(*pp));
+  for (int32_t b = 0; b < B; ++b) {
+    const int64_t keys = std::max(bp.seq[b].L - drop, 1), n = ceil_div(keys, c);
+    pp->chunk[b] = (uint8_t)ceil_div(ceil_div(keys, n), CHUNK_UNIT);
+    pp->first[b + 1] = pp->first[b] + (int32_t)ceil_div(keys, pp->chunk[b] * CHUNK_UNIT);
+  }
+}
+
 ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   ScorePlan pl;
   pl.m_pad = (s.M + 15) / 16 * 16;
-  const bool f32 = s.dtype == WKV_F32;
   const int64_t rows_per_seq = (int64_t)s.Hkv * n_groups;
-  const int32_t Lmax = s.t_stride + s.w_obs;
-  const int64_t slots = pl.m_pad > 128 ? 256 : (f32 ? 512 : 768);
-  pl.chunk1 = pick_chunk(bp, s.B, rows_per_seq, 0, 256, MAX_CHUNK1, slots);
-  pl.n_chunks1 = (int32_t)ceil_div(Lmax, pl.chunk1);
-  pl.chunk2 = pick_chunk(bp, s.B, rows_per_seq, s.w_obs, 256, max_chunk2(f32), slots);
-  pl.n_chunks2 = (int32_t)ceil_div(s.t_stride > 0 ? s.t_stride : 1, pl.chunk2);
-  // every pass-2 workgroup re-reads rows * n_chunks1 partials when it folds them itself: worth
-  // it (one launch less) only while that stays a few KB
-  pl.fold_in_pass2 = pl.n_chunks1 <= 16;
+  // Workgroups that the device holds at a time (256 compute units): two per unit with one row group (half the
+  // LDS and the registers), else one.  Up to 1024 keys per compute unit one is better all the same: the
+  // shorter chain of a smaller chunk does not make up for the second prologue and the larger fold (16384
+  // tokens, 8 KV heads: passes of 14.0 + 14.5 us with one, 15.5 + 18.5 us with two; 32768 tokens: 19.6 + 19.5 against
+  // 20.3 + 23.1 us; from 65536 on the same).
+  const int32_t wave_rows = s.dtype == WKV_F32 && s.d == 128 ? 64 : 128;
+  int64_t keys = 0;
+  for (int32_t b = 0; b < s.B; ++b) keys += bp.seq[b].L * rows_per_seq;
+  const int64_t slots = pl.m_pad <= wave_rows && keys > 256 * 1024 ? 512 : 256;
+  const int32_t shortest = 2 * CHUNK_UNIT, longest = 8192;
+  plan_pass(bp, s.B, 0, pick_chunk(bp, s.B, rows_per_seq, 0, shortest, longest, slots), &pl.pass[0]);
+  plan_pass(bp, s.B, s.w_obs, pick_chunk(bp, s.B, rows_per_seq, s.w_obs, shortest, longest, slots), &pl.pass[1]);
+  pl.n_chunks1 = 0;
+  for (int32_t b = 0; b < s.B; ++b) pl.n_chunks1 = std::max(pl.n_chunks1, pl.pass[0].first[b + 1] - pl.pass[0].first[b]);
+  // every pass-2 workgroup re-reads the partials of its rows when it folds them itself: 64 KB at 128 rows and 64
+  // chunks, about what the extra launch costs
+  pl.fold_in_pass2 = pl.n_chunks1 <= 64;
   return pl;
 }
 

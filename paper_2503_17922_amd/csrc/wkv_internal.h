@@ -20,10 +20,6 @@ struct SeqParam {
 };
 struct BatchParams {
   SeqParam seq[WKV_MAX_BATCH];
-  // The sequences in ascending length: the statistics pass dispatches the rows of short sequences
-  // first (in a batch of mixed lengths that shortens the launch; measured 6 % on a batch of eight
-  // prefixes between 4.8K and 31K tokens).  A permutation of 0 .. batch-1; identity beyond.
-  uint8_t by_length[WKV_MAX_BATCH];
 };
 
 // Windows to keep per (group, sequence) when the groups have budgets of their own (Section
@@ -56,6 +52,7 @@ struct Shape {
   int32_t t_stride, nw_max, k_max, nkeep_max;
   int32_t dtype;
   int32_t fill_padding;   // gather: zero the compact-cache rows past n_keep
+  uint32_t w_magic;   // r / w_obs == r * w_magic >> 16 for row numbers r < 256
   float c1;           // logit scale * log2(e): logits are handled in base-2 units
   int64_t q_sb, q_sh, q_st;
   int64_t kv_sb, kv_sh, kv_st;
@@ -63,16 +60,19 @@ struct Shape {
 };
 
 // How the score passes split the key axis into workgroup chunks.
-// Longest key chunk of one workgroup: pass 1 keeps nothing per key; pass 2 stages the chunk's
-// token scores in LDS (4 bytes per key).
-constexpr int32_t MAX_CHUNK1 = 8192;
-constexpr int32_t MAX_CHUNK2 = 4096;
-// fp32 query fragments take 64 KB of LDS per 128 softmax rows, which leaves less for the staging.
-constexpr int32_t max_chunk2(bool f32) { return f32 ? 2048 : MAX_CHUNK2; }
+// Token scores that the score pass stages in LDS before it pools them or writes them out.
+constexpr int32_t SCORE_SEG = 2048;
 
+// One pass: sequence b of a row takes the workgroups first[b] .. first[b+1]-1, chunk[b] keys each (the last one what
+// is left).  At least one each, so that the padding of its outputs has an owner.
+constexpr int32_t CHUNK_UNIT = 64;                // a tile for every key slot of a workgroup
+struct PassPlan {
+  int32_t first[WKV_MAX_BATCH + 1];
+  uint8_t chunk[WKV_MAX_BATCH];                   // in units of CHUNK_UNIT keys
+};
 struct ScorePlan {
-  int32_t chunk1, n_chunks1;   // stats pass
-  int32_t chunk2, n_chunks2;   // score pass (over t_stride)
+  PassPlan pass[2];            // statistics, scores
+  int32_t n_chunks1;           // most workgroups of a sequence in the statistics pass
   int32_t m_pad;               // rows padded to a multiple of 16
   bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
 };
@@ -99,7 +99,7 @@ struct ResidentPlan {
 };
 
 struct Workspace {
-  float2 *partials;   // [n_groups][B][Hkv][m_pad][n_chunks1] (running max, sum) in base 2
+  float2 *partials;   // [n_groups][B][Hkv][n_chunks1][m_pad] (running max, sum) in base 2
   float *lse;         // [n_groups][B][Hkv][m_pad] base-2 log-sum-exp of every softmax row
   float *t;           // [n_groups][B][Hkv][t_stride]
   float *s;           // [n_groups][B][Hkv][nw_max]

@@ -70,7 +70,7 @@ __device__ __forceinline__ void pool_windows(float *t_s, int w0, int w1, int win
     const int n = min(w1 * win, n_review) - w0 * win;
     if (p < win) {
       uint32_t drop = 0u;                              // one bit per token of this thread: at most 32 (see the assert)
-      static_assert(MAX_CHUNK2 + WKV_MAX_WIN <= 32 * NT, "tokens per thread");
+      static_assert(SCORE_SEG <= 32 * NT, "tokens per thread");
       for (int e = threadIdx.x, i = 0; e < n; e += NT, ++i) {
         const int first = e / win * win, last = min(first + win, n);
         const float v = t_s[e];

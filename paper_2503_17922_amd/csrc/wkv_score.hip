@@ -10,16 +10,17 @@
 //   pass 1 (stats)  per (row, key chunk): running maximum m and sum z = sum 2^(v - m) of the
 //                   base-2 logits v = (q.k) * scale * log2(e), with the causal mask of the
 //                   observation block applied.  Partials go to the workspace.
-//   fold            one tiny launch turns the partials of every row into lse2_i = m_i + log2(z_i).
+//   fold            the partials of every row become lse2_i = m_i + log2(z_i) (in pass 2's prologue; a launch
+//                   of its own when a row has very many chunks).
 //   pass 2 (score)  each workgroup recomputes its logits and writes t_j = sum_i 2^(v_ij - lse2_i).
 //
 // A caller whose prefill attention kept the normalisers of the observation rows hands them
 // over; pass 1 and the fold are then skipped and the keys are read once.
 //
 // Both passes run on the matrix pipe: v_mfma_f32_16x16x32_bf16 / _f16 for 16-bit inputs, v_mfma_f32_16x16x4_f32
-// for fp32 inputs, with the keys as the A operand, loaded straight from global memory into registers in
-// operand layout, so K never passes through LDS and the waves of a workgroup never synchronise in the
-// loop; the query rows are the B operand, read as pre-arranged fragments from LDS.
+// for fp32 inputs.  Every wave holds the query fragments of its row tiles in registers for the whole launch and
+// reads 16-key tiles from a ring in LDS that it fills itself, by DMA from global memory several tiles
+// ahead: the waves of a workgroup do not synchronise in the loop, and nothing but the keys crosses LDS.
 #include "wkv_device.h"
 #include "wkv_pool.h"
 
@@ -28,6 +29,51 @@ namespace wkv {
 // =========================================================================================
 // fold: per-chunk (m, z) partials of pass 1 -> one lse2 per row, once per (group, sequence, KV head)
 // =========================================================================================
+// Partials lie [chunk][row]: the threads of a workgroup take consecutive rows and every so many chunks, so the
+// reads are coalesced and, sixteen at a time, independent of each other.
+__device__ __forceinline__ void fold_rows(const float2 *__restrict__ part, int n_chunks, int m_pad, int r, int first, int step,
+                                          float &m, float &z) {
+  m = -INFINITY;
+  z = 0.0f;
+  constexpr int N = 16;                                 // (64 partials by two threads: two round trips)
+  for (int c = first; c < n_chunks; c += N * step) {
+    float2 p[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = part[(int64_t)min(c + i * step, n_chunks - 1) * m_pad + r];
+    float mn = m;
+#pragma unroll
+    for (int i = 0; i < N; ++i) mn = c + i * step < n_chunks ? fmaxf(mn, p[i].x) : mn;
+    if (mn == -INFINITY) continue;
+    z *= fast_exp2(m - mn);
+#pragma unroll
+    for (int i = 0; i < N; ++i) z += c + i * step < n_chunks ? p[i].y * fast_exp2(p[i].x - mn) : 0.0f;
+    m = mn;
+  }
+}
+
+// lse2 of the rows of one (group, sequence, KV head) into lse[0 .. rows-1] by NT threads; padded rows get +inf
+// (2^-inf = 0: they contribute nothing).  part_s: NT entries of scratch.  Synchronises before it returns.
+template <int NT>
+__device__ __forceinline__ void fold_all(const Shape &s, int n_chunks, int m_pad, const float2 *__restrict__ part, int rows,
+                                         float2 *part_s, float *lse) {
+  const int tpr = max(NT / rows, 1);                    // threads per row
+  for (int r0 = 0; r0 < rows; r0 += NT / tpr) {
+    const int r = r0 + threadIdx.x % (NT / tpr), which = threadIdx.x / (NT / tpr);
+    float m = -INFINITY, z = 0.0f;
+    if (r < s.M) fold_rows(part, n_chunks, m_pad, r, which, tpr, m, z);
+    part_s[threadIdx.x] = make_float2(m, z);
+    __syncthreads();
+    if (which == 0 && r < rows) {
+      for (int i = 1; i < tpr; ++i) {
+        const float2 p = part_s[threadIdx.x + i * (NT / tpr)];
+        merge_stats(m, z, p.x, p.y);
+      }
+      lse[r] = r < s.M ? m + fast_log2(z) : INFINITY;
+    }
+    __syncthreads();
+  }
+}
+
 constexpr int FOLD_THREADS = 256;
 
 __global__ __launch_bounds__(FOLD_THREADS) void fold_kernel(Shape s, ScorePlan pl, const float2 *__restrict__ partials,
@@ -35,28 +81,14 @@ __global__ __launch_bounds__(FOLD_THREADS) void fold_kernel(Shape s, ScorePlan p
   __shared__ float2 part_s[FOLD_THREADS];
   if (only_if && *only_if == 0u) return;
   const int64_t row = (int64_t)blockIdx.y * s.B * s.Hkv + blockIdx.x;
-  // TPR threads share a row; rows are handled in passes of FOLD_THREADS / TPR
-  const int TPR = pl.m_pad >= 128 ? 2 : (pl.m_pad >= 64 ? 4 : 8);
-  const int rows_per_pass = FOLD_THREADS / TPR;
-  for (int r0 = 0; r0 < pl.m_pad; r0 += rows_per_pass) {
-    const int r = r0 + threadIdx.x % rows_per_pass, part_id = threadIdx.x / rows_per_pass;
-    float m = -INFINITY, z = 0.0f;
-    if (r < s.M)
-      fold_partials_strided(partials + (row * pl.m_pad + r) * pl.n_chunks1, pl.n_chunks1, part_id, TPR, m, z);
-    __syncthreads();
-    part_s[threadIdx.x] = make_float2(m, z);
-    __syncthreads();
-    if (part_id == 0 && r < pl.m_pad) {
-      for (int i = 1; i < TPR; ++i) merge_stats(m, z, part_s[i * rows_per_pass + threadIdx.x].x, part_s[i * rows_per_pass + threadIdx.x].y);
-      lse[row * pl.m_pad + r] = r < s.M ? m + fast_log2(z) : INFINITY;   // padded rows: 2^-inf = 0
-    }
-  }
+  const int b = blockIdx.x / s.Hkv;
+  fold_all<FOLD_THREADS>(s, pl.pass[0].first[b + 1] - pl.pass[0].first[b], pl.m_pad, partials + row * pl.n_chunks1 * pl.m_pad, pl.m_pad, part_s,
+                         lse + row * pl.m_pad);
 }
 
 // The base-2 log-sum-exp of softmax row r of (group g, sequence b, KV head h): converted from the
 // caller's natural-log normalisers [B, Hq, w_obs] when they were handed over (the rows of a KV
-// head are contiguous there), else what the fold left in the workspace.  Padded rows get +inf
-// (2^-inf = 0: they contribute nothing).
+// head are contiguous there), else what the fold left in the workspace.  Padded rows get +inf.
 __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, const GroupPtrs &gp,
                                           const float *__restrict__ lse_ws, int g, int b, int h, int64_t row, int r) {
   if (r >= s.M) return INFINITY;
@@ -66,295 +98,385 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 }
 
 // =========================================================================================
-// MFMA kernels
+// the two passes
 // =========================================================================================
-// Orientation: D[key, query row] = sum_c K[key, c] * Q[row, c].  The keys are the A operand (16
-// keys x 64 bytes of each per step, loaded straight from global memory: lane l holds key
-// l%16, the 16-byte piece l/16 of a 64-byte run, so the four lanes of a key read 64 contiguous
-// bytes), the stacked query rows are the B operand (fragments pre-arranged in LDS, one
-// conflict-free ds_read_b128 each).  In the 16x16 result a lane holds 4 consecutive keys of
-// ONE query row per row tile, so a lane needs only MT row constants (reference / lse2), the
-// row statistics of pass 1 are in-lane accumulations merged once per chunk, and the column
-// sums of pass 2 are in-lane adds over the row tiles plus one 16-lane DPP reduction.
-// PASS 1: stats.  PASS 2: scores.
+// A 16x16 tile of logits takes 16 rows of each operand, 64 bytes of a row per step: lane l holds row l%16, the
+// 16-byte piece l/16.  Both operands have this layout, so which of them is A is a free choice per pass:
+//   PASS 1 (stats)   keys as A: a lane gets 4 consecutive keys of ONE query row per row tile, so the row
+//                    statistics are in-lane accumulations (RT of them), merged once per chunk.
+//   PASS 2 (scores)  queries as A: a lane gets 4 query rows of ONE key, so a key's column sum is in-lane adds
+//                    over all row tiles plus two permlane swaps.
 //
-// Up to 128 rows (HV = 1) a workgroup is 4 waves that take different key tiles of an iteration
-// and all MT row tiles each; three workgroups share a CU.  With 129..256 rows (HV = 2: eight
-// query heads per KV head at 32 observation queries) a workgroup is 8 waves: waves 0-3 work on
-// row tiles 0..MT-1 and waves 4-7 on row tiles MT..2MT-1 of the same key tiles (the second
-// read of a key tile hits the CU's vector cache), the 64 KB of query fragments allow one
-// workgroup per CU, and pass 2 adds the column sums of the two halves in its epilogue.
+// Waves.  HV waves share a key tile slot and take RT row tiles each (128 rows a wave at most, 64 for fp32 with 128
+// channels: the queries take RT * D * esize / 16 registers); the KW slots of a workgroup take the chunk's key
+// tiles in turn.  Two waves fit a SIMD.
 //
-// fp32 inputs take the same kernels with v_mfma_f32_16x16x4_f32 (fp32 products and sums): their passes are
-// bound by that instruction (32 cycles for 2 KFLOP), their query fragments are twice as large (64 KB per 128
-// rows: two workgroups per CU, half the chunk).  Eq. 1-2 of one 4096-token group (32q/8kv heads, d = 128):
-// 263 us with one vector FMA per product, thread per row / thread per key, 51 us here.
-template <int D, int MT, int HV, int PASS, int DT>
-__global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) void score_mfma_kernel(Shape s, BatchParams bp, GroupPtrs gp,
-                                                                   ScorePlan pl, float2 *__restrict__ partials,
-                                                                   const float *__restrict__ lse_g,
-                                                                   float *__restrict__ t_out,
-                                                                   float *__restrict__ s_pool,
-                                                                   const uint32_t *__restrict__ only_if) {
-  constexpr int ES = DT == DT_F32 ? 4 : 2;             // bytes per element
-  constexpr int KS = D * ES / 64;
-  constexpr int STEP = 16 * MF_KT;                    // keys per wave iteration
-  constexpr int NT = MF_THREADS * HV;                 // threads of the workgroup
+// The ring.  A slot has NS places of 16 key rows each.  A DMA instruction (global_load_lds_dwordx4) writes 64 pieces
+// of 16 bytes in lane order; which piece of its row a lane fetches is permuted (swizzle) so that the 16 lanes
+// that later read the same piece of 16 rows find them in different banks.  Global reads stay whole rows.
+// Tile i is in registers (the next one being read from LDS) while tiles i+2 .. i+NS are on their way; the loads are
+// counted by hand (s_waitcnt vmcnt), which holds because the loop has no other global access.  With one row group
+// a wave fills its own slot and the waves never synchronise in the loop; with several, the waves of a slot
+// fetch a part of each tile and the workgroup meets at a barrier per tile (fetching every tile once per row
+// group instead would leave half the bytes in flight).
+//
+// What bounds it.  Per 64 logits a SIMD issues one 16x16x32 MFMA (8.6 ns on random data at the clocks the chip then
+// holds) and one multiply-add, exponential and add (7.8 ns); they hardly overlap: 13 ns together in a loop of
+// nothing else, in whatever order they are written.  The 32K-token model (8 groups, 128 rows): 108 + 107 us for
+// the two passes, 70-76 us without the loads, 91-95 us without the arithmetic (5.9 TB/s: HBM).  The kernels before this
+// one kept the queries in LDS, read the keys in operand layout straight from global memory and took 111 + 107 us there;
+// 12.0 + 11.6 us for a group of 4096 tokens (now 9.4 + 8.8: half the code to fetch, one round of loads in the
+// prologue), 15.9 + 9.3 (fold) + 14.7 us for 16384 tokens (14.0 + 14.5), 28.3 + 27.7 us for 4096 tokens in fp32 (19.4 + 19.2),
+// 54 + 50 us for 48 rows of ragged sequences with 224 softmax rows (49 + 50).
+constexpr int score_slots(int row_groups) { return row_groups == 4 ? 2 : 4; }         // key tile slots of a workgroup
+constexpr int score_threads(int row_groups) { return 64 * row_groups * score_slots(row_groups); }
+
+template <int D, int DT, int RT, int HV>
+struct ScoreConfig {
+  static constexpr int ES = DT == DT_F32 ? 4 : 2;       // bytes per element
+  static constexpr int ROWB = D * ES;                   // bytes per key row
+  static constexpr int KS = ROWB / 64;                  // steps of a contraction
+  static constexpr int TILE = 16 * ROWB;
+  static constexpr int PPR = ROWB / 16;                 // 16-byte pieces per row: 8, 16 or 32
+  static constexpr int RPI = 64 / PPR;                  // rows per DMA instruction
+  static constexpr int LPT = TILE / 1024 / HV;          // DMA instructions per tile and wave
+  static constexpr int KW = score_slots(HV), NT = score_threads(HV), WAVES = NT / 64;
+  static constexpr int FIT = (HV == 1 ? 65536 : 131072) / (KW * TILE);
+  static constexpr int NS = FIT < 8 * HV ? FIT : 8 * HV;
+  static constexpr int RING = KW * NS * TILE;
+  // the queries pass through the part of the ring that is filled last
+  static constexpr int QBYTES = HV * RT * 16 * ROWB;
+  static constexpr int FIRST = NS - (QBYTES + KW * TILE - 1) / (KW * TILE);
+  static_assert(FIRST >= 0, "the queries fit the ring");
+  static_assert(NS >= 2, "a tile being read and one under way");
+  // Read the next tile's fragments while this one is computed.  fp32: a tile takes thousands of cycles on the matrix
+  // pipe, and its fragments twice the registers.
+  static constexpr bool AHEAD = DT != DT_F32;
+  static constexpr int SEG = HV == 4 ? SCORE_SEG / 2 : SCORE_SEG;
+  // where piece p of row r lies within its row's slot
+  static __device__ __forceinline__ int swizzle(int r, int p) { return p ^ (PPR == 8 ? (r >> 1) & 7 : r & 15); }
+};
+
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+// At most N loads outstanding, every LDS read returned.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
+
+template <int D, int DT, int RT, int HV, int PASS>
+__global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, BatchParams bp, GroupPtrs gp, ScorePlan pl,
+                                                                                 float2 *__restrict__ partials,
+                                                                                 const float *__restrict__ lse_g,
+                                                                                 float *__restrict__ t_out,
+                                                                                 float *__restrict__ s_pool,
+                                                                                 const uint32_t *__restrict__ only_if) {
+  using C = ScoreConfig<D, DT, RT, HV>;
+  constexpr int KS = C::KS, KW = C::KW, NT = C::NT, NS = C::NS, ROWS = HV * RT * 16;
+  __shared__ __attribute__((aligned(1024))) char ring[C::RING];
+  __shared__ __attribute__((aligned(16))) float t_s[PASS == 2 ? HV * (C::SEG + KW * 16) : 4];     // token scores of a segment
+  __shared__ __attribute__((aligned(16))) float lse_s[PASS == 2 ? ROWS : 4];
+  __shared__ float2 part_s[PASS == 2 ? NT : KW * ROWS];
   // Launched behind the single-read kernel as its fall-back: nothing to do unless that kernel
   // raised the word (uniform over the grid).
   if (only_if && *only_if == 0u) return;
-  constexpr int MTT = MT * HV;                        // row tiles of the workgroup
-  constexpr int TS_MAX = max_chunk2(DT == DT_F32);
-  constexpr int TS_LEN = TS_MAX + WKV_MAX_WIN + 256;  // token scores of a chunk, the rest of its last window, the scrap area
-  __shared__ uint4 qfrag[MTT * KS * 64];
-  __shared__ float2 wave_part[PASS == 1 ? MF_WAVES * HV : 1][MT * 16];
-  // Pass 2 collects the chunk's token scores here and writes them out once at the end: global
-  // stores inside the loop would share the vector-memory counter with the key prefetch and make
-  // every wait for keys also wait for store acknowledgements.
-  __shared__ __attribute__((aligned(16))) float t_s[PASS == 2 ? HV * TS_LEN : 1];
-  __shared__ float lse_s[PASS == 2 ? MTT * 16 : 1];
 
   // Pass 2 walks the work items in the opposite order of pass 1: the keys pass 1 read last
   // are the ones most likely still held by the memory-side cache.
-  const int bx = PASS == 1 ? blockIdx.x : gridDim.x - 1 - blockIdx.x;
-  const int bh = PASS == 1 ? blockIdx.y : gridDim.y - 1 - blockIdx.y;
+  const int x = PASS == 1 ? blockIdx.x : gridDim.x - 1 - blockIdx.x;
+  const int h = PASS == 1 ? blockIdx.y : gridDim.y - 1 - blockIdx.y;
   const int g = PASS == 1 ? blockIdx.z : gridDim.z - 1 - blockIdx.z;
-  const int h = bh % s.Hkv;
-  const int b = PASS == 1 ? bp.by_length[bh / s.Hkv] : bh / s.Hkv;      // statistics: short sequences first
+  const PassPlan &pp = pl.pass[PASS - 1];
+  int b = 0;
+  while (b + 1 < s.B && x >= pp.first[b + 1]) ++b;
+  const int bx = x - pp.first[b];                           // chunk of the sequence
   const int L = bp.seq[b].L;
   const int n_review = L - s.w_obs;
   const int64_t row = ((int64_t)g * s.B + b) * s.Hkv + h;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int half = wave / MF_WAVES, kw = wave % MF_WAVES;   // row half, key tile slot of this wave
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = wave / KW, kw = wave % KW;               // row group, key tile slot of this wave
   const int col = lane & 15, quad = lane >> 4;
 
-  const int chunk = PASS == 1 ? pl.chunk1 : pl.chunk2;
-  const int limit = PASS == 1 ? L : n_review;         // keys that matter to this pass
-  int c0 = bx * chunk, c1 = min(c0 + chunk, limit);   // keys c0 .. c1-1 of the row
-  int w0 = 0, w1 = 0;
+  const int chunk = pp.chunk[b] * CHUNK_UNIT;
+  const int limit = PASS == 1 ? L : n_review;               // keys that matter to this pass
+  const int c_first = bx * chunk;
+  int c0 = c_first, cend = min(c0 + chunk, limit);          // keys c0 .. cend-1 of the row
+  int seg_len = PASS == 1 ? 0x40000000 : C::SEG;            // pass 2 writes its scores out a segment at a time
+  int win = 1;
   if (PASS == 2 && s_pool) {
     // A window belongs to the chunk that holds its first token: the workgroup scores and pools whole
     // windows, whatever their size, and no token is scored twice.
-    const int win = bp.seq[b].win;
-    w0 = (c0 + win - 1) / win;
-    w1 = (c1 + win - 1) / win;
-    c0 = w0 * win;
-    c1 = min(w1 * win, limit);
+    win = bp.seq[b].win;
+    c0 = (c0 + win - 1) / win * win;
+    cend = min((cend + win - 1) / win * win, limit);
+    seg_len = C::SEG / win * win;
   }
   float *trow = PASS == 2 ? t_out + row * s.t_stride : nullptr;
+  if (PASS == 2 && !s_pool)                                 // the row's padding
+    for (int j = n_review + threadIdx.x; j < (x + 1 == pp.first[b + 1] ? s.t_stride : 0); j += NT) trow[j] = 0.0f;
+  if (PASS == 2 && c0 >= cend) return;
+  float2 *part = partials + row * pl.n_chunks1 * pl.m_pad;
 
-  if (PASS == 2) {
-    if (c0 >= n_review || c0 >= c1) {
-      if (!s_pool)
-        for (int j = c0 + threadIdx.x; j < min(c0 + chunk, s.t_stride); j += NT) trow[j] = 0.0f;
-      return;
-    }
+  // ---- the key stream -------------------------------------------------------------------------
+  const char *kbase = (const char *)gp.k[g] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * C::ES;
+  const int64_t kst = s.kv_st * C::ES;
+  const bool wide = kst * 16 >= 0x7fffffff;                 // rows too far apart for 32-bit offsets within a tile
+  uint32_t off[C::LPT];                                     // this lane's piece of each of its DMA instructions, from the tile's first row
+#pragma unroll
+  for (int n = 0; n < C::LPT; ++n) {
+    const int r = (half * C::LPT + n) * C::RPI + lane / C::PPR;
+    off[n] = (uint32_t)((uint32_t)r * (uint32_t)kst + C::swizzle(r, lane % C::PPR) * 16);
   }
-  if (PASS == 1 && c0 >= L) {                         // a chunk past the end of a short sequence
-    for (int r = threadIdx.x; r < pl.m_pad; r += NT)
-      partials[(row * pl.m_pad + r) * pl.n_chunks1 + bx] = make_float2(-INFINITY, 0.0f);
-    return;
-  }
-  // Loads that depend on nothing staged below go out first, so that their latencies overlap: the
-  // query fragments of this workgroup and the first key tile of every wave.
-  QStage<D, MTT, NT, ES> qstage;
-  qstage.load(s, gp.q[g], b, h);
-  const int cend = c1;
-  const char *kbase = (const char *)gp.k[g] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * ES + quad * 16;
-  const int64_t kstride = s.kv_st * ES;
-  int j0 = c0 + kw * STEP;
-  KFrags<KS> ka, kb;
-  load_k<KS>(ka, kbase, kstride, j0, col, max(cend, 1));
-
-  if (PASS == 2) {
-    // The base-2 log-sum-exp of the MT*16 rows, into LDS.  With few chunks per row the workgroup
-    // folds the (m, z) partials of pass 1 itself (TPR adjacent lanes share a row; the query
-    // and key loads issued above are in flight meanwhile); otherwise a fold launch or the caller provided them.
-    constexpr int TPR = NT / (MTT * 16);
-    const int r = threadIdx.x / TPR, part = threadIdx.x % TPR;
-    if (pl.fold_in_pass2) {
-      float m = -INFINITY, z = 0.0f;
-      if (r < s.M) fold_partials_strided(partials + (row * pl.m_pad + r) * pl.n_chunks1, pl.n_chunks1, part, TPR, m, z);
+  const uint32_t ring_lds = lds_address(ring) + kw * (NS * C::TILE) + half * (C::LPT * 1024);
+  // keys j .. j+15 (this wave's part) into place `slot`; rows from cend on are not read (their lanes fetch row cend-1 again)
+  auto fetch = [&](int j, int slot) __attribute__((always_inline)) {
+    const uint32_t dst = ring_lds + slot * C::TILE;
+    if (j + 16 <= cend && !wide) {
+      const char *base = kbase + (int64_t)j * kst;
 #pragma unroll
-      for (int off = 1; off < TPR; off <<= 1) {
-        const float m2 = __shfl_xor(m, off), z2 = __shfl_xor(z, off);
-        merge_stats(m, z, m2, z2);
-      }
-      if (part == 0) lse_s[r] = r < s.M ? m + fast_log2(z) : INFINITY;      // padded rows: 2^-inf = 0
-    } else if (part == 0) {
-      lse_s[r] = row_lse2(s, pl, gp, lse_g, g, b, h, row, r);
-    }
-  }
-  qstage.store(qfrag);
-  __syncthreads();
-
-  // per-lane row constants: this lane's query row of its row tile mt is 16*(half*MT + mt) + col
-  float lse_r[MT], mref[MT], zsum[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    lse_r[mt] = PASS == 2 ? lse_s[(half * MT + mt) * 16 + col] : 0.0f;
-    mref[mt] = -INFINITY;
-    zsum[mt] = 0.0f;
-  }
-
-  const float sc = s.c1;
-
-  // One wave iteration: prefetch the keys of the next iteration into `kn`, compute on `kf`.
-  // The loop below calls it with the two buffers swapped in turn, so no register copies are
-  // needed and the wait for a buffer sits a whole iteration after its loads were issued.
-  auto iteration = [&](const KFrags<KS> &kf, KFrags<KS> &kn, const int j0) __attribute__((always_inline)) {
-    // The query fragments are loop invariant; without this barrier the compiler hoists all of
-    // them into registers (128 VGPRs) and spills.  They are meant to be re-read from LDS.
-    asm volatile("" ::: "memory");
-    // ---- prefetch the next iteration's keys while this one is computed --------------------
-    // Unconditional: a prefetch behind a branch makes every wait for `kf` also wait for it.
-    // Past the end of the chunk the row index clamps to the chunk's last key (a cache hit).
-    load_k<KS>(kn, kbase, kstride, j0 + MF_WAVES * STEP, col, cend);
-
-    // ---- logits acc[n][mt][e] = k_{j0+16n+4*quad+e} . q_{16*mt+col}, and their exponentials --------
-    // Written so that the MFMAs of row tile mt and the exponentials of row tile mt-1 alternate
-    // in ONE basic block: the matrix pipe and the vector ALU then overlap inside a wave instead
-    // of taking turns (the rare paths - mask, re-reference - come after the block).
-    f32x4 acc[MF_KT][MT];
-    float psum[MT];                                     // pass 1: sum of the tile's terms per row
-    f32x4 tq[MF_KT];                                    // pass 2: column sums over this lane's rows
-#pragma unroll
-    for (int n = 0; n < MF_KT; ++n) tq[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int mt = 0; mt <= MT; ++mt) {
-      if (mt < MT) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const uint4 qraw = qfrag[((half * MT + mt) * KS + ks) * 64 + lane];
-          const bf16x8 qb = *(const bf16x8 *)&qraw;
-#pragma unroll
-          for (int n = 0; n < MF_KT; ++n)
-            acc[n][mt] = mfma_64b<DT>(kf.f[n][ks], qb, ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[n][mt]);
-        }
-      }
-      if (mt > 0) {
-        const int m1 = mt - 1;
-        if (PASS == 1) {
-          float a = 0.0f;
-#pragma unroll
-          for (int n = 0; n < MF_KT; ++n)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a += fast_exp2(fmaf(acc[n][m1][e], sc, -mref[m1]));
-          psum[m1] = a;
-        } else {
-#pragma unroll
-          for (int n = 0; n < MF_KT; ++n)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) tq[n][e] += fast_exp2(fmaf(acc[n][m1][e], sc, -lse_r[m1]));
-        }
-      }
-    }
-
-    if (PASS == 1) {
-      if (j0 + STEP > n_review) {
-        // tiles that touch the observation block: causal mask (key j visible to observation
-        // query io iff j <= n_review + io) and the end of the sequence; redo their sums
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const int r = (half * MT + mt) * 16 + col;
-          const int last_vis = r < s.M ? n_review + (r % s.w_obs) : -1;
-          float a = 0.0f;
-#pragma unroll
-          for (int n = 0; n < MF_KT; ++n)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int j = j0 + n * 16 + quad * 4 + e;
-              if (j > last_vis || j >= cend) acc[n][mt][e] = -INFINITY;
-              a += fast_exp2(fmaf(acc[n][mt][e], sc, -mref[mt]));
-            }
-          psum[mt] = a;
-        }
-      }
-      // A sum that is huge, infinite or NaN (first tile: mref = -inf) means a logit far above the
-      // row's reference: re-reference the row and redo its part of the tile.
-      bool redo = false;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) redo |= !(psum[mt] <= MF_BIG);
-      if (__any(redo)) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          if (!(psum[mt] <= MF_BIG)) {
-            float vmax = -INFINITY;
-#pragma unroll
-            for (int n = 0; n < MF_KT; ++n)
-#pragma unroll
-              for (int e = 0; e < 4; ++e) vmax = fmaxf(vmax, acc[n][mt][e]);
-            const float nref = fmaxf(mref[mt], vmax * sc);
-            float a = 0.0f;
-            if (nref != -INFINITY) {
-              zsum[mt] *= fast_exp2(mref[mt] - nref);      // mref = -inf: 2^-inf = 0 and zsum is 0
-              mref[mt] = nref;
-#pragma unroll
-              for (int n = 0; n < MF_KT; ++n)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) a += fast_exp2(fmaf(acc[n][mt][e], sc, -nref));
-            }
-            psum[mt] = a;
-          }
-        }
-      }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) zsum[mt] += psum[mt];
+      for (int n = 0; n < C::LPT; ++n)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + n * 1024), "v"(off[n]), "s"(base) : "memory");
     } else {
-      // t_j: the lane's partial column sums, summed over the 16 lanes (rows 16*mt + 0..15)
-      // Every lane stores (lanes other than the first of each 16 into a scrap area past the
-      // chunk): a store under a lane predicate would put a branch into the middle of the block.
-      float *ts = t_s + half * TS_LEN;
-      float *dst = col == 0 ? ts + (j0 - c0) + quad * 4 : ts + TS_MAX + WKV_MAX_WIN + lane * 4;
 #pragma unroll
-      for (int n = 0; n < MF_KT; ++n) {
+      for (int n = 0; n < C::LPT; ++n) {
+        const int r = (half * C::LPT + n) * C::RPI + lane / C::PPR;
+        const char *p = kbase + (int64_t)min(j + r, cend - 1) * kst + C::swizzle(r, lane % C::PPR) * 16;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst + n * 1024), "v"(p) : "memory");
+      }
+    }
+  };
+  // The order of this wave's tiles: KW apart within a segment, segment by segment.
+  int jf = c0 + kw * 16, jf_end = min(c0 + seg_len, cend), slot_f = 0;      // the next tile to fetch
+  auto fetch_next = [&]() __attribute__((always_inline)) {
+    fetch(jf, slot_f);
+    slot_f = slot_f == NS - 1 ? 0 : slot_f + 1;
+    jf += KW * 16;
+    while (PASS == 2 && (HV > 1 ? jf - kw * 16 : jf) >= jf_end && jf_end < cend) {
+      jf = jf_end + kw * 16;
+      jf_end = min(jf_end + seg_len, cend);
+    }
+  };
 #pragma unroll
-        for (int e = 0; e < 4; ++e) tq[n][e] = row16_sum(tq[n][e]);
-        *(f32x4 *)(dst + (col == 0 ? n * 16 : 0)) = tq[n];                // 4 consecutive keys per quad
+  for (int i = 0; i < C::FIRST; ++i) fetch_next();
+
+  // ---- the queries: into the ring's other places as fragments (lane l: row l%16 of a row tile, piece l/16 of a step),
+  // from there into registers.  Rows past the last one repeat it: their statistics are never used and their
+  // normaliser is +inf.
+  constexpr int FRAGS = HV * RT * KS, PER_SLOT = (NS - C::FIRST) * C::TILE / 1024;
+  auto frag_at = [&](int f) __attribute__((always_inline)) {
+    return f / PER_SLOT * (NS * C::TILE) + C::FIRST * C::TILE + f % PER_SLOT * 1024;
+  };
+  for (int f = wave; f < FRAGS; f += C::WAVES) {
+    const int r = min(f / KS * 16 + col, s.M - 1);
+    const int hq = (int)((uint32_t)r * s.w_magic >> 16), io = r - hq * s.w_obs;      // r / w_obs, r % w_obs
+    const char *qp = (const char *)gp.q[g] +
+                     ((int64_t)b * s.q_sb + (int64_t)(h * s.G + hq) * s.q_sh + (int64_t)io * s.q_st) * C::ES + f % KS * 64 + quad * 16;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_address(ring) + frag_at(f)), "v"(qp) : "memory");
+  }
+  if (PASS == 2) {
+    if (pl.fold_in_pass2) fold_all<NT>(s, pl.pass[0].first[b + 1] - pl.pass[0].first[b], pl.m_pad, part, ROWS, part_s, lse_s);
+    else
+      for (int r = threadIdx.x; r < ROWS; r += NT) lse_s[r] = row_lse2(s, pl, gp, lse_g, g, b, h, row, r);
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+  bf16x8 qf[RT][KS];
+#pragma unroll
+  for (int mt = 0; mt < RT; ++mt)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[mt][ks] = *(const bf16x8 *)(ring + frag_at((half * RT + mt) * KS + ks) + lane * 16);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+#pragma unroll
+  for (int i = C::FIRST; i < NS; ++i) fetch_next();
+  const float sc = s.c1;
+  float mref[PASS == 1 ? RT : 1], zsum[PASS == 1 ? RT : 1];  // pass 1: reference and sum of query row (half*RT + mt)*16 + col
+  bool settled = false;                                     // (uniform) every sum of this wave is large enough for its reference
+  if (PASS == 1) {
+#pragma unroll
+    for (int mt = 0; mt < RT; ++mt) { mref[mt] = 0.0f; zsum[mt] = 0.0f; }
+  }
+
+  // ---- tiles -----------------------------------------------------------------------------------
+  // Meeting of the workgroup without the wait for outstanding loads that __syncthreads() brings.
+  auto barrier = [&]() __attribute__((always_inline)) { asm volatile("s_barrier" ::: "memory"); };
+  struct Frags { bf16x8 f[KS]; };
+  const uint32_t lane_row = col * C::ROWB;
+  int slot_r = 0;                                           // the slot read next
+  auto read_frags = [&](Frags &kf) __attribute__((always_inline)) {
+    const char *p = ring + kw * (NS * C::TILE) + slot_r * C::TILE + lane_row;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kf.f[ks] = *(const bf16x8 *)(p + C::swizzle(col, ks * 4 + quad) * 16);
+    slot_r = slot_r == NS - 1 ? 0 : slot_r + 1;
+  };
+  auto logits = [&](const Frags &kf, int mt) __attribute__((always_inline)) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      acc = PASS == 1 ? mfma_64b<DT>(kf.f[ks], qf[mt][ks], acc) : mfma_64b<DT>(qf[mt][ks], kf.f[ks], acc);
+    return acc;
+  };
+
+  // Statistics of one tile, with care: the causal mask (key j visible to observation query io iff
+  // j <= n_review + io), the end of the sequence, and rows whose reference does not suit their logits.  A
+  // reference is good while the sum taken with it stays between MF_LOW (what underflowed is negligible) and
+  // MF_BIG; otherwise it moves to the larger of the tile's maximum and the sum so far.
+  auto careful = [&](const Frags &kf, int j0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int mt = 0; mt < RT; ++mt) {
+      f32x4 acc = logits(kf, mt);
+      const int r = min((half * RT + mt) * 16 + col, s.M - 1);
+      const int last = min(n_review + r - (int)((uint32_t)r * s.w_magic >> 16) * s.w_obs, cend - 1);
+      float vmax = -INFINITY, a = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[e] = j0 + quad * 4 + e <= last ? acc[e] * sc : -INFINITY;
+        vmax = fmaxf(vmax, acc[e]);
+        a += fast_exp2(acc[e] - mref[mt]);
+      }
+      const float z = zsum[mt];
+      if (!(a <= MF_BIG) || !(z + a >= MF_LOW)) {
+        const float have = z > 0.0f ? mref[mt] + fast_log2(z) : -INFINITY;
+        const float nref = fmaxf(vmax, have);
+        if (nref != -INFINITY) {                            // else the row has seen no key yet
+          a = fast_exp2(have - nref);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a += fast_exp2(acc[e] - nref);
+          mref[mt] = nref;
+          zsum[mt] = a;
+        }
+      } else {
+        zsum[mt] = z + a;
       }
     }
   };
 
-  while (j0 < cend) {
-    iteration(ka, kb, j0);
-    j0 += MF_WAVES * STEP;
-    if (j0 >= cend) break;
-    iteration(kb, ka, j0);
-    j0 += MF_WAVES * STEP;
-  }
+  auto tile = [&](Frags &kf, Frags &kn, int j0, int seg0) __attribute__((always_inline)) {
+    if (C::AHEAD) {                                         // tile i+1 out of the ring, tile i+NS into the slot tile i left
+      wait_vmcnt<(NS - 2) * C::LPT>();
+      if (HV > 1) barrier();                                // (every part of it; every wave has tile i in registers)
+      read_frags(kn);
+    } else {
+      wait_vmcnt<(NS - 1) * C::LPT>();
+      if (HV > 1) barrier();
+      read_frags(kf);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // its place is free for the fetch below
+      if (HV > 1) barrier();
+    }
+    fetch_next();
+    if (PASS == 1) {
+      bool care = j0 + 16 > min(n_review, cend);            // uniform
+      if (!care) {
+        f32x4 acc[RT];
+        float psum[RT];
+#pragma unroll
+        for (int mt = 0; mt <= RT; ++mt) {                  // the MFMAs of a row tile beside the exponentials of the one before
+          if (mt < RT) acc[mt] = logits(kf, mt);
+          if (mt > 0) {
+            const int m1 = mt - 1;
+            float a = fast_exp2(fmaf(acc[m1][0], sc, -mref[m1]));
+#pragma unroll
+            for (int e = 1; e < 4; ++e) a += fast_exp2(fmaf(acc[m1][e], sc, -mref[m1]));
+            psum[m1] = a;
+          }
+        }
+        float big = psum[0];
+#pragma unroll
+        for (int mt = 1; mt < RT; ++mt) big = fmaxf(big, psum[mt]);
+        bool bad = !(big <= MF_BIG);
+        if (!settled) {
+          float low = zsum[0] + psum[0];
+#pragma unroll
+          for (int mt = 1; mt < RT; ++mt) low = fminf(low, zsum[mt] + psum[mt]);
+          bad |= !(low >= MF_LOW);
+        }
+        care = __any(bad);
+        if (!care) {
+#pragma unroll
+          for (int mt = 0; mt < RT; ++mt) zsum[mt] += psum[mt];
+          settled = true;
+        }
+      }
+      if (care) {
+        careful(kf, j0);
+        if (!settled) {
+          float low = zsum[0];
+#pragma unroll
+          for (int mt = 1; mt < RT; ++mt) low = fminf(low, zsum[mt]);
+          settled = __all(low >= MF_LOW);
+        }
+      }
+    } else {
+      f32x4 acc[RT];
+      float ta = 0.0f, tb = 0.0f;
+#pragma unroll
+      for (int mt = 0; mt <= RT; ++mt) {
+        if (mt < RT) acc[mt] = logits(kf, mt);
+        if (mt > 0) {
+          const int m1 = mt - 1;
+          // (from LDS every time: 4 * RT of them would not fit beside the queries)
+          const f32x4 lse = *(const f32x4 *)&lse_s[(half * RT + m1) * 16 + quad * 4];
+          ta += fast_exp2(fmaf(acc[m1][0], sc, -lse[0]));
+          tb += fast_exp2(fmaf(acc[m1][1], sc, -lse[1]));
+          ta += fast_exp2(fmaf(acc[m1][2], sc, -lse[2]));
+          tb += fast_exp2(fmaf(acc[m1][3], sc, -lse[3]));
+        }
+      }
+      // (the four lanes of a key store the same value to the same place: no branch in the loop)
+      t_s[half * (C::SEG + KW * 16) + j0 - seg0 + col] = quads_sum(ta + tb);
+    }
+  };
 
-  if (PASS == 2) {
+  Frags ka, kb;
+  if (C::AHEAD) {
+    wait_vmcnt<(NS - 1) * C::LPT>();
+    if (HV > 1) barrier();
+    read_frags(ka);
+  }
+  for (int seg0 = c0; seg0 < cend; seg0 += seg_len) {
+    const int seg_end = min(seg0 + seg_len, cend);
+    // with row groups every slot takes a tile in every round, if need be one past the end (masked in pass 1, past the
+    // scores that count in pass 2): the waves meet at barriers
+    for (int j = seg0 + kw * 16; (HV > 1 ? j - kw * 16 : j) < seg_end; j += KW * 16) {
+      tile(ka, kb, j, seg0);
+      if (C::AHEAD) ka = kb;
+    }
+    if (PASS == 1) break;
     __syncthreads();
-    if (HV == 2) {                                    // column sums of the second half of the rows
-      for (int j = threadIdx.x; j < cend - c0; j += NT) t_s[j] += t_s[TS_LEN + j];
+    if (HV > 1) {                                           // column sums of the other row groups
+      for (int i = threadIdx.x; i < seg_end - seg0; i += NT) {
+        float x = t_s[i];
+#pragma unroll
+        for (int v = 1; v < HV; ++v) x += t_s[v * (C::SEG + KW * 16) + i];
+        t_s[i] = x;
+      }
       __syncthreads();
     }
-    if (s_pool) {
-      // Eq. 3-4 on the chunk's token scores while they are in LDS
-      pool_windows<NT>(t_s, w0, w1, bp.seq[b].win, bp.seq[b].p, n_review, s_pool + row * s.nw_max);
-    } else {
-      const int cend_fill = min(c0 + chunk, s.t_stride);
-      for (int j = c0 + threadIdx.x; j < cend_fill; j += NT) trow[j] = j < cend ? t_s[j - c0] : 0.0f;
-    }
+    if (s_pool)                                             // Eq. 3-4 while the token scores are in LDS
+      pool_windows<NT>(t_s, seg0 / win, (seg_end + win - 1) / win, win, bp.seq[b].p, n_review, s_pool + row * s.nw_max);
+    else
+      for (int i = threadIdx.x; i < seg_end - seg0; i += NT) trow[seg0 + i] = t_s[i];
+    if (seg_end == cend) break;
+    __syncthreads();
   }
+
   if (PASS == 1) {
-    // merge the 4 quads of each row (lanes col, col+16, col+32, col+48), then the 4 waves
+    // merge the 4 quads of each row, then the KW waves
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      float m = mref[mt], z = zsum[mt];
-#pragma unroll
-      for (int off = 16; off < 64; off <<= 1) {
-        const float m2 = __shfl_xor(m, off), z2 = __shfl_xor(z, off);
-        merge_stats(m, z, m2, z2);
-      }
-      if (quad == 0) wave_part[wave][mt * 16 + col] = make_float2(m, z);
+    for (int mt = 0; mt < RT; ++mt) {
+      float m = zsum[mt] > 0.0f ? mref[mt] : -INFINITY, z = zsum[mt];
+      Pair pm = swap_halves(m, m), pz = swap_halves(z, z);
+      merge_stats(pm.a, pz.a, pm.b, pz.b);
+      m = pm.a; z = pz.a;
+      pm = swap_rows(m, m); pz = swap_rows(z, z);
+      merge_stats(pm.a, pz.a, pm.b, pz.b);
+      if (quad == 0) part_s[kw * ROWS + (half * RT + mt) * 16 + col] = make_float2(pm.a, pz.a);
     }
     __syncthreads();
-    for (int r = threadIdx.x; r < pl.m_pad; r += NT) {           // m_pad <= MTT*16
-      const int w0 = r / (MT * 16) * MF_WAVES, rr = r % (MT * 16);   // the waves that hold row r
-      float m = wave_part[w0][rr].x, z = wave_part[w0][rr].y;
-      for (int w = 1; w < MF_WAVES; ++w) merge_stats(m, z, wave_part[w0 + w][rr].x, wave_part[w0 + w][rr].y);
-      partials[(row * pl.m_pad + r) * pl.n_chunks1 + bx] = make_float2(m, z);
+    for (int r = threadIdx.x; r < pl.m_pad; r += NT) {           // m_pad <= ROWS
+      float m = part_s[r].x, z = part_s[r].y;
+      for (int w = 1; w < KW; ++w) merge_stats(m, z, part_s[w * ROWS + r].x, part_s[w * ROWS + r].y);
+      part[(int64_t)bx * pl.m_pad + r] = make_float2(m, z);
     }
   }
 }
@@ -362,18 +484,18 @@ __global__ __launch_bounds__(MF_THREADS * HV, HV == 1 && DT != DT_F32 ? 3 : 2) v
 // =========================================================================================
 // launch
 // =========================================================================================
-template <int D, int MT, int HV, int DT>
-static hipError_t launch_mfma(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp,
-                              int32_t n_groups, bool have_lse, float2 *partials, float *lse, float *t_out,
-                              float *s_pool, hipStream_t stream, hipEvent_t mid, const uint32_t *only_if) {
-  dim3 block(MF_THREADS * HV);
+template <int D, int DT, int RT, int HV>
+static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
+                                bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
+                                hipEvent_t mid, const uint32_t *only_if) {
+  const dim3 block(ScoreConfig<D, DT, RT, HV>::NT);
   hipError_t e;
   if (have_lse) {                                      // no statistics pass: pass 2 reads the caller's normalisers
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
   } else {
-    dim3 g1(pl.n_chunks1, s.B * s.Hkv, n_groups);
-    hipLaunchKernelGGL((score_mfma_kernel<D, MT, HV, 1, DT>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
+    dim3 g1(pl.pass[0].first[s.B], s.Hkv, n_groups);
+    hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 1>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
@@ -384,29 +506,42 @@ static hipError_t launch_mfma(const Shape &s, const BatchParams &bp, const Score
   }
   ScorePlan pl2 = pl;
   if (have_lse) pl2.fold_in_pass2 = false;
-  dim3 g2(pl.n_chunks2, s.B * s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_mfma_kernel<D, MT, HV, 2, DT>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
+  dim3 g2(pl.pass[1].first[s.B], s.Hkv, n_groups);
+  hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 2>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
   return hipGetLastError();
+}
+
+template <int D, int DT>
+static hipError_t launch_rows(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
+                              bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
+                              hipEvent_t mid, const uint32_t *only_if) {
+  // Row tiles per wave: the counts of the usual head layouts (w_obs of 8 to 32 with 1 to 8 query heads per KV
+  // head) are met exactly, the rest rounds up; a wave holds eight at most, four of fp32 with 128 channels.
+  const int mt = pl.m_pad / 16;
+#define WKV_ROWS(RR, HH) \
+  if (mt <= RR * HH) return launch_passes<D, DT, RR, HH>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
+  if constexpr (DT == DT_F32 && D == 128) {
+    WKV_ROWS(1, 1) WKV_ROWS(2, 1) WKV_ROWS(4, 1) WKV_ROWS(4, 2) WKV_ROWS(4, 4)
+  } else {
+    WKV_ROWS(1, 1) WKV_ROWS(2, 1) WKV_ROWS(4, 1) WKV_ROWS(6, 1) WKV_ROWS(7, 1) WKV_ROWS(8, 1) WKV_ROWS(6, 2) WKV_ROWS(7, 2) WKV_ROWS(8, 2)
+  }
+#undef WKV_ROWS
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_score(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp,
                         int32_t n_groups, bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool,
                         hipStream_t stream, hipEvent_t mid, const uint32_t *only_if) {
-  const int mt = pl.m_pad / 16;
-#define WKV_MFMA_TYPE(DD, MM, HH, TT) \
-  return launch_mfma<DD, MM, HH, TT>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
-#define WKV_MFMA_CASE(DD, MM, HH)                                     \
-  if (s.d == DD && mt <= MM * HH) {                                   \
-    if (s.dtype == WKV_BF16) WKV_MFMA_TYPE(DD, MM, HH, DT_BF16)       \
-    if (s.dtype == WKV_F16) WKV_MFMA_TYPE(DD, MM, HH, DT_F16)         \
-    WKV_MFMA_TYPE(DD, MM, HH, DT_F32)                                 \
+#define WKV_TYPE(DD, TT) return launch_rows<DD, TT>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
+  if (s.d == 128) {
+    if (s.dtype == WKV_BF16) WKV_TYPE(128, DT_BF16)
+    if (s.dtype == WKV_F16) WKV_TYPE(128, DT_F16)
+    WKV_TYPE(128, DT_F32)
   }
-  WKV_MFMA_CASE(128, 1, 1) WKV_MFMA_CASE(128, 2, 1) WKV_MFMA_CASE(128, 4, 1) WKV_MFMA_CASE(128, 8, 1)
-  WKV_MFMA_CASE(64, 1, 1) WKV_MFMA_CASE(64, 2, 1) WKV_MFMA_CASE(64, 4, 1) WKV_MFMA_CASE(64, 8, 1)
-  WKV_MFMA_CASE(128, 8, 2) WKV_MFMA_CASE(64, 8, 2)      // 129..256 rows: two halves of 8 row tiles
-#undef WKV_MFMA_CASE
-#undef WKV_MFMA_TYPE
-  return hipErrorInvalidValue;
+  if (s.dtype == WKV_BF16) WKV_TYPE(64, DT_BF16)
+  if (s.dtype == WKV_F16) WKV_TYPE(64, DT_F16)
+  WKV_TYPE(64, DT_F32)
+#undef WKV_TYPE
 }
 
 }  // namespace wkv

@@ -9,7 +9,7 @@
 namespace wkv {
 
 constexpr int POOL_THREADS = 256;
-constexpr int POOL_TOKENS = 2048;      // tokens a workgroup stages
+constexpr int POOL_TOKENS = SCORE_SEG;      // tokens a workgroup stages
 
 // Windows that a workgroup pools: as many as fit its staging area.
 __host__ __device__ __forceinline__ int pool_windows_per_block(int win) { return POOL_TOKENS / win; }
