@@ -263,7 +263,8 @@ wkv_status wkv_compress_groups(const wkv_problem *problem, int32_t n_groups, int
                                void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /*
- * Diagnostic twin of wkv_compress_groups (same arguments, same results, same launches): it
+ * Diagnostic twin of wkv_compress_groups (same arguments, same results, same launches except that the
+ * selection and the gather of a small call are not merged into one): it
  * brackets every kernel of the path with HIP events on the caller's stream, waits for the
  * stream, and reports each kernel's duration.  It creates and destroys HIP events and blocks
  * the calling thread, so it is for benchmarks and profiling, not for serving.

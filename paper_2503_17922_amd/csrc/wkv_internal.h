@@ -22,14 +22,6 @@ struct BatchParams {
   SeqParam seq[WKV_MAX_BATCH];
 };
 
-// Windows to keep per (group, sequence) when the groups have budgets of their own (Section
-// 2.2.3); index g * B + b.  Not in use: every group keeps SeqParam::k windows.
-constexpr int32_t MAX_GROUP_K = 1024;
-struct GroupK {
-  int32_t in_use;
-  uint16_t k[MAX_GROUP_K];
-};
-
 // Per-group device pointers of the scored layer.
 struct GroupPtrs {
   const void *q[WKV_MAX_GROUPS];
@@ -43,6 +35,30 @@ struct LayerPtrs {
   const void *v_in[WKV_MAX_LAYERS];
   void *k_out[WKV_MAX_LAYERS];
   void *v_out[WKV_MAX_LAYERS];
+};
+
+// Windows to keep per (group, sequence) when the groups have budgets of their own (Section
+// 2.2.3); index g * B + b.  Not in use: every group keeps SeqParam::k windows.
+constexpr int32_t MAX_GROUP_K = 1024;
+struct GroupK {
+  int32_t in_use;
+  uint16_t k[MAX_GROUP_K];
+  // Host only.  Not null: the selection's launch also gathers these layers, gamma per group (see selects_and_gathers).
+  const LayerPtrs *gather;
+  int32_t gamma;
+};
+
+// The same for a call small enough for one launch of selection and gather: everything its kernel needs besides
+// Shape, in a block a quarter of the size.
+constexpr int32_t SMALL_BATCH = 8, SMALL_GROUPS = 8, SMALL_LAYERS = 8;
+constexpr int32_t SMALL_WORKGROUPS = 512;         // what the device holds at once
+constexpr int32_t SMALL_WINDOWS = 8192;
+struct SmallJob {
+  SeqParam seq[SMALL_BATCH];
+  uint16_t k[SMALL_GROUPS * SMALL_BATCH];
+  const void *in[SMALL_LAYERS][2];
+  void *out[SMALL_LAYERS][2];
+  int32_t gamma, own_budgets, esize;
 };
 
 // Problem shape as the kernels see it.
@@ -108,6 +124,16 @@ struct Workspace {
   size_t t_offset, s_offset;   // byte offsets of t and s from the base
   size_t bytes;
 };
+
+// Selection and gather in one launch?  Up to 40 MB of compact cache: the workgroups that the device holds at once
+// (the selection is repeated in each) keep fewer rows in flight than the gather's own launch, which costs more than
+// the launch saves from there on (67 MB: 70.4 against 69.1 us a call, 34 MB: 45.9 against 47.3, 17 MB: 33.7 against 35.5).
+constexpr int64_t SMALL_BYTES = 40 << 20;
+inline bool selects_and_gathers(const Shape &s, int32_t n_groups, int32_t gamma) {
+  const int64_t pairs = (int64_t)2 * n_groups * gamma * s.B * s.Hkv;
+  return s.B <= SMALL_BATCH && n_groups <= SMALL_GROUPS && n_groups * gamma <= SMALL_LAYERS && s.nw_max <= SMALL_WINDOWS &&
+         pairs <= SMALL_WORKGROUPS && pairs * s.nkeep_max * s.d * elem_bytes(s.dtype) <= SMALL_BYTES;
+}
 
 // ---- host-side helpers (wkv_host.cpp) ---------------------------------------------------
 void set_error(const char *fmt, ...);

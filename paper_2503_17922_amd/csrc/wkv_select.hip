@@ -51,60 +51,55 @@ hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, 
 }
 
 // ------------------------------------------------------------------------------------------
-// Top-k windows.  One 1024-thread workgroup per (group, sequence, KV head).  Bound by its chain of
+// Top-k windows.  One workgroup per (group, sequence, KV head).  Bound by its chain of
 // synchronised steps, not by data (a row is a few KB), so every step is one that needs few of them:
 //   1. window scores -> order-preserving uint32 keys in LDS, their smallest and largest on the way
-//   2. the k-th largest key T by digits of the range the keys really span: 2048 bins over [lo, hi],
+//   2. the k-th largest key T by digits of the range the keys really span: two bins per thread over [lo, hi],
 //      descend into the bin that holds the k-th, until the windows that still fit are exactly a bin
-//      or a bin is one key wide (11 bits a pass: at most three passes, two for ordinary scores.
+//      or a bin is one key wide (9 to 11 bits a pass: at most four passes, two for ordinary scores.
 //      Window scores differ in their low bits only, so digits taken from the top of the word put
 //      nearly all of them into one bin and serialise the LDS counters)
 //   3. window w is kept iff key > T, or key == T and fewer than take_eq equal windows precede it
 //      (=> lower index wins ties).  Its output slot is (#greater before w) + min(#equal before w,
 //      take_eq): ballots per wave and 1024 windows, one scan over all their counts, so the list comes
 //      out ascending without a sort
-//   4. expansion to token positions, the observation window appended, -1 padding.
+//   4. expansion to token positions, the observation window appended, -1 padding
 // The 32K-token configuration (64 rows of 2046 windows, k = 256): 12.2 us with 8-bit digits from the
-// top and three synchronisations per 1024 windows in step 3, 9.2 us so.
+// top and three synchronisations per 1024 windows in step 3, 9.2 us so; a mixed batch (512 rows of up to 3900
+// windows): 19.7 us, 18.0 us so with 1024 threads, 13.8 us with 512.
 // ------------------------------------------------------------------------------------------
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int TOPK_THREADS = 1024;
+constexpr int SMALL_THREADS = 256;        // where 8192 windows are enough
 constexpr int TOPK_WAVES = TOPK_THREADS / 64;
-constexpr int TOPK_BINS = 2048;
 constexpr int TOPK_ITERS = WKV_MAX_WINDOWS / TOPK_THREADS;
-static_assert(TOPK_ITERS <= 32 && TOPK_BINS == 2 * TOPK_THREADS, "one mask bit per 1024 windows, two bins a thread");
+static_assert(TOPK_ITERS <= 32, "one mask bit per window of a thread");
 
 __device__ __forceinline__ uint32_t float_to_key(float f) {
   const uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams bp, GroupK gk,
-                                                            const float *__restrict__ sc,
-                                                            int32_t *__restrict__ win_idx,
-                                                            int32_t *__restrict__ tok_idx,
-                                                            int32_t *__restrict__ n_keep) {
-  extern __shared__ uint32_t keys[];            // [nw_max], later reused for the selected list
-  __shared__ uint32_t hist[TOPK_BINS];
-  __shared__ uint32_t wave_a[TOPK_WAVES], wave_b[TOPK_WAVES];
+// Steps 1-3 for the row of window scores srow: the selected windows, ascending, are left in keys (LDS, nw_max entries)
+// and, if wrow is not null, written there.  Returns the number of review tokens they hold.
+template <int NT>
+__device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, const float *__restrict__ srow, uint32_t *keys,
+                                              int32_t *__restrict__ wrow) {
+  __shared__ uint32_t hist[2 * NT];
+  __shared__ uint32_t wave_a[NT / 64], wave_b[NT / 64];
   __shared__ uint32_t counts[TOPK_ITERS * TOPK_WAVES];      // windows per wave and 1024: greater | equal << 16
   __shared__ uint32_t sh_bin, sh_above, sh_count;
-  const int bh = blockIdx.x, b = bh / s.Hkv, g = blockIdx.y;
-  SeqParam sp = bp.seq[b];
-  if (gk.in_use) sp.k = gk.k[g * s.B + b];      // the group's own budget
-  const int n_review = sp.L - s.w_obs;
+  const int n_review = sp.L - w_obs;
   const int nw = (n_review + sp.win - 1) / sp.win;
   const int k = sp.k;
-  const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
-  int32_t *wrow = win_idx + row * s.k_max;
-  int32_t *trow = tok_idx + row * s.nkeep_max;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int n_rev_kept = 0;
 
   if (k > 0) {
     // ---- 1. keys and their range ------------------------------------------------------------
-    const float *srow = sc + row * s.nw_max;
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    for (int w = tid; w < nw; w += TOPK_THREADS) {
+    for (int w = tid; w < nw; w += NT) {
       const uint32_t key = float_to_key(srow[w]);
       keys[w] = key;
       kmin = min(kmin, key);
@@ -116,24 +111,26 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams
       kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
     }
     if (lane == 0) { wave_a[wave] = kmin; wave_b[wave] = kmax; }
-    hist[tid] = 0u; hist[tid + TOPK_THREADS] = 0u;
+    hist[tid] = 0u; hist[tid + NT] = 0u;
     __syncthreads();
     uint32_t lo = wave_a[0], hi = wave_b[0];
 #pragma unroll
-    for (int i = 1; i < TOPK_WAVES; ++i) { lo = min(lo, wave_a[i]); hi = max(hi, wave_b[i]); }
+    for (int i = 1; i < NT / 64; ++i) { lo = min(lo, wave_a[i]); hi = max(hi, wave_b[i]); }
 
     // ---- 2. the k-th largest key ----------------------------------------------------------------
     uint32_t remaining = (uint32_t)k, take_eq, T;
+    constexpr int digit_bits = NT == 1024 ? 11 : NT == 512 ? 10 : 9;
+    static_assert(2 * NT == 1 << digit_bits, "two bins a thread");
     for (;;) {
       const int bits = 32 - __clz((int)((hi - lo) | 1u));
-      const int shift = max(bits - 11, 0);
-      for (int w = tid; w < nw; w += TOPK_THREADS) {
+      const int shift = max(bits - digit_bits, 0);
+      for (int w = tid; w < nw; w += NT) {
         const uint32_t key = keys[w];
         if (key >= lo && key <= hi) atomicAdd(&hist[(key - lo) >> shift], 1u);
       }
       __syncthreads();
-      // windows in strictly higher bins: thread tid looks at bins 2047 - 2*tid and 2046 - 2*tid
-      const uint32_t c0 = hist[TOPK_BINS - 1 - 2 * tid], c1 = hist[TOPK_BINS - 2 - 2 * tid];
+      // windows in strictly higher bins: thread tid looks at the 2*tid-th and the next bin from the top
+      const uint32_t c0 = hist[2 * NT - 1 - 2 * tid], c1 = hist[2 * NT - 2 - 2 * tid];
       uint32_t incl = c0 + c1;
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
@@ -144,11 +141,11 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams
       __syncthreads();
       uint32_t above = incl - c0 - c1;
 #pragma unroll
-      for (int i = 0; i < TOPK_WAVES; ++i) above += i < wave ? wave_a[i] : 0u;
-      if (above < remaining && above + c0 >= remaining) { sh_bin = TOPK_BINS - 1 - 2 * tid; sh_above = above; sh_count = c0; }
+      for (int i = 0; i < NT / 64; ++i) above += i < wave ? wave_a[i] : 0u;
+      if (above < remaining && above + c0 >= remaining) { sh_bin = 2 * NT - 1 - 2 * tid; sh_above = above; sh_count = c0; }
       above += c0;
-      if (above < remaining && above + c1 >= remaining) { sh_bin = TOPK_BINS - 2 - 2 * tid; sh_above = above; sh_count = c1; }
-      hist[TOPK_BINS - 1 - 2 * tid] = 0u; hist[TOPK_BINS - 2 - 2 * tid] = 0u;
+      if (above < remaining && above + c1 >= remaining) { sh_bin = 2 * NT - 2 - 2 * tid; sh_above = above; sh_count = c1; }
+      hist[2 * NT - 1 - 2 * tid] = 0u; hist[2 * NT - 2 - 2 * tid] = 0u;
       __syncthreads();
       const uint32_t bin_lo = lo + (sh_bin << shift);
       remaining -= sh_above;
@@ -163,28 +160,28 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams
 
     // ---- 3. ordered compaction -------------------------------------------------------------
     uint32_t gt_bits = 0u, eq_bits = 0u;          // this thread's windows, one bit per 1024
-    const int iters = (nw + TOPK_THREADS - 1) / TOPK_THREADS;
+    const int iters = (nw + NT - 1) / NT;
     for (int i = 0; i < iters; ++i) {
-      const int w = i * TOPK_THREADS + tid;
+      const int w = i * NT + tid;
       const uint32_t key = w < nw ? keys[w] : 0u;
       const bool gt = w < nw && key > T, eq = w < nw && key == T;
       gt_bits |= (uint32_t)gt << i;
       eq_bits |= (uint32_t)eq << i;
       const int n_gt = __popcll(__ballot(gt)), n_eq = __popcll(__ballot(eq));
-      if (lane == 0) counts[i * TOPK_WAVES + wave] = (uint32_t)n_gt | (uint32_t)n_eq << 16;
+      if (lane == 0) counts[i * (NT / 64) + wave] = (uint32_t)n_gt | (uint32_t)n_eq << 16;
     }
     __syncthreads();                              // every key has been read: the array is free
     if (wave == 0) {                              // exclusive scan of the counts, in window order
       uint32_t base = 0u;
-      for (int c = 0; c < iters * TOPK_WAVES; c += 64) {
-        const uint32_t v = c + lane < iters * TOPK_WAVES ? counts[c + lane] : 0u;
+      for (int c = 0; c < iters * (NT / 64); c += 64) {
+        const uint32_t v = c + lane < iters * (NT / 64) ? counts[c + lane] : 0u;
         uint32_t incl = v;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
           const uint32_t o = (uint32_t)__shfl_up((int)incl, off);
           if (lane >= off) incl += o;
         }
-        if (c + lane < iters * TOPK_WAVES) counts[c + lane] = base + incl - v;
+        if (c + lane < iters * (NT / 64)) counts[c + lane] = base + incl - v;
         base += (uint32_t)__shfl((int)incl, 63);
       }
     }
@@ -193,12 +190,12 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams
     for (int i = 0; i < iters; ++i) {
       const bool gt = gt_bits >> i & 1u, eq = eq_bits >> i & 1u;
       const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
-      const uint32_t before = counts[i * TOPK_WAVES + wave];
+      const uint32_t before = counts[i * (NT / 64) + wave];
       const uint32_t gt_before = (before & 0xffffu) + __popcll(bgt & below), eq_before = (before >> 16) + __popcll(beq & below);
       if (gt || (eq && eq_before < take_eq)) {
         const uint32_t slot = gt_before + min(eq_before, take_eq);
-        keys[slot] = (uint32_t)(i * TOPK_THREADS + tid);
-        wrow[slot] = i * TOPK_THREADS + tid;
+        keys[slot] = (uint32_t)(i * NT + tid);
+        if (wrow) wrow[slot] = i * NT + tid;
       }
     }
     __syncthreads();
@@ -208,33 +205,129 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(Shape s, BatchParams
     const int missing = ((int)keys[k - 1] + 1) * sp.win - n_review;
     if (missing > 0) n_rev_kept -= missing;
   }
-  for (int i = k + tid; i < s.k_max; i += TOPK_THREADS) wrow[i] = -1;
+  return n_rev_kept;
+}
 
-  // ---- 4. token positions ------------------------------------------------------------------
-  const int nk = n_rev_kept + s.w_obs;
-  for (int r = tid; r < s.nkeep_max; r += TOPK_THREADS) {
-    int tok = -1;
+// Position of retained row r: row r - m*win of the m-th selected window, or of the observation window; -1 past the last.
+struct TokenOf {
+  const uint32_t *keys;                         // the selected windows
+  int win, L, n_rev_kept, nk;
+  uint32_t magic;                               // r / win == umulhi(r, magic) for r < 2^32 / win; 0 for win = 1
+  __device__ __forceinline__ TokenOf(const SeqParam &sp, int w_obs, const uint32_t *sel, int kept)
+      : keys(sel), win(sp.win), L(sp.L), n_rev_kept(kept), nk(kept + w_obs), magic(0xffffffffu / (uint32_t)sp.win + 1u) {}
+  __device__ __forceinline__ int operator()(int r) const {
     if (r < n_rev_kept) {
-      const int m = r / sp.win;
-      tok = (int)keys[m] * sp.win + (r - m * sp.win);
-    } else if (r < nk) {
-      tok = n_review + (r - n_rev_kept);
+      const int m = win == 1 ? r : (int)__umulhi((uint32_t)r, magic);
+      return (int)keys[m] * win + (r - m * win);
     }
-    trow[r] = tok;
+    return r < nk ? L - nk + r : -1;
   }
-  if (tid == 0) n_keep[row] = nk;
+};
+
+template <int NT>
+__global__ __launch_bounds__(NT) void topk_kernel(Shape s, BatchParams bp, GroupK gk,
+                                                            const float *__restrict__ sc,
+                                                            int32_t *__restrict__ win_idx,
+                                                            int32_t *__restrict__ tok_idx,
+                                                            int32_t *__restrict__ n_keep) {
+  extern __shared__ uint32_t keys[];            // [nw_max], later reused for the selected list
+  const int bh = blockIdx.x, b = bh / s.Hkv, g = blockIdx.y;
+  SeqParam sp = bp.seq[b];
+  if (gk.in_use) sp.k = gk.k[g * s.B + b];      // the group's own budget
+  const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
+  int32_t *wrow = win_idx + row * s.k_max;
+  const int n_rev_kept = select_windows<NT>(sp, s.w_obs, sc + row * s.nw_max, keys, wrow);
+  for (int i = sp.k + threadIdx.x; i < s.k_max; i += NT) wrow[i] = -1;
+  const TokenOf token(sp, s.w_obs, keys, n_rev_kept);
+  for (int r = threadIdx.x; r < s.nkeep_max; r += NT) tok_idx[row * s.nkeep_max + r] = token(r);
+  if (threadIdx.x == 0) n_keep[row] = token.nk;
+}
+
+// Selection and gather in one launch, for calls with few (row, tensor) pairs: every workgroup selects the windows of its
+// row for itself and copies its share of the kept rows of one layer's K or V.  The selection is a few
+// microseconds of latency whether one workgroup of a row does it or all of them, and a launch less is worth
+// more than that.  The pairs times `splits` fit the device at once; with more, the repeated selection would
+// cost a round of its own.  A 4096-token group of four layers: 5.3 + 6.7 us apart, 9.5 us so with 256 threads (14 us
+// with 1024: sixteen waves at every synchronisation); 16384 tokens: 5.7 + 14.9 us, 18.1 us so.
+template <int LPR>  // 16-byte pieces per row
+__global__ __launch_bounds__(SMALL_THREADS) void select_gather_kernel(Shape s, SmallJob job, const float *__restrict__ sc,
+                                                                     int32_t *__restrict__ win_idx, int32_t *__restrict__ tok_idx,
+                                                                     int32_t *__restrict__ n_keep) {
+  extern __shared__ uint32_t keys[];
+  constexpr int ROWS = SMALL_THREADS / LPR, AHEAD = 4;
+  const int split = blockIdx.x, bh = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv, layer = blockIdx.z >> 1, is_v = blockIdx.z & 1;
+  const int g = layer / job.gamma;
+  SeqParam sp = job.seq[b];
+  if (job.own_budgets) sp.k = job.k[g * s.B + b];
+  const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
+  const bool writer = split == 0 && blockIdx.z == 2 * g * job.gamma;       // this row's index outputs are this workgroup's
+  int32_t *wrow = writer ? win_idx + row * s.k_max : nullptr;
+  const int n_rev_kept = select_windows<SMALL_THREADS>(sp, s.w_obs, sc + row * s.nw_max, keys, wrow);
+  const TokenOf token(sp, s.w_obs, keys, n_rev_kept);
+  const int nk = token.nk, n_write = s.fill_padding ? s.nkeep_max : nk;
+
+  const int piece = threadIdx.x % LPR;
+  const char *src = (const char *)job.in[layer][is_v] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * job.esize + piece * 16;
+  char *dst = (char *)job.out[layer][is_v] + ((int64_t)b * s.o_sb + (int64_t)h * s.o_sh) * job.esize + piece * 16;
+  const int64_t in_step = s.kv_st * job.esize, out_step = s.o_st * job.esize;
+  const int share = (n_write + gridDim.x - 1) / gridDim.x, r_end = min((split + 1) * share, n_write);
+  for (int r0 = split * share + threadIdx.x / LPR; r0 < r_end; r0 += ROWS * AHEAD) {
+    u32x4 v[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const int r = r0 + u * ROWS;
+      v[u] = u32x4{0u, 0u, 0u, 0u};
+      if (r < min(r_end, nk))
+        v[u] = __builtin_nontemporal_load((const u32x4 *)(src + (int64_t)token(r) * in_step));
+    }
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+      if (r0 + u * ROWS < r_end) __builtin_nontemporal_store(v[u], (u32x4 *)(dst + (int64_t)(r0 + u * ROWS) * out_step));
+  }
+  if (!writer) return;
+  for (int i = sp.k + threadIdx.x; i < s.k_max; i += SMALL_THREADS) wrow[i] = -1;
+  for (int r = threadIdx.x; r < s.nkeep_max; r += SMALL_THREADS) tok_idx[row * s.nkeep_max + r] = token(r);
+  if (threadIdx.x == 0) n_keep[row] = nk;
+}
+
+static hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
+                                       int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
+  SmallJob job;
+  job.gamma = gk.gamma;
+  job.own_budgets = gk.in_use;
+  job.esize = (int32_t)elem_bytes(s.dtype);
+  for (int b = 0; b < s.B; ++b) job.seq[b] = bp.seq[b];
+  for (int i = 0; i < n_groups * s.B; ++i) job.k[i] = gk.k[i];
+  for (int l = 0; l < n_groups * gk.gamma; ++l) {
+    job.in[l][0] = gk.gather->k_in[l]; job.in[l][1] = gk.gather->v_in[l];
+    job.out[l][0] = gk.gather->k_out[l]; job.out[l][1] = gk.gather->v_out[l];
+  }
+  const int pairs = 2 * n_groups * gk.gamma * s.B * s.Hkv;
+  const int lpr = (int)(s.d * job.esize / 16), rows = SMALL_THREADS / lpr;
+  const int splits = max(min(SMALL_WORKGROUPS / pairs, (s.nkeep_max + rows - 1) / rows), 1);
+  dim3 grid(splits, s.B * s.Hkv, 2 * n_groups * gk.gamma);
+  const size_t lds = (size_t)(s.nw_max > 0 ? s.nw_max : 1) * sizeof(uint32_t);
+  if (lpr == 8) hipLaunchKernelGGL(select_gather_kernel<8>, grid, dim3(SMALL_THREADS), lds, stream, s, job, sc, win_idx, tok_idx, n_keep);
+  else if (lpr == 16) hipLaunchKernelGGL(select_gather_kernel<16>, grid, dim3(SMALL_THREADS), lds, stream, s, job, sc, win_idx, tok_idx, n_keep);
+  else hipLaunchKernelGGL(select_gather_kernel<32>, grid, dim3(SMALL_THREADS), lds, stream, s, job, sc, win_idx, tok_idx, n_keep);
+  return hipGetLastError();
 }
 
 hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
                        int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
+  if (gk.gather) return launch_select_gather(s, bp, gk, n_groups, sc, win_idx, tok_idx, n_keep, stream);
   const size_t lds = (size_t)(s.nw_max > 0 ? s.nw_max : 1) * sizeof(uint32_t);
   if (lds > 48 * 1024) {     // beyond the default dynamic-LDS limit: raise it (per device, any thread)
-    hipError_t e = hipFuncSetAttribute((const void *)topk_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipError_t e = hipFuncSetAttribute((const void *)topk_kernel<TOPK_THREADS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        WKV_MAX_WINDOWS * (int)sizeof(uint32_t));
     if (e != hipSuccess) return e;
   }
   dim3 grid(s.B * s.Hkv, n_groups);
-  hipLaunchKernelGGL(topk_kernel, grid, dim3(TOPK_THREADS), lds, stream, s, bp, gk, sc, win_idx, tok_idx, n_keep);
+  // Half the threads where a thread still has few windows: cheaper synchronisation, and more rows on a compute unit.
+  if (s.nw_max <= 4096)
+    hipLaunchKernelGGL(topk_kernel<TOPK_THREADS / 2>, grid, dim3(TOPK_THREADS / 2), lds, stream, s, bp, gk, sc, win_idx, tok_idx, n_keep);
+  else
+    hipLaunchKernelGGL(topk_kernel<TOPK_THREADS>, grid, dim3(TOPK_THREADS), lds, stream, s, bp, gk, sc, win_idx, tok_idx, n_keep);
   return hipGetLastError();
 }
 
