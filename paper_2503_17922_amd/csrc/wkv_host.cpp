@@ -180,6 +180,11 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   const int32_t shortest = 2 * CHUNK_UNIT, longest = 8192;
   plan_pass(bp, s.B, 0, pick_chunk(bp, s.B, rows_per_seq, 0, shortest, longest, slots), &pl.pass[0]);
   plan_pass(bp, s.B, s.w_obs, pick_chunk(bp, s.B, rows_per_seq, s.w_obs, shortest, longest, slots), &pl.pass[1]);
+  // Keys that the memory-side cache holds until the second pass are better left there; a larger stream reads
+  // faster past it.  One layer of 32768 tokens a group, 8 KV heads, whole call: 1 to 3 groups (67 to 201 MB) 57.5, 87.8, 116.5 us
+  // with plain loads, 57.6, 87.9, 115.8 with nontemporal ones, 6 groups (403 MB) 206.2 and 201.1; the 32K model's passes (537
+  // MB) 390 and 370 us; 16384 tokens and four layers 45.9 and 48.1 us; 256 softmax rows, 134 MB 118.8 and 123.0 us.
+  pl.nontemporal = keys * s.d * elem_bytes(s.dtype) > MEMORY_CACHE_BYTES;
   pl.n_chunks1 = 0;
   for (int32_t b = 0; b < s.B; ++b) pl.n_chunks1 = std::max(pl.n_chunks1, pl.pass[0].first[b + 1] - pl.pass[0].first[b]);
   // every pass-2 workgroup re-reads the partials of its rows when it folds them itself: 64 KB at 128 rows and 64

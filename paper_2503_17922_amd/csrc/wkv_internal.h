@@ -8,6 +8,9 @@
 
 namespace wkv {
 
+// The chip's memory-side cache.
+constexpr int64_t MEMORY_CACHE_BYTES = (int64_t)256 << 20;
+
 inline int64_t elem_bytes(int32_t dtype) { return dtype == WKV_F32 ? 4 : 2; }
 
 // Per-sequence parameters, passed to kernels by value inside the kernel argument block so
@@ -90,6 +93,7 @@ struct ScorePlan {
   PassPlan pass[2];            // statistics, scores
   int32_t n_chunks1;           // most workgroups of a sequence in the statistics pass
   int32_t m_pad;               // rows padded to a multiple of 16
+  bool nontemporal;            // the key loads put nothing into the memory-side cache
   bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
 };
 

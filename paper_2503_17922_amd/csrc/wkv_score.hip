@@ -164,7 +164,9 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 
-template <int D, int DT, int RT, int HV, int PASS>
+// NT_LOADS: the keys are not put into the memory-side cache (see plan_score).  Kernels of their own, as a branch at every fetch
+// costs small calls 1 %.
+template <int D, int DT, int RT, int HV, int PASS, bool NT_LOADS>
 __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, BatchParams bp, GroupPtrs gp, ScorePlan pl,
                                                                                  float2 *__restrict__ partials,
                                                                                  const float *__restrict__ lse_g,
@@ -233,9 +235,15 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
     const uint32_t dst = ring_lds + slot * C::TILE;
     if (j + 16 <= cend && !wide) {
       const char *base = kbase + (int64_t)j * kst;
+      if constexpr (NT_LOADS) {
 #pragma unroll
-      for (int n = 0; n < C::LPT; ++n)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + n * 1024), "v"(off[n]), "s"(base) : "memory");
+        for (int n = 0; n < C::LPT; ++n)
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst + n * 1024), "v"(off[n]), "s"(base) : "memory");
+      } else {
+#pragma unroll
+        for (int n = 0; n < C::LPT; ++n)
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + n * 1024), "v"(off[n]), "s"(base) : "memory");
+      }
     } else {
 #pragma unroll
       for (int n = 0; n < C::LPT; ++n) {
@@ -484,7 +492,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
 // =========================================================================================
 // launch
 // =========================================================================================
-template <int D, int DT, int RT, int HV>
+template <int D, int DT, int RT, int HV, bool NT_LOADS>
 static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
                                 bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
                                 hipEvent_t mid, const uint32_t *only_if) {
@@ -495,7 +503,7 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
     if (s.t_stride <= 0) return hipSuccess;
   } else {
     dim3 g1(pl.pass[0].first[s.B], s.Hkv, n_groups);
-    hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 1>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
+    hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 1, NT_LOADS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
@@ -507,7 +515,7 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
   ScorePlan pl2 = pl;
   if (have_lse) pl2.fold_in_pass2 = false;
   dim3 g2(pl.pass[1].first[s.B], s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 2>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
+  hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 2, NT_LOADS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
   return hipGetLastError();
 }
 
@@ -519,7 +527,9 @@ static hipError_t launch_rows(const Shape &s, const BatchParams &bp, const Score
   // head) are met exactly, the rest rounds up; a wave holds eight at most, four of fp32 with 128 channels.
   const int mt = pl.m_pad / 16;
 #define WKV_ROWS(RR, HH) \
-  if (mt <= RR * HH) return launch_passes<D, DT, RR, HH>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
+  if (mt <= RR * HH) \
+    return pl.nontemporal ? launch_passes<D, DT, RR, HH, true>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if) \
+                          : launch_passes<D, DT, RR, HH, false>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
   if constexpr (DT == DT_F32 && D == 128) {
     WKV_ROWS(1, 1) WKV_ROWS(2, 1) WKV_ROWS(4, 1) WKV_ROWS(4, 2) WKV_ROWS(4, 4)
   } else {
