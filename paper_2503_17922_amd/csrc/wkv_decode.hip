@@ -36,6 +36,14 @@ constexpr int DEC_THREADS = 256;
 constexpr int DEC_WAVES = DEC_THREADS / 64;
 constexpr int DEC_U = 4;            // row tiles per wave batch (loads in flight: 2 * DEC_U per lane)
 
+// A 16-byte piece of a cache row.  STREAM: a nontemporal load, which puts nothing into the memory-side cache; a kernel
+// that only reads such a stream reaches 7.0 TB/s with it, 6.1 without (1 GB in 1536 ranges).
+template <bool STREAM>
+__device__ __forceinline__ uint4 load_piece(const void *p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(uint4, STREAM ? __builtin_nontemporal_load((const u32x4 *)p) : *(const u32x4 *)p);
+}
+
 struct half_t { uint16_t bits; };             // element tag of IEEE half tensors (uint16_t stands for bfloat16)
 
 template <typename T> struct Piece;           // the 16-byte piece of a row held by one lane
@@ -142,7 +150,7 @@ __device__ __forceinline__ bool nothing_to_do(const DecodeShape &s, int bh, int 
   return true;
 }
 
-template <typename T, int D, int G>
+template <typename T, int D, int G, bool STREAM>
 __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape s, const T *__restrict__ q_new,
                                                                      const T *__restrict__ k_cache,
                                                                      const T *__restrict__ v_cache,
@@ -187,8 +195,8 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
 #pragma unroll
     for (int u = 0; u < DEC_U; ++u) {
       const int64_t off = (int64_t)min(c0 + (t0 + u * DEC_WAVES) * KPT + slot, cend - 1) * s.st + piece * E;
-      kr[u] = *(const uint4 *)(kc + off);
-      vr[u] = *(const uint4 *)(vc + off);
+      kr[u] = load_piece<STREAM>(kc + off);
+      vr[u] = load_piece<STREAM>(vc + off);
     }
   };
   int t0 = wave;
@@ -286,7 +294,8 @@ template <int N, class F>
 __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
 }
-template <int D, int G, bool F16>
+// STREAM: 0 plain loads, 1 values stream, 2 keys too (see launch_partial_g).
+template <int D, int G, bool F16, int STREAM>
 __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mfma_kernel(
     DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ n_valid, float *__restrict__ part) {
@@ -326,9 +335,9 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
   auto load_block = [&](int blk) {
     const int r0 = c0 + blk * 16;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kr[ks] = *(const uint4 *)(kc + (int64_t)min(r0 + col, cend - 1) * s.st + ks * 32);
+    for (int ks = 0; ks < KS; ++ks) kr[ks] = load_piece<(STREAM > 1)>(kc + (int64_t)min(r0 + col, cend - 1) * s.st + ks * 32);
 #pragma unroll
-    for (int t = 0; t < VT; ++t) vr[t] = *(const uint4 *)(vc + (int64_t)min(r0 + quad * 4 + t * (4 / VT) + sub, cend - 1) * s.st);
+    for (int t = 0; t < VT; ++t) vr[t] = load_piece<(STREAM > 0)>(vc + (int64_t)min(r0 + quad * 4 + t * (4 / VT) + sub, cend - 1) * s.st);
   };
   int blk = wave;
   load_block(blk);
@@ -523,12 +532,28 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
 template <typename T, int D, int G>
 static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, const void *kc, const void *vc,
                              const int32_t *n_valid, float *part, hipStream_t stream) {
-  if constexpr (sizeof(T) == 2)     // bf16 / fp16: scores on the matrix pipe
-    hipLaunchKernelGGL((decode_partial_mfma_kernel<D, G, !__is_same(T, uint16_t)>), grid, dim3(DEC_THREADS), 0, stream, s,
-                       (const uint16_t *)q, (const uint16_t *)kc, (const uint16_t *)vc, n_valid, part);
-  else
-    hipLaunchKernelGGL((decode_partial_kernel<T, D, G>), grid, dim3(DEC_THREADS), 0, stream, s, (const T *)q, (const T *)kc,
-                       (const T *)vc, n_valid, part);
+  // Where a model's caches (32 layers, say) exceed the memory-side cache, no row is found there at the next token,
+  // and the values, as both caches in fp32, are best streamed.  32 layers, one sequence of 4128 rows (18 MB
+  // a layer): 12.45 us a layer with plain loads, 11.61 so; eight in fp32 (287 MB a layer): 60.1 and 53.9; eleven of mixed
+  // lengths, f16 (38 MB a layer): 19.3 and 17.8.  (A layer of 7 MB whose caches stay there: 8.3 us, 8.7 if streamed.)
+  // Keys of 16-bit caches are read in operand layout, 64 bytes of a row at a time, and a streamed line may be gone when
+  // its other half is asked for: they stream only where a layer by itself exceeds the memory-side cache.  Four layers of
+  // 64 sequences of 4128 rows (1.1 GB a layer): 779 us with plain loads, 688 with both streamed (values alone: 2 % more);
+  // of the eleven sequences above: 77.4, 76.2, 71.7 us with values alone.
+  const int64_t bytes = 2 * (int64_t)s.B * s.Hkv * s.capacity * D * (int64_t)sizeof(T);
+  const int stream_level = bytes > MEMORY_CACHE_BYTES ? 2 : bytes > MEMORY_CACHE_BYTES / 32 ? 1 : 0;
+#define WKV_PARTIAL(KERNEL, E) \
+  hipLaunchKernelGGL(KERNEL, grid, dim3(DEC_THREADS), 0, stream, s, (const E *)q, (const E *)kc, (const E *)vc, n_valid, part)
+  if constexpr (sizeof(T) == 2) {   // bf16 / fp16: scores on the matrix pipe
+    constexpr bool F16 = !__is_same(T, uint16_t);
+    if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2>), uint16_t);
+    else if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1>), uint16_t);
+    else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0>), uint16_t);
+  } else {
+    if (stream_level) WKV_PARTIAL((decode_partial_kernel<T, D, G, true>), T);
+    else WKV_PARTIAL((decode_partial_kernel<T, D, G, false>), T);
+  }
+#undef WKV_PARTIAL
 }
 
 template <typename T, int D>

@@ -38,3 +38,29 @@ def test_row_counts_around_range_edges(dtype, G, d, rows, device):
             np.testing.assert_allclose(got[b, h * G:(h + 1) * G], want, rtol=1e-3, atol=2e-5, err_msg=f"rows {n} h{h}")
             assert torch.equal(kc[b, h, n], kn[b, h]) and torch.equal(vc[b, h, n], vn[b, h])
     assert n_valid.cpu().tolist() == [[n + 1] * H for n in rows]
+
+
+@pytest.mark.parametrize("dtype,G,d", [("bf16", 4, 128), ("f16", 7, 64), ("f32", 2, 128)])
+@pytest.mark.parametrize("cache_mb", [7, 9, 257])
+def test_row_loads_by_cache_size(dtype, G, d, cache_mb, device):
+    # the loads of the rows are chosen by the size of a layer's caches: below 8 MB, to 256 MB, above
+    H, tdt = 2, {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
+    cap = (cache_mb << 20) // (2 * H * d * tdt.itemsize)
+    rows = min(cap - 1, 5003)
+    gen = torch.Generator(device=device).manual_seed(cache_mb)
+    mk = lambda *shape: torch.randn(shape, device=device, dtype=torch.float32, generator=gen).to(tdt)
+    kc, vc = (torch.full((1, H, cap, d), float("nan"), dtype=tdt, device=device) for _ in range(2))
+    kc[:, :, :rows], vc[:, :, :rows] = mk(1, H, rows, d), mk(1, H, rows, d)
+    q, kn, vn = 2 * mk(1, G * H, d), mk(1, H, d), mk(1, H, d)
+    n_valid = torch.full((1, H), rows, dtype=torch.int32, device=device)
+    shape = W.DecodeShape(batch=1, n_q_heads=G * H, n_kv_heads=H, head_dim=d, capacity=cap,
+                          dtype={"bf16": W.WKV_BF16, "f16": W.WKV_F16, "f32": W.WKV_F32}[dtype])
+    ws = torch.empty(W.wkv_decode_workspace_bytes(shape), dtype=torch.uint8, device=device)
+    out = torch.zeros((1, G * H, d), dtype=torch.float32, device=device)
+    W.wkv_decode_step(shape, q, kn, vn, kc, vc, n_valid, out, ws)
+    torch.cuda.synchronize()
+    f64 = lambda t: t.to("cpu").to(torch.float64).numpy()
+    for h in range(H):
+        want, *_ = O.decode_step(f64(q[0, h * G:(h + 1) * G]), f64(kc[0, h, :rows]), f64(vc[0, h, :rows]), f64(kn[0, h]), f64(vn[0, h]))
+        np.testing.assert_allclose(f64(out[0, h * G:(h + 1) * G]), want, rtol=1e-3, atol=2e-5, err_msg=f"h{h}")
+    assert torch.equal(kc[0, :, rows], kn[0]) and n_valid.cpu().tolist() == [[rows + 1] * H]
