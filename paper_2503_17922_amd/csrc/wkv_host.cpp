@@ -185,6 +185,11 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   // with plain loads, 57.6, 87.9, 115.8 with nontemporal ones, 6 groups (403 MB) 206.2 and 201.1; the 32K model's passes (537
   // MB) 390 and 370 us; 16384 tokens and four layers 45.9 and 48.1 us; 256 softmax rows, 134 MB 118.8 and 123.0 us.
   pl.nontemporal = keys * s.d * elem_bytes(s.dtype) > MEMORY_CACHE_BYTES;
+  // Key tiles fetched twice, once per row group, against a barrier per tile: worth it while a chunk is short enough for
+  // the two waves to stay together and the cache has room for what they lose.  Whole calls with a barrier / with rings
+  // of their own: three ragged f16 sequences, 224 rows (17 MB of keys a group) 80.3 / 75.5 us; 16384 tokens, 256 rows, one group
+  // (34 MB) 53.9 / 51.7 us, 64 channels, four groups (67 MB) 92.0 / 85.1 us; 134 MB 118.0 / 117.0 us; 268 MB 289.6 / 292.6 us.
+  pl.own_rings = keys * s.d * elem_bytes(s.dtype) <= MEMORY_CACHE_BYTES / 2;
   pl.n_chunks1 = 0;
   for (int32_t b = 0; b < s.B; ++b) pl.n_chunks1 = std::max(pl.n_chunks1, pl.pass[0].first[b + 1] - pl.pass[0].first[b]);
   // every pass-2 workgroup re-reads the partials of its rows when it folds them itself: 64 KB at 128 rows and 64

@@ -94,6 +94,7 @@ struct ScorePlan {
   int32_t n_chunks1;           // most workgroups of a sequence in the statistics pass
   int32_t m_pad;               // rows padded to a multiple of 16
   bool nontemporal;            // the key loads put nothing into the memory-side cache
+  bool own_rings;              // with two row groups of 16-bit inputs every wave fetches its key tiles itself
   bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
 };
 

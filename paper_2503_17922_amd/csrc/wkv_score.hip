@@ -116,9 +116,10 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 // that later read the same piece of 16 rows find them in different banks.  Global reads stay whole rows.
 // Tile i is in registers (the next one being read from LDS) while tiles i+2 .. i+NS are on their way; the loads are
 // counted by hand (s_waitcnt vmcnt), which holds because the loop has no other global access.  With one row group
-// a wave fills its own slot and the waves never synchronise in the loop; with several, the waves of a slot
-// fetch a part of each tile and the workgroup meets at a barrier per tile (fetching every tile once per row
-// group instead would leave half the bytes in flight).
+// a wave fills its own slot and the waves never synchronise in the loop.  With several, the waves of a slot fetch a part
+// of each tile and the workgroup meets at a barrier per tile, or (OWN_RINGS, two groups of 16-bit inputs) every wave
+// fetches whole tiles for itself: half the bytes in flight, no barriers, and the second of a slot's waves finds the
+// tile in the L2, as long as the two do not drift too far apart (see plan_score).
 //
 // What bounds it.  Per 64 logits a SIMD issues one 16x16x32 MFMA (8.6 ns on random data at the clocks the chip then
 // holds) and one multiply-add, exponential and add (7.8 ns); they hardly overlap: 13 ns together in a loop of
@@ -131,7 +132,7 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 constexpr int score_slots(int row_groups) { return row_groups == 4 ? 2 : 4; }         // key tile slots of a workgroup
 constexpr int score_threads(int row_groups) { return 64 * row_groups * score_slots(row_groups); }
 
-template <int D, int DT, int RT, int HV>
+template <int D, int DT, int RT, int HV, bool OWN_RINGS>
 struct ScoreConfig {
   static constexpr int ES = DT == DT_F32 ? 4 : 2;       // bytes per element
   static constexpr int ROWB = D * ES;                   // bytes per key row
@@ -139,14 +140,17 @@ struct ScoreConfig {
   static constexpr int TILE = 16 * ROWB;
   static constexpr int PPR = ROWB / 16;                 // 16-byte pieces per row: 8, 16 or 32
   static constexpr int RPI = 64 / PPR;                  // rows per DMA instruction
-  static constexpr int LPT = TILE / 1024 / HV;          // DMA instructions per tile and wave
+  static constexpr bool SHARED = HV > 1 && !OWN_RINGS;
+  static constexpr int PARTS = SHARED ? HV : 1;         // waves that fetch a tile together
+  static constexpr int LPT = TILE / 1024 / PARTS;       // DMA instructions per tile and wave
   static constexpr int KW = score_slots(HV), NT = score_threads(HV), WAVES = NT / 64;
-  static constexpr int FIT = (HV == 1 ? 65536 : 131072) / (KW * TILE);
-  static constexpr int NS = FIT < 8 * HV ? FIT : 8 * HV;
-  static constexpr int RING = KW * NS * TILE;
+  static constexpr int RINGS = SHARED ? KW : WAVES;
+  static constexpr int FIT = (HV == 1 ? 65536 : 131072) / (RINGS * TILE);
+  static constexpr int NS = FIT < 8 * PARTS ? FIT : 8 * PARTS;
+  static constexpr int RING = RINGS * NS * TILE;
   // the queries pass through the part of the ring that is filled last
   static constexpr int QBYTES = HV * RT * 16 * ROWB;
-  static constexpr int FIRST = NS - (QBYTES + KW * TILE - 1) / (KW * TILE);
+  static constexpr int FIRST = NS - (QBYTES + RINGS * TILE - 1) / (RINGS * TILE);
   static_assert(FIRST >= 0, "the queries fit the ring");
   static_assert(NS >= 2, "a tile being read and one under way");
   // Read the next tile's fragments while this one is computed.  fp32: a tile takes thousands of cycles on the matrix
@@ -166,14 +170,14 @@ __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)
 
 // NT_LOADS: the keys are not put into the memory-side cache (see plan_score).  Kernels of their own, as a branch at every fetch
 // costs small calls 1 %.
-template <int D, int DT, int RT, int HV, int PASS, bool NT_LOADS>
+template <int D, int DT, int RT, int HV, int PASS, bool NT_LOADS, bool OWN_RINGS>
 __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, BatchParams bp, GroupPtrs gp, ScorePlan pl,
                                                                                  float2 *__restrict__ partials,
                                                                                  const float *__restrict__ lse_g,
                                                                                  float *__restrict__ t_out,
                                                                                  float *__restrict__ s_pool,
                                                                                  const uint32_t *__restrict__ only_if) {
-  using C = ScoreConfig<D, DT, RT, HV>;
+  using C = ScoreConfig<D, DT, RT, HV, OWN_RINGS>;
   constexpr int KS = C::KS, KW = C::KW, NT = C::NT, NS = C::NS, ROWS = HV * RT * 16;
   __shared__ __attribute__((aligned(1024))) char ring[C::RING];
   __shared__ __attribute__((aligned(16))) float t_s[PASS == 2 ? HV * (C::SEG + KW * 16) : 4];     // token scores of a segment
@@ -198,6 +202,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = wave / KW, kw = wave % KW;               // row group, key tile slot of this wave
   const int col = lane & 15, quad = lane >> 4;
+  const int my_ring = C::SHARED ? kw : wave, my_part = C::SHARED ? half : 0;
 
   const int chunk = pp.chunk[b] * CHUNK_UNIT;
   const int limit = PASS == 1 ? L : n_review;               // keys that matter to this pass
@@ -226,10 +231,10 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   uint32_t off[C::LPT];                                     // this lane's piece of each of its DMA instructions, from the tile's first row
 #pragma unroll
   for (int n = 0; n < C::LPT; ++n) {
-    const int r = (half * C::LPT + n) * C::RPI + lane / C::PPR;
+    const int r = (my_part * C::LPT + n) * C::RPI + lane / C::PPR;
     off[n] = (uint32_t)((uint32_t)r * (uint32_t)kst + C::swizzle(r, lane % C::PPR) * 16);
   }
-  const uint32_t ring_lds = lds_address(ring) + kw * (NS * C::TILE) + half * (C::LPT * 1024);
+  const uint32_t ring_lds = lds_address(ring) + my_ring * (NS * C::TILE) + my_part * (C::LPT * 1024);
   // keys j .. j+15 (this wave's part) into place `slot`; rows from cend on are not read (their lanes fetch row cend-1 again)
   auto fetch = [&](int j, int slot) __attribute__((always_inline)) {
     const uint32_t dst = ring_lds + slot * C::TILE;
@@ -247,7 +252,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
     } else {
 #pragma unroll
       for (int n = 0; n < C::LPT; ++n) {
-        const int r = (half * C::LPT + n) * C::RPI + lane / C::PPR;
+        const int r = (my_part * C::LPT + n) * C::RPI + lane / C::PPR;
         const char *p = kbase + (int64_t)min(j + r, cend - 1) * kst + C::swizzle(r, lane % C::PPR) * 16;
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst + n * 1024), "v"(p) : "memory");
       }
@@ -259,7 +264,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
     fetch(jf, slot_f);
     slot_f = slot_f == NS - 1 ? 0 : slot_f + 1;
     jf += KW * 16;
-    while (PASS == 2 && (HV > 1 ? jf - kw * 16 : jf) >= jf_end && jf_end < cend) {
+    while (PASS == 2 && (C::SHARED ? jf - kw * 16 : jf) >= jf_end && jf_end < cend) {
       jf = jf_end + kw * 16;
       jf_end = min(jf_end + seg_len, cend);
     }
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   const uint32_t lane_row = col * C::ROWB;
   int slot_r = 0;                                           // the slot read next
   auto read_frags = [&](Frags &kf) __attribute__((always_inline)) {
-    const char *p = ring + kw * (NS * C::TILE) + slot_r * C::TILE + lane_row;
+    const char *p = ring + my_ring * (NS * C::TILE) + slot_r * C::TILE + lane_row;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) kf.f[ks] = *(const bf16x8 *)(p + C::swizzle(col, ks * 4 + quad) * 16);
     slot_r = slot_r == NS - 1 ? 0 : slot_r + 1;
@@ -362,14 +367,14 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   auto tile = [&](Frags &kf, Frags &kn, int j0, int seg0) __attribute__((always_inline)) {
     if (C::AHEAD) {                                         // tile i+1 out of the ring, tile i+NS into the slot tile i left
       wait_vmcnt<(NS - 2) * C::LPT>();
-      if (HV > 1) barrier();                                // (every part of it; every wave has tile i in registers)
+      if (C::SHARED) barrier();                             // (every part of it; every wave has tile i in registers)
       read_frags(kn);
     } else {
       wait_vmcnt<(NS - 1) * C::LPT>();
-      if (HV > 1) barrier();
+      if (C::SHARED) barrier();
       read_frags(kf);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // its place is free for the fetch below
-      if (HV > 1) barrier();
+      if (C::SHARED) barrier();
     }
     fetch_next();
     if (PASS == 1) {
@@ -438,14 +443,14 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   Frags ka, kb;
   if (C::AHEAD) {
     wait_vmcnt<(NS - 1) * C::LPT>();
-    if (HV > 1) barrier();
+    if (C::SHARED) barrier();
     read_frags(ka);
   }
   for (int seg0 = c0; seg0 < cend; seg0 += seg_len) {
     const int seg_end = min(seg0 + seg_len, cend);
     // with row groups every slot takes a tile in every round, if need be one past the end (masked in pass 1, past the
     // scores that count in pass 2): the waves meet at barriers
-    for (int j = seg0 + kw * 16; (HV > 1 ? j - kw * 16 : j) < seg_end; j += KW * 16) {
+    for (int j = seg0 + kw * 16; (C::SHARED ? j - kw * 16 : j) < seg_end; j += KW * 16) {
       tile(ka, kb, j, seg0);
       if (C::AHEAD) ka = kb;
     }
@@ -492,18 +497,18 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
 // =========================================================================================
 // launch
 // =========================================================================================
-template <int D, int DT, int RT, int HV, bool NT_LOADS>
+template <int D, int DT, int RT, int HV, bool NT_LOADS, bool OWN_RINGS = false>
 static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
                                 bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
                                 hipEvent_t mid, const uint32_t *only_if) {
-  const dim3 block(ScoreConfig<D, DT, RT, HV>::NT);
+  const dim3 block(score_threads(HV));
   hipError_t e;
   if (have_lse) {                                      // no statistics pass: pass 2 reads the caller's normalisers
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
   } else {
     dim3 g1(pl.pass[0].first[s.B], s.Hkv, n_groups);
-    hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 1, NT_LOADS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
+    hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 1, NT_LOADS, OWN_RINGS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
@@ -515,7 +520,7 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
   ScorePlan pl2 = pl;
   if (have_lse) pl2.fold_in_pass2 = false;
   dim3 g2(pl.pass[1].first[s.B], s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 2, NT_LOADS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
+  hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 2, NT_LOADS, OWN_RINGS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
   return hipGetLastError();
 }
 
@@ -526,16 +531,20 @@ static hipError_t launch_rows(const Shape &s, const BatchParams &bp, const Score
   // Row tiles per wave: the counts of the usual head layouts (w_obs of 8 to 32 with 1 to 8 query heads per KV
   // head) are met exactly, the rest rounds up; a wave holds eight at most, four of fp32 with 128 channels.
   const int mt = pl.m_pad / 16;
+#define WKV_PASSES(RR, HH, ...) \
+  launch_passes<D, DT, RR, HH, __VA_ARGS__>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if)
 #define WKV_ROWS(RR, HH) \
-  if (mt <= RR * HH) \
-    return pl.nontemporal ? launch_passes<D, DT, RR, HH, true>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if) \
-                          : launch_passes<D, DT, RR, HH, false>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
+  if (mt <= RR * HH) { \
+    if constexpr (HH == 2 && DT != DT_F32) if (pl.own_rings) return WKV_PASSES(RR, HH, false, true); \
+    return pl.nontemporal ? WKV_PASSES(RR, HH, true) : WKV_PASSES(RR, HH, false); \
+  }
   if constexpr (DT == DT_F32 && D == 128) {
     WKV_ROWS(1, 1) WKV_ROWS(2, 1) WKV_ROWS(4, 1) WKV_ROWS(4, 2) WKV_ROWS(4, 4)
   } else {
     WKV_ROWS(1, 1) WKV_ROWS(2, 1) WKV_ROWS(4, 1) WKV_ROWS(6, 1) WKV_ROWS(7, 1) WKV_ROWS(8, 1) WKV_ROWS(6, 2) WKV_ROWS(7, 2) WKV_ROWS(8, 2)
   }
 #undef WKV_ROWS
+#undef WKV_PASSES
   return hipErrorInvalidValue;
 }
 

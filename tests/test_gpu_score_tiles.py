@@ -55,3 +55,12 @@ def test_key_rows_too_far_apart_for_32_bit_offsets(device):
     W.wkv_compress_groups(problem, 1, 1, st.q, None, [k], [v], [ko], [vo], wi, ti, nk, st.workspace)
     torch.cuda.synchronize()
     assert torch.equal(wi, st.win_idx) and torch.equal(ti, st.tok_idx) and torch.equal(ko, st.k_out[0]) and torch.equal(vo, st.k_out[0])
+
+
+@pytest.mark.parametrize("n_groups", [3, 5, 8])
+def test_two_row_groups_by_size_of_the_key_stream(n_groups, device):
+    # 256 softmax rows: key tiles fetched by every wave (101 MB of keys), by the waves of a slot together (168 MB), and
+    # so by nontemporal loads (269 MB)
+    w = S.scaled_workload(S.make_workload("c4"), name="streams", n_groups=n_groups, gamma=1, n_q_heads=64, seq_len=[16397], win=[24], top_p=[9],
+                          k_windows=[80])
+    run_and_check(w, device, n_oracle=4, n_gather_cpu=2, stage_groups=[1])
