@@ -75,7 +75,7 @@ __device__ __forceinline__ float quads_max(float x) {
 }
 
 // ---- MFMA building blocks ----------------------------------
-constexpr int MF_THREADS = 256;           // per row half (see score_mfma_kernel)
+constexpr int MF_THREADS = 256;           // of a workgroup of the single-read kernel
 constexpr int MF_WAVES = 4;              // waves that share the key tiles of an iteration
 constexpr int MF_KT = 2;                 // key tiles of 16 per wave iteration (share each B fragment)
 constexpr float MF_BIG = 1.0e30f;        // a tile sum above this re-references the row (2^100)
