@@ -358,11 +358,13 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
     float sc[4], pr[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) sc[e] = r0 + e < cend ? acc[e] * s.c1 : -INFINITY;
-    const float mn = fmaxf(m, quads_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]))));   // finite: the block has a row
-    const float corr = fast_exp2(m - mn);        // m = -inf: 0
+    const float mn = fmaxf(m, quads_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]))));
+    // -inf: every row so far has a logit of -inf (an infinite key, products that overflow) and weighs nothing
+    const bool none = mn == -INFINITY;
+    const float corr = none ? 1.0f : fast_exp2(m - mn);        // m = -inf: 0
     m = mn;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pr[e] = fast_exp2(sc[e] - mn);
+    for (int e = 0; e < 4; ++e) pr[e] = none ? 0.0f : fast_exp2(sc[e] - mn);
     l = l * corr + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
     if (__any(corr != 1.0f && col < G))
       static_for<G>([&](auto g) {
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
     float4 oo = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int w = 0; w < DEC_WAVES; ++w) {
-      const float a = fast_exp2(ml_s[w][g].x - mm);          // wave 0 has at least one row: mm is finite
+      const float a = mm == -INFINITY ? 0.0f : fast_exp2(ml_s[w][g].x - mm);      // (no row of the range weighs anything)
       const float4 x = *(const float4 *)&o_s[w][g][c];
       ll = fmaf(ml_s[w][g].y, a, ll);
       oo.x = fmaf(x.x, a, oo.x); oo.y = fmaf(x.y, a, oo.y); oo.z = fmaf(x.z, a, oo.z); oo.w = fmaf(x.w, a, oo.w);
