@@ -79,9 +79,19 @@ def native():
     if _calls is None:
         lib()
         module = importlib.import_module("._native", __name__)
-        module.set_slow_stream(_current_stream)
+        module.bind(_current_stream, _structure, Problem, _Problem, DecodeShape, _DecodeShape)
         _calls = module
     return _calls
+
+
+def _structure(o, kind):
+    """The structure that a ctypes function with a pointer to ``kind`` as its first argument would get from ``o.ref()``."""
+    r = o.ref()
+    try:
+        C.POINTER(kind).from_param(r)
+    except TypeError as e:
+        raise C.ArgumentError(f"argument 1: {e}") from None
+    return r._obj if hasattr(r, "_obj") else r.contents        # of byref(), of a pointer
 
 
 def _current_stream() -> int:
@@ -170,7 +180,6 @@ class Problem:
                     nkeep_max = dims.nkeep_max
             if nkeep_max is not None:      # an invalid problem keeps the placeholder; every call rejects it anyway
                 self.c.out_stride_b, self.c.out_stride_h, self.c.out_stride_t = n_kv_heads * nkeep_max * d, nkeep_max * d, d
-        self._addr = C.addressof(self.c)
 
     def ref(self):
         return C.byref(self.c)
@@ -284,7 +293,6 @@ class DecodeShape:
                  scale: float = 0.0, cache_strides=None, flags: int = 0):
         cache_strides = cache_strides or (n_kv_heads * capacity * head_dim, capacity * head_dim, head_dim)
         self.c = _DecodeShape(batch, n_q_heads, n_kv_heads, head_dim, dtype, scale, capacity, *cache_strides, flags)
-        self._addr = C.addressof(self.c)
 
     def ref(self):
         return C.byref(self.c)

@@ -13,18 +13,37 @@
 
 namespace {
 
-PyObject *s_addr, *s_data_ptr, *s_numel, *s_element_size;     // interned attribute names
+PyObject *s_c, *s_data_ptr, *s_numel, *s_element_size;        // interned attribute names
 PyObject *slow_stream;                                        // callable: the current stream by torch's public API
 PyObject *get_device, *get_raw_stream;                        // torch._C functions behind it, once torch has initialised the GPU
+PyObject *convert;                                            // callable (o, structure type): what ctypes takes from o.ref()
 
 // Every converter returns false with a Python exception set.
-bool address(PyObject *o, void **out) {
-  PyObject *v = PyObject_GetAttr(o, s_addr);
-  if (!v) return false;
-  *out = PyLong_AsVoidPtr(v);
-  Py_DECREF(v);
-  return !PyErr_Occurred();
-}
+// The structure behind a Problem or DecodeShape, held until the call is over.  Taken from `.c` as it is now (an object
+// may be copied or given another structure), of exactly this type; anything else goes to `convert`, which accepts and
+// refuses what a ctypes call of the same function does.
+struct Kind { PyObject *wrapper, *structure; };
+Kind problem_kind, shape_kind;
+struct Structure {
+  Py_buffer view;
+  Structure() { view.obj = nullptr; }
+  ~Structure() { if (view.obj) PyBuffer_Release(&view); }
+  Structure(const Structure &) = delete;
+  bool fill(PyObject *o, const Kind &kind) {
+    PyObject *c = nullptr;
+    if ((PyObject *)Py_TYPE(o) == kind.wrapper && !(c = PyObject_GetAttr(o, s_c))) return false;
+    if (!c || (PyObject *)Py_TYPE(c) != kind.structure) {
+      Py_XDECREF(c);
+      if (!convert) { PyErr_SetString(PyExc_RuntimeError, "bind was not called"); return false; }
+      if (!(c = PyObject_CallFunctionObjArgs(convert, o, kind.structure, nullptr))) return false;
+    }
+    const bool ok = PyObject_GetBuffer(c, &view, PyBUF_SIMPLE) == 0;
+    Py_DECREF(c);                                // the buffer keeps it
+    return ok;
+  }
+  const wkv_problem *problem() const { return (const wkv_problem *)view.buf; }
+  const wkv_decode_shape *shape() const { return (const wkv_decode_shape *)view.buf; }
+};
 
 bool pointer(PyObject *o, void **out) {
   if (o == Py_None) { *out = nullptr; return true; }
@@ -94,7 +113,7 @@ bool stream_of(PyObject *o, void **out) {
     v = PyObject_CallOneArg(get_raw_stream, dev);
     Py_DECREF(dev);
   } else {
-    if (!slow_stream) { PyErr_SetString(PyExc_RuntimeError, "set_slow_stream was not called"); return false; }
+    if (!slow_stream) { PyErr_SetString(PyExc_RuntimeError, "bind was not called"); return false; }
     v = PyObject_CallNoArgs(slow_stream);        // initialises torch's GPU side where that has not happened yet
   }
   if (!v) return false;
@@ -129,71 +148,78 @@ PyObject *call(F &&f) {
 
 // (shape, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, workspace, stream)
 PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *sh, *t[7], *ws, *st;
+  Structure sh;
+  void *t[7], *ws, *st;
   size_t bytes;
-  if (!arity(n, 10) || !address(a[0], &sh)) return nullptr;
+  if (!arity(n, 10) || !sh.fill(a[0], shape_kind)) return nullptr;
   for (int i = 0; i < 7; ++i) if (!pointer(a[1 + i], &t[i])) return nullptr;
   if (!workspace(a[8], &ws, &bytes) || !stream_of(a[9], &st)) return nullptr;
-  return call([&] { return wkv_decode_step((const wkv_decode_shape *)sh, t[0], t[1], t[2], t[3], t[4], (int32_t *)t[5], (float *)t[6], ws, bytes, st); });
+  return call([&] { return wkv_decode_step(sh.shape(), t[0], t[1], t[2], t[3], t[4], (int32_t *)t[5], (float *)t[6], ws, bytes, st); });
 }
 
 // (shape, q_new, k_new, v_new, k_cache, v_cache, n_valid, out, stream)
 PyObject *decode_step_static(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *sh, *t[7], *st;
-  if (!arity(n, 9) || !address(a[0], &sh)) return nullptr;
+  Structure sh;
+  void *t[7], *st;
+  if (!arity(n, 9) || !sh.fill(a[0], shape_kind)) return nullptr;
   for (int i = 0; i < 7; ++i) if (!pointer(a[1 + i], &t[i])) return nullptr;
   if (!stream_of(a[8], &st)) return nullptr;
-  return call([&] { return wkv_decode_step_static((const wkv_decode_shape *)sh, t[0], t[1], t[2], t[3], t[4], (int32_t *)t[5], (float *)t[6], st); });
+  return call([&] { return wkv_decode_step_static(sh.shape(), t[0], t[1], t[2], t[3], t[4], (int32_t *)t[5], (float *)t[6], st); });
 }
 
 // (problem, q_obs, k_first, lse_obs, t_out, workspace, stream)
 PyObject *score(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *pr, *t[4], *ws, *st;
+  Structure pr;
+  void *t[4], *ws, *st;
   size_t bytes;
-  if (!arity(n, 7) || !address(a[0], &pr)) return nullptr;
+  if (!arity(n, 7) || !pr.fill(a[0], problem_kind)) return nullptr;
   for (int i = 0; i < 4; ++i) if (!pointer(a[1 + i], &t[i])) return nullptr;
   if (!workspace(a[5], &ws, &bytes) || !stream_of(a[6], &st)) return nullptr;
-  return call([&] { return wkv_score((const wkv_problem *)pr, t[0], t[1], (const float *)t[2], (float *)t[3], ws, bytes, st); });
+  return call([&] { return wkv_score(pr.problem(), t[0], t[1], (const float *)t[2], (float *)t[3], ws, bytes, st); });
 }
 
 // (problem, t, s_out, stream)
 PyObject *window_pool(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *pr, *t, *s, *st;
-  if (!arity(n, 4) || !address(a[0], &pr) || !pointer(a[1], &t) || !pointer(a[2], &s) || !stream_of(a[3], &st)) return nullptr;
-  return call([&] { return wkv_window_pool((const wkv_problem *)pr, (const float *)t, (float *)s, st); });
+  Structure pr;
+  void *t, *s, *st;
+  if (!arity(n, 4) || !pr.fill(a[0], problem_kind) || !pointer(a[1], &t) || !pointer(a[2], &s) || !stream_of(a[3], &st)) return nullptr;
+  return call([&] { return wkv_window_pool(pr.problem(), (const float *)t, (float *)s, st); });
 }
 
 // (problem, s, win_idx_out, tok_idx_out, n_keep_out, stream)
 PyObject *topk_windows(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *pr, *t[4], *st;
-  if (!arity(n, 6) || !address(a[0], &pr)) return nullptr;
+  Structure pr;
+  void *t[4], *st;
+  if (!arity(n, 6) || !pr.fill(a[0], problem_kind)) return nullptr;
   for (int i = 0; i < 4; ++i) if (!pointer(a[1 + i], &t[i])) return nullptr;
   if (!stream_of(a[5], &st)) return nullptr;
-  return call([&] { return wkv_topk_windows((const wkv_problem *)pr, (const float *)t[0], (int32_t *)t[1], (int32_t *)t[2], (int32_t *)t[3], st); });
+  return call([&] { return wkv_topk_windows(pr.problem(), (const float *)t[0], (int32_t *)t[1], (int32_t *)t[2], (int32_t *)t[3], st); });
 }
 
 // (problem, k_layers, v_layers, tok_idx, n_keep, k_out_layers, v_out_layers, stream)
 PyObject *gather_group(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *pr, *ti, *nk, *st;
+  Structure pr;
+  void *ti, *nk, *st;
   Pointers<WKV_MAX_LAYERS> k, v, ko, vo;
-  if (!arity(n, 8) || !address(a[0], &pr) || !k.fill(a[1]) || !v.fill(a[2]) || !pointer(a[3], &ti) || !pointer(a[4], &nk) ||
+  if (!arity(n, 8) || !pr.fill(a[0], problem_kind) || !k.fill(a[1]) || !v.fill(a[2]) || !pointer(a[3], &ti) || !pointer(a[4], &nk) ||
       !ko.fill(a[5]) || !vo.fill(a[6]) || !stream_of(a[7], &st)) return nullptr;
   const int32_t layers = (int32_t)(k.n > WKV_MAX_LAYERS ? WKV_MAX_LAYERS + 1 : k.n);
-  return call([&] { return wkv_gather_group((const wkv_problem *)pr, layers, k.p, v.p, (const int32_t *)ti, (const int32_t *)nk, ko.p, vo.p, st); });
+  return call([&] { return wkv_gather_group(pr.problem(), layers, k.p, v.p, (const int32_t *)ti, (const int32_t *)nk, ko.p, vo.p, st); });
 }
 
 // (problem, gamma, q_obs, lse_obs, k_layers, v_layers, k_out_layers, v_out_layers, win_idx, tok_idx, n_keep, workspace, stream)
 PyObject *compress_group(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *pr, *q, *lse, *t[3], *ws, *st;
+  Structure pr;
+  void *q, *lse, *t[3], *ws, *st;
   size_t bytes;
   int32_t gamma;
   Pointers<WKV_MAX_LAYERS> k, v, ko, vo;
-  if (!arity(n, 13) || !address(a[0], &pr) || !integer(a[1], &gamma) || !pointer(a[2], &q) || !pointer(a[3], &lse) || !k.fill(a[4]) ||
+  if (!arity(n, 13) || !pr.fill(a[0], problem_kind) || !integer(a[1], &gamma) || !pointer(a[2], &q) || !pointer(a[3], &lse) || !k.fill(a[4]) ||
       !v.fill(a[5]) || !ko.fill(a[6]) || !vo.fill(a[7])) return nullptr;
   for (int i = 0; i < 3; ++i) if (!pointer(a[8 + i], &t[i])) return nullptr;
   if (!workspace(a[11], &ws, &bytes) || !stream_of(a[12], &st)) return nullptr;
   return call([&] {
-    return wkv_compress_group((const wkv_problem *)pr, gamma, q, (const float *)lse, k.p, v.p, ko.p, vo.p, (int32_t *)t[0], (int32_t *)t[1],
+    return wkv_compress_group(pr.problem(), gamma, q, (const float *)lse, k.p, v.p, ko.p, vo.p, (int32_t *)t[0], (int32_t *)t[1],
                               (int32_t *)t[2], ws, bytes, st);
   });
 }
@@ -201,13 +227,14 @@ PyObject *compress_group(PyObject *, PyObject *const *a, Py_ssize_t n) {
 // (problem, n_groups, gamma, q_obs_groups, lse_obs_groups | None, k_windows_groups | None (nested), k_layers, v_layers,
 //  k_out_layers, v_out_layers, win_idx, tok_idx, n_keep, workspace, stream)
 PyObject *compress_groups(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  void *pr, *t[3], *ws, *st;
+  Structure pr;
+  void *t[3], *ws, *st;
   size_t bytes;
   int32_t n_groups, gamma;
   Pointers<WKV_MAX_LAYERS> k, v, ko, vo;
   Pointers<WKV_MAX_GROUPS> q, lse;
   int32_t budgets[WKV_MAX_GROUPS * WKV_MAX_BATCH];
-  if (!arity(n, 15) || !address(a[0], &pr) || !integer(a[1], &n_groups) || !integer(a[2], &gamma) || !q.fill(a[3])) return nullptr;
+  if (!arity(n, 15) || !pr.fill(a[0], problem_kind) || !integer(a[1], &n_groups) || !integer(a[2], &gamma) || !q.fill(a[3])) return nullptr;
   if (a[4] != Py_None && !lse.fill(a[4])) return nullptr;
   if (a[5] != Py_None) {                     // row-major, as the ABI wants it; entries a caller leaves out are -1: refused
     std::memset(budgets, 0xff, sizeof budgets);
@@ -232,31 +259,36 @@ PyObject *compress_groups(PyObject *, PyObject *const *a, Py_ssize_t n) {
   for (int i = 0; i < 3; ++i) if (!pointer(a[10 + i], &t[i])) return nullptr;
   if (!workspace(a[13], &ws, &bytes) || !stream_of(a[14], &st)) return nullptr;
   return call([&] {
-    return wkv_compress_groups((const wkv_problem *)pr, n_groups, gamma, q.p, a[4] == Py_None ? nullptr : (const float *const *)lse.p,
+    return wkv_compress_groups(pr.problem(), n_groups, gamma, q.p, a[4] == Py_None ? nullptr : (const float *const *)lse.p,
                                a[5] == Py_None ? nullptr : budgets, k.p, v.p, ko.p, vo.p, (int32_t *)t[0], (int32_t *)t[1],
                                (int32_t *)t[2], ws, bytes, st);
   });
 }
 
-PyObject *set_slow_stream(PyObject *, PyObject *f) {
-  Py_INCREF(f);
-  Py_XSETREF(slow_stream, f);
+// (slow_stream, convert, Problem, its structure, DecodeShape, its structure)
+PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  if (!arity(n, 6)) return nullptr;
+  PyObject **to[6] = {&slow_stream, &convert, &problem_kind.wrapper, &problem_kind.structure, &shape_kind.wrapper, &shape_kind.structure};
+  for (int i = 0; i < 6; ++i) {
+    Py_INCREF(a[i]);
+    Py_XSETREF(*to[i], a[i]);
+  }
   Py_RETURN_NONE;
 }
 
 #define FAST(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(decode_step), FAST(decode_step_static), FAST(score), FAST(window_pool), FAST(topk_windows),
                          FAST(gather_group), FAST(compress_group), FAST(compress_groups),
-                         {"set_slow_stream", set_slow_stream, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+                         FAST(bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
 PyMODINIT_FUNC PyInit__native(void) {
-  s_addr = PyUnicode_InternFromString("_addr");
+  s_c = PyUnicode_InternFromString("c");
   s_data_ptr = PyUnicode_InternFromString("data_ptr");
   s_numel = PyUnicode_InternFromString("numel");
   s_element_size = PyUnicode_InternFromString("element_size");
-  if (!s_addr || !s_data_ptr || !s_numel || !s_element_size) return nullptr;
+  if (!s_c || !s_data_ptr || !s_numel || !s_element_size) return nullptr;
   return PyModule_Create(&module);
 }
