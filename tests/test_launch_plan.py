@@ -1,0 +1,38 @@
+"""Launch planning of the score passes (host code, no GPU): the lengths it picks, and what picking them costs."""
+import os
+import subprocess
+import time
+
+import paper_2503_17922_amd as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_chunk_lengths_are_those_of_a_full_search(tmp_path):
+    from paper_2503_17922_amd import build as B
+    exe = B.build_host_sanitized(str(tmp_path), [os.path.join(ROOT, "tests", "c", "launch_plan.cpp"),
+                                                 os.path.join(ROOT, "tests", "c", "launch_stubs.cpp")], exe_name="launch_plan")
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0")
+    env.pop("LD_PRELOAD", None)          # the sanitizer runtime must come first in the link order of the process
+    res = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+
+
+def _microseconds(f, calls=200):
+    best = float("inf")
+    for _ in range(15):
+        t = time.perf_counter()
+        for _ in range(calls):
+            f()
+        best = min(best, (time.perf_counter() - t) / calls)
+    return best * 1e6
+
+
+def test_planning_a_large_batch_costs_little_more_than_validating_it():
+    lens = [4096 + 37 * i for i in range(64)]
+    p = W.Problem(n_q_heads=32, n_kv_heads=8, head_dim=128, w_obs=32, seq_len=lens, win=[8] * 64, top_p=[8] * 64, k_windows=[64] * 64,
+                  dtype=W.WKV_BF16)
+    validation = _microseconds(lambda: W.wkv_get_dims(p))
+    for groups in (1, 8):
+        planning = _microseconds(lambda: W.wkv_workspace_bytes(p, groups))     # validates and plans
+        assert planning < 5 * validation, f"{groups} groups: {planning:.1f} us, validation alone {validation:.1f} us"
