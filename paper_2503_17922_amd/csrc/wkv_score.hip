@@ -169,6 +169,23 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 
+// A DMA instruction of the ring: 64 lanes fetch 16 bytes each, to lds, lds + 16, ... in lane order.  From base + off bytes, or from
+// an address per lane.  m0 holds the LDS address; naming it as overwritten keeps the compiler's own uses of it, should there be any,
+// clear of this one (it is a reserved register, which clang warns of: nothing relies on its being preserved).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <bool NT_LOADS>
+__device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *base, uint32_t off) {
+  if constexpr (NT_LOADS)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *p) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(p) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 // NT_LOADS: the keys are not put into the memory-side cache (see plan_score).  Kernels of their own, as a branch at every fetch
 // costs small calls 1 %.
 template <int D, int DT, int RT, int HV, int PASS, bool NT_LOADS, bool OWN_RINGS>
@@ -241,21 +258,14 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
     const uint32_t dst = ring_lds + slot * C::TILE;
     if (j + 16 <= cend && !wide) {
       const char *base = kbase + (int64_t)j * kst;
-      if constexpr (NT_LOADS) {
 #pragma unroll
-        for (int n = 0; n < C::LPT; ++n)
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst + n * 1024), "v"(off[n]), "s"(base) : "memory");
-      } else {
-#pragma unroll
-        for (int n = 0; n < C::LPT; ++n)
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + n * 1024), "v"(off[n]), "s"(base) : "memory");
-      }
+      for (int n = 0; n < C::LPT; ++n) dma_to_lds<NT_LOADS>(dst + n * 1024, base, off[n]);
     } else {
 #pragma unroll
       for (int n = 0; n < C::LPT; ++n) {
         const int r = (my_part * C::LPT + n) * C::RPI + lane / C::PPR;
         const char *p = kbase + (int64_t)min(j + r, cend - 1) * kst + C::swizzle(r, lane % C::PPR) * 16;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst + n * 1024), "v"(p) : "memory");
+        dma_to_lds(dst + n * 1024, p);
       }
     }
   };
@@ -285,7 +295,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
     const int hq = (int)((uint32_t)r * s.w_magic >> 16), io = r - hq * s.w_obs;      // r / w_obs, r % w_obs
     const char *qp = (const char *)gp.q[g] +
                      ((int64_t)b * s.q_sb + (int64_t)(h * s.G + hq) * s.q_sh + (int64_t)io * s.q_st) * C::ES + f % KS * 64 + quad * 16;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_address(ring) + frag_at(f)), "v"(qp) : "memory");
+    dma_to_lds(lds_address(ring) + frag_at(f), qp);
   }
   if (PASS == 2) {
     if (pl.fold_in_pass2) fold_all<NT>(s, pl.pass[0].first[b + 1] - pl.pass[0].first[b], pl.m_pad, part, ROWS, part_s, lse_s);
