@@ -212,12 +212,11 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
   WKV_MARK(2)
   if (!s_pool && (e = launch_pool(pr.shape, pr.bp, n_groups, ws.t, ws.s, stream)) != hipSuccess) return hip_fail(e, "pool launch");
   if (!ev && selects_and_gathers(pr.shape, n_groups, gamma)) {        // (timed stage by stage they stay apart)
-    gk.gather = &lp;
-    gk.gamma = gamma;
+    e = launch_select_gather(pr.shape, pr.bp, gk, lp, n_groups, gamma, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);
+    return e == hipSuccess ? WKV_OK : hip_fail(e, "selection and gather launch");
   }
   e = launch_topk(pr.shape, pr.bp, gk, n_groups, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);
   if (e != hipSuccess) return hip_fail(e, "select launch");
-  if (gk.gather) return WKV_OK;
   WKV_MARK(3)
   e = launch_gather(pr.shape, lp, n_layers, gamma, tok_idx_out, n_keep_out, stream);
   if (e != hipSuccess) return hip_fail(e, "gather launch");

@@ -46,9 +46,6 @@ constexpr int32_t MAX_GROUP_K = 1024;
 struct GroupK {
   int32_t in_use;
   uint16_t k[MAX_GROUP_K];
-  // Host only.  Not null: the selection's launch also gathers these layers, gamma per group (see selects_and_gathers).
-  const LayerPtrs *gather;
-  int32_t gamma;
 };
 
 // The same for a call small enough for one launch of selection and gather: everything its kernel needs besides
@@ -164,6 +161,9 @@ hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, 
                        float *s_out, hipStream_t stream);
 hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
                        int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream);
+// The same, and the rows of the layers `lp`, gamma per group, in one launch (see selects_and_gathers).
+hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, const GroupK &gk, const LayerPtrs &lp, int32_t n_groups, int32_t gamma,
+                                const float *sc, int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream);
 hipError_t launch_gather(const Shape &s, const LayerPtrs &lp, int32_t n_layers, int32_t gamma,
                          const int32_t *tok_idx, const int32_t *n_keep, hipStream_t stream);
 

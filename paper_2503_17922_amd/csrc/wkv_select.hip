@@ -290,22 +290,22 @@ __global__ __launch_bounds__(SMALL_THREADS) void select_gather_kernel(Shape s, S
   if (threadIdx.x == 0) n_keep[row] = nk;
 }
 
-static hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
-                                       int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
+hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, const GroupK &gk, const LayerPtrs &lp, int32_t n_groups, int32_t gamma,
+                                const float *sc, int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
   SmallJob job;
-  job.gamma = gk.gamma;
+  job.gamma = gamma;
   job.own_budgets = gk.in_use;
   job.esize = (int32_t)elem_bytes(s.dtype);
   for (int b = 0; b < s.B; ++b) job.seq[b] = bp.seq[b];
   for (int i = 0; i < n_groups * s.B; ++i) job.k[i] = gk.k[i];
-  for (int l = 0; l < n_groups * gk.gamma; ++l) {
-    job.in[l][0] = gk.gather->k_in[l]; job.in[l][1] = gk.gather->v_in[l];
-    job.out[l][0] = gk.gather->k_out[l]; job.out[l][1] = gk.gather->v_out[l];
+  for (int l = 0; l < n_groups * gamma; ++l) {
+    job.in[l][0] = lp.k_in[l]; job.in[l][1] = lp.v_in[l];
+    job.out[l][0] = lp.k_out[l]; job.out[l][1] = lp.v_out[l];
   }
-  const int pairs = 2 * n_groups * gk.gamma * s.B * s.Hkv;
+  const int pairs = 2 * n_groups * gamma * s.B * s.Hkv;
   const int lpr = (int)(s.d * job.esize / 16), rows = SMALL_THREADS / lpr;
   const int splits = max(min(SMALL_WORKGROUPS / pairs, (s.nkeep_max + rows - 1) / rows), 1);
-  dim3 grid(splits, s.B * s.Hkv, 2 * n_groups * gk.gamma);
+  dim3 grid(splits, s.B * s.Hkv, 2 * n_groups * gamma);
   const size_t lds = (size_t)(s.nw_max > 0 ? s.nw_max : 1) * sizeof(uint32_t);
   if (lpr == 8) hipLaunchKernelGGL(select_gather_kernel<8>, grid, dim3(SMALL_THREADS), lds, stream, s, job, sc, win_idx, tok_idx, n_keep);
   else if (lpr == 16) hipLaunchKernelGGL(select_gather_kernel<16>, grid, dim3(SMALL_THREADS), lds, stream, s, job, sc, win_idx, tok_idx, n_keep);
@@ -315,7 +315,6 @@ static hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, co
 
 hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, int32_t n_groups, const float *sc,
                        int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
-  if (gk.gather) return launch_select_gather(s, bp, gk, n_groups, sc, win_idx, tok_idx, n_keep, stream);
   const size_t lds = (size_t)(s.nw_max > 0 ? s.nw_max : 1) * sizeof(uint32_t);
   if (lds > 48 * 1024) {     // beyond the default dynamic-LDS limit: raise it (per device, any thread)
     hipError_t e = hipFuncSetAttribute((const void *)topk_kernel<TOPK_THREADS>, hipFuncAttributeMaxDynamicSharedMemorySize,
