@@ -5,7 +5,7 @@
 // is read once and used for G = Hq/Hkv dot products, so the step is bound by the HBM stream of
 // the two caches; what matters is that the arithmetic per row stays well below the memory rate.
 //
-//   partial kernel  grid (splits, B*Hkv): a workgroup walks one key range of one KV head, over the rows
+//   partial kernel  grid (B*Hkv, splits): a workgroup walks one key range of one KV head, over the rows
 //                   that are in the cache already.
 //                   fp32 inputs: everything on the vector ALU, as follows.  16-bit inputs: the
 //                   scores come from the matrix pipe (decode_partial_mfma_kernel below), the
@@ -161,7 +161,8 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
   constexpr int KPT = 64 / LPK;              // rows per wave load instruction
   __shared__ float wave_state[DEC_WAVES][G][D + 2];
 
-  const int bh = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv, split = blockIdx.x;
+  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv);
+  const int bh = item.head, b = bh / s.Hkv, h = bh % s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / LPK, piece = lane % LPK;
   const int n = n_valid[bh];
@@ -306,7 +307,8 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
   __shared__ __attribute__((aligned(16))) float o_s[DEC_WAVES][G][D];
   __shared__ float2 ml_s[DEC_WAVES][G];
 
-  const int bh = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv, split = blockIdx.x;
+  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv);
+  const int bh = item.head, b = bh / s.Hkv, h = bh % s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, quad = lane >> 4;            // score side: head, 4 rows
   const int piece = lane % LPK, sub = col / LPK;          // value side: 16-byte piece, which of the quad's rows in flight
@@ -561,7 +563,7 @@ static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, con
 template <typename T, int D>
 static hipError_t launch_decode_t(const DecodeShape &s, const void *q, const void *kn, const void *vn, void *kc, void *vc,
                                   int32_t *n_valid, float *out, float *part, hipStream_t stream) {
-  dim3 grid(s.n_splits, s.B * s.Hkv);
+  const dim3 grid(s.B * s.Hkv, s.n_splits);
 #define WKV_DEC_CASE(GG) \
   case GG: launch_partial_g<T, D, GG>(s, grid, q, kc, vc, n_valid, part, stream); break;
   switch (s.G) {

@@ -1,17 +1,22 @@
-"""Launch planning of the score passes (host code, no GPU): the lengths it picks, and what picking them costs."""
+"""Launch planning (host code, no GPU): the chunk lengths of the score passes and what picking them costs, the order of the
+decode step's key ranges."""
 import os
 import subprocess
 import time
+
+import pytest
 
 import paper_2503_17922_amd as W
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_chunk_lengths_are_those_of_a_full_search(tmp_path):
+@pytest.mark.parametrize("program", ["launch_plan", "decode_ranges"])
+def test_plans(program, tmp_path):
+    # chunk lengths are those of a search of every length; every key range is taken once, with the rows of a batch spread over the chip
     from paper_2503_17922_amd import build as B
-    exe = B.build_host_sanitized(str(tmp_path), [os.path.join(ROOT, "tests", "c", "launch_plan.cpp"),
-                                                 os.path.join(ROOT, "tests", "c", "launch_stubs.cpp")], exe_name="launch_plan")
+    exe = B.build_host_sanitized(str(tmp_path), [os.path.join(ROOT, "tests", "c", program + ".cpp"),
+                                                 os.path.join(ROOT, "tests", "c", "launch_stubs.cpp")], exe_name=program)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0")
     env.pop("LD_PRELOAD", None)          # the sanitizer runtime must come first in the link order of the process
     res = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
