@@ -536,14 +536,18 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
 template <typename T, int D, int G>
 static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, const void *kc, const void *vc,
                              const int32_t *n_valid, float *part, hipStream_t stream) {
-  // Where a model's caches (32 layers, say) exceed the memory-side cache, no row is found there at the next token,
-  // and the values, as both caches in fp32, are best streamed.  32 layers, one sequence of 4128 rows (18 MB
-  // a layer): 12.45 us a layer with plain loads, 11.61 so; eight in fp32 (287 MB a layer): 60.1 and 53.9; eleven of mixed
-  // lengths, f16 (38 MB a layer): 19.3 and 17.8.  (A layer of 7 MB whose caches stay there: 8.3 us, 8.7 if streamed.)
+  // Where a model's caches exceed the memory-side cache, no row is found there at the next token, and the values, as both
+  // caches in fp32, are best streamed.  How many layers there are and (n_valid is on the device) how many rows the library
+  // cannot know: the line is that of 32 layers of full caches.  Us a layer with plain loads / with values streamed, where the rows
+  // were in that cache (one to four layers, again and again) and where they were not (32 layers, or three sets of 8): 8 MB a layer
+  // 9.8 / 10.2 and 10.1-10.6 / 10.3-10.6; 17 MB 10.3-10.9 / 10.5-11.1 and 11.9-12.1 / 11.2-11.8; 34 MB 13.5 / 13.5 and
+  // 14.4 / 14.2; 67 MB 19.2 / 19.4 and 21.7 / 20.9; eleven sequences of mixed lengths, f16 (38 MB) 16.1 / 16.3 and 17.9 / 16.8; eight in
+  // fp32 (271 MB) 59.5 / 53.4.
   // Keys of 16-bit caches are read in operand layout, 64 bytes of a row at a time, and a streamed line may be gone when
-  // its other half is asked for: they stream only where a layer by itself exceeds the memory-side cache.  Four layers of
-  // 64 sequences of 4128 rows (1.1 GB a layer): 779 us with plain loads, 688 with both streamed (values alone: 2 % more);
-  // of the eleven sequences above: 77.4, 76.2, 71.7 us with values alone.
+  // its other half is asked for: they stream only where a layer's caches by themselves exceed the memory-side cache.  Full caches gain
+  // there, mixed ones, which leave more of the chip waiting for single loads, lose some of it again.  64 sequences of 4128 rows (1.1 GB
+  // a layer): 193 us plain, 173 with values streamed, 170 with both; 256 of 300 rows (556 MB of capacity) 73, 70 and 63; 48 of 300 to 4000
+  // rows (294 MB of 789) 80, 75 and 80; of the eleven sequences above: 17.9, 16.8 and 17.5.
   const int64_t bytes = 2 * (int64_t)s.B * s.Hkv * s.capacity * D * (int64_t)sizeof(T);
   const int stream_level = bytes > MEMORY_CACHE_BYTES ? 2 : bytes > MEMORY_CACHE_BYTES / 32 ? 1 : 0;
 #define WKV_PARTIAL(KERNEL, E) \
