@@ -192,7 +192,8 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   // Keys that the memory-side cache holds until the second pass are better left there; a larger stream reads
   // faster past it.  One layer of 32768 tokens a group, 8 KV heads, whole call: 1 to 3 groups (67 to 201 MB) 57.5, 87.8, 116.5 us
   // with plain loads, 57.6, 87.9, 115.8 with nontemporal ones, 6 groups (403 MB) 206.2 and 201.1; the 32K model's passes (537
-  // MB) 390 and 370 us; 16384 tokens and four layers 45.9 and 48.1 us; 256 softmax rows, 134 MB 118.8 and 123.0 us.
+  // MB) 390 and 370 us; 16384 tokens and four layers 45.9 and 48.1 us; 256 softmax rows, 134 MB 118.8 and 123.0 us.  fp32, 32 rows:
+  // 134 MB 74.9 and 79.0, 335 MB 170.3 and 166.9, 1.07 GB 503 and 445 us; 128 rows and more wait for the matrix pipe, 1 GB 1182 and 1178.
   pl.nontemporal = keys * s.d * elem_bytes(s.dtype) > MEMORY_CACHE_BYTES;
   // Key tiles fetched twice, once per row group, against a barrier per tile: worth it while a chunk is short enough for
   // the two waves to stay together and the cache has room for what they lose.  Whole calls with a barrier / with rings
