@@ -123,13 +123,16 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 //
 // What bounds it.  Per 64 logits a SIMD issues one 16x16x32 MFMA (8.6 ns on random data at the clocks the chip then
 // holds) and one multiply-add, exponential and add (7.8 ns); they hardly overlap: 13 ns together in a loop of
-// nothing else, in whatever order they are written.  The 32K-token model (8 groups, 128 rows): 107 + 103 us for the two
+// nothing else, in whatever order they are written.  The 32K-token model (8 groups, 128 rows): 103 + 100 us for the two
 // passes (shortest launches 92 + 90), 70-76 us without the loads; with plain loads 108 + 107 us, of which the loads alone 91-95
 // (5.9 TB/s; a reading kernel reaches 7.0 by nontemporal loads, 6.1 without).  The kernels before this
 // one kept the queries in LDS, read the keys in operand layout straight from global memory and took 111 + 107 us there;
 // 12.0 + 11.6 us for a group of 4096 tokens (now 9.0 + 10.1, fold included: half the code to fetch, one round of loads in the
 // prologue), 15.9 + 9.3 (fold) + 14.7 us for 16384 tokens (13.8 + 15.7), 28.3 + 27.7 us for 4096 tokens in fp32 (19.5 + 20.2),
 // 54 + 50 us for 48 rows of ragged sequences with 224 softmax rows (31 + 31).
+// With two row groups a pass takes the sum of the two, not the longer: 16381 tokens, 8 groups, 256 rows 53 us of arithmetic by these
+// figures and 38 us of keys at 7.0 TB/s, measured 97-99; the ragged sequences 12 us of arithmetic, measured 31.  One workgroup a
+// compute unit, two waves a SIMD, and with shared rings a barrier per tile: while these wait there is nothing else to run.
 constexpr int score_slots(int row_groups) { return row_groups == 4 ? 2 : 4; }         // key tile slots of a workgroup
 constexpr int score_threads(int row_groups) { return 64 * row_groups * score_slots(row_groups); }
 

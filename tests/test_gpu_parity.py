@@ -48,7 +48,7 @@ def run_and_check(w: S.Workload, device, n_oracle=None, n_gather_cpu=None, stage
     gather (None = all); every slice is additionally compared on the device.
     stage_groups: the groups whose four stage calls are run and compared too (None = all).
     For every oracle problem the token scores t and window scores s of the stage calls AND what the
-    batched call itself computed (its s, or its t when it pools in the selection kernel, read back
+    batched call itself computed (its s, or its t when windows are pooled in a launch of their own, read back
     from the workspace) are compared element by element.
     """
     st = P.DeviceState(w, device, as_f16=as_f16, flags=flags)
@@ -205,7 +205,7 @@ def _mini(**kw):
     dict(head_dim=64, seq_len=[3000], k_windows=[40]),
     dict(n_q_heads=16, n_kv_heads=2, w_obs=32, seq_len=[1500]),           # 256 rows: two row halves per workgroup
     dict(n_q_heads=10, n_kv_heads=2, w_obs=32, seq_len=[9000, 700], win=[16, 8], top_p=[8, 8], k_windows=[40, 9]),   # 160 rows, several chunks
-    dict(n_q_heads=16, n_kv_heads=2, w_obs=32, head_dim=64, seq_len=[2500], win=[24], top_p=[5], k_windows=[17]),     # 256 rows, d=64, pooling in the selection kernel
+    dict(n_q_heads=16, n_kv_heads=2, w_obs=32, head_dim=64, seq_len=[2500], win=[24], top_p=[5], k_windows=[17]),     # 256 rows, d=64, windows across chunks
     dict(n_q_heads=14, n_kv_heads=2, w_obs=19, seq_len=[3100]),           # 133 rows: 9 row tiles
     dict(dtype="f32", head_dim=128, seq_len=[900]),
     dict(dtype="f32", head_dim=64, n_q_heads=4, n_kv_heads=1, w_obs=64, seq_len=[600]),
@@ -277,7 +277,7 @@ def test_fp16_config_c2(device):
 @pytest.mark.parametrize("kw", [
     dict(),                                                               # 128 rows, ragged tail
     dict(n_q_heads=16, n_kv_heads=2, w_obs=32, seq_len=[2500, 900], win=[16, 8], top_p=[8, 8], k_windows=[20, 11]),   # 256 rows
-    dict(head_dim=64, seq_len=[3000], win=[24], top_p=[7], k_windows=[40]),     # pooling in the selection kernel
+    dict(head_dim=64, seq_len=[3000], win=[24], top_p=[7], k_windows=[40]),     # windows across chunks
 ])
 def test_half_inputs_with_half_values(kw, device):
     # IEEE half tensors drawn as half: 11 significant bits, so the _f16 MFMA operands carry mantissa
@@ -319,7 +319,7 @@ SINGLE_READ_CASES = [
     dict(seq_len=[16], k_windows=[0]),                                    # no review context at all
     dict(seq_len=[17], win=[8], k_windows=[1]),                           # one review token
     dict(seq_len=[272, 256, 528], win=[8, 16, 8], top_p=[8, 8, 3], k_windows=[5, 7, 9]),   # review context ends exactly on slice boundaries
-    dict(win=[24], top_p=[7], k_windows=[9]),                             # token scores to memory, pooled by the selection kernel
+    dict(win=[24], top_p=[7], k_windows=[9]),                             # token scores to memory, pooled by a launch of its own
     dict(n_q_heads=6, n_kv_heads=2, w_obs=5),                             # 15 softmax rows
     dict(n_q_heads=4, n_kv_heads=4, w_obs=1),
     dict(head_dim=64, seq_len=[3000], k_windows=[40]),
@@ -472,7 +472,7 @@ def _check_lse_handoff(w, device, groups_oracle):
 
 
 def test_lse_handoff_small_configs(device):
-    _check_lse_handoff(S.make_workload("c1"), device, groups_oracle=[0])          # fp32, generic kernels
+    _check_lse_handoff(S.make_workload("c1"), device, groups_oracle=[0])          # fp32
     _check_lse_handoff(S.make_workload("c2"), device, groups_oracle=[0])          # bf16, MFMA kernels, outlier channels
     w = _mini(seq_len=[777, 130, 2049], win=[8, 16, 32], top_p=[8, 5, 16], k_windows=[20, 3, 11], n_groups=2, gamma=2)
     _check_lse_handoff(w, device, groups_oracle=[0, 1])                           # ragged batch, two groups
