@@ -1,7 +1,7 @@
 // Shared-index row gather (WindowKV Section 2.2.2): every layer of a group keeps the K and V
 // rows at the group's retained positions.  A pure copy, bound by HBM bandwidth.
 //
-// Mapping: a row of head_dim elements is 256 or 512 bytes; `LPR` lanes (16 B each) cover one
+// Mapping: a row of head_dim elements is 128, 256 or 512 bytes; `LPR` lanes (16 B each) cover one
 // row, so one 256-thread workgroup moves 256/LPR rows per load instruction and keeps UNROLL
 // such instructions in flight per lane.  grid.x walks row blocks of the compact cache,
 // grid.y the (sequence, KV head) pairs, grid.z the (layer, K|V) tensors, so neighbouring

@@ -212,7 +212,7 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
 // workgroups keep the row statistics of one row tile set in registers).  It is taken only when the
 // caller asks for it: on MI355X the exchange of the row statistics between workgroups costs more
 // than the second read of the keys it saves (measured at the 32K configuration: 0.57 ms against
-// 0.21 ms for the two passes), so the library never chooses it by itself.
+// 0.20 ms for the two passes), so the library never chooses it by itself.
 ResidentPlan plan_resident(const Shape &s, const BatchParams &bp, const ScorePlan &plan, int32_t n_groups, int32_t flags) {
   ResidentPlan rp;
   std::memset(&rp, 0, sizeof(rp));

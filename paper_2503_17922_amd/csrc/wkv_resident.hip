@@ -136,10 +136,10 @@ __global__ __launch_bounds__(MF_THREADS, 3) void score_resident_kernel(Shape s, 
     // One tile pair (2 x 16 keys) against all row tiles.  PASS 1 accumulates the row statistics,
     // PASS 2 writes the column sums into t_s.  The MFMAs of row tile mt and the exponentials of
     // row tile mt-1 alternate in one basic block, so that the matrix pipe and the vector ALU
-    // overlap inside a wave (see the two-pass kernel, which has the same body).
+    // overlap inside a wave, as in the two-pass kernels.
     auto tile_pair = [&](auto pass_tag, const KFrags<KS> &kf, const int j0) __attribute__((always_inline)) {
       constexpr int PASS = decltype(pass_tag)::value;
-      asm volatile("" ::: "memory");                   // keep the query fragments in LDS (see the two-pass kernel)
+      asm volatile("" ::: "memory");                   // the query fragments stay in LDS: beside the keys they do not fit the registers
       f32x4 acc[MF_KT][MT];
       float psum[MT];
       f32x4 tq[MF_KT];
