@@ -88,6 +88,16 @@ __device__ __forceinline__ float row_lanes_sum(float x) {
   return x;
 }
 
+// Sum and maximum over the wave, in every lane: DPP steps inside rows of 16 lanes, then two permlane swaps.
+__device__ __forceinline__ float wave_sum(float x) { return quads_sum(row16_sum(x)); }
+__device__ __forceinline__ float wave_max(float x) {
+  x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, false)));  // quad_perm [1,0,3,2]
+  x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xF, 0xF, false)));  // quad_perm [2,3,0,1]
+  x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x141, 0xF, 0xF, false))); // row_half_mirror
+  x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x140, 0xF, 0xF, false))); // row_mirror
+  return quads_max(x);
+}
+
 // Merge the online-softmax state (m2, l2, o2) into (m, l, o); all in base 2.
 template <int E>
 __device__ __forceinline__ void merge_state(float &m, float &l, float (&o)[E], float m2, float l2, const float (&o2)[E]) {
@@ -161,8 +171,8 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
   constexpr int KPT = 64 / LPK;              // rows per wave load instruction
   __shared__ float wave_state[DEC_WAVES][G][D + 2];
 
-  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv);
-  const int bh = item.head, b = bh / s.Hkv, h = bh % s.Hkv, split = item.range;
+  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv, s.heads_magic);
+  const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / LPK, piece = lane % LPK;
   const int n = n_valid[bh];
@@ -177,7 +187,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     float f[E];
-    Piece<T>::unpack(*(const uint4 *)(q_new + ((int64_t)b * s.Hq + (int64_t)h * G + g) * D + piece * E), f);
+    Piece<T>::unpack(*(const uint4 *)(q_new + ((int64_t)bh * G + g) * D + piece * E), f);
 #pragma unroll
     for (int c = 0; c < E; ++c) qv[g][c] = f[c] * s.c1;
   }
@@ -285,7 +295,12 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
 // A long cache is bound by the stream of its rows.  A single sequence (a block or two per wave) is bound by
 // the length of the code itself, fetched anew in every launch, and by LDS round trips: hence no
 // LDS in the loop and no shuffles through it at the end.  One 32q/8kv-head layer with 4128 rows in ranges of
-// 64, bf16: 10.6 us with probabilities through LDS and ds_bpermute reductions, 8.6 us so.
+// 64, bf16: 10.6 us with probabilities through LDS and ds_bpermute reductions, 8.6 us so.  A wave requests two blocks at a time, all it
+// has in a range of 128 rows, and waits for memory once; the arithmetic of both is one piece of code, and the heads' numbers are
+// divided by multiplication.  Such a layer with its merge 11.3 us with one block requested ahead of the one in hand (the compiler
+// put the request of the second behind the arrival of the first), 10.1 us so; eleven sequences of mixed lengths, 28q/4kv heads, f16, a layer
+// 16.6 and 14.8 us; 64 sequences 169 and 167.  Ranges of 64 rows, one block a wave: 10.9, 14.7 and 167 us.  Three waves a SIMD: with
+// four, the registers of two blocks spill.
 // The value of lane N of each 16-lane DPP row, in all its lanes.
 template <int N>
 __device__ __forceinline__ float row_bcast(float x) {
@@ -297,9 +312,9 @@ __device__ __forceinline__ void static_for(F &&f) {
 }
 // STREAM: 0 plain loads, 1 values stream, 2 keys too (see launch_partial_g).
 template <int D, int G, bool F16, int STREAM>
-__global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mfma_kernel(
-    DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *__restrict__ k_cache,
-    const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ n_valid, float *__restrict__ part) {
+__global__ __launch_bounds__(DEC_THREADS, 3) void decode_partial_mfma_kernel(
+    DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *k_cache,
+    const uint16_t *v_cache, const int32_t *__restrict__ n_valid, float *__restrict__ part) {
   constexpr int E = 8;
   constexpr int LPK = D / E;                 // lanes per row (value side): 16 or 8
   constexpr int VT = D / 32;                 // value loads per block of 16 rows: rows of a quad / rows it reads at once
@@ -307,9 +322,9 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
   __shared__ __attribute__((aligned(16))) float o_s[DEC_WAVES][G][D];
   __shared__ float2 ml_s[DEC_WAVES][G];
 
-  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv);
-  const int bh = item.head, b = bh / s.Hkv, h = bh % s.Hkv, split = item.range;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv, s.heads_magic);
+  const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;            // score side: head, 4 rows
   const int piece = lane % LPK, sub = col / LPK;          // value side: 16-byte piece, which of the quad's rows in flight
   const int n = n_valid[bh];
@@ -319,13 +334,12 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
   const uint16_t *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh + quad * 8;
   const uint16_t *vc = v_cache + (int64_t)b * s.sb + (int64_t)h * s.sh + piece * E;
 
-  // query rows as B fragments: lane (head col, quad) holds channels 32*ks + 8*quad .. +7; heads >= G are zero
+  // query rows as B fragments: lane (head col, quad) holds channels 32*ks + 8*quad .. +7; columns past the
+  // last head repeat it and are not used
   bf16x8 qb[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (col < G) v = *(const uint4 *)(q_new + ((int64_t)b * s.Hq + (int64_t)h * G + col) * D + ks * 32 + quad * 8);
-    qb[ks] = *(const bf16x8 *)&v;
+    qb[ks] = *(const bf16x8 *)(q_new + ((int64_t)bh * G + min(col, G - 1)) * D + ks * 32 + quad * 8);
   }
 
   float m = -INFINITY, l = 0.0f;             // of head `col` (lanes with col < G), l over this lane's rows only
@@ -333,29 +347,21 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
 #pragma unroll
   for (int i = 0; i < G * E; ++i) o[i] = 0.0f;
 
-  uint4 kr[KS], vr[VT];
-  auto load_block = [&](int blk) {
+  // Blocks of 16 rows, every DEC_WAVES-th of the range, two at a time: a range of 128 rows is one round trip to memory.
+  struct Block { uint4 k[KS], v[VT]; };
+  auto load_block = [&](Block &x, int blk) __attribute__((always_inline)) {
     const int r0 = c0 + blk * 16;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kr[ks] = load_piece<(STREAM > 1)>(kc + (int64_t)min(r0 + col, cend - 1) * s.st + ks * 32);
+    for (int ks = 0; ks < KS; ++ks) x.k[ks] = load_piece<(STREAM > 1)>(kc + (int64_t)min(r0 + col, cend - 1) * s.st + ks * 32);
 #pragma unroll
-    for (int t = 0; t < VT; ++t) vr[t] = load_piece<(STREAM > 0)>(vc + (int64_t)min(r0 + quad * 4 + t * (4 / VT) + sub, cend - 1) * s.st);
+    for (int t = 0; t < VT; ++t) x.v[t] = load_piece<(STREAM > 0)>(vc + (int64_t)min(r0 + quad * 4 + t * (4 / VT) + sub, cend - 1) * s.st);
   };
-  int blk = wave;
-  load_block(blk);
-  for (; c0 + blk * 16 < cend; blk += DEC_WAVES) {
-    uint4 kcur[KS], vcur[VT];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kcur[ks] = kr[ks];
-#pragma unroll
-    for (int t = 0; t < VT; ++t) vcur[t] = vr[t];
-    load_block(blk + DEC_WAVES);               // next block (past the end: the last row again)
-
+  auto attend = [&](const Block &x, int blk) __attribute__((always_inline)) {
     // scores of 16 rows x 16 (padded) heads
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      acc = mfma_16x16x32<F16>(*(const bf16x8 *)&kcur[ks], qb[ks], acc);
+      acc = mfma_16x16x32<F16>(*(const bf16x8 *)&x.k[ks], qb[ks], acc);
     const int r0 = c0 + blk * 16 + quad * 4;
     float sc[4], pr[4];
 #pragma unroll
@@ -377,7 +383,7 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
 #pragma unroll
     for (int t = 0; t < VT; ++t) {
       float vf[E];
-      if constexpr (F16) Piece<half_t>::unpack(vcur[t], vf); else Piece<uint16_t>::unpack(vcur[t], vf);
+      if constexpr (F16) Piece<half_t>::unpack(x.v[t], vf); else Piece<uint16_t>::unpack(x.v[t], vf);
       static_for<G>([&](auto g) {
         float p = row_bcast<g>(pr[t * (4 / VT)]);
         if constexpr (LPK == 8) {                // two rows of the quad at once: its upper 8 lanes take the second
@@ -388,6 +394,19 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
         for (int i = 0; i < E; ++i) o[g * E + i] = fmaf(p, vf[i], o[g * E + i]);
       });
     }
+  };
+  for (int blk = wave; c0 + blk * 16 < cend; blk += DEC_WAVES) {
+    Block x, next;
+    load_block(x, blk);
+    load_block(next, blk + DEC_WAVES);         // (past the end: the last row again)
+    __builtin_amdgcn_sched_barrier(0);         // both are requested before the first is looked at
+    for (bool more = c0 + (blk + DEC_WAVES) * 16 < cend;; more = false) {          // (one copy of the code, which every launch fetches anew)
+      attend(x, blk);
+      if (!more) break;
+      blk += DEC_WAVES;
+      x = next;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0), as it is by now: else the compiler waits for the queries among the first requests
   }
 
   // The wave's totals.  After the two swap steps lane (quad, piece) holds 2*G of a piece's sums: those of
@@ -435,26 +454,27 @@ __global__ __launch_bounds__(DEC_THREADS, G <= 4 ? 4 : 3) void decode_partial_mf
 // One workgroup per (sequence, KV head, query head): D/4 lanes hold a row of outputs, so GROUPS key ranges
 // are summed side by side.  Bound by its chain of round trips to memory (the data is a few KB a head), hence
 // the outputs of the first ranges are requested together with the statistics that weigh them.  At 8 KV heads and
-// 33 ranges 4.9 us; 7.2 us for 18 ranges by one workgroup per KV head that summed them one after the other.
+// 33 ranges 3.3 us from first wave to last with shuffles through LDS and four ranges ahead (the 33rd took a round trip of its
+// own), 2.6 us with DPP reductions and six.
 template <typename T, int D, int NT>
 __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const T *__restrict__ q_new,
                                                                      const T *__restrict__ k_new, const T *__restrict__ v_new,
                                                                      T *k_cache, T *v_cache, const float *__restrict__ part,
                                                                      int32_t *n_valid, float *__restrict__ out) {
-  constexpr int COLS = D / 4, GROUPS = NT / COLS, AHEAD = 4, WAVES = NT / 64;
+  constexpr int COLS = D / 4, GROUPS = NT / COLS, AHEAD = NT == 64 ? 4 : 6, WAVES = NT / 64;
   constexpr int E = Piece<T>::E, LPK = D / E;
   __shared__ float wgt[NT];
   __shared__ __attribute__((aligned(16))) float acc_s[GROUPS][D];
   __shared__ float q_k[2];
   __shared__ float wave_m[WAVES], wave_l[WAVES];
-  const int bh = blockIdx.x, g = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv;
+  const int bh = blockIdx.x, g = blockIdx.y, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int grp = tid / COLS, col = tid % COLS;
-  const int64_t hq = (int64_t)b * s.Hq + (int64_t)h * s.G + g;
+  const int64_t hq = (int64_t)bh * s.G + g;
 
   // statistics of this head's ranges (one per thread), outputs of the first ranges, the new token
-  const float2 none = make_float2(-INFINITY, 0.0f);
-  const float2 ml = tid < s.n_splits ? part_stats(s, part)[part_index(s, bh, tid, g)] : none;
+  float2 ml = make_float2(-INFINITY, 0.0f);
+  if (tid < s.n_splits) ml = part_stats(s, part)[part_index(s, bh, tid, g)];
   const float4 *po = (const float4 *)(part + part_index(s, bh, 0, g) * D) + col;     // range sp: sp * G * COLS further on
   float4 pre[AHEAD];
 #pragma unroll
@@ -479,13 +499,10 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
     }
   }
   if (last_wave) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off);
+    dot = wave_sum(dot);
     if (lane == 0) q_k[0] = dot * s.c1;
   }
-  float m = ml.x;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  float m = wave_max(ml.x);
   if (lane == 0) wave_m[wave] = m;
   if (tid == 0) q_k[1] = ml.x;                          // NaN: the cache is full or its count is invalid
   __syncthreads();
@@ -496,8 +513,7 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
   const float a = fast_exp2(ml.x - m);                  // a range without rows: 0
   float l = ml.x == -INFINITY ? 0.0f : ml.y * a;
   if (tid < s.n_splits) wgt[tid] = a;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+  l = wave_sum(l);
   if (lane == 0) wave_l[wave] = l;
   __syncthreads();
   const float w_new = fast_exp2(logit - m);

@@ -299,6 +299,7 @@ wkv_status validate_decode(const wkv_decode_shape *p, Decode *out) {
   const double scale = p->scale > 0.0f ? (double)p->scale : 1.0 / std::sqrt((double)p->head_dim);
   s.c1 = (float)(scale * 1.4426950408889634074);
   s.sb = p->cache_stride_b; s.sh = p->cache_stride_h; s.st = p->cache_stride_t;
+  s.heads_magic = division_magic(s.B * s.Hkv); s.kv_magic = division_magic(s.Hkv);
   // Key ranges: about 1536 workgroups if every cache were full (six per compute unit; n_valid is not known
   // here, and in a batch of mixed lengths a good part of them finds nothing to do), of at least 128 rows (two
   // blocks per wave: with one, the fixed cost and the merge outweigh the shorter chain), multiples of 64 rows (a

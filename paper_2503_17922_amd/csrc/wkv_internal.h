@@ -11,6 +11,12 @@ namespace wkv {
 // The chip's memory-side cache.
 constexpr int64_t MEMORY_CACHE_BYTES = (int64_t)256 << 20;
 
+// n / d == divide(n, division_magic(d)) while n * d < 2^32.
+inline uint32_t division_magic(int32_t d) { return d == 1 ? 0u : 0xffffffffu / (uint32_t)d + 1u; }
+__host__ __device__ inline int32_t divide(uint32_t n, uint32_t magic) {
+  return (int32_t)(magic == 0u ? n : (uint32_t)((uint64_t)n * magic >> 32));
+}
+
 inline int64_t elem_bytes(int32_t dtype) { return dtype == WKV_F32 ? 4 : 2; }
 
 // Per-sequence parameters, passed to kernels by value inside the kernel argument block so
@@ -180,6 +186,7 @@ struct DecodeShape {
   int32_t keep_count;        // leave n_valid as it is (the caller advances it after the group's last layer)
   float c1;                  // scale * log2(e)
   int64_t sb, sh, st;        // cache strides in elements
+  uint32_t heads_magic, kv_magic;      // division_magic of the heads (B * Hkv) and of Hkv
 };
 // Which key range workgroup (x, y) of the partial kernel's grid (heads, ranges) takes.  Range by range: the first ranges of all caches
 // go first, the ones that many caches of a mixed batch do not reach last.  The heads start nine further on in every range, so
@@ -187,9 +194,13 @@ struct DecodeShape {
 // Head by head, with 2, 4, 8 or 24 ranges, the first ranges of all heads share an XCD and those of the late ones idle: 48 sequences of 300 to
 // 4000 rows, 32q/8kv, 128 channels 95 us a layer and 67 so, 11 with 32 KV heads 94 and 73; without the nine, 16 of up to 32000 rows
 // and 4 KV heads 108 and 79.  Equal lengths 1 to 2 % faster so, but 8 sequences of 32768 rows 177 us head by head and 182 so.
+// (The kernels pass division_magic(heads): the compiler's divisions by two run-time numbers are a good part of the code that stands
+// before the first load.  Exact, as x < heads and 9 * y < 9 * 1536 / heads.)
 struct RangeOf {
   int32_t head, range;
   __host__ __device__ RangeOf(int32_t x, int32_t y, int32_t heads) : head((int32_t)((uint32_t)(x + 9 * y) % (uint32_t)heads)), range(y) {}
+  __host__ __device__ RangeOf(int32_t x, int32_t y, int32_t heads, uint32_t magic)
+      : head(x + 9 * y - divide((uint32_t)(x + 9 * y), magic) * heads), range(y) {}
 };
 struct Decode {
   DecodeShape shape;

@@ -1,0 +1,54 @@
+"""The decode step's blocks of 16 rows, taken two at a time by four waves: row counts around the ends of single and paired blocks in
+ranges of one, two and three pairs a wave; and the divisions by multiplication that find a workgroup's head."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_17922_amd as W
+from oracle import wkv_oracle as O
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_divisions_by_multiplication(tmp_path):
+    from paper_2503_17922_amd import build as B
+    exe = B.build_host_sanitized(str(tmp_path), [os.path.join(ROOT, "tests", "c", "division_magic.cpp"),
+                                                 os.path.join(ROOT, "tests", "c", "launch_stubs.cpp")], exe_name="division_magic")
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0")
+    env.pop("LD_PRELOAD", None)          # the sanitizer runtime must come first in the link order of the process
+    res = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,G,d", [("bf16", 4, 128), ("f16", 8, 128), ("f16", 2, 64)])
+@pytest.mark.parametrize("cap", [130, 770, 2300])            # 768 caches: ranges of 128, 448 and 1152 rows
+def test_pairs_of_blocks(dtype, G, d, cap, device):
+    B, H, tdt = 96, 8, {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    edges = [0, 1, 15, 16, 17, 63, 64, 65, 80, 112, 113, 127, 128, 129, 191, 192, 193, 240, 255, 256, 257, 319, 320, 321, 383, 384, 385]
+    rows = [n for n in edges if n < cap]
+    rows = (rows + [cap - 1 - n for n in rows] * 8)[:B]
+    gen = torch.Generator(device=device).manual_seed(cap + G)
+    mk = lambda *shape: torch.randn(shape, device=device, dtype=torch.float32, generator=gen).to(tdt)
+    kc, vc, q, kn, vn = mk(B, H, cap, d), mk(B, H, cap, d), 2 * mk(B, G * H, d), mk(B, H, d), mk(B, H, d)
+    for b, n in enumerate(rows):                    # what lies past the retained rows must not matter
+        kc[b, :, n:] = float("nan")
+        vc[b, :, n:] = float("nan")
+    n_valid = torch.tensor(rows, dtype=torch.int32, device=device)[:, None].repeat(1, H).contiguous()
+    shape = W.DecodeShape(batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=d, capacity=cap,
+                          dtype={"bf16": W.WKV_BF16, "f16": W.WKV_F16}[dtype])
+    ws = torch.full((W.wkv_decode_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device=device)     # NaNs
+    out = torch.zeros((B, G * H, d), dtype=torch.float32, device=device)
+    f64 = lambda t: t.to("cpu").to(torch.float64).numpy()
+    k0, v0 = f64(kc), f64(vc)
+    W.wkv_decode_step(shape, q, kn, vn, kc, vc, n_valid, out, ws)
+    torch.cuda.synchronize()
+    got, qh, knh, vnh = f64(out), f64(q), f64(kn), f64(vn)
+    for b, n in enumerate(rows):
+        h = b % H
+        want, *_ = O.decode_step(qh[b, h * G:(h + 1) * G], k0[b, h, :n], v0[b, h, :n], knh[b, h], vnh[b, h])
+        # products of 16-bit inputs, sums in fp32: about 1e-6 of the largest value; 1e-3 is what the other decode tests ask for
+        np.testing.assert_allclose(got[b, h * G:(h + 1) * G], want, rtol=1e-3, atol=2e-5, err_msg=f"rows {n} h{h}")
