@@ -19,19 +19,27 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// One 64-byte step of the contraction: 16 rows of A against 16 rows of B, 16 bytes of each per lane
-// (lane l: row l%16, piece l/16).  16-bit types: one 16x16x32 instruction.  fp32: four 16x16x4 ones; the
+// One step of the contraction of TS rows of A with TS rows of B, 16 bytes of each per lane (lane l: row l % TS, piece
+// l / TS).  16-bit types: one 16x16x32 or 32x32x16 instruction.  fp32: four 16x16x4 ones; the
 // order in which they take the channels is the same for both operands, which is all a sum needs.
 enum { DT_BF16 = 0, DT_F16 = 1, DT_F32 = 2 };
-template <int DT>
-__device__ __forceinline__ f32x4 mfma_64b(bf16x8 a, bf16x8 b, f32x4 c) {
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+template <int TS> struct TileOf { typedef f32x4 acc; };
+template <> struct TileOf<32> { typedef f32x16 acc; };
+template <int DT, int TS>
+__device__ __forceinline__ typename TileOf<TS>::acc mfma_step(bf16x8 a, bf16x8 b, typename TileOf<TS>::acc c) {
   if constexpr (DT == DT_F32) {
+    static_assert(TS == 16, "fp32 tiles");
     const f32x4 av = __builtin_bit_cast(f32x4, a), bv = __builtin_bit_cast(f32x4, b);
 #pragma unroll
     for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[i], c, 0, 0, 0);
     return c;
-  } else {
+  } else if constexpr (TS == 16) {
     return mfma_16x16x32<DT == DT_F16>(a, b, c);
+  } else if constexpr (DT == DT_F16) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  } else {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
 }
 

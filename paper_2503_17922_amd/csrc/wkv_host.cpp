@@ -122,6 +122,7 @@ void fill_shape(const wkv_problem *p, const wkv_dims &dims, Shape *s, BatchParam
   for (int b = 0; b < p->batch; ++b) {
     bp->seq[b].L = p->seq_len[b];
     bp->seq[b].win = p->win[b];
+    bp->seq[b].win_magic = division_magic(p->win[b]);
     bp->seq[b].p = p->top_p[b] < p->win[b] ? p->top_p[b] : p->win[b];
     bp->seq[b].k = p->k_windows[b];
   }

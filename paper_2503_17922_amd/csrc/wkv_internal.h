@@ -26,6 +26,7 @@ struct SeqParam {
   int32_t win;  // review-window size (omega)
   int32_t p;    // top-p, already clamped to [1, win]
   int32_t k;    // windows to keep
+  uint32_t win_magic;   // division_magic(win): token numbers are divided by window sizes by multiplication
 };
 struct BatchParams {
   SeqParam seq[WKV_MAX_BATCH];
@@ -87,7 +88,7 @@ constexpr int32_t SCORE_SEG = 2048;
 
 // One pass: sequence b of a row takes the workgroups first[b] .. first[b+1]-1, chunk[b] keys each (the last one what
 // is left).  At least one each, so that the padding of its outputs has an owner.
-constexpr int32_t CHUNK_UNIT = 64;                // a tile for every key slot of a workgroup
+constexpr int32_t CHUNK_UNIT = 64;                // a tile of 16 keys for every key slot of a workgroup
 struct PassPlan {
   int32_t first[WKV_MAX_BATCH + 1];
   uint8_t chunk[WKV_MAX_BATCH];                   // in units of CHUNK_UNIT keys
@@ -96,7 +97,7 @@ struct ScorePlan {
   PassPlan pass[2];            // statistics, scores
   int32_t n_chunks1;           // most workgroups of a sequence in the statistics pass
   int32_t m_pad;               // rows padded to a multiple of 16
-  bool nontemporal;            // the key loads put nothing into the memory-side cache
+  bool nontemporal;            // a long stream: the key loads put nothing into the memory-side cache, 16-bit inputs take 16-row tiles
   bool own_rings;              // with two row groups of 16-bit inputs every wave fetches its key tiles itself
   bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
 };

@@ -30,48 +30,59 @@ namespace wkv {
 // fold: per-chunk (m, z) partials of pass 1 -> one lse2 per row, once per (group, sequence, KV head)
 // =========================================================================================
 // Partials lie [chunk][row]: the threads of a workgroup take consecutive rows and every so many chunks, so the
-// reads are coalesced and, sixteen at a time, independent of each other.
-__device__ __forceinline__ void fold_rows(const float2 *__restrict__ part, int n_chunks, int m_pad, int r, int first, int step,
-                                          float &m, float &z) {
-  m = -INFINITY;
-  z = 0.0f;
-  constexpr int N = 16;                                 // (64 partials by two threads: two round trips)
-  for (int c = first; c < n_chunks; c += N * step) {
-    float2 p[N];
+// reads are coalesced and, sixteen at a time (64 partials by two threads: two round trips), independent of each other.
+constexpr int FOLD_AT_ONCE = 16;
+// NT threads fold `rows` rows (at most NT): this thread's row, its first chunk and the chunks from one to the next.
+template <int NT>
+struct FoldShare {
+  int tpr, row, first;
+  __device__ __forceinline__ FoldShare(int rows) : tpr(max(NT / rows, 1)) { row = threadIdx.x % (NT / tpr); first = threadIdx.x / (NT / tpr); }
+};
+// The partials of chunks at + first, tpr further on, ...  (Only as many requests as there are chunks for: each costs time before the
+// key stream begins.)
+template <int NT>
+__device__ __forceinline__ void fold_load(float2 (&p)[FOLD_AT_ONCE], const float2 *__restrict__ part, int n_chunks, int m_pad, const FoldShare<NT> &me, int at) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) p[i] = part[(int64_t)min(c + i * step, n_chunks - 1) * m_pad + r];
-    float mn = m;
-#pragma unroll
-    for (int i = 0; i < N; ++i) mn = c + i * step < n_chunks ? fmaxf(mn, p[i].x) : mn;
-    if (mn == -INFINITY) continue;
-    z *= fast_exp2(m - mn);
-#pragma unroll
-    for (int i = 0; i < N; ++i) z += c + i * step < n_chunks ? p[i].y * fast_exp2(p[i].x - mn) : 0.0f;
-    m = mn;
+  for (int i = 0; i < FOLD_AT_ONCE; ++i) {
+    p[i] = make_float2(-INFINITY, 0.0f);
+    if (at + i * me.tpr < n_chunks) p[i] = part[min(at + me.first + i * me.tpr, n_chunks - 1) * m_pad + me.row];
   }
 }
 
 // lse2 of the rows of one (group, sequence, KV head) into lse[0 .. rows-1] by NT threads; padded rows get +inf
-// (2^-inf = 0: they contribute nothing).  part_s: NT entries of scratch.  Synchronises before it returns.
+// (2^-inf = 0: they contribute nothing).  p: this thread's first partials, requested by the caller.  part_s: NT entries of scratch.
+// Synchronises before it returns.
 template <int NT>
-__device__ __forceinline__ void fold_all(const Shape &s, int n_chunks, int m_pad, const float2 *__restrict__ part, int rows,
-                                         float2 *part_s, float *lse) {
-  const int tpr = max(NT / rows, 1);                    // threads per row
-  for (int r0 = 0; r0 < rows; r0 += NT / tpr) {
-    const int r = r0 + threadIdx.x % (NT / tpr), which = threadIdx.x / (NT / tpr);
-    float m = -INFINITY, z = 0.0f;
-    if (r < s.M) fold_rows(part, n_chunks, m_pad, r, which, tpr, m, z);
-    part_s[threadIdx.x] = make_float2(m, z);
-    __syncthreads();
-    if (which == 0 && r < rows) {
-      for (int i = 1; i < tpr; ++i) {
-        const float2 p = part_s[threadIdx.x + i * (NT / tpr)];
-        merge_stats(m, z, p.x, p.y);
+__device__ __forceinline__ void fold_all(const Shape &s, int n_chunks, int m_pad, const float2 *__restrict__ part, int rows, const FoldShare<NT> &me,
+                                         float2 (&p)[FOLD_AT_ONCE], float2 *part_s, float *lse) {
+  float m = -INFINITY, z = 0.0f;
+  if (me.row < s.M) {
+    for (int at = 0;;) {
+      const int c = at + me.first;
+      float mn = m;
+#pragma unroll
+      for (int i = 0; i < FOLD_AT_ONCE; ++i) mn = c + i * me.tpr < n_chunks ? fmaxf(mn, p[i].x) : mn;
+      if (mn != -INFINITY) {
+        z *= fast_exp2(m - mn);
+#pragma unroll
+        for (int i = 0; i < FOLD_AT_ONCE; ++i) z += c + i * me.tpr < n_chunks ? p[i].y * fast_exp2(p[i].x - mn) : 0.0f;
+        m = mn;
       }
-      lse[r] = r < s.M ? m + fast_log2(z) : INFINITY;
+      at += FOLD_AT_ONCE * me.tpr;
+      if (at >= n_chunks) break;
+      fold_load(p, part, n_chunks, m_pad, me, at);
     }
-    __syncthreads();
   }
+  part_s[threadIdx.x] = make_float2(m, z);
+  __syncthreads();
+  if (me.first == 0 && me.row < rows) {
+    for (int i = 1; i < me.tpr; ++i) {
+      const float2 o = part_s[threadIdx.x + i * (NT / me.tpr)];
+      merge_stats(m, z, o.x, o.y);
+    }
+    lse[me.row] = me.row < s.M ? m + fast_log2(z) : INFINITY;
+  }
+  __syncthreads();
 }
 
 constexpr int FOLD_THREADS = 256;
@@ -82,8 +93,12 @@ __global__ __launch_bounds__(FOLD_THREADS) void fold_kernel(Shape s, ScorePlan p
   if (only_if && *only_if == 0u) return;
   const int64_t row = (int64_t)blockIdx.y * s.B * s.Hkv + blockIdx.x;
   const int b = blockIdx.x / s.Hkv;
-  fold_all<FOLD_THREADS>(s, pl.pass[0].first[b + 1] - pl.pass[0].first[b], pl.m_pad, partials + row * pl.n_chunks1 * pl.m_pad, pl.m_pad, part_s,
-                         lse + row * pl.m_pad);
+  const FoldShare<FOLD_THREADS> me(pl.m_pad);
+  const int n_chunks = pl.pass[0].first[b + 1] - pl.pass[0].first[b];
+  const float2 *part = partials + row * pl.n_chunks1 * pl.m_pad;
+  float2 p[FOLD_AT_ONCE];
+  if (me.row < s.M) fold_load(p, part, n_chunks, pl.m_pad, me, 0);
+  fold_all<FOLD_THREADS>(s, n_chunks, pl.m_pad, part, pl.m_pad, me, p, part_s, lse + row * pl.m_pad);
 }
 
 // The base-2 log-sum-exp of softmax row r of (group g, sequence b, KV head h): converted from the
@@ -100,69 +115,80 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 // =========================================================================================
 // the two passes
 // =========================================================================================
-// A 16x16 tile of logits takes 16 rows of each operand, 64 bytes of a row per step: lane l holds row l%16, the
-// 16-byte piece l/16.  Both operands have this layout, so which of them is A is a free choice per pass:
-//   PASS 1 (stats)   keys as A: a lane gets 4 consecutive keys of ONE query row per row tile, so the row
+// A tile of TS x TS logits takes TS rows of each operand, 64 lanes times 16 bytes per step: lane l holds row l % TS, piece l / TS
+// of the step.  TS = 32 (v_mfma_f32_32x32x16) or, on long streams and for fp32, 16 (v_mfma_f32_16x16x32, _16x16x4_f32).  In the result lane l
+// holds column l % TS, rows tile_row(e).  Both operands have this layout, so which of them is A is a free choice per pass:
+//   PASS 1 (stats)   keys as A: a lane gets TS * TS / 64 keys of ONE query row per row tile, so the row
 //                    statistics are in-lane accumulations (RT of them), merged once per chunk.
-//   PASS 2 (scores)  queries as A: a lane gets 4 query rows of ONE key, so a key's column sum is in-lane adds
-//                    over all row tiles plus two permlane swaps.
+//   PASS 2 (scores)  queries as A: a lane gets as many query rows of ONE key, so a key's column sum is in-lane adds
+//                    over all row tiles plus one or two permlane swaps.
 //
 // Waves.  HV waves share a key tile slot and take RT row tiles each (128 rows a wave at most, 64 for fp32 with 128
-// channels: the queries take RT * D * esize / 16 registers); the KW slots of a workgroup take the chunk's key
+// channels: the queries take RT * TS * D * esize / 256 registers); the KW slots of a workgroup take the chunk's key
 // tiles in turn.  Two waves fit a SIMD.
 //
-// The ring.  A slot has NS places of 16 key rows each.  A DMA instruction (global_load_lds_dwordx4) writes 64 pieces
+// The ring.  A slot has NS places of TS key rows each.  A DMA instruction (global_load_lds_dwordx4) writes 64 pieces
 // of 16 bytes in lane order; which piece of its row a lane fetches is permuted (swizzle) so that the 16 lanes
 // that later read the same piece of 16 rows find them in different banks.  Global reads stay whole rows.
-// Tile i is in registers (the next one being read from LDS) while tiles i+2 .. i+NS are on their way; the loads are
-// counted by hand (s_waitcnt vmcnt), which holds because the loop has no other global access.  With one row group
+// A tile is read into registers as a whole (16-row tiles of 16-bit inputs: while the one before is computed) and its place refilled at once; the
+// loads are counted by hand (s_waitcnt vmcnt), which holds because the loop has no other global access.  With one row group
 // a wave fills its own slot and the waves never synchronise in the loop.  With several, the waves of a slot fetch a part
-// of each tile and the workgroup meets at a barrier per tile, or (OWN_RINGS, two groups of 16-bit inputs) every wave
+// of each tile and the workgroup meets at a barrier per tile (a place is then refilled one tile later, when all have read it), or
+// (OWN_RINGS, two groups of 16-bit inputs) every wave
 // fetches whole tiles for itself: half the bytes in flight, no barriers, and the second of a slot's waves finds the
 // tile in the L2, as long as the two do not drift too far apart (see plan_score).
 //
-// What bounds it.  Per 64 logits a SIMD issues one 16x16x32 MFMA (8.6 ns on random data at the clocks the chip then
-// holds) and one multiply-add, exponential and add (7.8 ns); they hardly overlap: 13 ns together in a loop of
-// nothing else, in whatever order they are written.  The 32K-token model (8 groups, 128 rows): 103 + 100 us for the two
-// passes (shortest launches 92 + 90), 70-76 us without the loads; with plain loads 108 + 107 us, of which the loads alone 91-95
-// (5.9 TB/s; a reading kernel reaches 7.0 by nontemporal loads, 6.1 without).  The kernels before this
-// one kept the queries in LDS, read the keys in operand layout straight from global memory and took 111 + 107 us there;
-// 12.0 + 11.6 us for a group of 4096 tokens (now 9.0 + 10.1, fold included: half the code to fetch, one round of loads in the
-// prologue), 15.9 + 9.3 (fold) + 14.7 us for 16384 tokens (13.8 + 15.7), 28.3 + 27.7 us for 4096 tokens in fp32 (19.5 + 20.2),
-// 54 + 50 us for 48 rows of ragged sequences with 224 softmax rows (31 + 31).
-// With two row groups a pass takes the sum of the two, not the longer: 16381 tokens, 8 groups, 256 rows 53 us of arithmetic by these
-// figures and 38 us of keys at 7.0 TB/s, measured 97-99; the ragged sequences 12 us of arithmetic, measured 31.  One workgroup a
-// compute unit, two waves a SIMD, and with shared rings a barrier per tile: while these wait there is nothing else to run.
+// What bounds it.  Per 64 logits a SIMD issues a multiply-add, an exponential and an add (16 cycles) and one 16x16x32 MFMA or half a
+// 32x32x16 one (16 cycles of the matrix pipe).  In a loop of nothing else, two waves a SIMD: 34 cycles with 16-row tiles, 29 with 32-row
+// tiles, 26 where two waves take turns at the two by barriers; 18.1, 14.5 and 13.3 ns, as the clock falls from 2.4 to 1.9-2.0 GHz on random data
+// (it does not with zeros).  So a pass that lasts and also streams keys is bound by power: the 32K-token model (8 groups, 128
+// rows) takes 90 + 90 us from first wave to last, 84-86 without the arithmetic, 69 without the loads, and with 32-row tiles the clock is
+// 1.8-2.0 instead of 2.1-2.2 GHz: the same time, 4 % more for the second pass of the handed-over normalisers where the chip is warm.  Eight
+// waves in one workgroup, or paced by a barrier every 1 to 8 tiles so that none runs ahead: 105-125 us.  32-row tiles are for what
+// ends sooner: streams of at most 256 MB (plan_score).  Whole calls with 16- and with 32-row tiles: 4096 tokens 25.6 / 24.5 us, 16384 tokens 45.9 / 44.3,
+// 16381 tokens in 8 groups with 256 rows (268 MB) 282 / 266, ragged f16 sequences with 224 rows 71.6 / 71.0.
+// A workgroup's start, in microseconds for 4096 tokens (second pass of the 32K model): arguments and the first key requests 1.4 (2.4), queries 0.8
+// (1.5), partials to normalisers 0.8 (1.2), queries to registers 0.6 (0.7).  Requests are issued at 20 bytes a cycle and compute unit, so the 32 KB of queries cost what as many
+// keys cost.  The fold's requests stand before the queries', not behind them: 1.8 (3.6) us for the fold before.  Requested by whole rows instead
+// of fragments, the queries of 256 rows take 1.9 instead of 2.6 us.
 constexpr int score_slots(int row_groups) { return row_groups == 4 ? 2 : 4; }         // key tile slots of a workgroup
 constexpr int score_threads(int row_groups) { return 64 * row_groups * score_slots(row_groups); }
+// Rows of a tile.  Long key streams (NT_LOADS) take the smaller ones: see "What bounds it".
+constexpr int tile_size(int dt, bool nt_loads) { return dt == DT_F32 || nt_loads ? 16 : 32; }
 
-template <int D, int DT, int RT, int HV, bool OWN_RINGS>
+template <int D, int DT, int TS_, int RT, int HV, bool OWN_RINGS>
 struct ScoreConfig {
   static constexpr int ES = DT == DT_F32 ? 4 : 2;       // bytes per element
+  static constexpr int TS = TS_, E = TS * TS / 64;      // rows of a tile, logits of a lane
+  static constexpr int PPS = 64 / TS;                   // 16-byte pieces of a row per step of a contraction
   static constexpr int ROWB = D * ES;                   // bytes per key row
-  static constexpr int KS = ROWB / 64;                  // steps of a contraction
-  static constexpr int TILE = 16 * ROWB;
-  static constexpr int PPR = ROWB / 16;                 // 16-byte pieces per row: 8, 16 or 32
+  static constexpr int PPR = ROWB / 16;                 // pieces per row: 8, 16 or 32
+  static constexpr int KS = PPR / PPS;                  // steps of a contraction
+  static constexpr int TILE = TS * ROWB;
   static constexpr int RPI = 64 / PPR;                  // rows per DMA instruction
   static constexpr bool SHARED = HV > 1 && !OWN_RINGS;
   static constexpr int PARTS = SHARED ? HV : 1;         // waves that fetch a tile together
   static constexpr int LPT = TILE / 1024 / PARTS;       // DMA instructions per tile and wave
+  static constexpr int OFFS = LPT < 16 / RPI ? LPT : 16 / RPI;     // of them with offsets of their own (rows 16 apart are swizzled alike)
   static constexpr int KW = score_slots(HV), NT = score_threads(HV), WAVES = NT / 64;
   static constexpr int RINGS = SHARED ? KW : WAVES;
   static constexpr int FIT = (HV == 1 ? 65536 : 131072) / (RINGS * TILE);
   static constexpr int NS = FIT < 8 * PARTS ? FIT : 8 * PARTS;
   static constexpr int RING = RINGS * NS * TILE;
   // the queries pass through the part of the ring that is filled last
-  static constexpr int QBYTES = HV * RT * 16 * ROWB;
+  static constexpr int QBYTES = HV * RT * TILE;
   static constexpr int FIRST = NS - (QBYTES + RINGS * TILE - 1) / (RINGS * TILE);
   static_assert(FIRST >= 0, "the queries fit the ring");
   static_assert(NS >= 2, "a tile being read and one under way");
-  // Read the next tile's fragments while this one is computed.  fp32: a tile takes thousands of cycles on the matrix
-  // pipe, and its fragments twice the registers.
-  static constexpr bool AHEAD = DT != DT_F32;
+  // With 16-row tiles the next tile's fragments are read while this one is computed.  fp32: a tile takes thousands of cycles on the
+  // matrix pipe, and its fragments twice the registers.
+  static constexpr bool AHEAD = DT != DT_F32 && TS == 16;
   static constexpr int SEG = HV == 4 ? SCORE_SEG / 2 : SCORE_SEG;
+  static constexpr int T_S = SEG + KW * TS;             // token scores of a segment, and of the tiles that reach past its end
   // where piece p of row r lies within its row's slot
   static __device__ __forceinline__ int swizzle(int r, int p) { return p ^ (PPR == 8 ? (r >> 1) & 7 : r & 15); }
+  // row of a result that element e of a lane belongs to; sub: lane / TS
+  static __device__ __forceinline__ int tile_row(int sub, int e) { return e / 4 * (4 * PPS) + sub * 4 + e % 4; }
 };
 
 __device__ __forceinline__ uint32_t lds_address(const void *p) {
@@ -191,17 +217,19 @@ __device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *p) {
 
 // NT_LOADS: the keys are not put into the memory-side cache (see plan_score).  Kernels of their own, as a branch at every fetch
 // costs small calls 1 %.
-template <int D, int DT, int RT, int HV, int PASS, bool NT_LOADS, bool OWN_RINGS>
+// WAVE_ROWS: rows a wave takes, in RT tiles.
+template <int D, int DT, int WAVE_ROWS, int HV, int PASS, bool NT_LOADS, bool OWN_RINGS>
 __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, BatchParams bp, GroupPtrs gp, ScorePlan pl,
                                                                                  float2 *__restrict__ partials,
                                                                                  const float *__restrict__ lse_g,
                                                                                  float *__restrict__ t_out,
                                                                                  float *__restrict__ s_pool,
                                                                                  const uint32_t *__restrict__ only_if) {
-  using C = ScoreConfig<D, DT, RT, HV, OWN_RINGS>;
-  constexpr int KS = C::KS, KW = C::KW, NT = C::NT, NS = C::NS, ROWS = HV * RT * 16;
+  constexpr int RT = WAVE_ROWS / tile_size(DT, NT_LOADS);
+  using C = ScoreConfig<D, DT, tile_size(DT, NT_LOADS), RT, HV, OWN_RINGS>;
+  constexpr int KS = C::KS, KW = C::KW, NT = C::NT, NS = C::NS, TS = C::TS, E = C::E, ROWS = HV * RT * TS;
   __shared__ __attribute__((aligned(1024))) char ring[C::RING];
-  __shared__ __attribute__((aligned(16))) float t_s[PASS == 2 ? HV * (C::SEG + KW * 16) : 4];     // token scores of a segment
+  __shared__ __attribute__((aligned(16))) float t_s[PASS == 2 ? HV * C::T_S : 4];     // token scores of a segment
   __shared__ __attribute__((aligned(16))) float lse_s[PASS == 2 ? ROWS : 4];
   __shared__ float2 part_s[PASS == 2 ? NT : KW * ROWS];
   // Launched behind the single-read kernel as its fall-back: nothing to do unless that kernel
@@ -222,7 +250,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   const int64_t row = ((int64_t)g * s.B + b) * s.Hkv + h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = wave / KW, kw = wave % KW;               // row group, key tile slot of this wave
-  const int col = lane & 15, quad = lane >> 4;
+  const int col = lane % TS, sub = lane / TS;
   const int my_ring = C::SHARED ? kw : wave, my_part = C::SHARED ? half : 0;
 
   const int chunk = pp.chunk[b] * CHUNK_UNIT;
@@ -231,13 +259,15 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   int c0 = c_first, cend = min(c0 + chunk, limit);          // keys c0 .. cend-1 of the row
   int seg_len = PASS == 1 ? 0x40000000 : C::SEG;            // pass 2 writes its scores out a segment at a time
   int win = 1;
+  uint32_t win_magic = 0u;
   if (PASS == 2 && s_pool) {
     // A window belongs to the chunk that holds its first token: the workgroup scores and pools whole
     // windows, whatever their size, and no token is scored twice.
     win = bp.seq[b].win;
-    c0 = (c0 + win - 1) / win * win;
-    cend = min((cend + win - 1) / win * win, limit);
-    seg_len = C::SEG / win * win;
+    win_magic = bp.seq[b].win_magic;
+    c0 = divide(c0 + win - 1, win_magic) * win;
+    cend = min(divide(cend + win - 1, win_magic) * win, limit);
+    seg_len = divide(C::SEG, win_magic) * win;
   }
   float *trow = PASS == 2 ? t_out + row * s.t_stride : nullptr;
   if (PASS == 2 && !s_pool)                                 // the row's padding
@@ -249,60 +279,76 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   const char *kbase = (const char *)gp.k[g] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * C::ES;
   const int64_t kst = s.kv_st * C::ES;
   const bool wide = kst * 16 >= 0x7fffffff;                 // rows too far apart for 32-bit offsets within a tile
-  uint32_t off[C::LPT];                                     // this lane's piece of each of its DMA instructions, from the tile's first row
+  const int row_in_part = my_part * (C::LPT * C::RPI) + lane / C::PPR;      // of this lane's first DMA instruction
+  uint32_t off[C::OFFS];                                    // this lane's pieces, from the first row of its 16
 #pragma unroll
-  for (int n = 0; n < C::LPT; ++n) {
-    const int r = (my_part * C::LPT + n) * C::RPI + lane / C::PPR;
-    off[n] = (uint32_t)((uint32_t)r * (uint32_t)kst + C::swizzle(r, lane % C::PPR) * 16);
+  for (int n = 0; n < C::OFFS; ++n) {
+    const int r = row_in_part + n * C::RPI;
+    off[n] = (uint32_t)r * (uint32_t)kst + C::swizzle(r, lane % C::PPR) * 16;
   }
   const uint32_t ring_lds = lds_address(ring) + my_ring * (NS * C::TILE) + my_part * (C::LPT * 1024);
-  // keys j .. j+15 (this wave's part) into place `slot`; rows from cend on are not read (their lanes fetch row cend-1 again)
+  // keys j .. j+TS-1 (this wave's part) into place `slot`; rows from cend on are not read (their lanes fetch row cend-1 again)
   auto fetch = [&](int j, int slot) __attribute__((always_inline)) {
     const uint32_t dst = ring_lds + slot * C::TILE;
-    if (j + 16 <= cend && !wide) {
-      const char *base = kbase + (int64_t)j * kst;
+    if (j + TS <= cend && !wide) {
 #pragma unroll
-      for (int n = 0; n < C::LPT; ++n) dma_to_lds<NT_LOADS>(dst + n * 1024, base, off[n]);
+      for (int n = 0; n < C::LPT; ++n)
+        dma_to_lds<NT_LOADS>(dst + n * 1024, kbase + (int64_t)(j + n / C::OFFS * 16) * kst, off[n % C::OFFS]);
     } else {
+      int first = row_in_part;
+      asm volatile("" : "+v"(first));                       // what follows from it is not kept in registers between tiles
 #pragma unroll
       for (int n = 0; n < C::LPT; ++n) {
-        const int r = (my_part * C::LPT + n) * C::RPI + lane / C::PPR;
+        const int r = first + n * C::RPI;
         const char *p = kbase + (int64_t)min(j + r, cend - 1) * kst + C::swizzle(r, lane % C::PPR) * 16;
         dma_to_lds(dst + n * 1024, p);
       }
     }
   };
   // The order of this wave's tiles: KW apart within a segment, segment by segment.
-  int jf = c0 + kw * 16, jf_end = min(c0 + seg_len, cend), slot_f = 0;      // the next tile to fetch
+  int jf = c0 + kw * TS, jf_end = min(c0 + seg_len, cend), slot_f = 0;      // the next tile to fetch
   auto fetch_next = [&]() __attribute__((always_inline)) {
     fetch(jf, slot_f);
     slot_f = slot_f == NS - 1 ? 0 : slot_f + 1;
-    jf += KW * 16;
-    while (PASS == 2 && (C::SHARED ? jf - kw * 16 : jf) >= jf_end && jf_end < cend) {
-      jf = jf_end + kw * 16;
+    jf += KW * TS;
+    while (PASS == 2 && (C::SHARED ? jf - kw * TS : jf) >= jf_end && jf_end < cend) {
+      jf = jf_end + kw * TS;
       jf_end = min(jf_end + seg_len, cend);
     }
   };
 #pragma unroll
   for (int i = 0; i < C::FIRST; ++i) fetch_next();
 
-  // ---- the queries: into the ring's other places as fragments (lane l: row l%16 of a row tile, piece l/16 of a step),
-  // from there into registers.  Rows past the last one repeat it: their statistics are never used and their
-  // normaliser is +inf.
-  constexpr int FRAGS = HV * RT * KS, PER_SLOT = (NS - C::FIRST) * C::TILE / 1024;
-  auto frag_at = [&](int f) __attribute__((always_inline)) {
-    return f / PER_SLOT * (NS * C::TILE) + C::FIRST * C::TILE + f % PER_SLOT * 1024;
-  };
-  for (int f = wave; f < FRAGS; f += C::WAVES) {
-    const int r = min(f / KS * 16 + col, s.M - 1);
-    const int hq = (int)((uint32_t)r * s.w_magic >> 16), io = r - hq * s.w_obs;      // r / w_obs, r % w_obs
-    const char *qp = (const char *)gp.q[g] +
-                     ((int64_t)b * s.q_sb + (int64_t)(h * s.G + hq) * s.q_sh + (int64_t)io * s.q_st) * C::ES + f % KS * 64 + quad * 16;
-    dma_to_lds(lds_address(ring) + frag_at(f), qp);
+  // ---- the partials that this thread folds: requested here, they arrive together with the keys and the queries
+  const FoldShare<NT> share(ROWS);
+  const int n_parts = pl.pass[0].first[b + 1] - pl.pass[0].first[b];
+  float2 parts[PASS == 2 ? FOLD_AT_ONCE : 1];
+  if constexpr (PASS == 2)
+    if (pl.fold_in_pass2 && share.row < s.M) fold_load(parts, part, n_parts, pl.m_pad, share, 0);
+
+  // ---- the queries: into the ring's other places, tiles of rows as the keys', from there into registers as fragments.  Rows past the
+  // last one repeat it: their statistics are never used and their normaliser is +inf.
+  constexpr int PIECES = HV * RT * KS, PER_RING = (NS - C::FIRST) * KS;          // DMA instructions: all, what a ring takes
+  auto query_at = [&](int f) __attribute__((always_inline)) { return f / PER_RING * (NS * C::TILE) + C::FIRST * C::TILE + f % PER_RING * 1024; };
+  const char *qbase = (const char *)gp.q[g] + ((int64_t)b * s.q_sb + (int64_t)(h * s.G) * s.q_sh) * C::ES;
+  // rows one after the other at equal distances, as in a contiguous tensor: one offset per lane serves them all
+  const bool even = s.q_sh == (int64_t)s.w_obs * s.q_st && s.q_st < 0x1000000;
+  const uint32_t q_lane = (uint32_t)(lane / C::PPR) * (uint32_t)s.q_st * C::ES;
+  for (int f = wave; f < PIECES; f += C::WAVES) {
+    const int row = f * C::RPI + lane / C::PPR;
+    const uint32_t piece = C::swizzle(row, lane % C::PPR) * 16;
+    if (even && (f + 1) * C::RPI <= s.M) {
+      dma_to_lds<false>(lds_address(ring) + query_at(f), qbase + (int64_t)(f * C::RPI) * s.q_st * C::ES, q_lane + piece);
+    } else {
+      const int r = min(row, s.M - 1);
+      const int hq = (int)((uint32_t)r * s.w_magic >> 16), io = r - hq * s.w_obs;      // r / w_obs, r % w_obs
+      dma_to_lds(lds_address(ring) + query_at(f), qbase + ((int64_t)hq * s.q_sh + (int64_t)io * s.q_st) * C::ES + piece);
+    }
   }
   if (PASS == 2) {
-    if (pl.fold_in_pass2) fold_all<NT>(s, pl.pass[0].first[b + 1] - pl.pass[0].first[b], pl.m_pad, part, ROWS, part_s, lse_s);
-    else
+    if (pl.fold_in_pass2) {
+      if constexpr (PASS == 2) fold_all<NT>(s, n_parts, pl.m_pad, part, ROWS, share, parts, part_s, lse_s);
+    } else
       for (int r = threadIdx.x; r < ROWS; r += NT) lse_s[r] = row_lse2(s, pl, gp, lse_g, g, b, h, row, r);
   }
   wait_vmcnt<0>();
@@ -311,13 +357,16 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
 #pragma unroll
   for (int mt = 0; mt < RT; ++mt)
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[mt][ks] = *(const bf16x8 *)(ring + frag_at((half * RT + mt) * KS + ks) + lane * 16);
+    for (int ks = 0; ks < KS; ++ks)
+      qf[mt][ks] = *(const bf16x8 *)(ring + query_at((half * RT + mt) * KS) + ((col * C::ROWB + C::swizzle(col, sub) * 16) ^ (ks * C::PPS * 16)));
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __syncthreads();
+  // a place of shared rings stays empty until the first tile has been read by all, unless a tile is read ahead
+  constexpr bool LATE = C::SHARED && !C::AHEAD;
 #pragma unroll
-  for (int i = C::FIRST; i < NS; ++i) fetch_next();
+  for (int i = C::FIRST; i < NS - (LATE ? 1 : 0); ++i) fetch_next();
   const float sc = s.c1;
-  float mref[PASS == 1 ? RT : 1], zsum[PASS == 1 ? RT : 1];  // pass 1: reference and sum of query row (half*RT + mt)*16 + col
+  float mref[PASS == 1 ? RT : 1], zsum[PASS == 1 ? RT : 1];  // pass 1: reference and sum of query row (half*RT + mt)*TS + col
   bool settled = false;                                     // (uniform) every sum of this wave is large enough for its reference
   if (PASS == 1) {
 #pragma unroll
@@ -327,20 +376,21 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   // ---- tiles -----------------------------------------------------------------------------------
   // Meeting of the workgroup without the wait for outstanding loads that __syncthreads() brings.
   auto barrier = [&]() __attribute__((always_inline)) { asm volatile("s_barrier" ::: "memory"); };
-  struct Frags { bf16x8 f[KS]; };
-  const uint32_t lane_row = col * C::ROWB;
-  int slot_r = 0;                                           // the slot read next
-  auto read_frags = [&](Frags &kf) __attribute__((always_inline)) {
-    const char *p = ring + my_ring * (NS * C::TILE) + slot_r * C::TILE + lane_row;
+  typedef typename TileOf<TS>::acc acc_t;
+  struct Frags { bf16x8 f[KS]; } kf, kn;                    // this tile's keys, the next one's
+  uint32_t read_at = my_ring * (NS * C::TILE) + col * C::ROWB + C::swizzle(col, sub) * 16;     // of the place read next
+  const uint32_t ring_end = (my_ring + 1) * (NS * C::TILE);
+  auto read_keys = [&](Frags &k) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kf.f[ks] = *(const bf16x8 *)(p + C::swizzle(col, ks * 4 + quad) * 16);
-    slot_r = slot_r == NS - 1 ? 0 : slot_r + 1;
+    for (int ks = 0; ks < KS; ++ks) k.f[ks] = *(const bf16x8 *)(ring + (read_at ^ (ks * C::PPS * 16)));       // swizzle(col, ks * PPS + sub)
+    read_at += C::TILE;
+    if (read_at >= ring_end) read_at -= NS * C::TILE;
   };
-  auto logits = [&](const Frags &kf, int mt) __attribute__((always_inline)) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto logits = [&](int mt) __attribute__((always_inline)) {
+    acc_t acc = {};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      acc = PASS == 1 ? mfma_64b<DT>(kf.f[ks], qf[mt][ks], acc) : mfma_64b<DT>(qf[mt][ks], kf.f[ks], acc);
+      acc = PASS == 1 ? mfma_step<DT, TS>(kf.f[ks], qf[mt][ks], acc) : mfma_step<DT, TS>(qf[mt][ks], kf.f[ks], acc);
     return acc;
   };
 
@@ -348,16 +398,16 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   // j <= n_review + io), the end of the sequence, and rows whose reference does not suit their logits.  A
   // reference is good while the sum taken with it stays between MF_LOW (what underflowed is negligible) and
   // MF_BIG; otherwise it moves to the larger of the tile's maximum and the sum so far.
-  auto careful = [&](const Frags &kf, int j0) __attribute__((always_inline)) {
+  auto careful = [&](int j0) __attribute__((always_inline)) {
 #pragma unroll
     for (int mt = 0; mt < RT; ++mt) {
-      f32x4 acc = logits(kf, mt);
-      const int r = min((half * RT + mt) * 16 + col, s.M - 1);
+      acc_t acc = logits(mt);
+      const int r = min((half * RT + mt) * TS + col, s.M - 1);
       const int last = min(n_review + r - (int)((uint32_t)r * s.w_magic >> 16) * s.w_obs, cend - 1);
       float vmax = -INFINITY, a = 0.0f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[e] = j0 + quad * 4 + e <= last ? acc[e] * sc : -INFINITY;
+      for (int e = 0; e < E; ++e) {
+        acc[e] = j0 + C::tile_row(sub, e) <= last ? acc[e] * sc : -INFINITY;
         vmax = fmaxf(vmax, acc[e]);
         a += fast_exp2(acc[e] - mref[mt]);
       }
@@ -368,7 +418,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
         if (nref != -INFINITY) {                            // else the row has seen no key yet
           a = fast_exp2(have - nref);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) a += fast_exp2(acc[e] - nref);
+          for (int e = 0; e < E; ++e) a += fast_exp2(acc[e] - nref);
           mref[mt] = nref;
           zsum[mt] = a;
         }
@@ -378,95 +428,107 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
     }
   };
 
-  auto tile = [&](Frags &kf, Frags &kn, int j0, int seg0) __attribute__((always_inline)) {
-    if (C::AHEAD) {                                         // tile i+1 out of the ring, tile i+NS into the slot tile i left
-      wait_vmcnt<(NS - 2) * C::LPT>();
-      if (C::SHARED) barrier();                             // (every part of it; every wave has tile i in registers)
-      read_frags(kn);
-    } else {
-      wait_vmcnt<(NS - 1) * C::LPT>();
-      if (C::SHARED) barrier();
-      read_frags(kf);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // its place is free for the fetch below
-      if (C::SHARED) barrier();
-    }
-    fetch_next();
-    if (PASS == 1) {
-      bool care = j0 + 16 > min(n_review, cend);            // uniform
-      if (!care) {
-        f32x4 acc[RT];
-        float psum[RT];
-#pragma unroll
-        for (int mt = 0; mt <= RT; ++mt) {                  // the MFMAs of a row tile beside the exponentials of the one before
-          if (mt < RT) acc[mt] = logits(kf, mt);
-          if (mt > 0) {
-            const int m1 = mt - 1;
-            float a = fast_exp2(fmaf(acc[m1][0], sc, -mref[m1]));
-#pragma unroll
-            for (int e = 1; e < 4; ++e) a += fast_exp2(fmaf(acc[m1][e], sc, -mref[m1]));
-            psum[m1] = a;
-          }
-        }
-        float big = psum[0];
-#pragma unroll
-        for (int mt = 1; mt < RT; ++mt) big = fmaxf(big, psum[mt]);
-        bool bad = !(big <= MF_BIG);
-        if (!settled) {
-          float low = zsum[0] + psum[0];
-#pragma unroll
-          for (int mt = 1; mt < RT; ++mt) low = fminf(low, zsum[mt] + psum[mt]);
-          bad |= !(low >= MF_LOW);
-        }
-        care = __any(bad);
-        if (!care) {
-#pragma unroll
-          for (int mt = 0; mt < RT; ++mt) zsum[mt] += psum[mt];
-          settled = true;
-        }
-      }
-      if (care) {
-        careful(kf, j0);
-        if (!settled) {
-          float low = zsum[0];
-#pragma unroll
-          for (int mt = 1; mt < RT; ++mt) low = fminf(low, zsum[mt]);
-          settled = __all(low >= MF_LOW);
-        }
-      }
-    } else {
-      f32x4 acc[RT];
-      float ta = 0.0f, tb = 0.0f;
+  // The row tiles of one key tile: the MFMAs of a row tile beside the exponentials of the one before.  A row tile past the
+  // last row is left out (of the last row group, where the counts do not divide).
+  const bool one_less = HV > 1 && (half * RT + RT - 1) * TS >= s.M;                    // uniform
+  auto left_out = [&](int mt) __attribute__((always_inline)) { return HV > 1 && mt == RT - 1 && one_less; };
+  auto statistics = [&](int j0) __attribute__((always_inline)) {
+    bool care = j0 + TS > min(n_review, cend);              // uniform
+    if (!care) {
+      acc_t acc[RT];
+      float psum[RT];
 #pragma unroll
       for (int mt = 0; mt <= RT; ++mt) {
-        if (mt < RT) acc[mt] = logits(kf, mt);
-        if (mt > 0) {
+        if (mt < RT && !left_out(mt)) acc[mt] = logits(mt);
+        if (mt > 0 && !left_out(mt - 1)) {
           const int m1 = mt - 1;
-          // (from LDS every time: 4 * RT of them would not fit beside the queries)
-          const f32x4 lse = *(const f32x4 *)&lse_s[(half * RT + m1) * 16 + quad * 4];
-          ta += fast_exp2(fmaf(acc[m1][0], sc, -lse[0]));
-          tb += fast_exp2(fmaf(acc[m1][1], sc, -lse[1]));
-          ta += fast_exp2(fmaf(acc[m1][2], sc, -lse[2]));
-          tb += fast_exp2(fmaf(acc[m1][3], sc, -lse[3]));
+          float a[4];                                       // (four sums: half the additions one after the other, and less rounding)
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            const float x = fast_exp2(fmaf(acc[m1][e], sc, -mref[m1]));
+            a[e % 4] = e < 4 ? x : a[e % 4] + x;
+          }
+          psum[m1] = (a[0] + a[1]) + (a[2] + a[3]);
         }
       }
-      // (the four lanes of a key store the same value to the same place: no branch in the loop)
-      t_s[half * (C::SEG + KW * 16) + j0 - seg0 + col] = quads_sum(ta + tb);
+      if (left_out(RT - 1)) psum[RT - 1] = psum[0];         // (any sum that does not ask for care)
+      float big = psum[0];
+#pragma unroll
+      for (int mt = 1; mt < RT; ++mt) big = fmaxf(big, psum[mt]);
+      bool bad = !(big <= MF_BIG);
+      if (!settled) {
+        float low = zsum[0] + psum[0];
+#pragma unroll
+        for (int mt = 1; mt < RT; ++mt) low = fminf(low, zsum[mt] + psum[mt]);
+        bad |= !(low >= MF_LOW);
+      }
+      care = __any(bad);
+      if (!care) {
+#pragma unroll
+        for (int mt = 0; mt < RT; ++mt) zsum[mt] += psum[mt];
+        settled = true;
+      }
+    }
+    if (care) {
+      careful(j0);
+      if (!settled) {
+        float low = zsum[0];
+#pragma unroll
+        for (int mt = 1; mt < RT; ++mt) low = fminf(low, zsum[mt]);
+        settled = __all(low >= MF_LOW);
+      }
     }
   };
+  auto scores = [&](int j0, int seg0) __attribute__((always_inline)) {
+    // 32-row tiles: a tile's MFMAs, then its exponentials, as two tiles' results would not fit; the SIMD's other wave fills the gaps
+    constexpr int LAG = TS == 16 ? 1 : 0;
+    float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    acc_t acc[RT];
+#pragma unroll
+    for (int mt = 0; mt < RT + LAG; ++mt) {
+      if (mt < RT && !left_out(mt)) acc[mt] = logits(mt);
+      if (mt >= LAG && !left_out(mt - LAG)) {
+        const int m1 = mt - LAG;
+#pragma unroll
+        for (int e = 0; e < E; e += 4) {
+          // (from LDS every time: E * RT of them would not fit beside the queries)
+          const f32x4 lse = *(const f32x4 *)&lse_s[(half * RT + m1) * TS + C::tile_row(sub, e)];
+          t[e / 4 % 2 * 2] += fast_exp2(fmaf(acc[m1][e], sc, -lse[0]));
+          t[e / 4 % 2 * 2 + 1] += fast_exp2(fmaf(acc[m1][e + 1], sc, -lse[1]));
+          t[e / 4 % 2 * 2] += fast_exp2(fmaf(acc[m1][e + 2], sc, -lse[2]));
+          t[e / 4 % 2 * 2 + 1] += fast_exp2(fmaf(acc[m1][e + 3], sc, -lse[3]));
+        }
+        if (TS == 32) asm volatile("" ::: "memory");        // the normalisers of the next tile are not loaded yet, for want of registers
+      }
+    }
+    // (the lanes of a key store the same value to the same place: no branch in the loop)
+    const float sum = TS == 16 ? t[0] + t[1] : (t[0] + t[1]) + (t[2] + t[3]);
+    t_s[half * C::T_S + j0 - seg0 + col] = TS == 16 ? quads_sum(sum) : add_halves(sum, sum);
+  };
 
-  Frags ka, kb;
-  if (C::AHEAD) {
+  if constexpr (C::AHEAD) {
     wait_vmcnt<(NS - 1) * C::LPT>();
     if (C::SHARED) barrier();
-    read_frags(ka);
+    read_keys(kf);
   }
   for (int seg0 = c0; seg0 < cend; seg0 += seg_len) {
     const int seg_end = min(seg0 + seg_len, cend);
     // with row groups every slot takes a tile in every round, if need be one past the end (masked in pass 1, past the
     // scores that count in pass 2): the waves meet at barriers
-    for (int j = seg0 + kw * 16; (C::SHARED ? j - kw * 16 : j) < seg_end; j += KW * 16) {
-      tile(ka, kb, j, seg0);
-      if (C::AHEAD) ka = kb;
+    for (int j = seg0 + kw * TS; (C::SHARED ? j - kw * TS : j) < seg_end; j += KW * TS) {
+      if constexpr (C::AHEAD) {                             // the next tile out of the ring, a later one into the place this one left
+        wait_vmcnt<(NS - 2) * C::LPT>();
+        if (C::SHARED) barrier();                           // (every part of it; every wave has this tile in registers)
+        read_keys(kn);
+      } else {                                              // this tile out of the ring, a later one into its place or (LATE) that of the one before
+        wait_vmcnt<(NS - (LATE ? 2 : 1)) * C::LPT>();
+        if (C::SHARED) barrier();
+        read_keys(kf);
+        if (!LATE) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      }
+      fetch_next();
+      if (PASS == 1) statistics(j); else scores(j, seg0);
+      if (C::AHEAD) kf = kn;
     }
     if (PASS == 1) break;
     __syncthreads();
@@ -474,13 +536,13 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
       for (int i = threadIdx.x; i < seg_end - seg0; i += NT) {
         float x = t_s[i];
 #pragma unroll
-        for (int v = 1; v < HV; ++v) x += t_s[v * (C::SEG + KW * 16) + i];
+        for (int v = 1; v < HV; ++v) x += t_s[v * C::T_S + i];
         t_s[i] = x;
       }
       __syncthreads();
     }
     if (s_pool)                                             // Eq. 3-4 while the token scores are in LDS
-      pool_windows<NT>(t_s, seg0 / win, (seg_end + win - 1) / win, win, bp.seq[b].p, n_review, s_pool + row * s.nw_max);
+      pool_windows<NT>(t_s, divide(seg0, win_magic), divide(seg_end + win - 1, win_magic), win, bp.seq[b].p, n_review, s_pool + row * s.nw_max);
     else
       for (int i = threadIdx.x; i < seg_end - seg0; i += NT) trow[seg0 + i] = t_s[i];
     if (seg_end == cend) break;
@@ -488,16 +550,18 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   }
 
   if (PASS == 1) {
-    // merge the 4 quads of each row, then the KW waves
+    // merge the lanes of each row, then the KW waves
 #pragma unroll
     for (int mt = 0; mt < RT; ++mt) {
       float m = zsum[mt] > 0.0f ? mref[mt] : -INFINITY, z = zsum[mt];
       Pair pm = swap_halves(m, m), pz = swap_halves(z, z);
       merge_stats(pm.a, pz.a, pm.b, pz.b);
-      m = pm.a; z = pz.a;
-      pm = swap_rows(m, m); pz = swap_rows(z, z);
-      merge_stats(pm.a, pz.a, pm.b, pz.b);
-      if (quad == 0) part_s[kw * ROWS + (half * RT + mt) * 16 + col] = make_float2(pm.a, pz.a);
+      if constexpr (TS == 16) {
+        m = pm.a; z = pz.a;
+        pm = swap_rows(m, m); pz = swap_rows(z, z);
+        merge_stats(pm.a, pz.a, pm.b, pz.b);
+      }
+      if (sub == 0) part_s[kw * ROWS + (half * RT + mt) * TS + col] = make_float2(pm.a, pz.a);
     }
     __syncthreads();
     for (int r = threadIdx.x; r < pl.m_pad; r += NT) {           // m_pad <= ROWS
@@ -511,7 +575,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
 // =========================================================================================
 // launch
 // =========================================================================================
-template <int D, int DT, int RT, int HV, bool NT_LOADS, bool OWN_RINGS = false>
+template <int D, int DT, int WAVE_ROWS, int HV, bool NT_LOADS, bool OWN_RINGS = false>
 static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
                                 bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
                                 hipEvent_t mid, const uint32_t *only_if) {
@@ -522,7 +586,7 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
     if (s.t_stride <= 0) return hipSuccess;
   } else {
     dim3 g1(pl.pass[0].first[s.B], s.Hkv, n_groups);
-    hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 1, NT_LOADS, OWN_RINGS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
+    hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 1, NT_LOADS, OWN_RINGS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
@@ -534,7 +598,7 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
   ScorePlan pl2 = pl;
   if (have_lse) pl2.fold_in_pass2 = false;
   dim3 g2(pl.pass[1].first[s.B], s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_kernel<D, DT, RT, HV, 2, NT_LOADS, OWN_RINGS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
+  hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 2, NT_LOADS, OWN_RINGS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
   return hipGetLastError();
 }
 
@@ -542,20 +606,22 @@ template <int D, int DT>
 static hipError_t launch_rows(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
                               bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
                               hipEvent_t mid, const uint32_t *only_if) {
-  // Row tiles per wave: the counts of the usual head layouts (w_obs of 8 to 32 with 1 to 8 query heads per KV
-  // head) are met exactly, the rest rounds up; a wave holds eight at most, four of fp32 with 128 channels.
-  const int mt = pl.m_pad / 16;
+  // Rows per wave: the counts of the usual head layouts (w_obs of 8 to 32 with 1 to 8 query heads per KV head) are met exactly where
+  // the tiles have 16 rows, in steps of 32 where they have 32; a wave holds 128 at most, 64 of fp32 with 128 channels.
 #define WKV_PASSES(RR, HH, ...) \
-  launch_passes<D, DT, RR, HH, __VA_ARGS__>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if)
-#define WKV_ROWS(RR, HH) \
-  if (mt <= RR * HH) { \
-    if constexpr (HH == 2 && DT != DT_F32) if (pl.own_rings) return WKV_PASSES(RR, HH, false, true); \
-    return pl.nontemporal ? WKV_PASSES(RR, HH, true) : WKV_PASSES(RR, HH, false); \
-  }
+  if (s.M <= RR * HH) return launch_passes<D, DT, RR, HH, __VA_ARGS__>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
+#define WKV_ROWS(RR, HH) if (pl.nontemporal) { WKV_PASSES(RR, HH, true) } else { WKV_PASSES(RR, HH, false) }
   if constexpr (DT == DT_F32 && D == 128) {
-    WKV_ROWS(1, 1) WKV_ROWS(2, 1) WKV_ROWS(4, 1) WKV_ROWS(4, 2) WKV_ROWS(4, 4)
+    WKV_ROWS(16, 1) WKV_ROWS(32, 1) WKV_ROWS(64, 1) WKV_ROWS(64, 2) WKV_ROWS(64, 4)
+  } else if constexpr (DT == DT_F32) {
+    WKV_ROWS(16, 1) WKV_ROWS(32, 1) WKV_ROWS(64, 1) WKV_ROWS(96, 1) WKV_ROWS(112, 1) WKV_ROWS(128, 1) WKV_ROWS(96, 2) WKV_ROWS(112, 2) WKV_ROWS(128, 2)
+  } else if (pl.nontemporal) {
+    WKV_PASSES(16, 1, true) WKV_PASSES(32, 1, true) WKV_PASSES(64, 1, true) WKV_PASSES(96, 1, true) WKV_PASSES(112, 1, true) WKV_PASSES(128, 1, true)
+    WKV_PASSES(96, 2, true) WKV_PASSES(112, 2, true) WKV_PASSES(128, 2, true)
   } else {
-    WKV_ROWS(1, 1) WKV_ROWS(2, 1) WKV_ROWS(4, 1) WKV_ROWS(6, 1) WKV_ROWS(7, 1) WKV_ROWS(8, 1) WKV_ROWS(6, 2) WKV_ROWS(7, 2) WKV_ROWS(8, 2)
+    WKV_PASSES(32, 1, false) WKV_PASSES(64, 1, false) WKV_PASSES(96, 1, false) WKV_PASSES(128, 1, false)
+    if (pl.own_rings) { WKV_PASSES(96, 2, false, true) WKV_PASSES(128, 2, false, true) }
+    WKV_PASSES(96, 2, false) WKV_PASSES(128, 2, false)
   }
 #undef WKV_ROWS
 #undef WKV_PASSES

@@ -91,7 +91,7 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
   __shared__ uint32_t counts[TOPK_ITERS * TOPK_WAVES];      // windows per wave and 1024: greater | equal << 16
   __shared__ uint32_t sh_bin, sh_above, sh_count;
   const int n_review = sp.L - w_obs;
-  const int nw = (n_review + sp.win - 1) / sp.win;
+  const int nw = divide(n_review + sp.win - 1, sp.win_magic);
   const int k = sp.k;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int n_rev_kept = 0;
@@ -212,12 +212,12 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
 struct TokenOf {
   const uint32_t *keys;                         // the selected windows
   int win, L, n_rev_kept, nk;
-  uint32_t magic;                               // r / win == umulhi(r, magic) for r < 2^32 / win; 0 for win = 1
+  uint32_t magic;
   __device__ __forceinline__ TokenOf(const SeqParam &sp, int w_obs, const uint32_t *sel, int kept)
-      : keys(sel), win(sp.win), L(sp.L), n_rev_kept(kept), nk(kept + w_obs), magic(0xffffffffu / (uint32_t)sp.win + 1u) {}
+      : keys(sel), win(sp.win), L(sp.L), n_rev_kept(kept), nk(kept + w_obs), magic(sp.win_magic) {}
   __device__ __forceinline__ int operator()(int r) const {
     if (r < n_rev_kept) {
-      const int m = win == 1 ? r : (int)__umulhi((uint32_t)r, magic);
+      const int m = divide(r, magic);
       return (int)keys[m] * win + (r - m * win);
     }
     return r < nk ? L - nk + r : -1;
