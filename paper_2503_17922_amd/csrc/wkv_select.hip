@@ -66,7 +66,8 @@ hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, 
 //   4. expansion to token positions, the observation window appended, -1 padding
 // The 32K-token configuration (64 rows of 2046 windows, k = 256): 12.2 us with 8-bit digits from the
 // top and three synchronisations per 1024 windows in step 3, 9.2 us so; a mixed batch (512 rows of up to 3900
-// windows): 19.7 us, 18.0 us so with 1024 threads, 13.8 us with 512.
+// windows): 19.7 us, 18.0 us so with 1024 threads, 13.8 us with 512.  With scans by DPP and a thread's scores requested
+// together: 9.6 -> 8.0 us and 12.0 -> 10.2 us.
 // ------------------------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -79,6 +80,27 @@ static_assert(TOPK_ITERS <= 32, "one mask bit per window of a thread");
 __device__ __forceinline__ uint32_t float_to_key(float f) {
   const uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// Over the lanes of a wave by DPP steps (a shuffle through LDS takes 100 cycles and more, and there are a dozen of these in a
+// row): shifts within rows of 16 lanes, then the last lane of a row, of two rows, into the ones after.  Lanes
+// without a source add 0, the smallest key.
+template <class F>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, F op) {
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false));     // row_shr:1
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false));     // row_shr:2
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false));     // row_shr:4
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false));     // row_shr:8
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));     // row_bcast:15
+  return op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));  // row_bcast:31
+}
+// Sums up to and including each lane; the largest of all lanes.
+__device__ __forceinline__ uint32_t wave_sums(uint32_t x) {
+  return wave_scan(x, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a + b; });
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+__device__ __forceinline__ uint32_t wave_largest(uint32_t x) {
+  return last_lane(wave_scan(x, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return max(a, b); }));
 }
 
 // Steps 1-3 for the row of window scores srow: the selected windows, ascending, are left in keys (LDS, nw_max entries)
@@ -99,17 +121,21 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
   if (k > 0) {
     // ---- 1. keys and their range ------------------------------------------------------------
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    for (int w = tid; w < nw; w += NT) {
-      const uint32_t key = float_to_key(srow[w]);
-      keys[w] = key;
-      kmin = min(kmin, key);
-      kmax = max(kmax, key);
-    }
+    constexpr int AT_ONCE = 4;                    // scores requested together
+    for (int w0 = tid; w0 < nw; w0 += AT_ONCE * NT) {
+      float x[AT_ONCE];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
-      kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
+      for (int i = 0; i < AT_ONCE; ++i) x[i] = srow[min(w0 + i * NT, nw - 1)];
+#pragma unroll
+      for (int i = 0; i < AT_ONCE; ++i) {         // (past the end: the last one's key again, written nowhere)
+        const uint32_t key = float_to_key(x[i]);
+        if (w0 + i * NT < nw) keys[w0 + i * NT] = key;
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
+      }
     }
+    kmin = ~wave_largest(~kmin);
+    kmax = wave_largest(kmax);
     if (lane == 0) { wave_a[wave] = kmin; wave_b[wave] = kmax; }
     hist[tid] = 0u; hist[tid + NT] = 0u;
     __syncthreads();
@@ -131,12 +157,7 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
       __syncthreads();
       // windows in strictly higher bins: thread tid looks at the 2*tid-th and the next bin from the top
       const uint32_t c0 = hist[2 * NT - 1 - 2 * tid], c1 = hist[2 * NT - 2 - 2 * tid];
-      uint32_t incl = c0 + c1;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_up((int)incl, off);
-        if (lane >= off) incl += o;
-      }
+      const uint32_t incl = wave_sums(c0 + c1);
       if (lane == 63) wave_a[wave] = incl;
       __syncthreads();
       uint32_t above = incl - c0 - c1;
@@ -175,14 +196,9 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
       uint32_t base = 0u;
       for (int c = 0; c < iters * (NT / 64); c += 64) {
         const uint32_t v = c + lane < iters * (NT / 64) ? counts[c + lane] : 0u;
-        uint32_t incl = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const uint32_t o = (uint32_t)__shfl_up((int)incl, off);
-          if (lane >= off) incl += o;
-        }
+        const uint32_t incl = wave_sums(v);
         if (c + lane < iters * (NT / 64)) counts[c + lane] = base + incl - v;
-        base += (uint32_t)__shfl((int)incl, 63);
+        base += last_lane(incl);
       }
     }
     __syncthreads();
@@ -248,7 +264,9 @@ __global__ __launch_bounds__(NT) void topk_kernel(Shape s, BatchParams bp, Group
 // microseconds of latency whether one workgroup of a row does it or all of them, and a launch less is worth
 // more than that.  The pairs times `splits` fit the device at once; with more, the repeated selection would
 // cost a round of its own.  A 4096-token group of four layers: 5.3 + 6.7 us apart, 9.5 us so with 256 threads (14 us
-// with 1024: sixteen waves at every synchronisation); 16384 tokens: 5.7 + 14.9 us, 18.1 us so.
+// with 1024: sixteen waves at every synchronisation); 16384 tokens: 5.7 + 14.9 us, 18.1 us so.  8.7 and 18.1 us with scans through
+// LDS and a workgroup's rows copied four a lane at a time, 7.8 and 17.4 us with scans by DPP, the next rows requested before these are stored, and a
+// pair's workgroups interleaved; six or eight rows a lane, 640 to 1024 workgroups: within 2 %, one shape's gain another's loss.
 template <int LPR>  // 16-byte pieces per row
 __global__ __launch_bounds__(SMALL_THREADS) void select_gather_kernel(Shape s, SmallJob job, const float *__restrict__ sc,
                                                                      int32_t *__restrict__ win_idx, int32_t *__restrict__ tok_idx,
@@ -270,19 +288,27 @@ __global__ __launch_bounds__(SMALL_THREADS) void select_gather_kernel(Shape s, S
   const char *src = (const char *)job.in[layer][is_v] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * job.esize + piece * 16;
   char *dst = (char *)job.out[layer][is_v] + ((int64_t)b * s.o_sb + (int64_t)h * s.o_sh) * job.esize + piece * 16;
   const int64_t in_step = s.kv_st * job.esize, out_step = s.o_st * job.esize;
-  const int share = (n_write + gridDim.x - 1) / gridDim.x, r_end = min((split + 1) * share, n_write);
-  for (int r0 = split * share + threadIdx.x / LPR; r0 < r_end; r0 += ROWS * AHEAD) {
-    u32x4 v[AHEAD];
+  // rows ROWS * gridDim.x apart: the workgroups of a pair write one dense stretch; the next AHEAD rows are requested before these are stored
+  const int step = ROWS * (int)gridDim.x;
+  int r0 = split * ROWS + threadIdx.x / LPR;
+  u32x4 v[AHEAD];
+  auto request = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < AHEAD; ++u) {
-      const int r = r0 + u * ROWS;
+      const int r = r0 + u * step;
       v[u] = u32x4{0u, 0u, 0u, 0u};
-      if (r < min(r_end, nk))
-        v[u] = __builtin_nontemporal_load((const u32x4 *)(src + (int64_t)token(r) * in_step));
+      if (r < nk) v[u] = __builtin_nontemporal_load((const u32x4 *)(src + (int64_t)token(r) * in_step));
     }
+  };
+  request(r0);
+  for (; r0 < n_write; r0 += step * AHEAD) {
+    u32x4 out[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) out[u] = v[u];
+    request(r0 + step * AHEAD);
 #pragma unroll
     for (int u = 0; u < AHEAD; ++u)
-      if (r0 + u * ROWS < r_end) __builtin_nontemporal_store(v[u], (u32x4 *)(dst + (int64_t)(r0 + u * ROWS) * out_step));
+      if (r0 + u * step < n_write) __builtin_nontemporal_store(out[u], (u32x4 *)(dst + (int64_t)(r0 + u * step) * out_step));
   }
   if (!writer) return;
   for (int i = sp.k + threadIdx.x; i < s.k_max; i += SMALL_THREADS) wrow[i] = -1;

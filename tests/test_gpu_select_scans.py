@@ -1,0 +1,35 @@
+"""Top-k at window counts around waves, workgroups and the scores that a thread requests together, with spread, equal, few-valued and infinite
+scores, against a stable sort."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_17922_amd as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nw", [1, 2, 63, 64, 65, 255, 256, 257, 511, 513, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 16385])
+def test_top_k_by_window_count(nw, device):
+    H, win, w_obs = 6, 3, 2
+    L = nw * win - 1 + w_obs                       # the last window is partial
+    rng = np.random.default_rng(nw)
+    s = rng.standard_normal((1, H, nw)).astype(np.float32)
+    s[0, 1] = 0.25                                 # ties everywhere: lower indices win
+    s[0, 2] = rng.integers(0, 3, nw)
+    s[0, 3] = np.abs(s[0, 3]) * 1e-30
+    s[0, 4, rng.integers(0, nw)] = np.inf
+    s[0, 5, rng.integers(0, nw, max(nw // 2, 1))] = -np.inf
+    for k in sorted({1, (nw + 1) // 2, nw}):
+        p = W.Problem(n_q_heads=H, n_kv_heads=H, head_dim=64, w_obs=w_obs, seq_len=[L], win=[win], top_p=[win], k_windows=[k], dtype=W.WKV_BF16)
+        wi = torch.full((1, H, k), -7, dtype=torch.int32, device=device)
+        ti = torch.full((1, H, k * win + w_obs), -7, dtype=torch.int32, device=device)
+        nk = torch.zeros((1, H), dtype=torch.int32, device=device)
+        W.wkv_topk_windows(p, torch.from_numpy(s).to(device), wi, ti, nk)
+        torch.cuda.synchronize()
+        for h in range(H):
+            want = np.sort(np.argsort(-s[0, h], kind="stable")[:k])
+            assert np.array_equal(wi[0, h].cpu().numpy(), want), (nw, k, h)
+            tok = np.concatenate([np.arange(w * win, min((w + 1) * win, L - w_obs)) for w in want] + [np.arange(L - w_obs, L)])
+            assert int(nk[0, h]) == len(tok) and np.array_equal(ti[0, h, : len(tok)].cpu().numpy(), tok)
+            assert bool((ti[0, h, len(tok):] == -1).all())
