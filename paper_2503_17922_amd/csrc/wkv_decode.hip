@@ -34,6 +34,7 @@ static __device__ __align__(256) unsigned char scratch[WKV_DECODE_STATIC_SCRATCH
 
 constexpr int DEC_THREADS = 256;
 constexpr int DEC_WAVES = DEC_THREADS / 64;
+constexpr int WIDE_THREADS = 512;   // where a range is a block for each of eight waves (see launch_partial_g)
 constexpr int DEC_U = 4;            // row tiles per wave batch (loads in flight: 2 * DEC_U per lane)
 
 // A 16-byte piece of a cache row.  STREAM: a nontemporal load, which puts nothing into the memory-side cache; a kernel
@@ -311,16 +312,17 @@ __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
 }
 // STREAM: 0 plain loads, 1 values stream, 2 keys too (see launch_partial_g).
-template <int D, int G, bool F16, int STREAM>
-__global__ __launch_bounds__(DEC_THREADS, 3) void decode_partial_mfma_kernel(
+template <int D, int G, bool F16, int STREAM, int NT>
+__global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
     DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *k_cache,
     const uint16_t *v_cache, const int32_t *__restrict__ n_valid, float *__restrict__ part) {
-  constexpr int E = 8;
+  constexpr int E = 8, WAVES = NT / 64;
+  constexpr bool PAIRS = WAVES == DEC_WAVES;
   constexpr int LPK = D / E;                 // lanes per row (value side): 16 or 8
   constexpr int VT = D / 32;                 // value loads per block of 16 rows: rows of a quad / rows it reads at once
   constexpr int KS = D / 32;                 // MFMA steps over the channels
-  __shared__ __attribute__((aligned(16))) float o_s[DEC_WAVES][G][D];
-  __shared__ float2 ml_s[DEC_WAVES][G];
+  __shared__ __attribute__((aligned(16))) float o_s[WAVES][G][D];
+  __shared__ float2 ml_s[WAVES][G];
 
   const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv, s.heads_magic);
   const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
@@ -347,7 +349,7 @@ __global__ __launch_bounds__(DEC_THREADS, 3) void decode_partial_mfma_kernel(
 #pragma unroll
   for (int i = 0; i < G * E; ++i) o[i] = 0.0f;
 
-  // Blocks of 16 rows, every DEC_WAVES-th of the range, two at a time: a range of 128 rows is one round trip to memory.
+  // Blocks of 16 rows, every WAVES-th of the range, by four waves two at a time: a range of 128 rows is one round trip to memory.
   struct Block { uint4 k[KS], v[VT]; };
   auto load_block = [&](Block &x, int blk) __attribute__((always_inline)) {
     const int r0 = c0 + blk * 16;
@@ -395,18 +397,22 @@ __global__ __launch_bounds__(DEC_THREADS, 3) void decode_partial_mfma_kernel(
       });
     }
   };
-  for (int blk = wave; c0 + blk * 16 < cend; blk += DEC_WAVES) {
+  for (int blk = wave; c0 + blk * 16 < cend; blk += WAVES) {
     Block x, next;
     load_block(x, blk);
-    load_block(next, blk + DEC_WAVES);         // (past the end: the last row again)
-    __builtin_amdgcn_sched_barrier(0);         // both are requested before the first is looked at
-    for (bool more = c0 + (blk + DEC_WAVES) * 16 < cend;; more = false) {          // (one copy of the code, which every launch fetches anew)
+    if constexpr (PAIRS) {
+      load_block(next, blk + WAVES);           // (past the end: the last row again)
+      __builtin_amdgcn_sched_barrier(0);       // both are requested before the first is looked at
+      for (bool more = c0 + (blk + WAVES) * 16 < cend;; more = false) {            // (one copy of the code, which every launch fetches anew)
+        attend(x, blk);
+        if (!more) break;
+        blk += WAVES;
+        x = next;
+      }
+      __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), as it is by now: else the compiler waits for the queries among the first requests
+    } else {
       attend(x, blk);
-      if (!more) break;
-      blk += DEC_WAVES;
-      x = next;
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0), as it is by now: else the compiler waits for the queries among the first requests
   }
 
   // The wave's totals.  After the two swap steps lane (quad, piece) holds 2*G of a piece's sums: those of
@@ -432,14 +438,14 @@ __global__ __launch_bounds__(DEC_THREADS, 3) void decode_partial_mfma_kernel(
   __syncthreads();
 
   // merge the waves: a thread takes four channels of one head
-  for (int i = threadIdx.x; i < G * (D / 4); i += DEC_THREADS) {
+  for (int i = threadIdx.x; i < G * (D / 4); i += NT) {
     const int g = i / (D / 4), c = i % (D / 4) * 4;
     float mm = -INFINITY, ll = 0.0f;
 #pragma unroll
-    for (int w = 0; w < DEC_WAVES; ++w) mm = fmaxf(mm, ml_s[w][g].x);
+    for (int w = 0; w < WAVES; ++w) mm = fmaxf(mm, ml_s[w][g].x);
     float4 oo = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int w = 0; w < DEC_WAVES; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
       const float a = mm == -INFINITY ? 0.0f : fast_exp2(ml_s[w][g].x - mm);      // (no row of the range weighs anything)
       const float4 x = *(const float4 *)&o_s[w][g][c];
       ll = fmaf(ml_s[w][g].y, a, ll);
@@ -566,16 +572,26 @@ static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, con
   // rows (294 MB of 789) 80, 75 and 80; of the eleven sequences above: 17.9, 16.8 and 17.5.
   const int64_t bytes = 2 * (int64_t)s.B * s.Hkv * s.capacity * D * (int64_t)sizeof(T);
   const int stream_level = bytes > MEMORY_CACHE_BYTES ? 2 : bytes > MEMORY_CACHE_BYTES / 32 ? 1 : 0;
-#define WKV_PARTIAL(KERNEL, E) \
-  hipLaunchKernelGGL(KERNEL, grid, dim3(DEC_THREADS), 0, stream, s, (const E *)q, (const E *)kc, (const E *)vc, n_valid, part)
+#define WKV_PARTIAL(KERNEL, E, NT) \
+  hipLaunchKernelGGL(KERNEL, grid, dim3(NT), 0, stream, s, (const E *)q, (const E *)kc, (const E *)vc, n_valid, part)
   if constexpr (sizeof(T) == 2) {   // bf16 / fp16: scores on the matrix pipe
     constexpr bool F16 = !__is_same(T, uint16_t);
-    if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2>), uint16_t);
-    else if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1>), uint16_t);
-    else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0>), uint16_t);
+    // Ranges of 128 rows by eight waves with a block each instead of four with two: half the arithmetic in a row, twice the states to
+    // merge.  Up to four heads it pays, us a layer with four / eight waves: 32q/8kv heads, one sequence of 4128 rows 9.65 / 9.46, two 12.15 /
+    // 12.42, three of 1000 to 3000 rows 11.33 / 10.31, eight of 1000 rows 11.23 / 11.13; 32q/32kv, six of 100 to 700 rows 12.98 / 12.37.  Six heads and
+    // more: 12q/2kv 7.82 / 8.12, eleven mixed sequences with 28q/4kv 14.5 / 16.0, 64q/8kv heads of 64 channels 13.4 / 14.9.
+    if constexpr (D == 128 && G <= 4)
+      if (s.chunk <= WIDE_THREADS / 64 * 16 && stream_level < 2) {
+        if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, WIDE_THREADS>), uint16_t, WIDE_THREADS);
+        else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, WIDE_THREADS>), uint16_t, WIDE_THREADS);
+        return;
+      }
+    if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS>), uint16_t, DEC_THREADS);
+    else if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS>), uint16_t, DEC_THREADS);
+    else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS>), uint16_t, DEC_THREADS);
   } else {
-    if (stream_level) WKV_PARTIAL((decode_partial_kernel<T, D, G, true>), T);
-    else WKV_PARTIAL((decode_partial_kernel<T, D, G, false>), T);
+    if (stream_level) WKV_PARTIAL((decode_partial_kernel<T, D, G, true>), T, DEC_THREADS);
+    else WKV_PARTIAL((decode_partial_kernel<T, D, G, false>), T, DEC_THREADS);
   }
 #undef WKV_PARTIAL
 }
