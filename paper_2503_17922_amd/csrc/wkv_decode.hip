@@ -462,6 +462,8 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
 // the outputs of the first ranges are requested together with the statistics that weigh them.  At 8 KV heads and
 // 33 ranges 3.3 us from first wave to last with shuffles through LDS and four ranges ahead (the 33rd took a round trip of its
 // own), 2.6 us with DPP reductions and six.
+// With few ranges one wave does it all and weighs them without LDS, a lane each (16 sequences of 500 rows 11.53 -> 11.28 us a layer; four
+// waves that each weigh up to 64 ranges for themselves, 9.55 -> 9.84 us for one sequence of 4128 rows: not so).
 template <typename T, int D, int NT>
 __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const T *__restrict__ q_new,
                                                                      const T *__restrict__ k_new, const T *__restrict__ v_new,
@@ -469,7 +471,8 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
                                                                      int32_t *n_valid, float *__restrict__ out) {
   constexpr int COLS = D / 4, GROUPS = NT / COLS, AHEAD = NT == 64 ? 4 : 6, WAVES = NT / 64;
   constexpr int E = Piece<T>::E, LPK = D / E;
-  __shared__ float wgt[NT];
+  constexpr bool FEW = NT == 64;
+  __shared__ float wgt[FEW ? 1 : NT];
   __shared__ __attribute__((aligned(16))) float acc_s[GROUPS][D];
   __shared__ float q_k[2];
   __shared__ float wave_m[WAVES], wave_l[WAVES];
@@ -485,9 +488,9 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
   float4 pre[AHEAD];
 #pragma unroll
   for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(grp + u * GROUPS, s.n_splits - 1) * s.G * COLS];
-  const bool last_wave = wave == WAVES - 1;       // this wave also takes q . k_new
+  const bool takes_dot = wave == WAVES - 1;       // this wave also takes q . k_new
   float dot = 0.0f;
-  if (last_wave && lane < LPK) {
+  if (takes_dot && lane < LPK) {
     float qf[E], kf[E];
     Piece<T>::unpack(*(const uint4 *)(q_new + hq * D + lane * E), qf);
     Piece<T>::unpack(*(const uint4 *)(k_new + (int64_t)bh * D + lane * E), kf);
@@ -504,38 +507,53 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
       else *(uint4 *)(v_cache + off) = *(const uint4 *)(v_new + (int64_t)bh * D + pc * E);
     }
   }
-  if (last_wave) {
-    dot = wave_sum(dot);
-    if (lane == 0) q_k[0] = dot * s.c1;
+  float logit, m, l, a, w_new, first;                   // first: m of range 0; NaN: the cache is full or its count is invalid
+  if (takes_dot) dot = wave_sum(dot) * s.c1;
+  if constexpr (FEW) {
+    logit = dot;
+    first = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ml.x), 0));
+    m = fmaxf(logit, wave_max(ml.x));
+    a = fast_exp2(ml.x - m);                            // a range without rows: 0
+    w_new = fast_exp2(logit - m);
+    l = w_new + wave_sum(ml.x == -INFINITY ? 0.0f : ml.y * a);
+  } else {
+    if (takes_dot && lane == 0) q_k[0] = dot;
+    m = wave_max(ml.x);
+    if (lane == 0) wave_m[wave] = m;
+    if (tid == 0) q_k[1] = ml.x;
+    __syncthreads();
+    logit = q_k[0];
+    first = q_k[1];
+    m = logit;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) m = fmaxf(m, wave_m[w]);
+    a = fast_exp2(ml.x - m);                            // a range without rows: 0
+    l = wave_sum(ml.x == -INFINITY ? 0.0f : ml.y * a);
+    if (tid < s.n_splits) wgt[tid] = a;
+    if (lane == 0) wave_l[wave] = l;
+    __syncthreads();
+    w_new = fast_exp2(logit - m);
+    l = w_new;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) l += wave_l[w];
   }
-  float m = wave_max(ml.x);
-  if (lane == 0) wave_m[wave] = m;
-  if (tid == 0) q_k[1] = ml.x;                          // NaN: the cache is full or its count is invalid
-  __syncthreads();
-  const float logit = q_k[0];
-  m = logit;
-#pragma unroll
-  for (int w = 0; w < WAVES; ++w) m = fmaxf(m, wave_m[w]);
-  const float a = fast_exp2(ml.x - m);                  // a range without rows: 0
-  float l = ml.x == -INFINITY ? 0.0f : ml.y * a;
-  if (tid < s.n_splits) wgt[tid] = a;
-  l = wave_sum(l);
-  if (lane == 0) wave_l[wave] = l;
-  __syncthreads();
-  const float w_new = fast_exp2(logit - m);
-  l = w_new;
-#pragma unroll
-  for (int w = 0; w < WAVES; ++w) l += wave_l[w];
 
   // (outputs of a range without rows are whatever memory held: skipped, not multiplied by zero)
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int sp = grp; sp < s.n_splits; sp += AHEAD * GROUPS) {
+  for (int sp0 = 0; sp0 < s.n_splits; sp0 += AHEAD * GROUPS) {          // (uniform: the weights come from other lanes)
+    const int sp = sp0 + grp;
+    float w[AHEAD];
 #pragma unroll
     for (int u = 0; u < AHEAD; ++u) {
-      const float w = sp + u * GROUPS < s.n_splits ? wgt[sp + u * GROUPS] : 0.0f;
-      if (w != 0.0f) { o.x = fmaf(pre[u].x, w, o.x); o.y = fmaf(pre[u].y, w, o.y); o.z = fmaf(pre[u].z, w, o.z); o.w = fmaf(pre[u].w, w, o.w); }
+      const int at = sp + u * GROUPS;
+      if constexpr (FEW) w[u] = __shfl(a, at);
+      else w[u] = at < s.n_splits ? wgt[at] : 0.0f;
+      if (at >= s.n_splits) w[u] = 0.0f;
     }
-    if (sp + AHEAD * GROUPS < s.n_splits)
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+      if (w[u] != 0.0f) { o.x = fmaf(pre[u].x, w[u], o.x); o.y = fmaf(pre[u].y, w[u], o.y); o.z = fmaf(pre[u].z, w[u], o.z); o.w = fmaf(pre[u].w, w[u], o.w); }
+    if (sp0 + AHEAD * GROUPS < s.n_splits)
 #pragma unroll
       for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(sp + (AHEAD + u) * GROUPS, s.n_splits - 1) * s.G * COLS];
   }
@@ -547,7 +565,7 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
     for (int i = 0; i < GROUPS; ++i) x += acc_s[i][c];
     const float v = Piece<T>::value(v_new + (int64_t)bh * D + c);
     x = fmaf(w_new, v, x) / l;
-    out[hq * D + c] = q_k[1] != q_k[1] ? q_k[1] : x;
+    out[hq * D + c] = first != first ? first : x;
   }
   if (g == 0 && tid == 0 && !s.keep_count) {
     const int n = n_valid[bh];
@@ -613,12 +631,12 @@ static hipError_t launch_decode_t(const DecodeShape &s, const void *q, const voi
   // a wave reads eight ranges (16 at 64 channels) in its first round trip: with no more than that, one wave a head
   static_assert(DEC_MAX_SPLITS <= DEC_THREADS, "one thread per range");
   const dim3 heads(s.B * s.Hkv, s.G);
-  if (s.n_splits <= 1024 / D)
-    hipLaunchKernelGGL((decode_combine_kernel<T, D, 64>), heads, dim3(64), 0, stream, s, (const T *)q, (const T *)kn, (const T *)vn,
-                       (T *)kc, (T *)vc, (const float *)part, n_valid, out);
-  else
-    hipLaunchKernelGGL((decode_combine_kernel<T, D, DEC_THREADS>), heads, dim3(DEC_THREADS), 0, stream, s, (const T *)q,
-                       (const T *)kn, (const T *)vn, (T *)kc, (T *)vc, (const float *)part, n_valid, out);
+#define WKV_COMBINE(NT) \
+  hipLaunchKernelGGL((decode_combine_kernel<T, D, NT>), heads, dim3(NT), 0, stream, s, (const T *)q, (const T *)kn, (const T *)vn, \
+                     (T *)kc, (T *)vc, (const float *)part, n_valid, out)
+  if (s.n_splits <= 1024 / D) WKV_COMBINE(64);
+  else WKV_COMBINE(DEC_THREADS);
+#undef WKV_COMBINE
   return hipGetLastError();
 }
 
