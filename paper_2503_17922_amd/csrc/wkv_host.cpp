@@ -303,8 +303,8 @@ wkv_status validate_decode(const wkv_decode_shape *p, Decode *out) {
   s.heads_magic = division_magic(s.B * s.Hkv); s.kv_magic = division_magic(s.Hkv);
   // Key ranges: about 1536 workgroups if every cache were full (six per compute unit; n_valid is not known
   // here, and in a batch of mixed lengths a good part of them finds nothing to do), of at least 128 rows (two
-  // blocks per wave: with one, the fixed cost and the merge outweigh the shorter chain), multiples of 64 rows (a
-  // block per wave).  Against 1024, 1280 and 2016 workgroups on 80 mixed batches of 2 to 64 (up to 1000, 4000 or 32000 rows, the
+  // blocks for each of four waves, or one for each of eight: with half of that the fixed cost and the merge outweigh the shorter chain),
+  // multiples of 64 rows (a block for each of four waves).  Against 1024, 1280 and 2016 workgroups on 80 mixed batches of 2 to 64 (up to 1000, 4000 or 32000 rows, the
   // shortest an eighth of the longest; 4, 8 and 32 KV heads): 6 %, 3 % slower and 1 % faster than 1536 in the mean; equal lengths the same.
   const int64_t rows = (int64_t)s.B * s.Hkv;
   constexpr int64_t total = 1536;

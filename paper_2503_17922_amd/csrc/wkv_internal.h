@@ -134,14 +134,16 @@ struct Workspace {
   size_t bytes;
 };
 
-// Selection and gather in one launch?  Up to 40 MB of compact cache: the workgroups that the device holds at once
+// Selection and gather in one launch?  Up to 40 MB of compact cache, 60 MB of one sequence: the workgroups that the device holds at once
 // (the selection is repeated in each) keep fewer rows in flight than the gather's own launch, which costs more than
-// the launch saves from there on (67 MB: 70.4 against 69.1 us a call, 34 MB: 45.9 against 47.3, 17 MB: 33.7 against 35.5).
-constexpr int64_t SMALL_BYTES = 40 << 20;
+// the launch saves from there on; sequences of their own lengths leave some of them idle sooner.  Whole calls in one launch / in two, one sequence:
+// 50 MB 53.2 / 54.5 and 52.8 / 54.0 us, 58 MB 58.7 / 59.6, 68 MB 66.4 / 67.0 and 56.3 / 54.9; batches of mixed lengths: 59 MB 77.0 / 74.4, 75 MB
+// 59.9 / 58.2; 34 MB 45.9 / 47.3, 17 MB 33.7 / 35.5 (either).
+constexpr int64_t SMALL_BYTES = 40 << 20, SMALL_BYTES_ONE = 60 << 20;
 inline bool selects_and_gathers(const Shape &s, int32_t n_groups, int32_t gamma) {
   const int64_t pairs = (int64_t)2 * n_groups * gamma * s.B * s.Hkv;
   return s.B <= SMALL_BATCH && n_groups <= SMALL_GROUPS && n_groups * gamma <= SMALL_LAYERS && s.nw_max <= SMALL_WINDOWS &&
-         pairs <= SMALL_WORKGROUPS && pairs * s.nkeep_max * s.d * elem_bytes(s.dtype) <= SMALL_BYTES;
+         pairs <= SMALL_WORKGROUPS && pairs * s.nkeep_max * s.d * elem_bytes(s.dtype) <= (s.B == 1 ? SMALL_BYTES_ONE : SMALL_BYTES);
 }
 
 // ---- host-side helpers (wkv_host.cpp) ---------------------------------------------------

@@ -17,9 +17,9 @@
 // A caller whose prefill attention kept the normalisers of the observation rows hands them
 // over; pass 1 and the fold are then skipped and the keys are read once.
 //
-// Both passes run on the matrix pipe: v_mfma_f32_16x16x32_bf16 / _f16 for 16-bit inputs, v_mfma_f32_16x16x4_f32
+// Both passes run on the matrix pipe: v_mfma_f32_32x32x16_bf16 / _f16 or _16x16x32 for 16-bit inputs, v_mfma_f32_16x16x4_f32
 // for fp32 inputs.  Every wave holds the query fragments of its row tiles in registers for the whole launch and
-// reads 16-key tiles from a ring in LDS that it fills itself, by DMA from global memory several tiles
+// reads tiles of 32 or 16 keys from a ring in LDS that it fills itself, by DMA from global memory several tiles
 // ahead: the waves of a workgroup do not synchronise in the loop, and nothing but the keys crosses LDS.
 #include "wkv_device.h"
 #include "wkv_pool.h"

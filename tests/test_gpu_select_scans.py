@@ -33,3 +33,16 @@ def test_top_k_by_window_count(nw, device):
             tok = np.concatenate([np.arange(w * win, min((w + 1) * win, L - w_obs)) for w in want] + [np.arange(L - w_obs, L)])
             assert int(nk[0, h]) == len(tok) and np.array_equal(ti[0, h, : len(tok)].cpu().numpy(), tok)
             assert bool((ti[0, h, len(tok):] == -1).all())
+
+
+@pytest.mark.parametrize("seq_len,k", [([9000], 476), ([9000], 477), ([5200, 4000], 156), ([5200, 4000], 157)])
+def test_compact_caches_around_the_limit_of_one_launch(seq_len, k, device):
+    # 60 MB (one sequence) and 40 MB (two) exactly, and a window more: one launch, and two
+    import wkv_synth as S
+    from tests.test_gpu_parity import run_and_check
+    n = len(seq_len)
+    nkeep = k * 8 + 32
+    limit = (60 if n == 1 else 40) << 20
+    assert (64 * n * nkeep * 256 <= limit) == (k in (476, 156)) and abs(64 * n * nkeep * 256 - limit) <= 64 * n * 8 * 256
+    w = S.scaled_workload(S.make_workload("c4"), name="limit", n_groups=1, gamma=4, seq_len=seq_len, win=[8] * n, top_p=[8] * n, k_windows=[k] + [k // 2] * (n - 1))
+    run_and_check(w, device, n_oracle=2, n_gather_cpu=1, stage_groups=[0])
