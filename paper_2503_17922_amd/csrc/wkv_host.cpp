@@ -174,6 +174,28 @@ static void plan_pass(const BatchParams &bp, int32_t B, int32_t drop, int32_t c,
   }
 }
 
+// Rows of a tile of the score passes.  32-row tiles take 15 % less time for the same logits (wkv_score.hip), but a wave's rows in
+// steps of 32.  Whole calls with 16- / with 32-row tiles, each on keys that the memory-side cache holds from the call before and on keys
+// that it does not, bf16:
+//   two row groups        always 32.  128 channels, 256 rows: 290 MB of keys 240, 241 / 213, 211 us, 540 MB 436, 438 / 397, 394; 64 channels, 224 rows,
+//                         290 MB 352, 349 / 285, 286.
+//   97 to 112 rows        16, as 32-row tiles make 128 of them: 128 channels, 17 MB 27.7, 29.2 / 28.5, 30.4; 101 MB 61.7, 65.7 / 63.4, 68.3; 201 MB
+//                         101, 108 / 104, 124; 64 channels, 201 MB 125, 128 / 123, 135; 290 MB 177, 176 / 181, 182.  Where little is computed 32 all the
+//                         same: 128 channels and at most 128 keys a workgroup, 4 MB 21.4, 22.6 / 20.8, 21.9; 64 channels up to HEAVY logits,
+//                         33 MB 39.7, 41.8 / 38.6, 40.8.
+//   at most 16 rows       32: 128 channels, 12 MB 19.6, 22.6 / 19.6, 21.9, 33 MB 26.6, 28.8 / 26.9, 29.0; 64 channels, 33 MB 29.4, 31.3 / 28.2, 30.3.
+//   other rows            32, but 16 on nontemporal streams of 128 channels, which are bound by power: 128 rows, 400 MB 186, 189 / 189, 194, 540 MB
+//                         259, 259 / 260, 262; 64 rows, 290 MB 132, 133 / 133, 133; 201 MB 92.8, 99.1 / 91.0, 98.2.  64 channels, 128 rows, 540 MB
+//                         330, 335 / 315, 319; 32 rows, 400 MB 181, 179 / 176, 174.
+constexpr int64_t HEAVY = (int64_t)3 << 24;       // logits of a call: 196608 a compute unit
+static int32_t score_tile(const Shape &s, const ScorePlan &pl, int64_t keys, bool two_groups) {
+  if (s.dtype == WKV_F32) return 16;
+  if (two_groups) return 32;
+  if (pl.m_pad != 112) return pl.nontemporal && s.d == 128 ? 16 : 32;
+  if (s.d == 64) return keys * pl.m_pad > HEAVY ? 16 : 32;
+  return *std::max_element(pl.pass[0].chunk, pl.pass[0].chunk + s.B) > 2 ? 16 : 32;
+}
+
 ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   ScorePlan pl;
   pl.m_pad = (s.M + 15) / 16 * 16;
@@ -201,6 +223,7 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   // of their own: three ragged f16 sequences, 224 rows (17 MB of keys a group) 80.3 / 75.5 us; 16384 tokens, 256 rows, one group
   // (34 MB) 53.9 / 51.7 us, 64 channels, four groups (67 MB) 92.0 / 85.1 us; 134 MB 118.0 / 117.0 us; 268 MB 289.6 / 292.6 us.
   pl.own_rings = keys * s.d * elem_bytes(s.dtype) <= MEMORY_CACHE_BYTES / 2;
+  pl.tile = score_tile(s, pl, keys, pl.m_pad > wave_rows);
   pl.n_chunks1 = 0;
   for (int32_t b = 0; b < s.B; ++b) pl.n_chunks1 = std::max(pl.n_chunks1, pl.pass[0].first[b + 1] - pl.pass[0].first[b]);
   // every pass-2 workgroup re-reads the partials of its rows when it folds them itself: 64 KB at 128 rows and 64

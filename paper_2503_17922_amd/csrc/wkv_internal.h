@@ -97,7 +97,8 @@ struct ScorePlan {
   PassPlan pass[2];            // statistics, scores
   int32_t n_chunks1;           // most workgroups of a sequence in the statistics pass
   int32_t m_pad;               // rows padded to a multiple of 16
-  bool nontemporal;            // a long stream: the key loads put nothing into the memory-side cache, 16-bit inputs take 16-row tiles
+  int32_t tile;                // rows of a tile: 32 or 16 (fp32: 16)
+  bool nontemporal;            // a long stream: the key loads put nothing into the memory-side cache
   bool own_rings;              // with two row groups of 16-bit inputs every wave fetches its key tiles itself
   bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
 };

@@ -116,7 +116,7 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 // the two passes
 // =========================================================================================
 // A tile of TS x TS logits takes TS rows of each operand, 64 lanes times 16 bytes per step: lane l holds row l % TS, piece l / TS
-// of the step.  TS = 32 (v_mfma_f32_32x32x16) or, on long streams and for fp32, 16 (v_mfma_f32_16x16x32, _16x16x4_f32).  In the result lane l
+// of the step.  TS = 32 (v_mfma_f32_32x32x16) or 16 (v_mfma_f32_16x16x32, fp32: _16x16x4_f32; score_tile says which).  In the result lane l
 // holds column l % TS, rows tile_row(e).  Both operands have this layout, so which of them is A is a free choice per pass:
 //   PASS 1 (stats)   keys as A: a lane gets TS * TS / 64 keys of ONE query row per row tile, so the row
 //                    statistics are in-lane accumulations (RT of them), merged once per chunk.
@@ -144,17 +144,14 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, c
 // (it does not with zeros).  So a pass that lasts and also streams keys is bound by power: the 32K-token model (8 groups, 128
 // rows) takes 90 + 90 us from first wave to last, 84-86 without the arithmetic, 69 without the loads, and with 32-row tiles the clock is
 // 1.8-2.0 instead of 2.1-2.2 GHz: the same time, 4 % more for the second pass of the handed-over normalisers where the chip is warm.  Eight
-// waves in one workgroup, or paced by a barrier every 1 to 8 tiles so that none runs ahead: 105-125 us.  32-row tiles are for what
-// ends sooner: streams of at most 256 MB (plan_score).  Whole calls with 16- and with 32-row tiles: 4096 tokens 25.6 / 24.5 us, 16384 tokens 45.9 / 44.3,
-// 16381 tokens in 8 groups with 256 rows (268 MB) 282 / 266, ragged f16 sequences with 224 rows 71.6 / 71.0.
+// waves in one workgroup, or paced by a barrier every 1 to 8 tiles so that none runs ahead: 105-125 us.  With two row groups the
+// arithmetic is what takes longest, and 32-row tiles pay however long the stream is (score_tile has both sides).
 // A workgroup's start, in microseconds for 4096 tokens (second pass of the 32K model): arguments and the first key requests 1.4 (2.4), queries 0.8
 // (1.5), partials to normalisers 0.8 (1.2), queries to registers 0.6 (0.7).  Requests are issued at 20 bytes a cycle and compute unit, so the 32 KB of queries cost what as many
 // keys cost.  The fold's requests stand before the queries', not behind them: 1.8 (3.6) us for the fold before.  Requested by whole rows instead
 // of fragments, the queries of 256 rows take 1.9 instead of 2.6 us.
 constexpr int score_slots(int row_groups) { return row_groups == 4 ? 2 : 4; }         // key tile slots of a workgroup
 constexpr int score_threads(int row_groups) { return 64 * row_groups * score_slots(row_groups); }
-// Rows of a tile.  Long key streams (NT_LOADS) take the smaller ones: see "What bounds it".
-constexpr int tile_size(int dt, bool nt_loads) { return dt == DT_F32 || nt_loads ? 16 : 32; }
 
 template <int D, int DT, int TS_, int RT, int HV, bool OWN_RINGS>
 struct ScoreConfig {
@@ -217,17 +214,17 @@ __device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *p) {
 
 // NT_LOADS: the keys are not put into the memory-side cache (see plan_score).  Kernels of their own, as a branch at every fetch
 // costs small calls 1 %.
-// WAVE_ROWS: rows a wave takes, in RT tiles.
-template <int D, int DT, int WAVE_ROWS, int HV, int PASS, bool NT_LOADS, bool OWN_RINGS>
+// TS: rows of a tile (see score_tile in wkv_host.cpp).  WAVE_ROWS: rows a wave takes, in RT tiles.
+template <int D, int DT, int WAVE_ROWS, int HV, int PASS, int TS, bool NT_LOADS, bool OWN_RINGS>
 __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, BatchParams bp, GroupPtrs gp, ScorePlan pl,
                                                                                  float2 *__restrict__ partials,
                                                                                  const float *__restrict__ lse_g,
                                                                                  float *__restrict__ t_out,
                                                                                  float *__restrict__ s_pool,
                                                                                  const uint32_t *__restrict__ only_if) {
-  constexpr int RT = WAVE_ROWS / tile_size(DT, NT_LOADS);
-  using C = ScoreConfig<D, DT, tile_size(DT, NT_LOADS), RT, HV, OWN_RINGS>;
-  constexpr int KS = C::KS, KW = C::KW, NT = C::NT, NS = C::NS, TS = C::TS, E = C::E, ROWS = HV * RT * TS;
+  constexpr int RT = WAVE_ROWS / TS;
+  using C = ScoreConfig<D, DT, TS, RT, HV, OWN_RINGS>;
+  constexpr int KS = C::KS, KW = C::KW, NT = C::NT, NS = C::NS, E = C::E, ROWS = HV * RT * TS;
   __shared__ __attribute__((aligned(1024))) char ring[C::RING];
   __shared__ __attribute__((aligned(16))) float t_s[PASS == 2 ? HV * C::T_S : 4];     // token scores of a segment
   __shared__ __attribute__((aligned(16))) float lse_s[PASS == 2 ? ROWS : 4];
@@ -575,7 +572,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
 // =========================================================================================
 // launch
 // =========================================================================================
-template <int D, int DT, int WAVE_ROWS, int HV, bool NT_LOADS, bool OWN_RINGS = false>
+template <int D, int DT, int WAVE_ROWS, int HV, int TS, bool NT_LOADS, bool OWN_RINGS = false>
 static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
                                 bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
                                 hipEvent_t mid, const uint32_t *only_if) {
@@ -586,7 +583,7 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
     if (s.t_stride <= 0) return hipSuccess;
   } else {
     dim3 g1(pl.pass[0].first[s.B], s.Hkv, n_groups);
-    hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 1, NT_LOADS, OWN_RINGS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
+    hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 1, TS, NT_LOADS, OWN_RINGS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
@@ -598,7 +595,7 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
   ScorePlan pl2 = pl;
   if (have_lse) pl2.fold_in_pass2 = false;
   dim3 g2(pl.pass[1].first[s.B], s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 2, NT_LOADS, OWN_RINGS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
+  hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 2, TS, NT_LOADS, OWN_RINGS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
   return hipGetLastError();
 }
 
@@ -606,22 +603,26 @@ template <int D, int DT>
 static hipError_t launch_rows(const Shape &s, const BatchParams &bp, const ScorePlan &pl, const GroupPtrs &gp, int32_t n_groups,
                               bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
                               hipEvent_t mid, const uint32_t *only_if) {
-  // Rows per wave: the counts of the usual head layouts (w_obs of 8 to 32 with 1 to 8 query heads per KV head) are met exactly where
-  // the tiles have 16 rows, in steps of 32 where they have 32; a wave holds 128 at most, 64 of fp32 with 128 channels.
+  // Rows per wave: the counts of the usual head layouts (w_obs of 8 to 32 with 1 to 8 query heads per KV head) in steps of 32, those
+  // of 16 where it pays (score_tile); a wave holds 128 at most, 64 of fp32 with 128 channels.
 #define WKV_PASSES(RR, HH, ...) \
   if (s.M <= RR * HH) return launch_passes<D, DT, RR, HH, __VA_ARGS__>(s, bp, pl, gp, n_groups, have_lse, partials, lse, t_out, s_pool, stream, mid, only_if);
-#define WKV_ROWS(RR, HH) if (pl.nontemporal) { WKV_PASSES(RR, HH, true) } else { WKV_PASSES(RR, HH, false) }
+#define WKV_ROWS(RR, HH) if (pl.nontemporal) { WKV_PASSES(RR, HH, 16, true) } else { WKV_PASSES(RR, HH, 16, false) }
   if constexpr (DT == DT_F32 && D == 128) {
     WKV_ROWS(16, 1) WKV_ROWS(32, 1) WKV_ROWS(64, 1) WKV_ROWS(64, 2) WKV_ROWS(64, 4)
   } else if constexpr (DT == DT_F32) {
     WKV_ROWS(16, 1) WKV_ROWS(32, 1) WKV_ROWS(64, 1) WKV_ROWS(96, 1) WKV_ROWS(112, 1) WKV_ROWS(128, 1) WKV_ROWS(96, 2) WKV_ROWS(112, 2) WKV_ROWS(128, 2)
+  } else if (pl.tile == 16) {
+    if (!pl.nontemporal) { WKV_PASSES(112, 1, 16, false) }
+    else if constexpr (D == 64) { WKV_PASSES(112, 1, 16, true) }
+    else { WKV_PASSES(16, 1, 16, true) WKV_PASSES(32, 1, 16, true) WKV_PASSES(64, 1, 16, true) WKV_PASSES(96, 1, 16, true) WKV_PASSES(112, 1, 16, true) WKV_PASSES(128, 1, 16, true) }
   } else if (pl.nontemporal) {
-    WKV_PASSES(16, 1, true) WKV_PASSES(32, 1, true) WKV_PASSES(64, 1, true) WKV_PASSES(96, 1, true) WKV_PASSES(112, 1, true) WKV_PASSES(128, 1, true)
-    WKV_PASSES(96, 2, true) WKV_PASSES(112, 2, true) WKV_PASSES(128, 2, true)
+    if constexpr (D == 64) { WKV_PASSES(32, 1, 32, true) WKV_PASSES(64, 1, 32, true) WKV_PASSES(96, 1, 32, true) WKV_PASSES(128, 1, 32, true) }
+    WKV_PASSES(96, 2, 32, true) WKV_PASSES(128, 2, 32, true)
   } else {
-    WKV_PASSES(32, 1, false) WKV_PASSES(64, 1, false) WKV_PASSES(96, 1, false) WKV_PASSES(128, 1, false)
-    if (pl.own_rings) { WKV_PASSES(96, 2, false, true) WKV_PASSES(128, 2, false, true) }
-    WKV_PASSES(96, 2, false) WKV_PASSES(128, 2, false)
+    WKV_PASSES(32, 1, 32, false) WKV_PASSES(64, 1, 32, false) WKV_PASSES(96, 1, 32, false) WKV_PASSES(128, 1, 32, false)
+    if (pl.own_rings) { WKV_PASSES(96, 2, 32, false, true) WKV_PASSES(128, 2, 32, false, true) }
+    WKV_PASSES(96, 2, 32, false) WKV_PASSES(128, 2, 32, false)
   }
 #undef WKV_ROWS
 #undef WKV_PASSES
