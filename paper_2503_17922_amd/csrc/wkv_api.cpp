@@ -128,7 +128,7 @@ wkv_status wkv_gather_group(const wkv_problem *problem, int32_t n_layers, const 
   st = fill_layers(n_layers, k_layers, v_layers, k_out_layers, v_out_layers, &lp);
   if (st != WKV_OK) return st;
   // one group: every layer reads the same index rows (gamma = n_layers)
-  hipError_t e = launch_gather(pr.shape, lp, n_layers, n_layers, tok_idx, n_keep, (hipStream_t)hip_stream);
+  hipError_t e = launch_gather(pr.shape, pr.bp, lp, n_layers, n_layers, tok_idx, n_keep, (hipStream_t)hip_stream);
   return e == hipSuccess ? WKV_OK : hip_fail(e, "wkv_gather_group launch");
 }
 
@@ -218,7 +218,7 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
   e = launch_topk(pr.shape, pr.bp, gk, n_groups, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);
   if (e != hipSuccess) return hip_fail(e, "select launch");
   WKV_MARK(3)
-  e = launch_gather(pr.shape, lp, n_layers, gamma, tok_idx_out, n_keep_out, stream);
+  e = launch_gather(pr.shape, pr.bp, lp, n_layers, gamma, tok_idx_out, n_keep_out, stream);
   if (e != hipSuccess) return hip_fail(e, "gather launch");
   WKV_MARK(4)
 #undef WKV_MARK

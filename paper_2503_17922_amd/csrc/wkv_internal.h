@@ -147,6 +147,30 @@ inline bool selects_and_gathers(const Shape &s, int32_t n_groups, int32_t gamma)
          pairs <= SMALL_WORKGROUPS && pairs * s.nkeep_max * s.d * elem_bytes(s.dtype) <= (s.B == 1 ? SMALL_BYTES_ONE : SMALL_BYTES);
 }
 
+// Workgroups over the rows of a compact cache, two pieces of `rows` rows each, `apart` pieces from one to the other; the ones from
+// `last` on share what is left, last_apart pieces apart: all but the very last hold two pieces.
+struct GatherGrid {
+  int32_t workgroups, last, last_apart;
+};
+inline GatherGrid gather_grid(int32_t nkeep_max, int32_t rows, int32_t apart) {
+  const int32_t pieces = (nkeep_max + rows - 1) / rows, last = pieces / (2 * apart) * apart, last_apart = (pieces % (2 * apart) + 1) / 2;
+  return {last + last_apart, last, last_apart};
+}
+
+// Threads of a gather's workgroup: single waves, unless much of the compact cache lies past the sequences' budgets; the workgroups
+// there zero it or find nothing to do, and each of them costs a start.  By 256 threads / one wave / as chosen, batches of 4 to 16, us:
+//   past the budgets left alone, budgets of less than 0.4 of the room in the mean: 128 threads.  0.16 25.5 / 34.8 / 22.0, 0.21 21.1 / 26.2 / 19.1, 0.29
+//   15.4 / 16.1 / 14.0, 0.33 20.2 / 22.7 / 19.7; from there on 0.41 222.7 / 212.7 / 216.2, 0.48 162.1 / 129.7 / 132.4, 0.56 162.8 / 146.0 / 147.7.
+//   zeroed, less than 3/8, rows of 128 bytes less than a third: 256 threads.  0.15 121.0 / 134.9, 0.22 217 / 230, 0.25 70.1 / 71.6, 0.32 66.8 / 73.8, 0.36
+//   57.0 / 61.9; from there on 0.46 213.5 / 192.5, 0.54 217.4 / 199.6; rows of 128 bytes 0.24 53.0 / 55.4, 0.36 85.7 / 66.4, 0.38 156.4 / 124.3.
+inline int32_t gather_threads(const Shape &s, const BatchParams &bp) {
+  int64_t kept = 0;
+  for (int32_t b = 0; b < s.B; ++b) kept += bp.seq[b].k * bp.seq[b].win + s.w_obs;
+  const int64_t room = (int64_t)s.B * s.nkeep_max;
+  if (s.fill_padding) return (s.d * elem_bytes(s.dtype) > 128 ? 8 * kept < 3 * room : 3 * kept < room) ? 256 : 64;
+  return 5 * kept < 2 * room ? 128 : 64;
+}
+
 // ---- host-side helpers (wkv_host.cpp) ---------------------------------------------------
 void set_error(const char *fmt, ...);
 wkv_status validate(const wkv_problem *p, wkv_dims *dims);
@@ -174,7 +198,7 @@ hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, 
 // The same, and the rows of the layers `lp`, gamma per group, in one launch (see selects_and_gathers).
 hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, const GroupK &gk, const LayerPtrs &lp, int32_t n_groups, int32_t gamma,
                                 const float *sc, int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream);
-hipError_t launch_gather(const Shape &s, const LayerPtrs &lp, int32_t n_layers, int32_t gamma,
+hipError_t launch_gather(const Shape &s, const BatchParams &bp, const LayerPtrs &lp, int32_t n_layers, int32_t gamma,
                          const int32_t *tok_idx, const int32_t *n_keep, hipStream_t stream);
 
 hipError_t launch_jaccard(const Shape &s, int32_t n_sets, const int32_t *tok_idx, const int32_t *n_keep, float *out,
