@@ -202,9 +202,13 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   const int64_t rows_per_seq = (int64_t)s.Hkv * n_groups;
   // Workgroups that the device holds at a time (256 compute units): two per unit with one row group (half the
   // LDS and the registers), else one.  Up to 1024 keys per compute unit one is better all the same: the
-  // shorter chain of a smaller chunk does not make up for the second prologue and the larger fold (16384
-  // tokens, 8 KV heads: passes of 14.0 + 14.5 us with one, 15.5 + 18.5 us with two; 32768 tokens: 19.6 + 19.5 against
-  // 20.3 + 23.1 us; from 65536 on the same).
+  // shorter chain of a smaller chunk does not make up for the second prologue and the larger fold.  Whole calls with one / with two, keys held / not held
+  // by the memory-side cache, 16-bit, thousands of keys:
+  //   128 channels, 128 rows   131 33.9 / 37.3, 34.0 / 37.6 us; 262 50.3 / 54.7, 53.9 / 58.5; 1300 182 / 167, 2097 270 / 243; mixed lengths 733 117.7 / 116.3,
+  //                            125.0 / 122.5, 1011 150.7 / 147.6
+  //   64 channels, 128 rows    131 29.7 / 30.6; 262 41.6 / 43.7; 393 48.7 / 48.3, 50.4 / 50.6; 524 58.2 / 56.8; 1049 96.3 / 86.1
+  // (Between 1024 and 2560 keys per unit one still takes less with 128 channels or few rows: 128 rows 524 73.1 / 79.5, 64 rows 67.3 / 70.4, 64 channels and
+  // 64 rows 45.0 / 48.1.)
   const int32_t wave_rows = s.dtype == WKV_F32 && s.d == 128 ? 64 : 128;
   int64_t keys = 0;
   for (int32_t b = 0; b < s.B; ++b) keys += bp.seq[b].L * rows_per_seq;
@@ -213,16 +217,20 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   plan_pass(bp, s.B, 0, pick_chunk(bp, s.B, rows_per_seq, 0, shortest, longest, slots), &pl.pass[0]);
   plan_pass(bp, s.B, s.w_obs, pick_chunk(bp, s.B, rows_per_seq, s.w_obs, shortest, longest, slots), &pl.pass[1]);
   // Keys that the memory-side cache holds until the second pass are better left there; a larger stream reads
-  // faster past it.  One layer of 32768 tokens a group, 8 KV heads, whole call: 1 to 3 groups (67 to 201 MB) 57.5, 87.8, 116.5 us
-  // with plain loads, 57.6, 87.9, 115.8 with nontemporal ones, 6 groups (403 MB) 206.2 and 201.1; the 32K model's passes (537
-  // MB) 390 and 370 us; 16384 tokens and four layers 45.9 and 48.1 us; 256 softmax rows, 134 MB 118.8 and 123.0 us.  fp32, 32 rows:
-  // 134 MB 74.9 and 79.0, 335 MB 170.3 and 166.9, 1.07 GB 503 and 445 us; 128 rows and more wait for the matrix pipe, 1 GB 1182 and 1178.
+  // faster past it.  Whole calls with plain / nontemporal loads, keys held / not held from the call before: 128 rows of 128 channels, 192 MB 104 / 112, 113 / 113 us,
+  // 254 MB 129 / 144, 139 / 144, 320 MB 162 / 164, 170 / 165, 384 MB 196 / 192, 201 / 192; 64 rows, 254 MB 119 / 128, 128 / 129, 320 MB 146 / 146, 153 / 147;
+  // 256 rows, 254 MB 195 / 200, 200 / 201, 320 MB 256 / 253, 257 / 254; 64 channels, 128 rows, 254 MB 150 / 166, 158 / 161, 384 MB 232 / 235, 231 / 235.  fp32, 32 rows:
+  // 134 MB 74.9 / 79.0, 335 MB 170.3 / 166.9, 1.07 GB 503 / 445; 128 rows and more wait for the matrix pipe, 1 GB 1182 / 1178.
   pl.nontemporal = keys * s.d * elem_bytes(s.dtype) > MEMORY_CACHE_BYTES;
   // Key tiles fetched twice, once per row group, against a barrier per tile: worth it while a chunk is short enough for
-  // the two waves to stay together and the cache has room for what they lose.  Whole calls with a barrier / with rings
-  // of their own: three ragged f16 sequences, 224 rows (17 MB of keys a group) 80.3 / 75.5 us; 16384 tokens, 256 rows, one group
-  // (34 MB) 53.9 / 51.7 us, 64 channels, four groups (67 MB) 92.0 / 85.1 us; 134 MB 118.0 / 117.0 us; 268 MB 289.6 / 292.6 us.
-  pl.own_rings = keys * s.d * elem_bytes(s.dtype) <= MEMORY_CACHE_BYTES / 2;
+  // the two waves to stay together and the cache has room for what they lose.  Whole calls with a barrier /
+  // with rings of their own, keys held / not held by the memory-side cache from the call before:
+  //   128 channels, to 192 rows    never: 8 MB 22.9 / 23.2, 23.8 / 24.5 us, 32 MB 40.6 / 41.9, 41.0 / 42.2, 64 MB 57.6 / 58.2, 61.5 / 63.2, 128 MB 90.4 / 97.2, 97.0 / 108.4
+  //   more rows                    19 MB 36.7 / 35.3, 64 MB 65.9 / 64.1, 70.6 / 70.7, 109 MB 95.8 / 92.9, 101.5 / 101.7, 128 MB 106.3 / 106.0, 114.3 / 121.1
+  //   64 channels                  16 MB 37.3 / 35.6, 96 MB 99.3 / 91.0, 102.3 / 97.7, 160 MB 164.3 / 159.6, 170.3 / 172.7 and 150.5 / 139.5, 156.6 / 150.7, 192 MB 189.7 /
+  //                                179.2, 193.4 / 184.4, 240 MB 197.4 / 194.2, 204.9 / 211.4
+  const int64_t bytes = keys * s.d * elem_bytes(s.dtype);
+  pl.own_rings = s.d == 64 ? bytes <= MEMORY_CACHE_BYTES * 3 / 4 : pl.m_pad > 192 && bytes <= MEMORY_CACHE_BYTES * 7 / 16;
   pl.tile = score_tile(s, pl, keys, pl.m_pad > wave_rows);
   pl.n_chunks1 = 0;
   for (int32_t b = 0; b < s.B; ++b) pl.n_chunks1 = std::max(pl.n_chunks1, pl.pass[0].first[b + 1] - pl.pass[0].first[b]);
