@@ -22,7 +22,8 @@ def _w(**kw):
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("q_heads,w_obs", [(2, 5), (2, 32), (4, 32), (6, 32), (14, 16), (8, 32), (12, 32), (14, 32), (16, 32)])
 def test_row_tiles(dtype, d, q_heads, w_obs, device):
-    # 5 .. 256 softmax rows on two KV heads: one to eight row tiles a wave, one, two and four row groups
+    # 5 .. 256 softmax rows on two KV heads: one to four tiles of 32 rows a wave and one or two row groups with 16-bit inputs, one to eight
+    # tiles of 16 rows and one, two or four groups with fp32 (16-row tiles of 16-bit inputs: test_gpu_score_streams)
     run_and_check(_w(dtype=dtype, head_dim=d, n_q_heads=q_heads, w_obs=w_obs, seq_len=[901, 430], win=[24, 8], top_p=[9, 8], k_windows=[7, 20]), device)
 
 
@@ -40,21 +41,41 @@ def test_windows_across_segments(win, top_p, device):
     run_and_check(w, device, n_oracle=5, n_gather_cpu=2, stage_groups=[1])
 
 
-def test_key_rows_too_far_apart_for_32_bit_offsets(device):
-    w = _w(w_obs=8, seq_len=[30], win=[4], top_p=[3], k_windows=[2], n_kv_heads=2, n_q_heads=8)
+def _compress_far_apart(w, device, stride):
+    """Compresses ``w`` with ``stride`` elements from token to token, the same keys and values for all groups (the storage of
+    sequences and heads lies between two tokens), and compares with contiguous caches."""
+    B, H, L, d, n = w.batch, w.n_kv_heads, max(w.seq_len), w.head_dim, w.n_groups
+    assert B * H * d <= stride and w.gamma == 1
+    near = 0.05 * torch.randn((B, H, L, d), dtype=torch.float32, device=device, generator=torch.Generator(device=device).manual_seed(w.seed))
+    near = near.to(torch.bfloat16)
+    flat = torch.zeros(stride * (L - 1) + B * H * d, dtype=torch.bfloat16, device=device)
+    far = flat.as_strided((B, H, L, d), (H * d, d, stride, 1))
+    far.copy_(near)
     st = P.DeviceState(w, device)
-    st.compress()
-    stride = (1 << 26) + 512                               # elements between tokens: 16 of them span more than 2 GiB
-    flat = torch.zeros(stride * 29 + 512, dtype=torch.bfloat16, device=device)
-    far = flat.as_strided((1, 2, 30, 128), (256, 128, stride, 1))
-    k, v = far, far
-    problem = P.make_problem(w, kv_strides=(256, 128, stride))
-    k.copy_(st.k[0])
-    wi, ti, nk = torch.empty_like(st.win_idx), torch.empty_like(st.tok_idx), torch.empty_like(st.n_keep)
-    ko, vo = torch.empty_like(st.k_out[0]), torch.empty_like(st.v_out[0])
-    W.wkv_compress_groups(problem, 1, 1, st.q, None, [k], [v], [ko], [vo], wi, ti, nk, st.workspace)
-    torch.cuda.synchronize()
-    assert torch.equal(wi, st.win_idx) and torch.equal(ti, st.tok_idx) and torch.equal(ko, st.k_out[0]) and torch.equal(vo, st.k_out[0])
+    outs = []
+    for kv, strides in ((near, None), (far, (H * d, d, stride))):
+        problem = P.make_problem(w, kv_strides=strides) if strides else P.make_problem(w)
+        wi, ti, nk = (torch.full_like(t, -7) for t in (st.win_idx, st.tok_idx, st.n_keep))
+        ko, vo = [torch.zeros_like(t) for t in st.k_out], [torch.zeros_like(t) for t in st.v_out]
+        W.wkv_compress_groups(problem, n, 1, st.q, None, [kv] * n, [kv] * n, ko, vo, wi, ti, nk, st.workspace)
+        torch.cuda.synchronize()
+        outs.append([wi, ti, nk, *ko, *vo])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+# a tile's rows lie within 32-bit offsets of its 16 rows while 16 of them span less than 2 GiB: from 2^26 elements of two bytes on they do not
+@pytest.mark.parametrize("stride", [(1 << 26) + 512, 1 << 26, (1 << 26) - 8])
+def test_key_rows_far_apart(stride, device):
+    # whole 32-row tiles and the tail of one
+    _compress_far_apart(_w(w_obs=8, seq_len=[70], win=[4], top_p=[3], k_windows=[5]), device, stride)
+
+
+def test_key_rows_far_apart_in_shared_tiles(device):
+    # two row groups of up to 192 rows fetch a tile of 32 rows together, and the offsets of the second reach over 31 rows: nearly 4 GiB
+    B, n, stride = 64, 4, (1 << 26) - 8
+    w = _w(n_groups=n, n_q_heads=20, w_obs=31, n_kv_heads=4, seq_len=[70] * B, win=[4] * B, top_p=[3] * B, k_windows=[5] * B)
+    _compress_far_apart(w, device, stride)
 
 
 @pytest.mark.parametrize("n_groups", [3, 5, 8])
