@@ -401,7 +401,9 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
     Block x, next;
     load_block(x, blk);
     if constexpr (PAIRS) {
-      load_block(next, blk + WAVES);           // (past the end: the last row again)
+      // (past the end: the last row again, which the chip has at hand.  Around a branch instead: one sequence of 4128 rows, 64q/8kv heads 10.30 ->
+      // 10.66 us a layer, eleven mixed with 12q/2kv 12.03 -> 12.85, sixteen of 70 rows 8.60 -> 8.83, 64 of 4128 rows 167.4 -> 168.7)
+      load_block(next, blk + WAVES);
       __builtin_amdgcn_sched_barrier(0);       // both are requested before the first is looked at
       for (bool more = c0 + (blk + WAVES) * 16 < cend;; more = false) {            // (one copy of the code, which every launch fetches anew)
         attend(x, blk);
@@ -409,7 +411,7 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
         blk += WAVES;
         x = next;
       }
-      __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), as it is by now: else the compiler waits for the queries among the first requests
+      __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), reached by now but for rows requested past the end; else the compiler waits for the queries among the first requests
     } else {
       attend(x, blk);
     }
@@ -595,18 +597,25 @@ static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, con
   if constexpr (sizeof(T) == 2) {   // bf16 / fp16: scores on the matrix pipe
     constexpr bool F16 = !__is_same(T, uint16_t);
     // Ranges of 128 rows by eight waves with a block each instead of four with two: half the arithmetic in a row, twice the states to
-    // merge.  Up to four heads it pays, us a layer with four / eight waves: 32q/8kv heads, one sequence of 4128 rows 9.65 / 9.46, two 12.15 /
-    // 12.42, three of 1000 to 3000 rows 11.33 / 10.31, eight of 1000 rows 11.23 / 11.13; 32q/32kv, six of 100 to 700 rows 12.98 / 12.37.  Six heads and
-    // more: 12q/2kv 7.82 / 8.12, eleven mixed sequences with 28q/4kv 14.5 / 16.0, 64q/8kv heads of 64 channels 13.4 / 14.9.
-    if constexpr (D == 128 && G <= 4)
+    // merge; the device holds 512 such workgroups, 768 of four waves.  With 128 channels and up to four heads it pays for one sequence and where many of
+    // the workgroups find no rows, as in batches of mixed lengths, which the host cannot tell from equal ones.  us a layer with four / eight
+    // waves (with one block ahead): 32q/8kv heads, one sequence of 4128 rows 9.18 / 8.97 (10.35), 6000 10.55 / 10.68 (12.13); three of 1000 to 3000 rows 11.28 / 10.25
+    // (13.05), four of 500 to 3000 11.41 / 10.23 (13.17); 32q/32kv, six of 100 to 700 12.50 / 11.94 (14.72).  It loses where more than 512 have rows: two of 4128
+    // 11.55 / 11.76 (13.59), three 13.85 / 14.97 (15.52); eight of 1000 rows, 512 workgroups, 11.15 / 11.05 (12.51).  64 channels: one of 4128 rows 8.19 / 8.08, two 9.02 /
+    // 9.29, three mixed 9.27 / 9.55, 32q/32kv six mixed 9.47 / 9.65.  Six heads and more: 12q/2kv 7.82 / 8.12, eleven mixed sequences with 28q/4kv 14.5 /
+    // 16.0, 64q/8kv heads of 64 channels 13.4 / 14.9.
+    constexpr bool WIDE = D == 128 && G <= 4;
+    if constexpr (WIDE)
       if (s.chunk <= WIDE_THREADS / 64 * 16 && stream_level < 2) {
         if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, WIDE_THREADS>), uint16_t, WIDE_THREADS);
         else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, WIDE_THREADS>), uint16_t, WIDE_THREADS);
         return;
       }
+    // (longer ranges than those are of caches that stream: as many as there can be of a cache, 128 rows each, are 16 MB)
+    static_assert(!WIDE || (int64_t)DEC_MAX_SPLITS * 128 * 2 * D * (int64_t)sizeof(T) > MEMORY_CACHE_BYTES / 32, "plain loads");
     if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS>), uint16_t, DEC_THREADS);
-    else if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS>), uint16_t, DEC_THREADS);
-    else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS>), uint16_t, DEC_THREADS);
+    else if (WIDE || stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS>), uint16_t, DEC_THREADS);
+    else if constexpr (!WIDE) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS>), uint16_t, DEC_THREADS);
   } else {
     if (stream_level) WKV_PARTIAL((decode_partial_kernel<T, D, G, true>), T, DEC_THREADS);
     else WKV_PARTIAL((decode_partial_kernel<T, D, G, false>), T, DEC_THREADS);

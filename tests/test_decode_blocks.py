@@ -1,5 +1,5 @@
-"""The decode step's blocks of 16 rows, taken two at a time by four waves: row counts around the ends of single and paired blocks in
-ranges of one, two and three pairs a wave; and the divisions by multiplication that find a workgroup's head."""
+"""The decode step's blocks of 16 rows: row counts around the ends of single and paired blocks, in ranges of one block for each of eight
+waves and of 1 to 9 pairs for each of four; and the divisions by multiplication that find a workgroup's head."""
 import os
 import subprocess
 
@@ -25,9 +25,14 @@ def test_divisions_by_multiplication(tmp_path):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,G,d", [("bf16", 4, 128), ("f16", 8, 128), ("f16", 2, 64)])
-@pytest.mark.parametrize("cap", [130, 770, 2300])            # 768 caches: ranges of 128, 448 and 1152 rows
-def test_pairs_of_blocks(dtype, G, d, cap, device):
-    B, H, tdt = 96, 8, {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+@pytest.mark.parametrize("B,cap,ranges", [
+    (96, 130, 2),           # ranges of 128 rows: a block for each of eight waves with 4 heads of 128 channels, else a pair for each of four
+    (40, 770, 4),           # 256 rows: two pairs a wave; with 128 channels 126 MB, of which the values are streamed
+    (96, 770, 2),           # 448 rows: three pairs and a block; with 128 channels 303 MB, keys streamed too
+    (96, 2300, 2),          # 1152 rows: nine pairs
+])
+def test_pairs_of_blocks(dtype, G, d, B, cap, ranges, device):
+    H, tdt = 8, {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
     edges = [0, 1, 15, 16, 17, 63, 64, 65, 80, 112, 113, 127, 128, 129, 191, 192, 193, 240, 255, 256, 257, 319, 320, 321, 383, 384, 385]
     rows = [n for n in edges if n < cap]
     rows = (rows + [cap - 1 - n for n in rows] * 8)[:B]
@@ -40,7 +45,9 @@ def test_pairs_of_blocks(dtype, G, d, cap, device):
     n_valid = torch.tensor(rows, dtype=torch.int32, device=device)[:, None].repeat(1, H).contiguous()
     shape = W.DecodeShape(batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=d, capacity=cap,
                           dtype={"bf16": W.WKV_BF16, "f16": W.WKV_F16}[dtype])
-    ws = torch.full((W.wkv_decode_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device=device)     # NaNs
+    ws_bytes = W.wkv_decode_workspace_bytes(shape)
+    assert ws_bytes == B * H * ranges * G * (d + 2) * 4, "the caches are not divided as this case means them to be"
+    ws = torch.full((ws_bytes,), 0xFF, dtype=torch.uint8, device=device)     # NaNs
     out = torch.zeros((B, G * H, d), dtype=torch.float32, device=device)
     f64 = lambda t: t.to("cpu").to(torch.float64).numpy()
     k0, v0 = f64(kc), f64(vc)
