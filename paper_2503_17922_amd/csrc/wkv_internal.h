@@ -222,11 +222,10 @@ struct DecodeShape {
 // Head by head, with 2, 4, 8 or 24 ranges, the first ranges of all heads share an XCD and those of the late ones idle: 48 sequences of 300 to
 // 4000 rows, 32q/8kv, 128 channels 95 us a layer and 67 so, 11 with 32 KV heads 94 and 73; without the nine, 16 of up to 32000 rows
 // and 4 KV heads 108 and 79.  Equal lengths 1 to 2 % faster so, but 8 sequences of 32768 rows 177 us head by head and 182 so.
-// (The kernels pass division_magic(heads): the compiler's divisions by two run-time numbers are a good part of the code that stands
+// (magic: division_magic(heads); the compiler's divisions by two run-time numbers are a good part of the code that stands
 // before the first load.  Exact, as x < heads and 9 * y < 9 * 1536 / heads.)
 struct RangeOf {
   int32_t head, range;
-  __host__ __device__ RangeOf(int32_t x, int32_t y, int32_t heads) : head((int32_t)((uint32_t)(x + 9 * y) % (uint32_t)heads)), range(y) {}
   __host__ __device__ RangeOf(int32_t x, int32_t y, int32_t heads, uint32_t magic)
       : head(x + 9 * y - divide((uint32_t)(x + 9 * y), magic) * heads), range(y) {}
 };

@@ -34,7 +34,7 @@ int main() {
         int missing = rows * s.n_splits;
         for (int y = 0; y < s.n_splits; ++y)
           for (int x = 0; x < rows; ++x) {
-            const RangeOf it(x, y, rows);
+            const RangeOf it(x, y, rows, s.heads_magic);
             if (it.head < 0 || it.head >= rows || it.range < 0 || it.range >= s.n_splits) { ++missing; continue; }
             char &c = seen[(size_t)it.head * s.n_splits + it.range];
             missing -= !c;
@@ -56,7 +56,7 @@ int main() {
           double all = 0.0;
           const int rows = s.B * s.Hkv;
           for (int id = 0; id < rows * s.n_splits; ++id) {
-            const RangeOf it(id % rows, id / rows, rows);
+            const RangeOf it(id % rows, id / rows, rows, s.heads_magic);
             const int left = n[it.head / s.Hkv] - it.range * s.chunk, take = left < 0 ? 0 : left < s.chunk ? left : s.chunk;
             xcd[id % 8] += take;
             all += take;

@@ -20,9 +20,10 @@ int main() {
       const int rows = batch * heads;
       for (int y = 0; y < d.shape.n_splits; ++y)
         for (int x = 0; x < rows; ++x) {
-          const RangeOf a(x, y, rows), b(x, y, rows, d.shape.heads_magic);
-          if (a.head != b.head || a.range != b.range || divide(b.head, d.shape.kv_magic) != b.head / heads) {
-            if (++failures < 10) std::printf("FAILED %d of %d, range %d: head %d, %d\n", x, rows, y, a.head, b.head);
+          const RangeOf it(x, y, rows, d.shape.heads_magic);
+          const int head = (x + 9 * y) % rows;
+          if (it.head != head || it.range != y || divide(it.head, d.shape.kv_magic) != head / heads) {
+            if (++failures < 10) std::printf("FAILED %d of %d, range %d: head %d, %d\n", x, rows, y, head, it.head);
           }
         }
     }
