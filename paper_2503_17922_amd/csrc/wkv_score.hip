@@ -275,7 +275,9 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   // ---- the key stream -------------------------------------------------------------------------
   const char *kbase = (const char *)gp.k[g] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * C::ES;
   const int64_t kst = s.kv_st * C::ES;
-  const bool wide = kst * 16 >= 0x7fffffff;                 // rows too far apart for 32-bit offsets within a tile
+  // rows too far apart for 32-bit offsets within a tile: below that 16 rows span less than 2 GiB, and the 31 that the offsets of a shared
+  // 32-row tile's second part reach over less than 4
+  const bool wide = kst * 16 >= 0x7fffffff;
   const int row_in_part = my_part * (C::LPT * C::RPI) + lane / C::PPR;      // of this lane's first DMA instruction
   uint32_t off[C::OFFS];                                    // this lane's pieces, from the first row of its 16
 #pragma unroll
