@@ -223,14 +223,17 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   // 134 MB 74.9 / 79.0, 335 MB 170.3 / 166.9, 1.07 GB 503 / 445; 128 rows and more wait for the matrix pipe, 1 GB 1182 / 1178.
   pl.nontemporal = keys * s.d * elem_bytes(s.dtype) > MEMORY_CACHE_BYTES;
   // Key tiles fetched twice, once per row group, against a barrier per tile: worth it while a chunk is short enough for
-  // the two waves to stay together and the cache has room for what they lose.  Whole calls with a barrier /
-  // with rings of their own, keys held / not held by the memory-side cache from the call before:
-  //   128 channels, to 192 rows    never: 8 MB 22.9 / 23.2, 23.8 / 24.5 us, 32 MB 40.6 / 41.9, 41.0 / 42.2, 64 MB 57.6 / 58.2, 61.5 / 63.2, 128 MB 90.4 / 97.2, 97.0 / 108.4
-  //   more rows                    19 MB 36.7 / 35.3, 64 MB 65.9 / 64.1, 70.6 / 70.7, 109 MB 95.8 / 92.9, 101.5 / 101.7, 128 MB 106.3 / 106.0, 114.3 / 121.1
-  //   64 channels                  16 MB 37.3 / 35.6, 96 MB 99.3 / 91.0, 102.3 / 97.7, 160 MB 164.3 / 159.6, 170.3 / 172.7 and 150.5 / 139.5, 156.6 / 150.7, 192 MB 189.7 /
-  //                                179.2, 193.4 / 184.4, 240 MB 197.4 / 194.2, 204.9 / 211.4
+  // the two waves to stay together and the cache has room for what they lose; not for the few tiles of the smallest calls.  Whole calls with a barrier / with
+  // rings of their own, keys held / not held by the memory-side cache from the call before, us:
+  //   128 channels, to 192 rows    7 MB 23.4 / 24.1, 24.4 / 25.0; 8 MB 22.9 / 23.2, 23.8 / 24.5; 17 MB 33.1 / 32.2, 33.8 / 32.7; 32 MB one length 40.6 / 41.9, 41.0 / 42.2, mixed
+  //                                45.4 / 44.7, 45.8 / 44.8; 53 MB mixed 70.7 / 69.4, 75.0 / 73.2; 99 MB mixed 94.4 / 93.1, 100.4 / 102.0; 105 MB mixed 132.8 / 128.0,
+  //                                138.3 / 134.5; 96 MB one length 75.5 / 77.2, 80.8 / 82.0; 128 MB 90.4 / 97.2, 97.0 / 108.4
+  //   more rows                    8 MB 28.7 / 29.1, 29.7 / 29.8; 19 MB 36.7 / 35.3; 53 MB mixed 83.6 / 78.6, 86.9 / 83.2; 64 MB 65.9 / 64.1, 70.6 / 70.7; 105 MB mixed 146.6 / 136.1,
+  //                                150.9 / 143.3; 109 MB 95.8 / 92.9, 101.5 / 101.7; 128 MB 106.3 / 106.0, 114.3 / 121.1
+  //   64 channels                  4 MB 22.8 / 22.4; 16 MB 37.3 / 35.6; 96 MB 99.3 / 91.0, 102.3 / 97.7; 160 MB 164.3 / 159.6, 170.3 / 172.7 and 150.5 / 139.5, 156.6 / 150.7;
+  //                                192 MB 189.7 / 179.2, 193.4 / 184.4; 240 MB 197.4 / 194.2, 204.9 / 211.4
   const int64_t bytes = keys * s.d * elem_bytes(s.dtype);
-  pl.own_rings = s.d == 64 ? bytes <= MEMORY_CACHE_BYTES * 3 / 4 : pl.m_pad > 192 && bytes <= MEMORY_CACHE_BYTES * 7 / 16;
+  pl.own_rings = s.d == 64 ? bytes <= MEMORY_CACHE_BYTES * 3 / 4 : bytes > ((int64_t)9 << 20) && bytes <= MEMORY_CACHE_BYTES * 7 / 16;
   pl.tile = score_tile(s, pl, keys, pl.m_pad > wave_rows);
   pl.n_chunks1 = 0;
   for (int32_t b = 0; b < s.B; ++b) pl.n_chunks1 = std::max(pl.n_chunks1, pl.pass[0].first[b + 1] - pl.pass[0].first[b]);

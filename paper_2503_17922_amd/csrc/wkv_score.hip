@@ -623,10 +623,7 @@ static hipError_t launch_rows(const Shape &s, const BatchParams &bp, const Score
     WKV_PASSES(96, 2, 32, true) WKV_PASSES(128, 2, 32, true)
   } else {
     WKV_PASSES(32, 1, 32, false) WKV_PASSES(64, 1, 32, false) WKV_PASSES(96, 1, 32, false) WKV_PASSES(128, 1, 32, false)
-    if (pl.own_rings) {
-      if constexpr (D == 64) { WKV_PASSES(96, 2, 32, false, true) }
-      WKV_PASSES(128, 2, 32, false, true)
-    }
+    if (pl.own_rings) { WKV_PASSES(96, 2, 32, false, true) WKV_PASSES(128, 2, 32, false, true) }
     WKV_PASSES(96, 2, 32, false) WKV_PASSES(128, 2, 32, false)
   }
 #undef WKV_ROWS

@@ -46,10 +46,9 @@ int main() {
     for (int d : {64, 128}) CHECK(plan(WKV_F32, d, rows, 8, 8, 16385).tile == 16);
   for (int dtype : {WKV_BF16, WKV_F16}) {
     // two row groups: rings of their own
-    for (int L : {4096, 16384, 32768}) {
-      CHECK(!plan(dtype, 128, 192, 8, 1, L).own_rings);
-      CHECK(plan(dtype, 128, 193, 8, 1, L).own_rings);
-      CHECK(plan(dtype, 64, 192, 8, 1, L).own_rings);
+    for (int rows : {160, 192, 193, 256}) {
+      CHECK(!plan(dtype, 128, rows, 8, 1, 4608).own_rings && plan(dtype, 128, rows, 8, 1, 4609).own_rings);        // 9 MB
+      CHECK(plan(dtype, 64, rows, 8, 1, 512).own_rings);
     }
     CHECK(plan(dtype, 128, 256, 8, 7, 8192).own_rings && !plan(dtype, 128, 256, 8, 7, 8193).own_rings);          // 112 MB
     CHECK(plan(dtype, 64, 256, 8, 12, 16384).own_rings && !plan(dtype, 64, 256, 8, 12, 16385).own_rings);        // 192 MB

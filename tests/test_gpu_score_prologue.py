@@ -54,7 +54,7 @@ def test_statistics_folded_by_the_second_pass(L, device):
 @pytest.mark.parametrize("q_heads,w_obs", [(5, 32), (5, 31), (7, 31), (7, 32)])
 @pytest.mark.parametrize("heads,L", [(1, 700), (8, 16397)])
 def test_rows_that_leave_a_tile_out(dtype, d, q_heads, w_obs, heads, L, device):
-    # 155 to 224 rows: five to seven tiles of 32 rows for two row groups of three or four, in rings of every wave's own or (128 channels to 192 rows, or
+    # 155 to 224 rows: five to seven tiles of 32 rows for two row groups of three or four, in rings of every wave's own or (128 channels up to 9 MB and
     # above 112 MB) shared
     groups = 1 if L < 1000 else 5 if d == 128 else 9
     w = S.scaled_workload(S.make_workload("c4"), name="left_out", dtype=dtype, head_dim=d, n_q_heads=q_heads * heads, n_kv_heads=heads, w_obs=w_obs,

@@ -1,6 +1,6 @@
 """GPU parity of the score passes on streams of keys large enough for each way of fetching them, in the types and row
-widths that the other tests take through small streams only: up to 112 MB of scored keys (192 MB of 64 channels) every wave fetches its own tiles
-where there are two row groups of 16-bit inputs, above that the waves of a slot share them, above 256 MB by nontemporal loads.  16-bit inputs of
+widths that the other tests take through small streams only: from 9 to 112 MB of scored keys (64 channels: up to 192 MB) every wave fetches its own tiles
+where there are two row groups of 16-bit inputs, else the waves of a slot share them, above 256 MB by nontemporal loads.  16-bit inputs of
 one row group take tiles of 16 rows on nontemporal streams of 128 channels and where 97 to 112 rows have much to compute, else of 32
 (test_score_plan has the rule).  Chunks hold several segments of pooled token scores (1024 of them with four row groups, else 2048)."""
 import pytest
@@ -25,6 +25,7 @@ MB = 1 << 20
     ("f16", 64, 64, 10, 0, 192),
     ("bf16", 64, 64, 14, 192, 256),         # shared
     ("f16", 64, 48, 14, 192, 256),          # 192 rows, shared
+    ("bf16", 128, 48, 2, 9, 112),           # 192 rows, rings of their own
     ("bf16", 128, 56, 6, 112, 256),         # 224 rows, shared
     ("f16", 64, 64, 17, 256, 512),          # shared, nontemporal
     ("f16", 64, 32, 17, 256, 512),          # one row group, nontemporal

@@ -72,9 +72,10 @@ def test_key_rows_far_apart(stride, device):
 
 
 def test_key_rows_far_apart_in_shared_tiles(device):
-    # two row groups of up to 192 rows fetch a tile of 32 rows together, and the offsets of the second reach over 31 rows: nearly 4 GiB
-    B, n, stride = 64, 4, (1 << 26) - 8
+    # two row groups of 128 channels fetch a tile of 32 rows together above 112 MB of scored keys, and the offsets of the second reach over 31 rows: nearly 4 GiB
+    B, n, stride = 64, 32, (1 << 26) - 8
     w = _w(n_groups=n, n_q_heads=20, w_obs=31, n_kv_heads=4, seq_len=[70] * B, win=[4] * B, top_p=[3] * B, k_windows=[5] * B)
+    assert B * n * w.n_kv_heads * 70 * 256 > 112 << 20
     _compress_far_apart(w, device, stride)
 
 
