@@ -243,6 +243,26 @@ ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups) {
   return pl;
 }
 
+void fill_score_args(const Shape &s, const BatchParams &bp, const ScorePlan &plan, const GroupPtrs &gp, int32_t n_groups, int32_t pass,
+                     bool fold, ScoreArgs *a, ScoreGrid *grid) {
+  const PassPlan &pp = plan.pass[pass], &stats = plan.pass[0];
+  for (int32_t b = 0; b < WKV_MAX_BATCH; ++b) a->ends[b] = b < s.B ? pp.first[b + 1] : INT32_MAX;
+  for (int32_t b = 0; b < s.B; ++b) {
+    const SeqParam &q = bp.seq[b];
+    a->seq[b] = {q.L, pp.first[b], stats.first[b + 1] - stats.first[b], pp.chunk[b] | (uint32_t)q.win << 8 | (uint32_t)q.p << 16, q.win_magic,
+                 pp.first[b + 1] - 1};
+  }
+  a->gp = gp;
+  a->m_pad = plan.m_pad;
+  a->n_chunks1 = plan.n_chunks1;
+  a->fold = fold;
+  a->hkv_magic = division_magic(s.Hkv);
+  a->items = pp.first[s.B];
+  *grid = score_grid(s.Hkv * n_groups, a->items);
+  a->row_bits = grid->row_bits;
+  a->last_x = grid->x - 1; a->last_y = grid->y - 1; a->last_z = grid->z - 1;
+}
+
 // The single-read kernel applies to 16-bit inputs with at most 128 softmax rows per KV head (its
 // workgroups keep the row statistics of one row tile set in registers).  It is taken only when the
 // caller asks for it: on MI355X the exchange of the row statistics between workgroups costs more

@@ -103,6 +103,35 @@ struct ScorePlan {
   bool fold_in_pass2;          // pass 2 folds the pass-1 partials itself (few chunks per row)
 };
 
+// What the score kernels read of their arguments, laid out for few dependent scalar loads: a workgroup's first request waits for every one of
+// them (a cold one takes 0.2 to 0.3 us), so the first trip fetches what lies at fixed places, `ends` of the first sequences among
+// it, and the second the one record of the workgroup's sequence and the pointers of its group.  With five trips in the first pass and eight in
+// the second, 1.4 and 1.8 us to the first key request; a call over 512 tokens of two KV heads 17.95 -> 16.25 us so, 4096 tokens 24.3 -> 23.7.
+struct ScoreSeq {
+  int32_t L, first, n_parts;   // prefix length, first workgroup of this pass, workgroups of the statistics pass
+  uint32_t packed;             // chunk in CHUNK_UNITs | win << 8 | p << 16
+  uint32_t win_magic;
+  int32_t last;                // last workgroup of this pass
+};
+constexpr int32_t ENDS_AT_ONCE = 8;
+struct ScoreArgs {
+  int32_t ends[WKV_MAX_BATCH]; // first workgroup after the sequence; INT32_MAX past the last sequence
+  ScoreSeq seq[WKV_MAX_BATCH];
+  GroupPtrs gp;
+  int32_t m_pad, n_chunks1, fold;       // fold: this pass folds the partials of the statistics pass
+  uint32_t hkv_magic;
+  int32_t row_bits, last_x, last_y, last_z, items;    // the launch grid (see ScoreGrid) and the workgroups of a row
+};
+// The launch grid: x the workgroup of a row, y the row (group, KV head).
+struct ScoreGrid {
+  int32_t x, y, z, row_bits;
+};
+inline ScoreGrid score_grid(int32_t rows, int32_t items) { return {items, rows, 1, 0}; }
+struct ScoreItem {
+  int32_t row, item;
+  __host__ __device__ ScoreItem(int32_t x, int32_t y, int32_t, int32_t) : row(y), item(x) {}
+};
+
 // ---- single-read score kernel ("resident keys") ----------------------------------------------------
 constexpr int32_t RK_SLICE = 256;        // keys a workgroup holds in registers between its two phases
 // Synchronisation words in the workspace (uint32, cleared at the start of every call): a few
@@ -176,6 +205,8 @@ void set_error(const char *fmt, ...);
 wkv_status validate(const wkv_problem *p, wkv_dims *dims);
 void fill_shape(const wkv_problem *p, const wkv_dims &dims, Shape *s, BatchParams *bp);
 ScorePlan plan_score(const Shape &s, const BatchParams &bp, int32_t n_groups);
+void fill_score_args(const Shape &s, const BatchParams &bp, const ScorePlan &plan, const GroupPtrs &gp, int32_t n_groups, int32_t pass,
+                     bool fold, ScoreArgs *a, ScoreGrid *grid);
 ResidentPlan plan_resident(const Shape &s, const BatchParams &bp, const ScorePlan &plan, int32_t n_groups, int32_t flags);
 Workspace carve_workspace(const Shape &s, const ScorePlan &plan, const ResidentPlan &rp, int32_t n_groups, void *base);
 

@@ -87,29 +87,28 @@ __device__ __forceinline__ void fold_all(const Shape &s, int n_chunks, int m_pad
 
 constexpr int FOLD_THREADS = 256;
 
-__global__ __launch_bounds__(FOLD_THREADS) void fold_kernel(Shape s, ScorePlan pl, const float2 *__restrict__ partials,
+__global__ __launch_bounds__(FOLD_THREADS) void fold_kernel(Shape s, ScoreArgs a, const float2 *__restrict__ partials,
                                                             float *__restrict__ lse, const uint32_t *__restrict__ only_if) {
   __shared__ float2 part_s[FOLD_THREADS];
   if (only_if && *only_if == 0u) return;
   const int64_t row = (int64_t)blockIdx.y * s.B * s.Hkv + blockIdx.x;
   const int b = blockIdx.x / s.Hkv;
-  const FoldShare<FOLD_THREADS> me(pl.m_pad);
-  const int n_chunks = pl.pass[0].first[b + 1] - pl.pass[0].first[b];
-  const float2 *part = partials + row * pl.n_chunks1 * pl.m_pad;
+  const FoldShare<FOLD_THREADS> me(a.m_pad);
+  const int n_chunks = a.seq[b].n_parts;
+  const float2 *part = partials + row * a.n_chunks1 * a.m_pad;
   float2 p[FOLD_AT_ONCE];
-  if (me.row < s.M) fold_load(p, part, n_chunks, pl.m_pad, me, 0);
-  fold_all<FOLD_THREADS>(s, n_chunks, pl.m_pad, part, pl.m_pad, me, p, part_s, lse + row * pl.m_pad);
+  if (me.row < s.M) fold_load(p, part, n_chunks, a.m_pad, me, 0);
+  fold_all<FOLD_THREADS>(s, n_chunks, a.m_pad, part, a.m_pad, me, p, part_s, lse + row * a.m_pad);
 }
 
-// The base-2 log-sum-exp of softmax row r of (group g, sequence b, KV head h): converted from the
+// The base-2 log-sum-exp of softmax row r of a (group, sequence b, KV head h): converted from the
 // caller's natural-log normalisers [B, Hq, w_obs] when they were handed over (the rows of a KV
 // head are contiguous there), else what the fold left in the workspace.  Padded rows get +inf.
-__device__ __forceinline__ float row_lse2(const Shape &s, const ScorePlan &pl, const GroupPtrs &gp,
-                                          const float *__restrict__ lse_ws, int g, int b, int h, int64_t row, int r) {
+__device__ __forceinline__ float row_lse2(const Shape &s, const float *__restrict__ given, const float *__restrict__ lse_ws, int m_pad, int b, int h,
+                                          int64_t row, int r) {
   if (r >= s.M) return INFINITY;
-  const float *given = gp.lse[g];
   if (given) return given[((int64_t)b * s.Hq + (int64_t)h * s.G) * s.w_obs + r] * 1.4426950408889634f;
-  return lse_ws[row * pl.m_pad + r];
+  return lse_ws[row * m_pad + r];
 }
 
 // =========================================================================================
@@ -216,7 +215,7 @@ __device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *p) {
 // costs small calls 1 %.
 // TS: rows of a tile (see score_tile in wkv_host.cpp).  WAVE_ROWS: rows a wave takes, in RT tiles.
 template <int D, int DT, int WAVE_ROWS, int HV, int PASS, int TS, bool NT_LOADS, bool OWN_RINGS>
-__global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, BatchParams bp, GroupPtrs gp, ScorePlan pl,
+__global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, ScoreArgs a,
                                                                                  float2 *__restrict__ partials,
                                                                                  const float *__restrict__ lse_g,
                                                                                  float *__restrict__ t_out,
@@ -229,20 +228,38 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   __shared__ __attribute__((aligned(16))) float t_s[PASS == 2 ? HV * C::T_S : 4];     // token scores of a segment
   __shared__ __attribute__((aligned(16))) float lse_s[PASS == 2 ? ROWS : 4];
   __shared__ float2 part_s[PASS == 2 ? NT : KW * ROWS];
+  // First trip for arguments: all at fixed places, requested together (see ScoreArgs; left to itself the compiler asks for each where it is used).
+  int ends[ENDS_AT_ONCE];
+#pragma unroll
+  for (int i = 0; i < ENDS_AT_ONCE; ++i) ends[i] = a.ends[i];
+  asm volatile("" ::"s"(ends[0]), "s"(ends[1]), "s"(ends[2]), "s"(ends[3]), "s"(ends[4]), "s"(ends[5]), "s"(ends[6]), "s"(ends[7]),
+               "s"(s.B), "s"(s.Hkv), "s"(s.w_obs), "s"(s.G), "s"(s.M), "s"(s.kv_st), "s"(s.kv_sh), "s"(s.kv_sb), "s"(s.q_st), "s"(s.q_sh), "s"(s.q_sb),
+               "s"(a.hkv_magic), "s"(a.row_bits), "s"(a.last_x), "s"(a.last_y), "s"(a.last_z), "s"(a.items), "s"(only_if));
   // Launched behind the single-read kernel as its fall-back: nothing to do unless that kernel
   // raised the word (uniform over the grid).
   if (only_if && *only_if == 0u) return;
 
   // Pass 2 walks the work items in the opposite order of pass 1: the keys pass 1 read last
   // are the ones most likely still held by the memory-side cache.
-  const int x = PASS == 1 ? blockIdx.x : gridDim.x - 1 - blockIdx.x;
-  const int h = PASS == 1 ? blockIdx.y : gridDim.y - 1 - blockIdx.y;
-  const int g = PASS == 1 ? blockIdx.z : gridDim.z - 1 - blockIdx.z;
-  const PassPlan &pp = pl.pass[PASS - 1];
+  const bool back = PASS == 2;
+  const ScoreItem item(back && a.row_bits == 0 ? a.last_x - blockIdx.x : blockIdx.x, back ? a.last_y - blockIdx.y : blockIdx.y,
+                       back ? a.last_z - blockIdx.z : blockIdx.z, a.row_bits);
+  const int x = item.item;
+  if (x >= a.items) return;
+  const int g = divide(item.row, a.hkv_magic), h = item.row - g * s.Hkv;
   int b = 0;
-  while (b + 1 < s.B && x >= pp.first[b + 1]) ++b;
-  const int bx = x - pp.first[b];                           // chunk of the sequence
-  const int L = bp.seq[b].L;
+#pragma unroll
+  for (int i = 0; i < ENDS_AT_ONCE; ++i) b += x >= ends[i];
+  if (b == ENDS_AT_ONCE)
+    while (b + 1 < s.B && x >= a.ends[b]) ++b;
+  // Second trip: the sequence and the group.
+  const ScoreSeq seq = a.seq[b];
+  const char *k_layer = (const char *)a.gp.k[g], *q_layer = (const char *)a.gp.q[g];
+  const float *given = a.gp.lse[g];
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(seq.L), "s"(seq.first), "s"(seq.n_parts), "s"(seq.packed), "s"(seq.win_magic), "s"(seq.last), "s"(k_layer), "s"(q_layer), "s"(given));
+  const int bx = x - seq.first;                             // chunk of the sequence
+  const int L = seq.L;
   const int n_review = L - s.w_obs;
   const int64_t row = ((int64_t)g * s.B + b) * s.Hkv + h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -250,7 +267,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   const int col = lane % TS, sub = lane / TS;
   const int my_ring = C::SHARED ? kw : wave, my_part = C::SHARED ? half : 0;
 
-  const int chunk = pp.chunk[b] * CHUNK_UNIT;
+  const int chunk = (seq.packed & 0xff) * CHUNK_UNIT;
   const int limit = PASS == 1 ? L : n_review;               // keys that matter to this pass
   const int c_first = bx * chunk;
   int c0 = c_first, cend = min(c0 + chunk, limit);          // keys c0 .. cend-1 of the row
@@ -260,20 +277,20 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
   if (PASS == 2 && s_pool) {
     // A window belongs to the chunk that holds its first token: the workgroup scores and pools whole
     // windows, whatever their size, and no token is scored twice.
-    win = bp.seq[b].win;
-    win_magic = bp.seq[b].win_magic;
+    win = seq.packed >> 8 & 0xff;
+    win_magic = seq.win_magic;
     c0 = divide(c0 + win - 1, win_magic) * win;
     cend = min(divide(cend + win - 1, win_magic) * win, limit);
     seg_len = divide(C::SEG, win_magic) * win;
   }
   float *trow = PASS == 2 ? t_out + row * s.t_stride : nullptr;
   if (PASS == 2 && !s_pool)                                 // the row's padding
-    for (int j = n_review + threadIdx.x; j < (x + 1 == pp.first[b + 1] ? s.t_stride : 0); j += NT) trow[j] = 0.0f;
+    for (int j = n_review + threadIdx.x; j < (x == seq.last ? s.t_stride : 0); j += NT) trow[j] = 0.0f;
   if (PASS == 2 && c0 >= cend) return;
-  float2 *part = partials + row * pl.n_chunks1 * pl.m_pad;
+  float2 *part = partials + row * a.n_chunks1 * a.m_pad;
 
   // ---- the key stream -------------------------------------------------------------------------
-  const char *kbase = (const char *)gp.k[g] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * C::ES;
+  const char *kbase = k_layer + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * C::ES;
   const int64_t kst = s.kv_st * C::ES;
   // rows too far apart for 32-bit offsets within a tile: below that 16 rows span less than 2 GiB, and the 31 that the offsets of a shared
   // 32-row tile's second part reach over less than 4
@@ -320,16 +337,16 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
 
   // ---- the partials that this thread folds: requested here, they arrive together with the keys and the queries
   const FoldShare<NT> share(ROWS);
-  const int n_parts = pl.pass[0].first[b + 1] - pl.pass[0].first[b];
+  const int n_parts = seq.n_parts;
   float2 parts[PASS == 2 ? FOLD_AT_ONCE : 1];
   if constexpr (PASS == 2)
-    if (pl.fold_in_pass2 && share.row < s.M) fold_load(parts, part, n_parts, pl.m_pad, share, 0);
+    if (a.fold && share.row < s.M) fold_load(parts, part, n_parts, a.m_pad, share, 0);
 
   // ---- the queries: into the ring's other places, tiles of rows as the keys', from there into registers as fragments.  Rows past the
   // last one repeat it: their statistics are never used and their normaliser is +inf.
   constexpr int PIECES = HV * RT * KS, PER_RING = (NS - C::FIRST) * KS;          // DMA instructions: all, what a ring takes
   auto query_at = [&](int f) __attribute__((always_inline)) { return f / PER_RING * (NS * C::TILE) + C::FIRST * C::TILE + f % PER_RING * 1024; };
-  const char *qbase = (const char *)gp.q[g] + ((int64_t)b * s.q_sb + (int64_t)(h * s.G) * s.q_sh) * C::ES;
+  const char *qbase = q_layer + ((int64_t)b * s.q_sb + (int64_t)(h * s.G) * s.q_sh) * C::ES;
   // rows one after the other at equal distances, as in a contiguous tensor: one offset per lane serves them all
   const bool even = s.q_sh == (int64_t)s.w_obs * s.q_st && s.q_st < 0x1000000;
   const uint32_t q_lane = (uint32_t)(lane / C::PPR) * (uint32_t)s.q_st * C::ES;
@@ -345,10 +362,10 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
     }
   }
   if (PASS == 2) {
-    if (pl.fold_in_pass2) {
-      if constexpr (PASS == 2) fold_all<NT>(s, n_parts, pl.m_pad, part, ROWS, share, parts, part_s, lse_s);
+    if (a.fold) {
+      if constexpr (PASS == 2) fold_all<NT>(s, n_parts, a.m_pad, part, ROWS, share, parts, part_s, lse_s);
     } else
-      for (int r = threadIdx.x; r < ROWS; r += NT) lse_s[r] = row_lse2(s, pl, gp, lse_g, g, b, h, row, r);
+      for (int r = threadIdx.x; r < ROWS; r += NT) lse_s[r] = row_lse2(s, given, lse_g, a.m_pad, b, h, row, r);
   }
   wait_vmcnt<0>();
   __syncthreads();
@@ -541,7 +558,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
       __syncthreads();
     }
     if (s_pool)                                             // Eq. 3-4 while the token scores are in LDS
-      pool_windows<NT>(t_s, divide(seg0, win_magic), divide(seg_end + win - 1, win_magic), win, bp.seq[b].p, n_review, s_pool + row * s.nw_max);
+      pool_windows<NT>(t_s, divide(seg0, win_magic), divide(seg_end + win - 1, win_magic), win, seq.packed >> 16, n_review, s_pool + row * s.nw_max);
     else
       for (int i = threadIdx.x; i < seg_end - seg0; i += NT) trow[seg0 + i] = t_s[i];
     if (seg_end == cend) break;
@@ -563,10 +580,10 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Ba
       if (sub == 0) part_s[kw * ROWS + (half * RT + mt) * TS + col] = make_float2(pm.a, pz.a);
     }
     __syncthreads();
-    for (int r = threadIdx.x; r < pl.m_pad; r += NT) {           // m_pad <= ROWS
+    for (int r = threadIdx.x; r < a.m_pad; r += NT) {           // m_pad <= ROWS
       float m = part_s[r].x, z = part_s[r].y;
       for (int w = 1; w < KW; ++w) merge_stats(m, z, part_s[w * ROWS + r].x, part_s[w * ROWS + r].y);
-      part[(int64_t)bx * pl.m_pad + r] = make_float2(m, z);
+      part[(int64_t)bx * a.m_pad + r] = make_float2(m, z);
     }
   }
 }
@@ -579,25 +596,25 @@ static hipError_t launch_passes(const Shape &s, const BatchParams &bp, const Sco
                                 bool have_lse, float2 *partials, float *lse, float *t_out, float *s_pool, hipStream_t stream,
                                 hipEvent_t mid, const uint32_t *only_if) {
   const dim3 block(score_threads(HV));
+  ScoreArgs a;
+  ScoreGrid grid;
   hipError_t e;
   if (have_lse) {                                      // no statistics pass: pass 2 reads the caller's normalisers
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
   } else {
-    dim3 g1(pl.pass[0].first[s.B], s.Hkv, n_groups);
-    hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 1, TS, NT_LOADS, OWN_RINGS>), g1, block, 0, stream, s, bp, gp, pl, partials, lse, t_out, s_pool, only_if);
+    fill_score_args(s, bp, pl, gp, n_groups, 0, false, &a, &grid);
+    hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 1, TS, NT_LOADS, OWN_RINGS>), dim3(grid.x, grid.y, grid.z), block, 0, stream, s, a, partials, lse, t_out, s_pool, only_if);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (mid && (e = hipEventRecord(mid, stream)) != hipSuccess) return e;
     if (s.t_stride <= 0) return hipSuccess;
     if (!pl.fold_in_pass2) {
-      hipLaunchKernelGGL(fold_kernel, dim3(s.B * s.Hkv, n_groups), dim3(FOLD_THREADS), 0, stream, s, pl, partials, lse, only_if);
+      hipLaunchKernelGGL(fold_kernel, dim3(s.B * s.Hkv, n_groups), dim3(FOLD_THREADS), 0, stream, s, a, partials, lse, only_if);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
-  ScorePlan pl2 = pl;
-  if (have_lse) pl2.fold_in_pass2 = false;
-  dim3 g2(pl.pass[1].first[s.B], s.Hkv, n_groups);
-  hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 2, TS, NT_LOADS, OWN_RINGS>), g2, block, 0, stream, s, bp, gp, pl2, partials, lse, t_out, s_pool, only_if);
+  fill_score_args(s, bp, pl, gp, n_groups, 1, pl.fold_in_pass2 && !have_lse, &a, &grid);
+  hipLaunchKernelGGL((score_kernel<D, DT, WAVE_ROWS, HV, 2, TS, NT_LOADS, OWN_RINGS>), dim3(grid.x, grid.y, grid.z), block, 0, stream, s, a, partials, lse, t_out, s_pool, only_if);
   return hipGetLastError();
 }
 
