@@ -39,24 +39,39 @@ template <int LPR, int NT, int APART>  // lanes per row, threads, pieces from on
 __global__ __launch_bounds__(NT) void gather_kernel(GatherShape s, LayerPtrs lp, const int32_t *__restrict__ tok_idx,
                                                     const int32_t *__restrict__ n_keep) {
   constexpr int ROWS = NT / LPR;                 // of a piece
-  const int bh = blockIdx.y, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv;
+  // Three trips to memory: the arguments, the positions with their count, the rows.  The barriers keep what is requested together
+  // together; by itself the compiler asked for n_keep, then for the positions, then for the tensors' addresses, and for the second row when the
+  // first had come: group by group, 32K-token model 198 -> 194 us, batch of mixed lengths 1113 -> 1071, 16K with 64 query heads 139 -> 133.5 (one piece
+  // a wave 200, 1183 and 141.5, three 198, 1110 and 140.5, four 207, 1143 and 147; 16 pieces apart the same as 8).
   const int layer = blockIdx.z >> 1;
   const bool is_v = blockIdx.z & 1;
+  const void *const *in = is_v ? lp.v_in : lp.k_in;
+  void *const *out = is_v ? lp.v_out : lp.k_out;
+  const char *src = (const char *)in[layer];
+  char *dst = (char *)out[layer];
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(src), "s"(dst), "s"(tok_idx), "s"(n_keep), "s"(s.kv_magic), "s"(s.Hkv), "s"(s.gamma_magic), "s"(s.rows), "s"(s.nkeep_max),
+               "s"(s.fill_padding), "s"(s.max_tok), "s"(s.last), "s"(s.last_apart), "s"(s.in_b), "s"(s.in_h), "s"(s.in_t), "s"(s.out_b), "s"(s.out_h), "s"(s.out_t));
+  const int bh = blockIdx.y, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv;
   const int row = divide(layer, s.gamma_magic) * s.rows + bh;          // of the index arrays
   const int32_t *idx = tok_idx + (int64_t)row * s.nkeep_max;
   const int step = ((int)blockIdx.x < s.last ? APART : s.last_apart) * ROWS;
   const int first = ((int)blockIdx.x / APART * (APART * GATHER_UNROLL) + (int)blockIdx.x % APART) * ROWS;
   const int r0 = first + threadIdx.x / LPR;
 
-  // (requested together with n_keep, which tells whether they count)
   int tok[GATHER_UNROLL];
 #pragma unroll
   for (int u = 0; u < GATHER_UNROLL; ++u) tok[u] = idx[min(r0 + u * step, s.nkeep_max - 1)];
-  const int nk = min(n_keep[row], s.nkeep_max);
+  int nk = n_keep[row];
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(nk));
+#pragma unroll
+  for (int u = 0; u < GATHER_UNROLL; ++u) asm volatile("" ::"v"(tok[u]));
+  nk = min(nk, s.nkeep_max);
   const int n_write = s.fill_padding ? s.nkeep_max : nk;   // rows past n_keep: zero-filled or left alone
   if (first >= n_write) return;
-  const char *src = (const char *)(is_v ? lp.v_in[layer] : lp.k_in[layer]) + b * s.in_b + h * s.in_h + threadIdx.x % LPR * 16;
-  char *dst = (char *)(is_v ? lp.v_out[layer] : lp.k_out[layer]) + b * s.out_b + h * s.out_h + threadIdx.x % LPR * 16;
+  src += b * s.in_b + h * s.in_h + threadIdx.x % LPR * 16;
+  dst += b * s.out_b + h * s.out_h + threadIdx.x % LPR * 16;
   u32x4 v[GATHER_UNROLL];
 #pragma unroll
   for (int u = 0; u < GATHER_UNROLL; ++u) {
