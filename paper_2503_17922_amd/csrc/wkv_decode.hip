@@ -161,6 +161,66 @@ __device__ __forceinline__ bool nothing_to_do(const DecodeShape &s, int bh, int 
   return true;
 }
 
+// Which range of which cache this workgroup takes, and the rows of that cache; by row counts where the host asks for it: the
+// workgroups take the whole ranges one after the other, cache by cache, then what the caches hold past them, then the ranges without
+// rows.  So the shorter ones come last, what has nothing to do takes nobody's place, and the ranges of a cache lie on all XCDs.  Every wave
+// finds its workgroup's range by itself: a lane counts the ranges of per_lane caches, a scan over the lanes tells whose the workgroup's number
+// falls among.  find_ranges_by_count has the figures.
+struct KeyRange {
+  int head, range, n;
+};
+template <bool BY_COUNT>
+__device__ __forceinline__ KeyRange find_range(const DecodeShape &s, const int32_t *__restrict__ n_valid) {
+  if constexpr (!BY_COUNT) {
+    const RangeOf it(blockIdx.x, blockIdx.y, s.B * s.Hkv, s.heads_magic);
+    return {it.head, it.range, load_scalar(n_valid + it.head)};
+  }
+  const int heads = s.B * s.Hkv, lane = threadIdx.x & 63;
+  int item = blockIdx.x + heads * blockIdx.y;
+  int n[DEC_PER_LANE], before[DEC_PER_LANE], count[DEC_PER_LANE];           // rows; ranges of the kinds before this one, of this one
+#pragma unroll
+  for (int j = 0; j < DEC_PER_LANE; ++j) {
+    n[j] = 0;
+    if (j < s.per_lane && j * 64 + lane < heads) n[j] = n_valid[j * 64 + lane];
+  }
+  int sum = 0;
+#pragma unroll
+  for (int j = 0; j < DEC_PER_LANE; ++j) {
+    before[j] = 0;
+    count[j] = n[j] > 0 && n[j] < s.capacity ? divide((uint32_t)n[j] >> 6, s.chunk_magic) : 0;
+    sum += count[j];
+  }
+  int upto = (int)wave_sums((uint32_t)sum);
+#pragma unroll
+  for (int kind = 1; kind < 3; ++kind) {                                    // (all uniform)
+    const int all = __builtin_amdgcn_readlane(upto, 63);
+    if (item < all) break;
+    item -= all;
+    sum = 0;
+#pragma unroll
+    for (int j = 0; j < DEC_PER_LANE; ++j) {
+      before[j] += count[j];
+      if (kind == 1) count[j] = n[j] > 0 && n[j] < s.capacity && before[j] * s.chunk < n[j];
+      else count[j] = j < s.per_lane && j * 64 + lane < heads ? s.n_splits - before[j] : 0;
+      sum += count[j];
+    }
+    upto = (int)wave_sums((uint32_t)sum);
+  }
+  const int src = __builtin_ctzll(__ballot(upto > item));
+  item -= __builtin_amdgcn_readlane(upto - sum, src);
+  int at = 0, have = __builtin_amdgcn_readlane(count[0], src), first = __builtin_amdgcn_readlane(before[0], src), rows = __builtin_amdgcn_readlane(n[0], src);
+#pragma unroll
+  for (int j = 1; j < DEC_PER_LANE; ++j) {
+    if (item < have) break;
+    item -= have;
+    at = j;
+    have = __builtin_amdgcn_readlane(count[j], src);
+    first = __builtin_amdgcn_readlane(before[j], src);
+    rows = __builtin_amdgcn_readlane(n[j], src);
+  }
+  return {at * 64 + src, first + item, rows};
+}
+
 template <typename T, int D, int G, bool STREAM>
 __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape s, const T *__restrict__ q_new,
                                                                      const T *__restrict__ k_cache,
@@ -172,12 +232,11 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
   constexpr int KPT = 64 / LPK;              // rows per wave load instruction
   __shared__ float wave_state[DEC_WAVES][G][D + 2];
 
-  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv, s.heads_magic);
+  const KeyRange item = find_range<false>(s, n_valid);
   const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / LPK, piece = lane % LPK;
-  const int n = n_valid[bh];
-  const int c0 = split * s.chunk, cend = min(c0 + s.chunk, n < s.capacity ? n : 0);
+  const int n = item.n, c0 = split * s.chunk, cend = min(c0 + s.chunk, n < s.capacity ? n : 0);
   if (nothing_to_do<G>(s, bh, split, n, c0, cend, part)) return;
 
   const T *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh;
@@ -312,7 +371,7 @@ __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
 }
 // STREAM: 0 plain loads, 1 values stream, 2 keys too (see launch_partial_g).
-template <int D, int G, bool F16, int STREAM, int NT>
+template <int D, int G, bool F16, int STREAM, int NT, bool BY_COUNT>
 __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
     DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *k_cache,
     const uint16_t *v_cache, const int32_t *__restrict__ n_valid, float *__restrict__ part) {
@@ -324,13 +383,15 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
   __shared__ __attribute__((aligned(16))) float o_s[WAVES][G][D];
   __shared__ float2 ml_s[WAVES][G];
 
-  const RangeOf item(blockIdx.x, blockIdx.y, s.B * s.Hkv, s.heads_magic);
+  // (all arguments together, ahead of the row count that depends on one of them)
+  asm volatile("" ::"s"(s.B), "s"(s.Hkv), "s"(s.heads_magic), "s"(s.kv_magic), "s"(s.chunk), "s"(s.capacity), "s"(s.c1), "s"(s.sb), "s"(s.sh), "s"(s.st),
+               "s"(s.per_lane), "s"(s.chunk_magic), "s"(s.n_splits), "s"(q_new), "s"(k_cache), "s"(v_cache), "s"(n_valid), "s"(part));
+  const KeyRange item = find_range<BY_COUNT>(s, n_valid);
   const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;            // score side: head, 4 rows
   const int piece = lane % LPK, sub = col / LPK;          // value side: 16-byte piece, which of the quad's rows in flight
-  const int n = n_valid[bh];
-  const int c0 = split * s.chunk, cend = min(c0 + s.chunk, n < s.capacity ? n : 0);
+  const int n = item.n, c0 = split * s.chunk, cend = min(c0 + s.chunk, n < s.capacity ? n : 0);
   if (nothing_to_do<G>(s, bh, split, n, c0, cend, part)) return;
 
   const uint16_t *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh + quad * 8;
@@ -413,6 +474,7 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
       }
       __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), reached by now but for rows requested past the end; else the compiler waits for the queries among the first requests
     } else {
+      __builtin_amdgcn_sched_barrier(0);       // the values too, before the scores wait for the keys
       attend(x, blk);
     }
   }
@@ -478,6 +540,9 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
   __shared__ __attribute__((aligned(16))) float acc_s[GROUPS][D];
   __shared__ float q_k[2];
   __shared__ float wave_m[WAVES], wave_l[WAVES];
+  // Two trips to memory: the arguments, then everything that follows from them.
+  asm volatile("" ::"s"(s.B), "s"(s.Hkv), "s"(s.G), "s"(s.d), "s"(s.kv_magic), "s"(s.capacity), "s"(s.n_splits), "s"(s.c1), "s"(s.sb), "s"(s.sh), "s"(s.st),
+               "s"(s.keep_count), "s"(q_new), "s"(k_new), "s"(v_new), "s"(k_cache), "s"(v_cache), "s"(part), "s"(n_valid), "s"(out));
   const int bh = blockIdx.x, g = blockIdx.y, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int grp = tid / COLS, col = tid % COLS;
@@ -490,24 +555,29 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
   float4 pre[AHEAD];
 #pragma unroll
   for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(grp + u * GROUPS, s.n_splits - 1) * s.G * COLS];
+  const bool appends = g == 0 && tid < 2 * LPK;             // the new row, by head 0's workgroup: keys, then values
+  uint4 row_piece = make_uint4(0, 0, 0, 0);
+  if (appends) row_piece = *(const uint4 *)((tid < LPK ? k_new : v_new) + (int64_t)bh * D + tid % LPK * E);
+  T v_piece[(D + NT - 1) / NT];                             // the new values of this thread's outputs
+#pragma unroll
+  for (int i = 0; i < (D + NT - 1) / NT; ++i) v_piece[i] = v_new[(int64_t)bh * D + min(tid + i * NT, D - 1)];
   const bool takes_dot = wave == WAVES - 1;       // this wave also takes q . k_new
-  float dot = 0.0f;
+  uint4 q_piece = make_uint4(0, 0, 0, 0), k_piece = q_piece;
   if (takes_dot && lane < LPK) {
+    q_piece = *(const uint4 *)(q_new + hq * D + lane * E);
+    k_piece = *(const uint4 *)(k_new + (int64_t)bh * D + lane * E);
+  }
+  // (of head 0's workgroup alone, which raises it at the end; in a vector register, as a scalar would be waited for at once)
+  int n = -1;
+  if (appends) n = n_valid[bh];
+  __builtin_amdgcn_sched_barrier(0);
+  float dot = 0.0f;
+  if (takes_dot) {
     float qf[E], kf[E];
-    Piece<T>::unpack(*(const uint4 *)(q_new + hq * D + lane * E), qf);
-    Piece<T>::unpack(*(const uint4 *)(k_new + (int64_t)bh * D + lane * E), kf);
+    Piece<T>::unpack(q_piece, qf);
+    Piece<T>::unpack(k_piece, kf);
 #pragma unroll
     for (int c = 0; c < E; ++c) dot = fmaf(qf[c], kf[c], dot);
-  }
-  // append (by head 0's workgroup); nobody reads the row from the caches in this launch
-  if (g == 0 && tid < 2 * LPK) {
-    const int n = n_valid[bh];
-    if (n >= 0 && n < s.capacity) {
-      const int pc = tid % LPK;
-      const int64_t off = (int64_t)b * s.sb + (int64_t)h * s.sh + (int64_t)n * s.st + pc * E;
-      if (tid < LPK) *(uint4 *)(k_cache + off) = *(const uint4 *)(k_new + (int64_t)bh * D + pc * E);
-      else *(uint4 *)(v_cache + off) = *(const uint4 *)(v_new + (int64_t)bh * D + pc * E);
-    }
   }
   float logit, m, l, a, w_new, first;                   // first: m of range 0; NaN: the cache is full or its count is invalid
   if (takes_dot) dot = wave_sum(dot) * s.c1;
@@ -560,19 +630,22 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
       for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(sp + (AHEAD + u) * GROUPS, s.n_splits - 1) * s.G * COLS];
   }
   *(float4 *)&acc_s[grp][col * 4] = o;
+  // (nobody reads the new row from the caches in this launch)
+  const bool fits = n >= 0 && n < s.capacity;
+  if (appends && fits)
+    *(uint4 *)((tid < LPK ? k_cache : v_cache) + ((int64_t)b * s.sb + (int64_t)h * s.sh + (int64_t)n * s.st + tid % LPK * E)) = row_piece;
   __syncthreads();
-  for (int c = tid; c < D; c += NT) {
+#pragma unroll
+  for (int k = 0; k < (D + NT - 1) / NT; ++k) {
+    const int c = tid + k * NT;
+    if (c >= D) break;
     float x = 0.0f;
 #pragma unroll
     for (int i = 0; i < GROUPS; ++i) x += acc_s[i][c];
-    const float v = Piece<T>::value(v_new + (int64_t)bh * D + c);
-    x = fmaf(w_new, v, x) / l;
+    x = fmaf(w_new, Piece<T>::value(&v_piece[k]), x) / l;
     out[hq * D + c] = first != first ? first : x;
   }
-  if (g == 0 && tid == 0 && !s.keep_count) {
-    const int n = n_valid[bh];
-    if (n >= 0 && n < s.capacity) n_valid[bh] = n + 1;
-  }
+  if (g == 0 && tid == 0 && !s.keep_count && fits) n_valid[bh] = n + 1;
 }
 
 template <typename T, int D, int G>
@@ -607,15 +680,23 @@ static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, con
     constexpr bool WIDE = D == 128 && G <= 4;
     if constexpr (WIDE)
       if (s.chunk <= WIDE_THREADS / 64 * 16 && stream_level < 2) {
-        if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, WIDE_THREADS>), uint16_t, WIDE_THREADS);
-        else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, WIDE_THREADS>), uint16_t, WIDE_THREADS);
+        if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, WIDE_THREADS, false>), uint16_t, WIDE_THREADS);
+        else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, WIDE_THREADS, false>), uint16_t, WIDE_THREADS);
         return;
       }
     // (longer ranges than those are of caches that stream: as many as there can be of a cache, 128 rows each, are 16 MB)
     static_assert(!WIDE || (int64_t)DEC_MAX_SPLITS * 128 * 2 * D * (int64_t)sizeof(T) > MEMORY_CACHE_BYTES / 32, "plain loads");
-    if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS>), uint16_t, DEC_THREADS);
-    else if (WIDE || stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS>), uint16_t, DEC_THREADS);
-    else if constexpr (!WIDE) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS>), uint16_t, DEC_THREADS);
+    if (s.per_lane) {
+      if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS, true>), uint16_t, DEC_THREADS);
+      else if (WIDE || stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS, true>), uint16_t, DEC_THREADS);
+      else if constexpr (!WIDE) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS, true>), uint16_t, DEC_THREADS);
+    } else if (stream_level == 2) {
+      WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS, false>), uint16_t, DEC_THREADS);
+    } else if (WIDE || stream_level == 1) {
+      WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS, false>), uint16_t, DEC_THREADS);
+    } else if constexpr (!WIDE) {
+      WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS, false>), uint16_t, DEC_THREADS);
+    }
   } else {
     if (stream_level) WKV_PARTIAL((decode_partial_kernel<T, D, G, true>), T, DEC_THREADS);
     else WKV_PARTIAL((decode_partial_kernel<T, D, G, false>), T, DEC_THREADS);

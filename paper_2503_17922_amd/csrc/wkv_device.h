@@ -43,6 +43,11 @@ __device__ __forceinline__ typename TileOf<TS>::acc mfma_step(bf16x8 a, bf16x8 b
   }
 }
 
+// A word that no kernel writes while this one runs, by a scalar load; the address is the same in all lanes.  (Behind an asm statement the
+// compiler takes a vector load by itself, as it cannot tell that nothing was written.)
+template <typename T>
+__device__ __forceinline__ T load_scalar(const T *p) { return *(const __attribute__((address_space(4))) T *)(uintptr_t)p; }
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
@@ -80,6 +85,28 @@ __device__ __forceinline__ float quads_max(float x) {
   x = fmaxf(p.a, p.b);
   p = swap_rows(x, x);
   return fmaxf(p.a, p.b);
+}
+
+// ---- scans over the wave --------------------------------------------------------------------------
+// Over the lanes of a wave by DPP steps (a shuffle through LDS takes 100 cycles and more, and there are a dozen of these in a
+// row): shifts within rows of 16 lanes, then the last lane of a row, of two rows, into the ones after.  Lanes
+// without a source add 0, the smallest key.
+template <class F>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, F op) {
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false));     // row_shr:1
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false));     // row_shr:2
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false));     // row_shr:4
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false));     // row_shr:8
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));     // row_bcast:15
+  return op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));  // row_bcast:31
+}
+// Sums up to and including each lane; the largest of all lanes.
+__device__ __forceinline__ uint32_t wave_sums(uint32_t x) {
+  return wave_scan(x, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a + b; });
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+__device__ __forceinline__ uint32_t wave_largest(uint32_t x) {
+  return last_lane(wave_scan(x, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return max(a, b); }));
 }
 
 // ---- MFMA building blocks ----------------------------------

@@ -3,7 +3,7 @@
 // Both stages touch only the token-score array (4 bytes per prefix token and KV head), about
 // 1/64 of the bytes of the key stream that produced it, so they are latency bound rather than
 // bandwidth bound: the design goal is few launches and no serial host involvement.
-#include "wkv_internal.h"
+#include "wkv_device.h"
 #include "wkv_pool.h"
 
 namespace wkv {
@@ -80,27 +80,6 @@ static_assert(TOPK_ITERS <= 32, "one mask bit per window of a thread");
 __device__ __forceinline__ uint32_t float_to_key(float f) {
   const uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// Over the lanes of a wave by DPP steps (a shuffle through LDS takes 100 cycles and more, and there are a dozen of these in a
-// row): shifts within rows of 16 lanes, then the last lane of a row, of two rows, into the ones after.  Lanes
-// without a source add 0, the smallest key.
-template <class F>
-__device__ __forceinline__ uint32_t wave_scan(uint32_t x, F op) {
-  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false));     // row_shr:1
-  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false));     // row_shr:2
-  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false));     // row_shr:4
-  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false));     // row_shr:8
-  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));     // row_bcast:15
-  return op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));  // row_bcast:31
-}
-// Sums up to and including each lane; the largest of all lanes.
-__device__ __forceinline__ uint32_t wave_sums(uint32_t x) {
-  return wave_scan(x, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a + b; });
-}
-__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
-__device__ __forceinline__ uint32_t wave_largest(uint32_t x) {
-  return last_lane(wave_scan(x, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return max(a, b); }));
 }
 
 // Steps 1-3 for the row of window scores srow: the selected windows, ascending, are left in keys (LDS, nw_max entries)
