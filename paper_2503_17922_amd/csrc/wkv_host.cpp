@@ -114,6 +114,7 @@ void fill_shape(const wkv_problem *p, const wkv_dims &dims, Shape *s, BatchParam
   s->fill_padding = (p->flags & WKV_KEEP_PADDING) ? 0 : 1;
   const double scale = p->scale > 0.0f ? (double)p->scale : 1.0 / std::sqrt((double)p->head_dim);
   s->w_magic = 65536u / (uint32_t)p->w_obs + 1u;
+  s->hkv_magic = division_magic(p->n_kv_heads);
   s->c1 = (float)(scale * 1.4426950408889634074);
   s->q_sb = p->q_stride_b; s->q_sh = p->q_stride_h; s->q_st = p->q_stride_t;
   s->kv_sb = p->kv_stride_b; s->kv_sh = p->kv_stride_h; s->kv_st = p->kv_stride_t;

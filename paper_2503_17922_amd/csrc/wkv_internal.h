@@ -62,10 +62,11 @@ constexpr int32_t SMALL_WORKGROUPS = 512;         // what the device holds at on
 constexpr int32_t SMALL_WINDOWS = 8192;
 struct SmallJob {
   SeqParam seq[SMALL_BATCH];
-  uint16_t k[SMALL_GROUPS * SMALL_BATCH];
+  int32_t k[SMALL_GROUPS * SMALL_BATCH];        // windows to keep, index g * B + b
   const void *in[SMALL_LAYERS][2];
   void *out[SMALL_LAYERS][2];
-  int32_t gamma, own_budgets, esize;
+  int32_t gamma, esize;
+  uint32_t gamma_magic;       // division_magic of gamma
 };
 
 // Problem shape as the kernels see it.
@@ -76,6 +77,7 @@ struct Shape {
   int32_t dtype;
   int32_t fill_padding;   // gather: zero the compact-cache rows past n_keep
   uint32_t w_magic;   // r / w_obs == r * w_magic >> 16 for row numbers r < 256
+  uint32_t hkv_magic; // division_magic(Hkv)
   float c1;           // logit scale * log2(e): logits are handled in base-2 units
   int64_t q_sb, q_sh, q_st;
   int64_t kv_sb, kv_sh, kv_st;

@@ -11,25 +11,29 @@ namespace wkv {
 constexpr int POOL_THREADS = 256;
 constexpr int POOL_TOKENS = SCORE_SEG;      // tokens a workgroup stages
 
-// Windows that a workgroup pools: as many as fit its staging area.
-__host__ __device__ __forceinline__ int pool_windows_per_block(int win) { return POOL_TOKENS / win; }
-
 __global__ __launch_bounds__(POOL_THREADS) void pool_kernel(Shape s, BatchParams bp, const float *__restrict__ t,
                                                                  float *__restrict__ s_out) {
   __shared__ __attribute__((aligned(16))) float t_s[POOL_TOKENS];
-  const int bh = blockIdx.y, b = bh / s.Hkv, g = blockIdx.z;
+  // Three trips to memory: the arguments, the sequence's record, its tokens (which came one trip after the other before).
+  asm volatile("" ::"s"(s.B), "s"(s.Hkv), "s"(s.hkv_magic), "s"(s.w_obs), "s"(s.t_stride), "s"(s.nw_max), "s"(t), "s"(s_out));
+  const int bh = blockIdx.y, b = divide(bh, s.hkv_magic), g = blockIdx.z;
   const SeqParam sp = bp.seq[b];
+  asm volatile("" ::"s"(sp.L), "s"(sp.win), "s"(sp.p), "s"(sp.win_magic));
   const int n_review = sp.L - s.w_obs;
-  const int nw = (n_review + sp.win - 1) / sp.win;
+  const int nw = divide(n_review + sp.win - 1, sp.win_magic);
   const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
   const float *trow = t + row * s.t_stride;
   float *srow = s_out + row * s.nw_max;
-  const int per = pool_windows_per_block(sp.win);
+  const int per = divide(POOL_TOKENS, sp.win_magic);        // windows that fit the staging area
   // sequences with small windows need fewer workgroups than the grid has per row; the last one fills up
   const int w0 = blockIdx.x * per, w1 = min(w0 + per, nw);
   if (w0 < w1) {
     const int tok0 = w0 * sp.win, n = min(w1 * sp.win, n_review) - tok0;
-    for (int i = threadIdx.x; i < n; i += POOL_THREADS) t_s[i] = trow[tok0 + i];
+    float x[POOL_TOKENS / POOL_THREADS];                    // (requested together)
+#pragma unroll
+    for (int i = 0; i < POOL_TOKENS / POOL_THREADS; ++i) x[i] = trow[tok0 + min((int)threadIdx.x + i * POOL_THREADS, n - 1)];
+#pragma unroll
+    for (int i = 0; i < POOL_TOKENS / POOL_THREADS; ++i) t_s[threadIdx.x + i * POOL_THREADS] = x[i];
     __syncthreads();
     pool_windows<POOL_THREADS>(t_s, w0, w1, sp.win, sp.p, n_review, srow);
   }
@@ -42,7 +46,7 @@ hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, 
   if (s.nw_max <= 0) return hipSuccess;
   int blocks = 1;
   for (int b = 0; b < s.B; ++b) {
-    const int nw = (bp.seq[b].L - s.w_obs + bp.seq[b].win - 1) / bp.seq[b].win, per = pool_windows_per_block(bp.seq[b].win);
+    const int nw = (bp.seq[b].L - s.w_obs + bp.seq[b].win - 1) / bp.seq[b].win, per = POOL_TOKENS / bp.seq[b].win;
     blocks = max(blocks, (nw + per - 1) / per);
   }
   dim3 grid(blocks, s.B * s.Hkv, n_groups);
@@ -67,7 +71,10 @@ hipError_t launch_pool(const Shape &s, const BatchParams &bp, int32_t n_groups, 
 // The 32K-token configuration (64 rows of 2046 windows, k = 256): 12.2 us with 8-bit digits from the
 // top and three synchronisations per 1024 windows in step 3, 9.2 us so; a mixed batch (512 rows of up to 3900
 // windows): 19.7 us, 18.0 us so with 1024 threads, 13.8 us with 512.  With scans by DPP and a thread's scores requested
-// together: 9.6 -> 8.0 us and 12.0 -> 10.2 us.
+// together: 9.6 -> 8.0 us and 12.0 -> 10.2 us.  The arguments came in a chain of six trips to memory, each asked for where it was
+// used, the scores in a seventh: with two, score, pool, selection and gather of 4096 tokens in fp32 one by one 56.7 -> 54.3 us (half of that the
+// pooling's tokens, requested together), and merged with the gather (below) 512 tokens of two heads 16.3 -> 15.7, 4096 tokens 22.7 -> 22.05,
+// 16384 tokens 42.2 -> 41.6.
 // ------------------------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -82,11 +89,25 @@ __device__ __forceinline__ uint32_t float_to_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// A thread's first scores of a row (past the row's room: the last one again), requested before its sequence is known.
+constexpr int SCORES_AT_ONCE = 4;
+template <int NT>
+struct FirstScores {
+  float x[SCORES_AT_ONCE];
+  __device__ __forceinline__ FirstScores(const float *__restrict__ srow, int nw_max) {
+#pragma unroll
+    for (int i = 0; i < SCORES_AT_ONCE; ++i) x[i] = 0.0f;
+    if (nw_max > 0)
+#pragma unroll
+      for (int i = 0; i < SCORES_AT_ONCE; ++i) x[i] = srow[min((int)threadIdx.x + i * NT, nw_max - 1)];
+  }
+};
+
 // Steps 1-3 for the row of window scores srow: the selected windows, ascending, are left in keys (LDS, nw_max entries)
 // and, if wrow is not null, written there.  Returns the number of review tokens they hold.
 template <int NT>
-__device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, const float *__restrict__ srow, uint32_t *keys,
-                                              int32_t *__restrict__ wrow) {
+__device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, const float *__restrict__ srow, const FirstScores<NT> &first,
+                                              uint32_t *keys, int32_t *__restrict__ wrow) {
   __shared__ uint32_t hist[2 * NT];
   __shared__ uint32_t wave_a[NT / 64], wave_b[NT / 64];
   __shared__ uint32_t counts[TOPK_ITERS * TOPK_WAVES];      // windows per wave and 1024: greater | equal << 16
@@ -100,18 +121,24 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
   if (k > 0) {
     // ---- 1. keys and their range ------------------------------------------------------------
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    constexpr int AT_ONCE = 4;                    // scores requested together
-    for (int w0 = tid; w0 < nw; w0 += AT_ONCE * NT) {
-      float x[AT_ONCE];
+    constexpr int AT_ONCE = SCORES_AT_ONCE;
+    float x[AT_ONCE];
+#pragma unroll
+    for (int i = 0; i < AT_ONCE; ++i) x[i] = first.x[i];
+    for (int w0 = tid;;) {
+#pragma unroll
+      for (int i = 0; i < AT_ONCE; ++i) {
+        const int w = w0 + i * NT;
+        const bool in = w < nw;
+        const uint32_t key = float_to_key(x[i]);
+        if (in) keys[w] = key;
+        kmin = min(kmin, in ? key : 0xffffffffu);
+        kmax = max(kmax, in ? key : 0u);
+      }
+      w0 += AT_ONCE * NT;
+      if (w0 >= nw) break;
 #pragma unroll
       for (int i = 0; i < AT_ONCE; ++i) x[i] = srow[min(w0 + i * NT, nw - 1)];
-#pragma unroll
-      for (int i = 0; i < AT_ONCE; ++i) {         // (past the end: the last one's key again, written nowhere)
-        const uint32_t key = float_to_key(x[i]);
-        if (w0 + i * NT < nw) keys[w0 + i * NT] = key;
-        kmin = min(kmin, key);
-        kmax = max(kmax, key);
-      }
     }
     kmin = ~wave_largest(~kmin);
     kmax = wave_largest(kmax);
@@ -226,12 +253,21 @@ __global__ __launch_bounds__(NT) void topk_kernel(Shape s, BatchParams bp, Group
                                                             int32_t *__restrict__ tok_idx,
                                                             int32_t *__restrict__ n_keep) {
   extern __shared__ uint32_t keys[];            // [nw_max], later reused for the selected list
-  const int bh = blockIdx.x, b = bh / s.Hkv, g = blockIdx.y;
-  SeqParam sp = bp.seq[b];
-  if (gk.in_use) sp.k = gk.k[g * s.B + b];      // the group's own budget
+  // Two trips to memory: the arguments; the sequence's record, the group's budget and the first scores.
+  asm volatile("" ::"s"(s.B), "s"(s.Hkv), "s"(s.hkv_magic), "s"(s.w_obs), "s"(s.nw_max), "s"(s.k_max), "s"(s.nkeep_max), "s"(gk.in_use), "s"(sc),
+               "s"(win_idx), "s"(tok_idx), "s"(n_keep));
+  const int bh = blockIdx.x, b = divide(bh, s.hkv_magic), g = blockIdx.y;
   const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
+  const float *srow = sc + row * s.nw_max;
+  const FirstScores<NT> first(srow, s.nw_max);
+  SeqParam sp = bp.seq[b];
+  const int own = g * s.B + b;                  // the group's own budget, if it has one: a half of a word, so that it is a scalar load
+  const uint32_t two = gk.in_use ? ((const uint32_t *)gk.k)[own >> 1] : 0u;
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(sp.L), "s"(sp.win), "s"(sp.k), "s"(sp.win_magic), "s"(two));
+  if (gk.in_use) sp.k = (int)(own & 1 ? two >> 16 : two & 0xffffu);
   int32_t *wrow = win_idx + row * s.k_max;
-  const int n_rev_kept = select_windows<NT>(sp, s.w_obs, sc + row * s.nw_max, keys, wrow);
+  const int n_rev_kept = select_windows<NT>(sp, s.w_obs, srow, first, keys, wrow);
   for (int i = sp.k + threadIdx.x; i < s.k_max; i += NT) wrow[i] = -1;
   const TokenOf token(sp, s.w_obs, keys, n_rev_kept);
   for (int r = threadIdx.x; r < s.nkeep_max; r += NT) tok_idx[row * s.nkeep_max + r] = token(r);
@@ -252,20 +288,31 @@ __global__ __launch_bounds__(SMALL_THREADS) void select_gather_kernel(Shape s, S
                                                                      int32_t *__restrict__ n_keep) {
   extern __shared__ uint32_t keys[];
   constexpr int ROWS = SMALL_THREADS / LPR, AHEAD = 4;
-  const int split = blockIdx.x, bh = blockIdx.y, b = bh / s.Hkv, h = bh % s.Hkv, layer = blockIdx.z >> 1, is_v = blockIdx.z & 1;
-  const int g = layer / job.gamma;
-  SeqParam sp = job.seq[b];
-  if (job.own_budgets) sp.k = job.k[g * s.B + b];
+  // Two trips to memory: the arguments; the sequence's record, its budget and the first scores.
+  const int split = blockIdx.x, bh = blockIdx.y, layer = blockIdx.z >> 1, is_v = blockIdx.z & 1;
+  const char *src = (const char *)job.in[layer][is_v];
+  char *dst = (char *)job.out[layer][is_v];
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(src), "s"(dst), "s"(s.B), "s"(s.Hkv), "s"(s.hkv_magic), "s"(s.w_obs), "s"(s.nw_max), "s"(s.k_max), "s"(s.nkeep_max), "s"(s.fill_padding),
+               "s"(s.kv_sb), "s"(s.kv_sh), "s"(s.kv_st), "s"(s.o_sb), "s"(s.o_sh), "s"(s.o_st), "s"(job.gamma), "s"(job.gamma_magic), "s"(job.esize),
+               "s"(sc), "s"(win_idx), "s"(tok_idx), "s"(n_keep));
+  const int b = divide(bh, s.hkv_magic), h = bh - b * s.Hkv, g = divide(layer, job.gamma_magic);
   const int64_t row = (int64_t)g * s.B * s.Hkv + bh;
+  const float *srow = sc + row * s.nw_max;
+  const FirstScores<SMALL_THREADS> first(srow, s.nw_max);
+  SeqParam sp = job.seq[b];
+  sp.k = job.k[g * s.B + b];
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(sp.L), "s"(sp.win), "s"(sp.k), "s"(sp.win_magic));
   const bool writer = split == 0 && blockIdx.z == 2 * g * job.gamma;       // this row's index outputs are this workgroup's
   int32_t *wrow = writer ? win_idx + row * s.k_max : nullptr;
-  const int n_rev_kept = select_windows<SMALL_THREADS>(sp, s.w_obs, sc + row * s.nw_max, keys, wrow);
+  const int n_rev_kept = select_windows<SMALL_THREADS>(sp, s.w_obs, srow, first, keys, wrow);
   const TokenOf token(sp, s.w_obs, keys, n_rev_kept);
   const int nk = token.nk, n_write = s.fill_padding ? s.nkeep_max : nk;
 
   const int piece = threadIdx.x % LPR;
-  const char *src = (const char *)job.in[layer][is_v] + ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * job.esize + piece * 16;
-  char *dst = (char *)job.out[layer][is_v] + ((int64_t)b * s.o_sb + (int64_t)h * s.o_sh) * job.esize + piece * 16;
+  src += ((int64_t)b * s.kv_sb + (int64_t)h * s.kv_sh) * job.esize + piece * 16;
+  dst += ((int64_t)b * s.o_sb + (int64_t)h * s.o_sh) * job.esize + piece * 16;
   const int64_t in_step = s.kv_st * job.esize, out_step = s.o_st * job.esize;
   // rows ROWS * gridDim.x apart: the workgroups of a pair write one dense stretch; the next AHEAD rows are requested before these are stored
   const int step = ROWS * (int)gridDim.x;
@@ -299,10 +346,10 @@ hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, const Gro
                                 const float *sc, int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream) {
   SmallJob job;
   job.gamma = gamma;
-  job.own_budgets = gk.in_use;
+  job.gamma_magic = division_magic(gamma);
   job.esize = (int32_t)elem_bytes(s.dtype);
   for (int b = 0; b < s.B; ++b) job.seq[b] = bp.seq[b];
-  for (int i = 0; i < n_groups * s.B; ++i) job.k[i] = gk.k[i];
+  for (int i = 0; i < n_groups * s.B; ++i) job.k[i] = gk.in_use ? gk.k[i] : bp.seq[i % s.B].k;
   for (int l = 0; l < n_groups * gamma; ++l) {
     job.in[l][0] = lp.k_in[l]; job.in[l][1] = lp.v_in[l];
     job.out[l][0] = lp.k_out[l]; job.out[l][1] = lp.v_out[l];

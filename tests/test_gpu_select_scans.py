@@ -35,6 +35,30 @@ def test_top_k_by_window_count(nw, device):
             assert bool((ti[0, h, len(tok):] == -1).all())
 
 
+@pytest.mark.parametrize("nw", [1, 100, 2047, 2048, 4096])
+def test_room_past_the_windows_of_a_sequence(nw, device):
+    # a thread's first scores are requested before its sequence is known: what lies past the windows of a shorter one counts for nothing
+    H, w_obs, room = 2, 1, 4200
+    rng = np.random.default_rng(nw)
+    s = rng.standard_normal((3, H, room)).astype(np.float32)
+    s[1, :, nw:] = np.nan
+    s[1, 1, nw:] = np.inf
+    k = [7, (nw + 1) // 2, 0]
+    p = W.Problem(n_q_heads=H, n_kv_heads=H, head_dim=64, w_obs=w_obs, seq_len=[room + w_obs, nw + w_obs, w_obs], win=[1] * 3, top_p=[1] * 3,
+                  k_windows=k, dtype=W.WKV_BF16)
+    d = W.wkv_get_dims(p)
+    wi = torch.full((3, H, d.k_max), -7, dtype=torch.int32, device=device)
+    ti = torch.full((3, H, d.nkeep_max), -7, dtype=torch.int32, device=device)
+    nk = torch.zeros((3, H), dtype=torch.int32, device=device)
+    W.wkv_topk_windows(p, torch.from_numpy(s).to(device), wi, ti, nk)
+    torch.cuda.synchronize()
+    for b, n in enumerate((room, nw, 0)):
+        for h in range(H):
+            want = np.sort(np.argsort(-s[b, h, :n], kind="stable")[: k[b]])
+            assert np.array_equal(wi[b, h, : k[b]].cpu().numpy(), want) and bool((wi[b, h, k[b]:] == -1).all())
+            assert int(nk[b, h]) == k[b] + w_obs and np.array_equal(ti[b, h, : k[b]].cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("seq_len,k", [([9000], 476), ([9000], 477), ([5200, 4000], 156), ([5200, 4000], 157)])
 def test_compact_caches_around_the_limit_of_one_launch(seq_len, k, device):
     # 60 MB (one sequence) and 40 MB (two) exactly, and a window more: one launch, and two
