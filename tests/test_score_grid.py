@@ -27,5 +27,5 @@ def test_batches_and_rows(batch, heads, groups, device):
     from tests.test_gpu_parity import run_and_check
     lens = [40 + 97 * ((5 * b) % batch) for b in range(batch)]
     w = S.scaled_workload(S.make_workload("c4"), name="score_grid", n_q_heads=4 * heads, n_kv_heads=heads, n_groups=groups, gamma=1, seq_len=lens,
-                          win=[8, 24] * (batch // 2) + [16] * (batch % 2), top_p=[5] * batch, k_windows=[1] * batch)
+                          win=[8, 24] * (batch // 2) + [16] * (batch % 2), top_p=[5] * batch, k_windows=[1] * batch, planted_spans=0)
     run_and_check(w, device, n_oracle=4, n_gather_cpu=1, stage_groups=[groups - 1])
