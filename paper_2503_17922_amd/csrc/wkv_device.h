@@ -48,6 +48,19 @@ __device__ __forceinline__ typename TileOf<TS>::acc mfma_step(bf16x8 a, bf16x8 b
 template <typename T>
 __device__ __forceinline__ T load_scalar(const T *p) { return *(const __attribute__((address_space(4))) T *)(uintptr_t)p; }
 
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+// A DMA instruction: 64 lanes fetch 16 bytes each from addresses of their own, to lds, lds + 16, ... in lane order.
+// m0 holds the LDS address; naming it as overwritten keeps the compiler's own uses of it, should there be any,
+// clear of this one (it is a reserved register, which clang warns of: nothing relies on its being preserved).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *p) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(p) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 

@@ -84,6 +84,20 @@ struct Shape {
   int64_t o_sb, o_sh, o_st;
 };
 
+inline SmallJob small_job(const Shape &s, const BatchParams &bp, const GroupK &gk, const LayerPtrs &lp, int32_t n_groups, int32_t gamma) {
+  SmallJob job;
+  job.gamma = gamma;
+  job.gamma_magic = division_magic(gamma);
+  job.esize = (int32_t)elem_bytes(s.dtype);
+  for (int b = 0; b < s.B; ++b) job.seq[b] = bp.seq[b];
+  for (int i = 0; i < n_groups * s.B; ++i) job.k[i] = gk.in_use ? gk.k[i] : bp.seq[i % s.B].k;
+  for (int l = 0; l < n_groups * gamma; ++l) {
+    job.in[l][0] = lp.k_in[l]; job.in[l][1] = lp.v_in[l];
+    job.out[l][0] = lp.k_out[l]; job.out[l][1] = lp.v_out[l];
+  }
+  return job;
+}
+
 // How the score passes split the key axis into workgroup chunks.
 // Token scores that the score pass stages in LDS before it pools them or writes them out.
 constexpr int32_t SCORE_SEG = 2048;
@@ -192,6 +206,24 @@ inline bool selects_and_gathers(const Shape &s, int32_t n_groups, int32_t gamma)
          pairs <= SMALL_WORKGROUPS && pairs * s.nkeep_max * s.d * elem_bytes(s.dtype) <= (s.B == 1 ? SMALL_BYTES_ONE : SMALL_BYTES);
 }
 
+// The whole call in one launch?  Every workgroup scores a whole row by itself (wkv_short.hip), which takes the place of the two passes where a row
+// is short, and as many workgroups as (row, tensor) pairs do so side by side: one a compute unit.
+constexpr int32_t SHORT_WORKGROUPS = 256;
+// Key tiles of 16 that a wave of eight holds, at most, by the row tiles of 16 (1, 2, 4 or 8): four are 512 keys.  0: not in one launch.  16-bit types take what
+// fits the registers; all of it gains, 16 to 128 rows a KV head, 200 to 1000 keys: 0.48 to 0.84 of the time of the passes with the merged selection
+// and gather, 1, 2, 4 and 8 sequences alike.  fp32 is a matrix product of 1/16 the rate, done by every workgroup: 16 rows of 64 channels 0.50 to 0.77,
+// 32 rows 0.64, 16 rows of 128 channels 0.61; 32 rows of 1000 keys would take 1.39, 64 rows of 512 keys 1.24, 32 rows of 128 channels 1.27.
+constexpr int32_t short_key_tiles(int32_t d, int32_t esize, int32_t row_tiles) {
+  if (esize == 4) return row_tiles == 1 ? (d == 64 ? 8 : 4) : d == 64 && row_tiles == 2 ? 4 : 0;
+  return row_tiles <= 2 || (d == 64 && row_tiles == 4) ? 8 : 4;
+}
+inline int32_t short_row_tiles(const Shape &s) { return s.M <= 16 ? 1 : s.M <= 32 ? 2 : s.M <= 64 ? 4 : s.M <= 128 ? 8 : 0; }
+inline bool whole_call_in_one(const Shape &s, int32_t n_groups, int32_t gamma) {
+  const int32_t tiles = short_row_tiles(s);
+  return tiles > 0 && s.t_stride + s.w_obs <= 128 * short_key_tiles(s.d, (int32_t)elem_bytes(s.dtype), tiles) && selects_and_gathers(s, n_groups, gamma) &&
+         2 * n_groups * gamma * s.B * s.Hkv <= SHORT_WORKGROUPS;
+}
+
 // Workgroups over the rows of a compact cache, two pieces of `rows` rows each, `apart` pieces from one to the other; the ones from
 // `last` on share what is left, last_apart pieces apart: all but the very last hold two pieces.
 struct GatherGrid {
@@ -245,6 +277,9 @@ hipError_t launch_topk(const Shape &s, const BatchParams &bp, const GroupK &gk, 
 // The same, and the rows of the layers `lp`, gamma per group, in one launch (see selects_and_gathers).
 hipError_t launch_select_gather(const Shape &s, const BatchParams &bp, const GroupK &gk, const LayerPtrs &lp, int32_t n_groups, int32_t gamma,
                                 const float *sc, int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream);
+// Scores, selection and the rows in one launch (see whole_call_in_one).
+hipError_t launch_short(const Shape &s, const BatchParams &bp, const GroupK &gk, const GroupPtrs &gp, const LayerPtrs &lp, int32_t n_groups, int32_t gamma,
+                        float *sc, int32_t *win_idx, int32_t *tok_idx, int32_t *n_keep, hipStream_t stream);
 hipError_t launch_gather(const Shape &s, const BatchParams &bp, const LayerPtrs &lp, int32_t n_layers, int32_t gamma,
                          const int32_t *tok_idx, const int32_t *n_keep, hipStream_t stream);
 

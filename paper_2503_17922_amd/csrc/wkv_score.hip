@@ -187,16 +187,11 @@ struct ScoreConfig {
   static __device__ __forceinline__ int tile_row(int sub, int e) { return e / 4 * (4 * PPS) + sub * 4 + e % 4; }
 };
 
-__device__ __forceinline__ uint32_t lds_address(const void *p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
-}
 // At most N loads outstanding, every LDS read returned.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 
-// A DMA instruction of the ring: 64 lanes fetch 16 bytes each, to lds, lds + 16, ... in lane order.  From base + off bytes, or from
-// an address per lane.  m0 holds the LDS address; naming it as overwritten keeps the compiler's own uses of it, should there be any,
-// clear of this one (it is a reserved register, which clang warns of: nothing relies on its being preserved).
+// A DMA instruction of the ring from base + off bytes (wkv_device.h has the one with an address per lane).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 template <bool NT_LOADS>
@@ -205,9 +200,6 @@ __device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *base, uint3
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
-}
-__device__ __forceinline__ void dma_to_lds(uint32_t lds, const char *p) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(p) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 

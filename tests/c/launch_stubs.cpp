@@ -18,6 +18,8 @@ hipError_t launch_topk(const Shape &, const BatchParams &, const GroupK &, int32
                        int32_t *, hipStream_t) { ++wkv_stub_launches; return hipSuccess; }
 hipError_t launch_select_gather(const Shape &, const BatchParams &, const GroupK &, const LayerPtrs &, int32_t, int32_t, const float *,
                                 int32_t *, int32_t *, int32_t *, hipStream_t) { ++wkv_stub_launches; return hipSuccess; }
+hipError_t launch_short(const Shape &, const BatchParams &, const GroupK &, const GroupPtrs &, const LayerPtrs &, int32_t, int32_t, float *, int32_t *,
+                        int32_t *, int32_t *, hipStream_t) { ++wkv_stub_launches; return hipSuccess; }
 hipError_t launch_gather(const Shape &, const BatchParams &, const LayerPtrs &, int32_t, int32_t, const int32_t *, const int32_t *, hipStream_t) {
   ++wkv_stub_launches; return hipSuccess;
 }
