@@ -39,13 +39,16 @@ struct FoldShare {
   __device__ __forceinline__ FoldShare(int rows) : tpr(max(NT / rows, 1)) { row = threadIdx.x % (NT / tpr); first = threadIdx.x / (NT / tpr); }
 };
 // The partials of chunks at + first, tpr further on, ...  (Only as many requests as there are chunks for: each costs time before the
-// key stream begins.)
+// key stream begins.  By offsets of 32 bits: at most 64 chunks of 256 rows here, and in fold_kernel the 2^15 that a sequence can have.)
 template <int NT>
 __device__ __forceinline__ void fold_load(float2 (&p)[FOLD_AT_ONCE], const float2 *__restrict__ part, int n_chunks, int m_pad, const FoldShare<NT> &me, int at) {
+  const uint32_t step = (uint32_t)(me.tpr * m_pad) * 8u, last = ((uint32_t)(n_chunks - 1) * m_pad + me.row) * 8u;
+  uint32_t off = ((uint32_t)(at + me.first) * m_pad + me.row) * 8u;
 #pragma unroll
   for (int i = 0; i < FOLD_AT_ONCE; ++i) {
     p[i] = make_float2(-INFINITY, 0.0f);
-    if (at + i * me.tpr < n_chunks) p[i] = part[min(at + me.first + i * me.tpr, n_chunks - 1) * m_pad + me.row];
+    if (at + i * me.tpr < n_chunks) p[i] = *(const float2 *)((const char *)part + min(off, last));
+    off += step;
   }
 }
 
@@ -149,6 +152,9 @@ __device__ __forceinline__ float row_lse2(const Shape &s, const float *__restric
 // (1.5), partials to normalisers 0.8 (1.2), queries to registers 0.6 (0.7).  Requests are issued at 20 bytes a cycle and compute unit, so the 32 KB of queries cost what as many
 // keys cost.  The fold's requests stand before the queries', not behind them: 1.8 (3.6) us for the fold before.  Requested by whole rows instead
 // of fragments, the queries of 256 rows take 1.9 instead of 2.6 us.
+// The start runs through its code once, at some 7 cycles an instruction (each launch fetches it anew), so its length counts as well: 120 comparisons of
+// the unrolled windows, which the compiler had put ahead of the key stream, 50 instructions per query request and 10 per partial, and a third trip
+// for arguments of the fold.  Without them 4096 tokens 22.25 -> 21.1 us a call, 16384 with sorted windows 41.2 -> 38.9, 256 rows of 16381 in 8 groups 277 -> 274.
 constexpr int score_slots(int row_groups) { return row_groups == 4 ? 2 : 4; }         // key tile slots of a workgroup
 constexpr int score_threads(int row_groups) { return 64 * row_groups * score_slots(row_groups); }
 
@@ -227,6 +233,7 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Sc
   asm volatile("" ::"s"(ends[0]), "s"(ends[1]), "s"(ends[2]), "s"(ends[3]), "s"(ends[4]), "s"(ends[5]), "s"(ends[6]), "s"(ends[7]),
                "s"(s.B), "s"(s.Hkv), "s"(s.w_obs), "s"(s.G), "s"(s.M), "s"(s.kv_st), "s"(s.kv_sh), "s"(s.kv_sb), "s"(s.q_st), "s"(s.q_sh), "s"(s.q_sb),
                "s"(a.hkv_magic), "s"(a.row_bits), "s"(a.last_x), "s"(a.last_y), "s"(a.last_z), "s"(a.items), "s"(only_if));
+  asm volatile("" ::"s"(partials), "s"(a.m_pad), "s"(a.n_chunks1), "s"(a.fold), "s"(s.w_magic), "s"(s_pool));
   // Launched behind the single-read kernel as its fall-back: nothing to do unless that kernel
   // raised the word (uniform over the grid).
   if (only_if && *only_if == 0u) return;
@@ -342,16 +349,25 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Sc
   // rows one after the other at equal distances, as in a contiguous tensor: one offset per lane serves them all
   const bool even = s.q_sh == (int64_t)s.w_obs * s.q_st && s.q_st < 0x1000000;
   const uint32_t q_lane = (uint32_t)(lane / C::PPR) * (uint32_t)s.q_st * C::ES;
-  for (int f = wave; f < PIECES; f += C::WAVES) {
-    const int row = f * C::RPI + lane / C::PPR;
-    const uint32_t piece = C::swizzle(row, lane % C::PPR) * 16;
-    if (even && (f + 1) * C::RPI <= s.M) {
-      dma_to_lds<false>(lds_address(ring) + query_at(f), qbase + (int64_t)(f * C::RPI) * s.q_st * C::ES, q_lane + piece);
-    } else {
-      const int r = min(row, s.M - 1);
-      const int hq = (int)((uint32_t)r * s.w_magic >> 16), io = r - hq * s.w_obs;      // r / w_obs, r % w_obs
-      dma_to_lds(lds_address(ring) + query_at(f), qbase + ((int64_t)hq * s.q_sh + (int64_t)io * s.q_st) * C::ES + piece);
-    }
+  // (whole groups of such rows without a loop: one would compute its addresses anew for every instruction, 0.3 to 0.5 us of a workgroup's start.
+  // The rows of a wave are STEP apart, a power of two, so that the swizzle of the later ones differs from the first one's by constants.)
+  constexpr int STEP = C::WAVES * C::RPI;
+  const int whole = even ? s.M / C::RPI : 0;                  // DMA instructions
+  const int row0 = wave * C::RPI + lane / C::PPR;
+  const uint32_t piece0 = C::swizzle(row0, lane % C::PPR) * 16;
+  const char *qp = qbase + (int64_t)(wave * C::RPI) * s.q_st * C::ES;
+#pragma unroll
+  for (int i = 0; i * C::WAVES < PIECES; ++i) {
+    const int f = wave + i * C::WAVES;
+    const uint32_t turned = (C::PPR == 8 ? (i * STEP >> 1) & 7 : (i * STEP) & 15) * 16;
+    if (f < (PIECES < whole ? PIECES : whole))
+      dma_to_lds<false>(lds_address(ring) + (PER_RING % C::WAVES == 0 ? query_at(i * C::WAVES) + wave * 1024 : query_at(f)), qp, q_lane + (piece0 ^ turned));
+    qp += (int64_t)STEP * s.q_st * C::ES;
+  }
+  for (int f = wave + (whole + C::WAVES - 1 - wave) / C::WAVES * C::WAVES; f < PIECES; f += C::WAVES) {
+    const int row = f * C::RPI + lane / C::PPR, r = min(row, s.M - 1);
+    const int hq = (int)((uint32_t)r * s.w_magic >> 16), io = r - hq * s.w_obs;      // r / w_obs, r % w_obs
+    dma_to_lds(lds_address(ring) + query_at(f), qbase + ((int64_t)hq * s.q_sh + (int64_t)io * s.q_st) * C::ES + C::swizzle(row, lane % C::PPR) * 16);
   }
   if (PASS == 2) {
     if (a.fold) {
@@ -549,9 +565,12 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Sc
       }
       __syncthreads();
     }
-    if (s_pool)                                             // Eq. 3-4 while the token scores are in LDS
-      pool_windows<NT>(t_s, divide(seg0, win_magic), divide(seg_end + win - 1, win_magic), win, seq.packed >> 16, n_review, s_pool + row * s.nw_max);
-    else
+    if (s_pool) {                                           // Eq. 3-4 while the token scores are in LDS
+      // (what the compiler knows nothing of before: else the hundred comparisons of the unrolled windows stand ahead of the key stream)
+      int w_here = win, p_here = (int)(seq.packed >> 16);
+      asm volatile("" : "+s"(w_here), "+s"(p_here));
+      pool_windows<NT>(t_s, divide(seg0, win_magic), divide(seg_end + win - 1, win_magic), w_here, p_here, n_review, s_pool + row * s.nw_max);
+    } else
       for (int i = threadIdx.x; i < seg_end - seg0; i += NT) trow[seg0 + i] = t_s[i];
     if (seg_end == cend) break;
     __syncthreads();
