@@ -114,14 +114,16 @@ __device__ __forceinline__ void merge_state(float &m, float &l, float (&o)[E], f
 // Partial results in the workspace: the outputs [B*Hkv][splits][G][D] of every key range (only of ranges that
 // hold rows), then their (m, l) [B*Hkv][splits][G].  A range past the end of a row has m = -inf; m of range 0
 // is NaN where the cache cannot take the new row.
-__device__ __forceinline__ int64_t part_index(const DecodeShape &s, int bh, int split, int g) {
-  return ((int64_t)bh * s.n_splits + split) * s.G + g;
+// (Byte offsets fit 32 bits: at most 65535 heads of one range each, or 1536 ranges, times eight query heads of 130 floats.  A launch runs
+// through its code once, at some 7 cycles an instruction, and products of 64 bits are a dozen of them.)
+__device__ __forceinline__ uint32_t part_index(const DecodeShape &s, int bh, int split, int g) {
+  return ((uint32_t)bh * s.n_splits + split) * s.G + g;
 }
-__device__ __forceinline__ float2 *part_stats(const DecodeShape &s, float *part) {
-  return (float2 *)(part + (int64_t)s.B * s.Hkv * s.n_splits * s.G * s.d);
+__device__ __forceinline__ float2 &part_stats(const DecodeShape &s, float *part, uint32_t at) {
+  return *(float2 *)((char *)part + (s.stats_at + at * 8u));
 }
-__device__ __forceinline__ const float2 *part_stats(const DecodeShape &s, const float *part) {
-  return (const float2 *)(part + (int64_t)s.B * s.Hkv * s.n_splits * s.G * s.d);
+__device__ __forceinline__ const float2 &part_stats(const DecodeShape &s, const float *part, uint32_t at) {
+  return *(const float2 *)((const char *)part + (s.stats_at + at * 8u));
 }
 
 // Merge the per-wave states in LDS ([wave][head][D outputs, m, l]) and store the workgroup's
@@ -144,9 +146,9 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeShape &s, floa
         oo += wave_state[w][g][c] * a;
       }
     }
-    const int64_t at = part_index(s, bh, split, g);
+    const uint32_t at = part_index(s, bh, split, g);
     part[at * D + c] = oo;
-    if (c == 0) part_stats(s, part)[at] = make_float2(mm, ll);
+    if (c == 0) part_stats(s, part, at) = make_float2(mm, ll);
   }
 }
 
@@ -154,9 +156,9 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeShape &s, floa
 template <int G>
 __device__ __forceinline__ bool nothing_to_do(const DecodeShape &s, int bh, int split, int n, int c0, int cend,
                                               float *__restrict__ part) {
-  if (c0 < cend) return false;
+  if (__builtin_expect(c0 < cend, 1)) return false;
   if (threadIdx.x < G)
-    part_stats(s, part)[part_index(s, bh, split, threadIdx.x)] =
+    part_stats(s, part, part_index(s, bh, split, threadIdx.x)) =
         make_float2(split == 0 && (n < 0 || n >= s.capacity) ? __uint_as_float(0x7fc00000u) : -INFINITY, 0.0f);
   return true;
 }
@@ -360,7 +362,9 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
 // divided by multiplication.  Such a layer with its merge 11.3 us with one block requested ahead of the one in hand (the compiler
 // put the request of the second behind the arrival of the first), 10.1 us so; eleven sequences of mixed lengths, 28q/4kv heads, f16, a layer
 // 16.6 and 14.8 us; 64 sequences 169 and 167.  Ranges of 64 rows, one block a wave: 10.9, 14.7 and 167 us.  Three waves a SIMD: with
-// four, the registers of two blocks spill.
+// four, the registers of two blocks spill.  Ranges of a block a wave without a state before it, a lane's rows by one multiplication each, the caches'
+// addresses while the row count is under way; here and in the merge offsets of 32 bits into the partial results: one sequence of 4128 rows through 32
+// layers 309 -> 298 us, of 20000 rows 22.0 -> 20.6 a layer, three of 4128 14.4 -> 13.7, fp32 with four 21.3 -> 20.8.
 // The value of lane N of each 16-lane DPP row, in all its lanes.
 template <int N>
 __device__ __forceinline__ float row_bcast(float x) {
@@ -385,17 +389,21 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
 
   // (all arguments together, ahead of the row count that depends on one of them)
   asm volatile("" ::"s"(s.B), "s"(s.Hkv), "s"(s.heads_magic), "s"(s.kv_magic), "s"(s.chunk), "s"(s.capacity), "s"(s.c1), "s"(s.sb), "s"(s.sh), "s"(s.st),
-               "s"(s.per_lane), "s"(s.chunk_magic), "s"(s.n_splits), "s"(q_new), "s"(k_cache), "s"(v_cache), "s"(n_valid), "s"(part));
+               "s"(s.per_lane), "s"(s.chunk_magic), "s"(s.n_splits), "s"(s.G), "s"(s.stats_at), "s"(q_new), "s"(k_cache), "s"(v_cache), "s"(n_valid), "s"(part));
   const KeyRange item = find_range<BY_COUNT>(s, n_valid);
   const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;            // score side: head, 4 rows
   const int piece = lane % LPK, sub = col / LPK;          // value side: 16-byte piece, which of the quad's rows in flight
+  const int64_t head_at = ((int64_t)b * s.sb + (int64_t)h * s.sh) * 2, row_bytes = s.st * 2;
+  const char *kc = (const char *)k_cache + head_at, *vc = (const char *)v_cache + head_at;
+
+  if (!PAIRS) {
+    __builtin_amdgcn_sched_barrier(0);       // (all that while the row count is under way)
+    asm volatile("" ::"s"(kc), "s"(vc));
+  }
   const int n = item.n, c0 = split * s.chunk, cend = min(c0 + s.chunk, n < s.capacity ? n : 0);
   if (nothing_to_do<G>(s, bh, split, n, c0, cend, part)) return;
-
-  const uint16_t *kc = k_cache + (int64_t)b * s.sb + (int64_t)h * s.sh + quad * 8;
-  const uint16_t *vc = v_cache + (int64_t)b * s.sb + (int64_t)h * s.sh + piece * E;
 
   // query rows as B fragments: lane (head col, quad) holds channels 32*ks + 8*quad .. +7; columns past the
   // last head repeat it and are not used
@@ -407,17 +415,37 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
 
   float m = -INFINITY, l = 0.0f;             // of head `col` (lanes with col < G), l over this lane's rows only
   float o[G * E];                            // [head][channel of the piece]
-#pragma unroll
-  for (int i = 0; i < G * E; ++i) o[i] = 0.0f;
 
   // Blocks of 16 rows, every WAVES-th of the range, by four waves two at a time: a range of 128 rows is one round trip to memory.
   struct Block { uint4 k[KS], v[VT]; };
+  // (Rows past the range: its last one again.)
   auto load_block = [&](Block &x, int blk) __attribute__((always_inline)) {
-    const int r0 = c0 + blk * 16;
+    const char *kr = kc, *vr = vc;
+    int64_t ka, va[VT];
+    if constexpr (PAIRS) {
+      const int r0 = c0 + blk * 16;
+      ka = min(r0 + col, cend - 1) * row_bytes;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) x.k[ks] = load_piece<(STREAM > 1)>(kc + (int64_t)min(r0 + col, cend - 1) * s.st + ks * 32);
+      for (int t = 0; t < VT; ++t) va[t] = min(r0 + quad * 4 + t * (4 / VT) + sub, cend - 1) * row_bytes;
+    } else {
+      // A lane's rows by one multiplication each, from the block's first, as row_bytes above 2^32 is as good as never: a launch of one short block a
+      // wave waits for its addresses.  (Of two blocks at once the longer scalar chain costs more: eleven mixed sequences with 28q/4kv heads 58.5 -> 59.5 us.)
+      const int r0 = min(c0 + blk * 16, cend - 1), rows = cend - 1 - r0;       // (uniform)
+      const uint32_t low = (uint32_t)row_bytes, high = (uint32_t)(row_bytes >> 32), rk = min(col, rows);
+      kr += r0 * row_bytes; vr += r0 * row_bytes;
+      ka = (int64_t)((uint64_t)rk * low);
 #pragma unroll
-    for (int t = 0; t < VT; ++t) x.v[t] = load_piece<(STREAM > 0)>(vc + (int64_t)min(r0 + quad * 4 + t * (4 / VT) + sub, cend - 1) * s.st);
+      for (int t = 0; t < VT; ++t) va[t] = (int64_t)((uint64_t)(uint32_t)min(quad * 4 + t * (4 / VT) + sub, rows) * low);
+      if (__builtin_expect(high != 0, 0)) {
+        ka += (int64_t)(rk * high) << 32;
+#pragma unroll
+        for (int t = 0; t < VT; ++t) va[t] += (int64_t)((uint32_t)min(quad * 4 + t * (4 / VT) + sub, rows) * high) << 32;
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) x.k[ks] = load_piece<(STREAM > 1)>(kr + ka + (quad * 16 + ks * 64));
+#pragma unroll
+    for (int t = 0; t < VT; ++t) x.v[t] = load_piece<(STREAM > 0)>(vr + va[t] + piece * 16);
   };
   auto attend = [&](const Block &x, int blk) __attribute__((always_inline)) {
     // scores of 16 rows x 16 (padded) heads
@@ -429,20 +457,22 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
     float sc[4], pr[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) sc[e] = r0 + e < cend ? acc[e] * s.c1 : -INFINITY;
-    const float mn = fmaxf(m, quads_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]))));
+    float mn = quads_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+    if (PAIRS) mn = fmaxf(m, mn);
     // -inf: every row so far has a logit of -inf (an infinite key, products that overflow) and weighs nothing
     const bool none = mn == -INFINITY;
-    const float corr = none ? 1.0f : fast_exp2(m - mn);        // m = -inf: 0
+    const float corr = none || !PAIRS ? 1.0f : fast_exp2(m - mn);        // m = -inf: 0
     m = mn;
 #pragma unroll
     for (int e = 0; e < 4; ++e) pr[e] = none ? 0.0f : fast_exp2(sc[e] - mn);
-    l = l * corr + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
-    if (__any(corr != 1.0f && col < G))
+    l = (PAIRS ? l * corr : 0.0f) + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
+    if (PAIRS && __any(corr != 1.0f && col < G))
       static_for<G>([&](auto g) {
         const float c = row_bcast<g>(corr);
 #pragma unroll
         for (int i = 0; i < E; ++i) o[g * E + i] *= c;
       });
+    if (!PAIRS) __builtin_amdgcn_sched_barrier(0);             // (no value is waited for before the scores are done)
 #pragma unroll
     for (int t = 0; t < VT; ++t) {
       float vf[E];
@@ -454,14 +484,26 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
           p = sub ? p1 : p;
         }
 #pragma unroll
-        for (int i = 0; i < E; ++i) o[g * E + i] = fmaf(p, vf[i], o[g * E + i]);
+        for (int i = 0; i < E; ++i) o[g * E + i] = PAIRS || t > 0 ? fmaf(p, vf[i], o[g * E + i]) : p * vf[i];
       });
     }
   };
-  for (int blk = wave; c0 + blk * 16 < cend; blk += WAVES) {
-    Block x, next;
-    load_block(x, blk);
-    if constexpr (PAIRS) {
+  if constexpr (!PAIRS) {                      // one block a wave, nothing before it (launch_partial_g)
+    if (c0 + wave * 16 < cend) {
+      Block x;
+      load_block(x, wave);
+      __builtin_amdgcn_sched_barrier(0);       // the values too, before the scores wait for the keys
+      attend(x, wave);
+    } else {
+#pragma unroll
+      for (int i = 0; i < G * E; ++i) o[i] = 0.0f;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < G * E; ++i) o[i] = 0.0f;
+    for (int blk = wave; c0 + blk * 16 < cend; blk += WAVES) {
+      Block x, next;
+      load_block(x, blk);
       // (past the end: the last row again, which the chip has at hand.  Around a branch instead: one sequence of 4128 rows, 64q/8kv heads 10.30 ->
       // 10.66 us a layer, eleven mixed with 12q/2kv 12.03 -> 12.85, sixteen of 70 rows 8.60 -> 8.83, 64 of 4128 rows 167.4 -> 168.7)
       load_block(next, blk + WAVES);
@@ -473,9 +515,6 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
         x = next;
       }
       __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), reached by now but for rows requested past the end; else the compiler waits for the queries among the first requests
-    } else {
-      __builtin_amdgcn_sched_barrier(0);       // the values too, before the scores wait for the keys
-      attend(x, blk);
     }
   }
 
@@ -515,9 +554,9 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
       ll = fmaf(ml_s[w][g].y, a, ll);
       oo.x = fmaf(x.x, a, oo.x); oo.y = fmaf(x.y, a, oo.y); oo.z = fmaf(x.z, a, oo.z); oo.w = fmaf(x.w, a, oo.w);
     }
-    const int64_t at = part_index(s, bh, split, g);
-    *(float4 *)(part + at * D + c) = oo;
-    if (c == 0) part_stats(s, part)[at] = make_float2(mm, ll);
+    const uint32_t at = part_index(s, bh, split, g);
+    *(float4 *)((char *)part + (at * D + c) * 4u) = oo;
+    if (c == 0) part_stats(s, part, at) = make_float2(mm, ll);
   }
 }
 
@@ -536,13 +575,13 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
   constexpr int COLS = D / 4, GROUPS = NT / COLS, AHEAD = NT == 64 ? 4 : 6, WAVES = NT / 64;
   constexpr int E = Piece<T>::E, LPK = D / E;
   constexpr bool FEW = NT == 64;
-  __shared__ float wgt[FEW ? 1 : NT];
+  __shared__ float wgt[FEW ? 1 : NT + AHEAD * GROUPS];             // (the ones past the last range are 0)
   __shared__ __attribute__((aligned(16))) float acc_s[GROUPS][D];
   __shared__ float q_k[2];
   __shared__ float wave_m[WAVES], wave_l[WAVES];
   // Two trips to memory: the arguments, then everything that follows from them.
   asm volatile("" ::"s"(s.B), "s"(s.Hkv), "s"(s.G), "s"(s.d), "s"(s.kv_magic), "s"(s.capacity), "s"(s.n_splits), "s"(s.c1), "s"(s.sb), "s"(s.sh), "s"(s.st),
-               "s"(s.keep_count), "s"(q_new), "s"(k_new), "s"(v_new), "s"(k_cache), "s"(v_cache), "s"(part), "s"(n_valid), "s"(out));
+               "s"(s.keep_count), "s"(s.stats_at), "s"(q_new), "s"(k_new), "s"(v_new), "s"(k_cache), "s"(v_cache), "s"(part), "s"(n_valid), "s"(out));
   const int bh = blockIdx.x, g = blockIdx.y, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int grp = tid / COLS, col = tid % COLS;
@@ -550,11 +589,19 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
 
   // statistics of this head's ranges (one per thread), outputs of the first ranges, the new token
   float2 ml = make_float2(-INFINITY, 0.0f);
-  if (tid < s.n_splits) ml = part_stats(s, part)[part_index(s, bh, tid, g)];
-  const float4 *po = (const float4 *)(part + part_index(s, bh, 0, g) * D) + col;     // range sp: sp * G * COLS further on
+  if (tid < s.n_splits) ml = part_stats(s, part, part_index(s, bh, tid, g));
+  const char *po = (const char *)part + part_index(s, bh, 0, g) * (D * 4u);         // range sp: sp * range_bytes further on
+  const uint32_t range_bytes = s.G * (D * 4u), last_range = (s.n_splits - 1) * range_bytes;
+  uint32_t out_at = grp * range_bytes;
   float4 pre[AHEAD];
+  auto request = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(grp + u * GROUPS, s.n_splits - 1) * s.G * COLS];
+    for (int u = 0; u < AHEAD; ++u) {
+      pre[u] = *(const float4 *)(po + (min(out_at, last_range) + col * 16u));
+      out_at += GROUPS * range_bytes;
+    }
+  };
+  request();
   const bool appends = g == 0 && tid < 2 * LPK;             // the new row, by head 0's workgroup: keys, then values
   uint4 row_piece = make_uint4(0, 0, 0, 0);
   if (appends) row_piece = *(const uint4 *)((tid < LPK ? k_new : v_new) + (int64_t)bh * D + tid % LPK * E);
@@ -601,7 +648,8 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
     for (int w = 0; w < WAVES; ++w) m = fmaxf(m, wave_m[w]);
     a = fast_exp2(ml.x - m);                            // a range without rows: 0
     l = wave_sum(ml.x == -INFINITY ? 0.0f : ml.y * a);
-    if (tid < s.n_splits) wgt[tid] = a;
+    wgt[tid] = tid < s.n_splits ? a : 0.0f;
+    if (tid < AHEAD * GROUPS) wgt[NT + tid] = 0.0f;
     if (lane == 0) wave_l[wave] = l;
     __syncthreads();
     w_new = fast_exp2(logit - m);
@@ -618,16 +666,20 @@ __global__ __launch_bounds__(NT) void decode_combine_kernel(DecodeShape s, const
 #pragma unroll
     for (int u = 0; u < AHEAD; ++u) {
       const int at = sp + u * GROUPS;
-      if constexpr (FEW) w[u] = __shfl(a, at);
-      else w[u] = at < s.n_splits ? wgt[at] : 0.0f;
-      if (at >= s.n_splits) w[u] = 0.0f;
+      if constexpr (FEW) {
+        w[u] = __shfl(a, at);                          // (by all lanes)
+        if (at >= s.n_splits) w[u] = 0.0f;
+      } else {
+        w[u] = wgt[at];
+      }
     }
 #pragma unroll
-    for (int u = 0; u < AHEAD; ++u)
-      if (w[u] != 0.0f) { o.x = fmaf(pre[u].x, w[u], o.x); o.y = fmaf(pre[u].y, w[u], o.y); o.z = fmaf(pre[u].z, w[u], o.z); o.w = fmaf(pre[u].w, w[u], o.w); }
-    if (sp0 + AHEAD * GROUPS < s.n_splits)
-#pragma unroll
-      for (int u = 0; u < AHEAD; ++u) pre[u] = po[(int64_t)min(sp + (AHEAD + u) * GROUPS, s.n_splits - 1) * s.G * COLS];
+    for (int u = 0; u < AHEAD; ++u) {
+      const bool counts = w[u] != 0.0f;
+      o.x = counts ? fmaf(pre[u].x, w[u], o.x) : o.x; o.y = counts ? fmaf(pre[u].y, w[u], o.y) : o.y;
+      o.z = counts ? fmaf(pre[u].z, w[u], o.z) : o.z; o.w = counts ? fmaf(pre[u].w, w[u], o.w) : o.w;
+    }
+    if (sp0 + AHEAD * GROUPS < s.n_splits) request();
   }
   *(float4 *)&acc_s[grp][col * 4] = o;
   // (nobody reads the new row from the caches in this launch)

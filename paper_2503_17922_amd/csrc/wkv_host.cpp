@@ -380,6 +380,8 @@ wkv_status validate_decode(const wkv_decode_shape *p, Decode *out) {
   s.n_splits = (int32_t)ceil_div(s.capacity, chunk);
   s.per_lane = find_ranges_by_count(s) ? (int32_t)ceil_div(rows, 64) : 0;
   s.chunk_magic = division_magic(s.chunk / 64);
+  static_assert((int64_t)65535 * 8 * (128 + 2) * (int64_t)sizeof(float) < (int64_t)1 << 32 && total < 65535, "32-bit offsets of the partial results");
+  s.stats_at = (uint32_t)(rows * s.n_splits * s.G * s.d * (int64_t)sizeof(float));
   out->ws_bytes = (size_t)rows * s.n_splits * s.G * (s.d + 2) * sizeof(float);
   return WKV_OK;
 }

@@ -59,3 +59,27 @@ def test_pairs_of_blocks(dtype, G, d, B, cap, ranges, device):
         want, *_ = O.decode_step(qh[b, h * G:(h + 1) * G], k0[b, h, :n], v0[b, h, :n], knh[b, h], vnh[b, h])
         # products of 16-bit inputs, sums in fp32: about 1e-6 of the largest value; 1e-3 is what the other decode tests ask for
         np.testing.assert_allclose(got[b, h * G:(h + 1) * G], want, rtol=1e-3, atol=2e-5, err_msg=f"rows {n} h{h}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("G", [2, 7])
+def test_rows_more_than_4_gib_apart(G, device):
+    # keys and values of one buffer, a row's bytes past 32 bits; ranges of a block for each of eight waves, and of pairs
+    d, cap, n, st = 128, 4, 3, (1 << 31) + 1024
+    buf = torch.empty(3 * st + 1024, dtype=torch.bfloat16, device=device)
+    row = lambda i, at: buf[i * st + at: i * st + at + d]
+    gen = torch.Generator(device=device).manual_seed(5)
+    mk = lambda *shape: torch.randn(shape, device=device, dtype=torch.float32, generator=gen).to(torch.bfloat16)
+    k, v, q, kn, vn = mk(n, d), mk(n, d), 2 * mk(1, G, d), mk(1, 1, d), mk(1, 1, d)
+    for i in range(n):
+        row(i, 0).copy_(k[i])
+        row(i, 512).copy_(v[i])
+    shape = W.DecodeShape(batch=1, n_q_heads=G, n_kv_heads=1, head_dim=d, capacity=cap, dtype=W.WKV_BF16, cache_strides=(d, d, st))
+    n_valid = torch.tensor([[n]], dtype=torch.int32, device=device)
+    out = torch.zeros((1, G, d), dtype=torch.float32, device=device)
+    W.wkv_decode_step(shape, q, kn, vn, buf, buf[512:], n_valid, out, torch.empty(W.wkv_decode_workspace_bytes(shape), dtype=torch.uint8, device=device))
+    torch.cuda.synchronize()
+    f64 = lambda t: t.to("cpu").to(torch.float64).numpy()
+    want, *_ = O.decode_step(f64(q[0]), f64(k), f64(v), f64(kn[0, 0]), f64(vn[0, 0]))
+    np.testing.assert_allclose(f64(out[0]), want, rtol=1e-3, atol=2e-5)
+    assert torch.equal(row(n, 0), kn[0, 0]) and torch.equal(row(n, 512), vn[0, 0])
