@@ -26,7 +26,7 @@ namespace wkv {
 // together: 9.6 -> 8.0 us and 12.0 -> 10.2 us.  The arguments came in a chain of six trips to memory, each asked for where it was
 // used, the scores in a seventh: with two, score, pool, selection and gather of 4096 tokens in fp32 one by one 56.7 -> 54.3 us (half of that the
 // pooling's tokens, requested together), and merged with the gather (below) 512 tokens of two heads 16.3 -> 15.7, 4096 tokens 22.7 -> 22.05,
-// 16384 tokens 42.2 -> 41.6.
+// 16384 tokens 42.2 -> 41.6.  A thread's first keys in registers, up to 64 counts scanned by every wave for itself: 21.1 -> 20.75 and 39.0 -> 38.6.
 // ------------------------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -74,23 +74,25 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
     // ---- 1. keys and their range ------------------------------------------------------------
     uint32_t kmin = 0xffffffffu, kmax = 0u;
     constexpr int AT_ONCE = SCORES_AT_ONCE;
-    float x[AT_ONCE];
+    uint32_t own[AT_ONCE];                        // the thread's first windows' stay with it, the others' go to LDS
 #pragma unroll
-    for (int i = 0; i < AT_ONCE; ++i) x[i] = first.x[i];
-    for (int w0 = tid;;) {
-#pragma unroll
-      for (int i = 0; i < AT_ONCE; ++i) {
-        const int w = w0 + i * NT;
-        const bool in = w < nw;
-        const uint32_t key = float_to_key(x[i]);
-        if (in) keys[w] = key;
-        kmin = min(kmin, in ? key : 0xffffffffu);
-        kmax = max(kmax, in ? key : 0u);
-      }
-      w0 += AT_ONCE * NT;
-      if (w0 >= nw) break;
+    for (int i = 0; i < AT_ONCE; ++i) {
+      const bool in = tid + i * NT < nw;
+      own[i] = float_to_key(first.x[i]);
+      kmin = min(kmin, in ? own[i] : 0xffffffffu);
+      kmax = max(kmax, in ? own[i] : 0u);
+    }
+    for (int w0 = tid + AT_ONCE * NT; w0 < nw; w0 += AT_ONCE * NT) {
+      float x[AT_ONCE];
 #pragma unroll
       for (int i = 0; i < AT_ONCE; ++i) x[i] = srow[min(w0 + i * NT, nw - 1)];
+#pragma unroll
+      for (int i = 0; i < AT_ONCE; ++i) {         // (past the end: the last one's key again, written nowhere)
+        const uint32_t key = float_to_key(x[i]);
+        if (w0 + i * NT < nw) keys[w0 + i * NT] = key;
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
+      }
     }
     kmin = ~wave_largest(~kmin);
     kmax = wave_largest(kmax);
@@ -108,7 +110,10 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
     for (;;) {
       const int bits = 32 - __clz((int)((hi - lo) | 1u));
       const int shift = max(bits - digit_bits, 0);
-      for (int w = tid; w < nw; w += NT) {
+#pragma unroll
+      for (int i = 0; i < AT_ONCE; ++i)
+        if (tid + i * NT < nw && own[i] >= lo && own[i] <= hi) atomicAdd(&hist[(own[i] - lo) >> shift], 1u);
+      for (int w = tid + AT_ONCE * NT; w < nw; w += NT) {
         const uint32_t key = keys[w];
         if (key >= lo && key <= hi) atomicAdd(&hist[(key - lo) >> shift], 1u);
       }
@@ -140,31 +145,45 @@ __device__ __forceinline__ int select_windows(const SeqParam &sp, int w_obs, con
     // ---- 3. ordered compaction -------------------------------------------------------------
     uint32_t gt_bits = 0u, eq_bits = 0u;          // this thread's windows, one bit per 1024
     const int iters = (nw + NT - 1) / NT;
-    for (int i = 0; i < iters; ++i) {
-      const int w = i * NT + tid;
-      const uint32_t key = w < nw ? keys[w] : 0u;
-      const bool gt = w < nw && key > T, eq = w < nw && key == T;
+    auto classify = [&](int i, bool in, uint32_t key) __attribute__((always_inline)) {
+      const bool gt = in && key > T, eq = in && key == T;
       gt_bits |= (uint32_t)gt << i;
       eq_bits |= (uint32_t)eq << i;
       const int n_gt = __popcll(__ballot(gt)), n_eq = __popcll(__ballot(eq));
       if (lane == 0) counts[i * (NT / 64) + wave] = (uint32_t)n_gt | (uint32_t)n_eq << 16;
+    };
+#pragma unroll
+    for (int i = 0; i < AT_ONCE; ++i)
+      if (i * NT < nw) classify(i, tid + i * NT < nw, own[i]);
+    for (int i = AT_ONCE; i < iters; ++i) {
+      const int w = i * NT + tid;
+      classify(i, w < nw, w < nw ? keys[w] : 0u);
     }
     __syncthreads();                              // every key has been read: the array is free
-    if (wave == 0) {                              // exclusive scan of the counts, in window order
-      uint32_t base = 0u;
-      for (int c = 0; c < iters * (NT / 64); c += 64) {
-        const uint32_t v = c + lane < iters * (NT / 64) ? counts[c + lane] : 0u;
-        const uint32_t incl = wave_sums(v);
-        if (c + lane < iters * (NT / 64)) counts[c + lane] = base + incl - v;
-        base += last_lane(incl);
+    // exclusive scan of the counts, in window order: up to 64 by every wave for itself, else by the first one
+    const int n_counts = iters * (NT / 64);
+    uint32_t mine = 0u;
+    if (n_counts <= 64) {
+      const uint32_t v = lane < n_counts ? counts[lane] : 0u;
+      mine = wave_sums(v) - v;
+    } else {
+      if (wave == 0) {
+        uint32_t base = 0u;
+        for (int c = 0; c < n_counts; c += 64) {
+          const uint32_t v = c + lane < n_counts ? counts[c + lane] : 0u;
+          const uint32_t incl = wave_sums(v);
+          if (c + lane < n_counts) counts[c + lane] = base + incl - v;
+          base += last_lane(incl);
+        }
       }
+      __syncthreads();
     }
-    __syncthreads();
     const unsigned long long below = (1ull << lane) - 1ull;
     for (int i = 0; i < iters; ++i) {
       const bool gt = gt_bits >> i & 1u, eq = eq_bits >> i & 1u;
       const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
-      const uint32_t before = counts[i * (NT / 64) + wave];
+      const int at = i * (NT / 64) + wave;
+      const uint32_t before = n_counts <= 64 ? (uint32_t)__builtin_amdgcn_readlane((int)mine, __builtin_amdgcn_readfirstlane(at)) : counts[at];
       const uint32_t gt_before = (before & 0xffffu) + __popcll(bgt & below), eq_before = (before >> 16) + __popcll(beq & below);
       if (gt || (eq && eq_before < take_eq)) {
         const uint32_t slot = gt_before + min(eq_before, take_eq);
