@@ -259,7 +259,7 @@ void fill_score_args(const Shape &s, const BatchParams &bp, const ScorePlan &pla
   a->fold = fold;
   a->hkv_magic = division_magic(s.Hkv);
   a->items = pp.first[s.B];
-  *grid = score_grid(s.Hkv * n_groups, a->items);
+  *grid = score_grid(s.Hkv, n_groups, a->items);
   a->row_bits = grid->row_bits;
   a->last_x = grid->x - 1; a->last_y = grid->y - 1; a->last_z = grid->z - 1;
 }

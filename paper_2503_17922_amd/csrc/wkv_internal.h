@@ -142,24 +142,28 @@ struct ScoreArgs {
 // the 8 XCDs, each with an L2 of its own: where the rows of a sequence allow, all workgroups of a row are on one XCD (of two to seven rows on a
 // share of them), so that its queries and partials come into one L2 instead of all eight.  Then x of the grid is the XCD, y and z the
 // rows and the row's workgroups: 2^row_bits rows in x, 8 >> row_bits workgroups of each.  Only where every XCD gets its equal share so;
-// else x is the workgroup and y the row.  Plain / by XCD: 8 heads of 4096 tokens 23.7 / 22.6 us, of 16384 43.4 / 42.1, in fp32 stage by
+// else, and with more rows than a grid has in y or `divide` takes (65535), x is the workgroup, y the KV head and z the group.  Plain / by XCD: 8 heads of 4096 tokens 23.7 / 22.6 us, of 16384 43.4 / 42.1, in fp32 stage by
 // stage 61.2 / 58.7; a mixed batch of 8 in 8 groups 1902 / 1877; ragged f16 with 224 rows a head in 4 groups 68.8 / 67.0; 32768 tokens in 8 groups, whose
 // queries are 1/16 of the keys, the same.
 struct ScoreGrid {
   int32_t x, y, z, row_bits;
 };
-inline ScoreGrid score_grid(int32_t rows, int32_t items) {
+inline ScoreGrid score_grid(int32_t heads, int32_t groups, int32_t items) {
+  const int64_t rows = (int64_t)heads * groups;
   int32_t bits = 0;
   while (bits < 3 && rows % (2 << bits) == 0) ++bits;
   const int32_t per = 8 >> bits;        // workgroups of a row side by side
-  if (bits == 0 || (items % per != 0 && rows != 1 << bits)) return {items, rows, 1, 0};
-  return {8, rows >> bits, (items + per - 1) / per, bits};
+  if (bits == 0 || rows > 65535 || items > 65535 || (items % per != 0 && rows != 1 << bits)) return {items, heads, groups, 0};
+  return {8, (int32_t)(rows >> bits), (items + per - 1) / per, bits};
 }
 struct ScoreItem {
-  int32_t row, item;           // item: past the row's last one for a few workgroups where 8 >> row_bits does not divide them
-  // (one bit or more: x is less than 8.  None: x is the item)
-  __host__ __device__ ScoreItem(int32_t x, int32_t y, int32_t z, int32_t row_bits)
-      : row((x & ((1 << row_bits) - 1)) + (y << row_bits)), item((z << (3 - row_bits)) + (x >> row_bits)) {}
+  int32_t group, head, item;   // item: past the row's last one for a few workgroups where 8 >> row_bits does not divide them
+  __host__ __device__ ScoreItem(int32_t x, int32_t y, int32_t z, int32_t row_bits, int32_t heads, uint32_t heads_magic) {
+    const int32_t row = (x & ((1 << row_bits) - 1)) + (y << row_bits), of = divide(row, heads_magic);
+    group = row_bits ? of : z;
+    head = row_bits ? row - of * heads : y;
+    item = row_bits ? (z << (3 - row_bits)) + (x >> row_bits) : x;
+  }
 };
 
 // ---- single-read score kernel ("resident keys") ----------------------------------------------------

@@ -242,10 +242,10 @@ __global__ __launch_bounds__(score_threads(HV), 2) void score_kernel(Shape s, Sc
   // are the ones most likely still held by the memory-side cache.
   const bool back = PASS == 2;
   const ScoreItem item(back && a.row_bits == 0 ? a.last_x - blockIdx.x : blockIdx.x, back ? a.last_y - blockIdx.y : blockIdx.y,
-                       back ? a.last_z - blockIdx.z : blockIdx.z, a.row_bits);
+                       back ? a.last_z - blockIdx.z : blockIdx.z, a.row_bits, s.Hkv, a.hkv_magic);
   const int x = item.item;
   if (x >= a.items) return;
-  const int g = divide(item.row, a.hkv_magic), h = item.row - g * s.Hkv;
+  const int g = item.group, h = item.head;
   int b = 0;
 #pragma unroll
   for (int i = 0; i < ENDS_AT_ONCE; ++i) b += x >= ends[i];

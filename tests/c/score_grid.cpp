@@ -15,26 +15,47 @@ static int failures = 0;
 int main() {
   for (int rows = 1; rows <= 72; ++rows)
     for (int items = 1; items <= 130; items += items < 40 ? 1 : 7) {
-      const ScoreGrid g = score_grid(rows, items);
+      const int groups = rows % 4 == 0 && items % 2 ? 4 : rows % 3 == 0 ? 3 : 1, heads = rows / groups;
+      const ScoreGrid g = score_grid(heads, groups, items);
       std::vector<int> taken(rows * items, 0), share(8, 0), xcds(rows, 0);
       int number = 0;
       for (int z = 0; z < g.z; ++z)
         for (int y = 0; y < g.y; ++y)
           for (int x = 0; x < g.x; ++x, ++number) {
-            const ScoreItem it(x, y, z, g.row_bits);
-            EXPECT(it.row >= 0 && it.row < rows && it.item >= 0, "%d rows of %d", rows, items);
+            const ScoreItem it(x, y, z, g.row_bits, heads, division_magic(heads));
+            const int row = it.group * heads + it.head;
+            EXPECT(it.group >= 0 && it.group < groups && it.head >= 0 && it.head < heads && it.item >= 0, "%d rows of %d", rows, items);
             if (it.item >= items) continue;
-            ++taken[it.row * items + it.item];
+            ++taken[row * items + it.item];
             ++share[number % 8];
-            xcds[it.row] |= 1 << number % 8;
+            xcds[row] |= 1 << number % 8;
           }
       for (int n : taken) EXPECT(n == 1, "%d rows of %d", rows, items);
       EXPECT(*std::max_element(share.begin(), share.end()) == (rows * items + 7) / 8, "%d rows of %d", rows, items);
       if (g.row_bits)
         for (int m : xcds) EXPECT(__builtin_popcount(m) <= 8 >> g.row_bits, "%d rows of %d", rows, items);
     }
-  EXPECT(score_grid(8, 32).row_bits == 3 && score_grid(64, 7).row_bits == 3 && score_grid(4, 63).row_bits == 2 && score_grid(12, 20).row_bits == 2, " ");
-  EXPECT(score_grid(12, 21).row_bits == 0 && score_grid(3, 40).row_bits == 0 && score_grid(2, 127).row_bits == 1, " ");
+  EXPECT(score_grid(8, 1, 32).row_bits == 3 && score_grid(8, 8, 7).row_bits == 3 && score_grid(4, 1, 63).row_bits == 2 && score_grid(4, 3, 20).row_bits == 2, " ");
+  EXPECT(score_grid(12, 1, 21).row_bits == 0 && score_grid(3, 1, 40).row_bits == 0 && score_grid(1, 2, 127).row_bits == 1, " ");
+  // As many heads and groups as a call may have: within what a grid has in y and z, and the group and head of every row right.
+  for (int heads : {1, 1023, 1024, 8192, 32767, 32768, 46342, 50000, 65535})
+    for (int groups : {1, 2, 3, 8, 64})
+      for (int items : {1, 8}) {
+        const ScoreGrid g = score_grid(heads, groups, items);
+        EXPECT(g.y <= 65535 && g.z <= 65535, "%d heads, %d groups", heads, groups);
+        int64_t wrong = 0, seen = 0;
+        std::vector<uint8_t> taken((size_t)heads * groups, 0);
+        for (int z = 0; z < g.z; ++z)
+          for (int y = 0; y < g.y; ++y)
+            for (int x = 0; x < g.x; ++x) {
+              const ScoreItem it(x, y, z, g.row_bits, heads, division_magic(heads));
+              const bool in = it.group >= 0 && it.group < groups && it.head >= 0 && it.head < heads;
+              if (!in) ++wrong;
+              else if (it.item < items) { ++seen; ++taken[(size_t)it.group * heads + it.head]; }
+            }
+        for (uint8_t n : taken) wrong += n != items;
+        EXPECT(wrong == 0 && seen == (int64_t)heads * groups * items, "%d heads, %d groups, %d items", heads, groups, items);
+      }
 
   Shape s;
   BatchParams bp;
