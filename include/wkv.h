@@ -350,6 +350,8 @@ size_t wkv_decode_workspace_bytes(const wkv_decode_shape *shape);
  *                  group's last layer (otherwise the second layer would find the counter already
  *                  advanced and attend to a row its cache does not hold yet)
  *   out            device float32 [batch, n_q_heads, head_dim]
+ * The results of a (b, h) depend on its own n_valid only: the counts of other sequences may be written
+ * while the step runs (a slot that another stream is filling).
  * A (b, h) whose n_valid is negative or already equals capacity cannot take the new row: its
  * caches and n_valid are left untouched and its rows of `out` are set to NaN.
  */

@@ -163,65 +163,17 @@ __device__ __forceinline__ bool nothing_to_do(const DecodeShape &s, int bh, int 
   return true;
 }
 
-// Which range of which cache this workgroup takes, and the rows of that cache; by row counts where the host asks for it: the
-// workgroups take the whole ranges one after the other, cache by cache, then what the caches hold past them, then the ranges without
-// rows.  So the shorter ones come last, what has nothing to do takes nobody's place, and the ranges of a cache lie on all XCDs.  Every wave
-// finds its workgroup's range by itself: a lane counts the ranges of per_lane caches, a scan over the lanes tells whose the workgroup's number
-// falls among.  find_ranges_by_count has the figures.
+// Which range of which cache this workgroup takes, and the rows of that cache.  It looks at the count of its own cache alone: a caller may
+// write the counts of other sequences meanwhile (a slot of the batch that is being filled anew).  Ranges dealt out by all counts, whole ones first,
+// would leave ranges of the others to nobody when a count changes between the start of two workgroups; they took, us a layer, own count / all: mixed
+// batches of 32q/8kv heads, 8 up to 8000 rows 27.6 / 26.5, 24 up to 4000 45.1 / 38.4, 64 up to 2000 59.5 / 55.1; 64 of 4128 167.5 / 168.3, 16 48.7 / 49.4.
 struct KeyRange {
   int head, range, n;
-};
-template <bool BY_COUNT>
-__device__ __forceinline__ KeyRange find_range(const DecodeShape &s, const int32_t *__restrict__ n_valid) {
-  if constexpr (!BY_COUNT) {
+  __device__ __forceinline__ KeyRange(const DecodeShape &s, const int32_t *__restrict__ n_valid) {
     const RangeOf it(blockIdx.x, blockIdx.y, s.B * s.Hkv, s.heads_magic);
-    return {it.head, it.range, load_scalar(n_valid + it.head)};
+    head = it.head; range = it.range; n = load_scalar(n_valid + head);
   }
-  const int heads = s.B * s.Hkv, lane = threadIdx.x & 63;
-  int item = blockIdx.x + heads * blockIdx.y;
-  int n[DEC_PER_LANE], before[DEC_PER_LANE], count[DEC_PER_LANE];           // rows; ranges of the kinds before this one, of this one
-#pragma unroll
-  for (int j = 0; j < DEC_PER_LANE; ++j) {
-    n[j] = 0;
-    if (j < s.per_lane && j * 64 + lane < heads) n[j] = n_valid[j * 64 + lane];
-  }
-  int sum = 0;
-#pragma unroll
-  for (int j = 0; j < DEC_PER_LANE; ++j) {
-    before[j] = 0;
-    count[j] = n[j] > 0 && n[j] < s.capacity ? divide((uint32_t)n[j] >> 6, s.chunk_magic) : 0;
-    sum += count[j];
-  }
-  int upto = (int)wave_sums((uint32_t)sum);
-#pragma unroll
-  for (int kind = 1; kind < 3; ++kind) {                                    // (all uniform)
-    const int all = __builtin_amdgcn_readlane(upto, 63);
-    if (item < all) break;
-    item -= all;
-    sum = 0;
-#pragma unroll
-    for (int j = 0; j < DEC_PER_LANE; ++j) {
-      before[j] += count[j];
-      if (kind == 1) count[j] = n[j] > 0 && n[j] < s.capacity && before[j] * s.chunk < n[j];
-      else count[j] = j < s.per_lane && j * 64 + lane < heads ? s.n_splits - before[j] : 0;
-      sum += count[j];
-    }
-    upto = (int)wave_sums((uint32_t)sum);
-  }
-  const int src = __builtin_ctzll(__ballot(upto > item));
-  item -= __builtin_amdgcn_readlane(upto - sum, src);
-  int at = 0, have = __builtin_amdgcn_readlane(count[0], src), first = __builtin_amdgcn_readlane(before[0], src), rows = __builtin_amdgcn_readlane(n[0], src);
-#pragma unroll
-  for (int j = 1; j < DEC_PER_LANE; ++j) {
-    if (item < have) break;
-    item -= have;
-    at = j;
-    have = __builtin_amdgcn_readlane(count[j], src);
-    first = __builtin_amdgcn_readlane(before[j], src);
-    rows = __builtin_amdgcn_readlane(n[j], src);
-  }
-  return {at * 64 + src, first + item, rows};
-}
+};
 
 template <typename T, int D, int G, bool STREAM>
 __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape s, const T *__restrict__ q_new,
@@ -234,7 +186,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
   constexpr int KPT = 64 / LPK;              // rows per wave load instruction
   __shared__ float wave_state[DEC_WAVES][G][D + 2];
 
-  const KeyRange item = find_range<false>(s, n_valid);
+  const KeyRange item(s, n_valid);
   const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / LPK, piece = lane % LPK;
@@ -375,7 +327,7 @@ __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
 }
 // STREAM: 0 plain loads, 1 values stream, 2 keys too (see launch_partial_g).
-template <int D, int G, bool F16, int STREAM, int NT, bool BY_COUNT>
+template <int D, int G, bool F16, int STREAM, int NT>
 __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
     DecodeShape s, const uint16_t *__restrict__ q_new, const uint16_t *k_cache,
     const uint16_t *v_cache, const int32_t *__restrict__ n_valid, float *__restrict__ part) {
@@ -389,8 +341,8 @@ __global__ __launch_bounds__(NT, 3) void decode_partial_mfma_kernel(
 
   // (all arguments together, ahead of the row count that depends on one of them)
   asm volatile("" ::"s"(s.B), "s"(s.Hkv), "s"(s.heads_magic), "s"(s.kv_magic), "s"(s.chunk), "s"(s.capacity), "s"(s.c1), "s"(s.sb), "s"(s.sh), "s"(s.st),
-               "s"(s.per_lane), "s"(s.chunk_magic), "s"(s.n_splits), "s"(s.G), "s"(s.stats_at), "s"(q_new), "s"(k_cache), "s"(v_cache), "s"(n_valid), "s"(part));
-  const KeyRange item = find_range<BY_COUNT>(s, n_valid);
+               "s"(s.n_splits), "s"(s.G), "s"(s.stats_at), "s"(q_new), "s"(k_cache), "s"(v_cache), "s"(n_valid), "s"(part));
+  const KeyRange item(s, n_valid);
   const int bh = item.head, b = divide(bh, s.kv_magic), h = bh - b * s.Hkv, split = item.range;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;            // score side: head, 4 rows
@@ -732,23 +684,15 @@ static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, con
     constexpr bool WIDE = D == 128 && G <= 4;
     if constexpr (WIDE)
       if (s.chunk <= WIDE_THREADS / 64 * 16 && stream_level < 2) {
-        if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, WIDE_THREADS, false>), uint16_t, WIDE_THREADS);
-        else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, WIDE_THREADS, false>), uint16_t, WIDE_THREADS);
+        if (stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, WIDE_THREADS>), uint16_t, WIDE_THREADS);
+        else WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, WIDE_THREADS>), uint16_t, WIDE_THREADS);
         return;
       }
     // (longer ranges than those are of caches that stream: as many as there can be of a cache, 128 rows each, are 16 MB)
     static_assert(!WIDE || (int64_t)DEC_MAX_SPLITS * 128 * 2 * D * (int64_t)sizeof(T) > MEMORY_CACHE_BYTES / 32, "plain loads");
-    if (s.per_lane) {
-      if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS, true>), uint16_t, DEC_THREADS);
-      else if (WIDE || stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS, true>), uint16_t, DEC_THREADS);
-      else if constexpr (!WIDE) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS, true>), uint16_t, DEC_THREADS);
-    } else if (stream_level == 2) {
-      WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS, false>), uint16_t, DEC_THREADS);
-    } else if (WIDE || stream_level == 1) {
-      WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS, false>), uint16_t, DEC_THREADS);
-    } else if constexpr (!WIDE) {
-      WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS, false>), uint16_t, DEC_THREADS);
-    }
+    if (stream_level == 2) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 2, DEC_THREADS>), uint16_t, DEC_THREADS);
+    else if (WIDE || stream_level == 1) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 1, DEC_THREADS>), uint16_t, DEC_THREADS);
+    else if constexpr (!WIDE) WKV_PARTIAL((decode_partial_mfma_kernel<D, G, F16, 0, DEC_THREADS>), uint16_t, DEC_THREADS);
   } else {
     if (stream_level) WKV_PARTIAL((decode_partial_kernel<T, D, G, true>), T, DEC_THREADS);
     else WKV_PARTIAL((decode_partial_kernel<T, D, G, false>), T, DEC_THREADS);

@@ -316,15 +316,6 @@ Workspace carve_workspace(const Shape &s, const ScorePlan &plan, const ResidentP
   return w;
 }
 
-// Ranges dealt out by the row counts (16-bit caches), where there can be caches of different lengths and a range is long enough that one
-// that waits for its place matters.  us a layer by RangeOf / by counts: chunks of 256 rows and more, mixed batches of 8 up to 8000 rows 32.3 / 29.0, 24 up to 4000
-// 47.9 / 43.5, 64 up to 2000 50.8 / 48.0, two of 32000 54.0 / 51.8, 64 of 4128 168.0 / 168.2; 128 rows, where finding the range (0.3 us) costs what it
-// gives: two of 4128 12.1 / 13.1, three mixed 9.9 / 10.3, eleven mixed of 28q/4kv heads 14.6 / 15.0; 192, eight of 4128 27.9 / 28.3; fp32, four up to 16000 50.5 / 51.4.
-// (The division of a row number by a chunk stays within 32 bits: capacity^2 < 2^44.)
-static bool find_ranges_by_count(const DecodeShape &s) {
-  return s.dtype != WKV_F32 && s.chunk >= 256 && s.B > 1 && s.n_splits > 1 && (int64_t)s.B * s.Hkv <= 64 * DEC_PER_LANE && s.capacity <= 1 << 22;
-}
-
 wkv_status validate_decode(const wkv_decode_shape *p, Decode *out) {
   g_err[0] = 0;
   if (!p) { set_error("shape is NULL"); return WKV_ERR_INVALID_ARG; }
@@ -378,8 +369,6 @@ wkv_status validate_decode(const wkv_decode_shape *p, Decode *out) {
   const int64_t chunk = std::max<int64_t>(ceil_div(ceil_div(s.capacity, splits), 64) * 64, 128);
   s.chunk = (int32_t)chunk;
   s.n_splits = (int32_t)ceil_div(s.capacity, chunk);
-  s.per_lane = find_ranges_by_count(s) ? (int32_t)ceil_div(rows, 64) : 0;
-  s.chunk_magic = division_magic(s.chunk / 64);
   static_assert((int64_t)65535 * 8 * (128 + 2) * (int64_t)sizeof(float) < (int64_t)1 << 32 && total < 65535, "32-bit offsets of the partial results");
   s.stats_at = (uint32_t)(rows * s.n_splits * s.G * s.d * (int64_t)sizeof(float));
   out->ws_bytes = (size_t)rows * s.n_splits * s.G * (s.d + 2) * sizeof(float);

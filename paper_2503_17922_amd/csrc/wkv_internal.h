@@ -301,11 +301,8 @@ struct DecodeShape {
   float c1;                  // scale * log2(e)
   int64_t sb, sh, st;        // cache strides in elements
   uint32_t heads_magic, kv_magic;      // division_magic of the heads (B * Hkv) and of Hkv
-  int32_t per_lane;          // heads whose row counts a lane looks at to find a workgroup's range (see find_range); 0: by RangeOf
-  uint32_t chunk_magic;      // division_magic of the chunk in units of 64 rows
   uint32_t stats_at;         // bytes from the partial outputs to their statistics
 };
-constexpr int32_t DEC_PER_LANE = 8;       // of them at most: 512 heads
 // Which key range workgroup (x, y) of the partial kernel's grid (heads, ranges) takes.  Range by range: the first ranges of all caches
 // go first, the ones that many caches of a mixed batch do not reach last.  The heads start nine further on in every range, so
 // that the ranges of one cache fall on other XCDs (workgroup numbers are dealt to the 8 of them in turn) and compute units each time.

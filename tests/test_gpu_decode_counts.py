@@ -1,5 +1,5 @@
-"""Decode steps whose key ranges are dealt out by the row counts: caches of every length around the ranges' ends, empty, full and with counts
-that are no counts, a length of its own for every KV head, for one to eight caches a lane."""
+"""Decode steps over long ranges by row counts: caches of every length around the ranges' ends, empty, full and with counts that are no counts, a
+length of its own for every KV head; and counts of one sequence that change while the step runs."""
 import numpy as np
 import pytest
 import torch
@@ -13,10 +13,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,G,d", [("bf16", 4, 128), ("f16", 7, 64)])
 @pytest.mark.parametrize("B,H,cap,chunk", [
     (2, 1, 70000, 320),         # two caches, 219 ranges each
-    (21, 3, 6300, 320),         # 63: a lane each but one
-    (13, 5, 6300, 320),         # 65: one lane has two
-    (16, 16, 1700, 320),        # 256: four a lane
-    (64, 8, 1100, 384),         # 512: eight a lane
+    (21, 3, 6300, 320),         # 63 caches of 20 ranges, 65 of them
+    (13, 5, 6300, 320),
+    (16, 16, 1700, 320),        # 256 of six
+    (64, 8, 1100, 384),         # 512 of three
 ])
 def test_ranges_by_count(dtype, G, d, B, H, cap, chunk, device):
     tdt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
@@ -55,3 +55,33 @@ def test_ranges_by_count(dtype, G, d, B, H, cap, chunk, device):
         else:
             assert np.isnan(mine).all(), f"rows {rows}"
     assert counts == [r + (0 <= r < cap) for r in n]
+
+
+@pytest.mark.parametrize("dtype,G,d", [("bf16", 4, 128), ("f16", 7, 64)])
+def test_counts_of_another_sequence_that_change_meanwhile(dtype, G, d, device):
+    # a slot of the batch is filled anew on another stream while the step runs: its own output may be of either count, the others' are theirs
+    B, H, cap, slot, steps = 16, 4, 6300, 3, 24
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device=device).manual_seed(G)
+    mk = lambda *shape: torch.randn(shape, device=device, dtype=torch.float32, generator=gen).to(tdt)
+    kc, vc, q, kn, vn = mk(B, H, cap, d), mk(B, H, cap, d), 2 * mk(B, G * H, d), mk(B, H, d), mk(B, H, d)
+    n_valid = (400 + 5800 * torch.rand((B, H), device=device, generator=gen)).to(torch.int32)
+    shape = W.DecodeShape(batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=d, capacity=cap, flags=W.WKV_DECODE_KEEP_COUNT,
+                          dtype={"bf16": W.WKV_BF16, "f16": W.WKV_F16}[dtype])
+    ws = torch.empty(W.wkv_decode_workspace_bytes(shape), dtype=torch.uint8, device=device)
+    out = torch.zeros((steps + 1, B, G * H, d), dtype=torch.float32, device=device)
+    W.wkv_decode_step(shape, q, kn, vn, kc, vc, n_valid, out[steps], ws)
+    # (what a range that nobody takes would leave to the merge: NaN, from the workspace)
+    clean = torch.full_like(ws, 0xFF)
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    for i in range(steps):
+        ws.copy_(clean)
+        W.wkv_decode_step(shape, q, kn, vn, kc, vc, n_valid, out[i], ws)
+        with torch.cuda.stream(other):
+            for j in range(8):
+                n_valid[slot].fill_((500, 6200)[j % 2])
+    torch.cuda.synchronize()
+    rest = [b for b in range(B) if b != slot]
+    for i in range(steps):
+        assert torch.equal(out[i, rest], out[steps, rest]), f"step {i}"
