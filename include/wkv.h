@@ -53,13 +53,15 @@ extern "C" {
  * does not) sets WKV_KEEP_PADDING and they are left as they were. */
 #define WKV_KEEP_PADDING   1
 /* How Eq. 1-2 read the keys of the scored layer.  The library uses its two-pass kernels (softmax
- * statistics, then scores: the keys are streamed twice).  WKV_SCORE_SINGLE_READ selects the
+ * statistics, then scores: the keys are streamed twice), except in a batched call over short prompts,
+ * which is one launch from one read of the keys; WKV_SCORE_TWO_PASS selects the two-pass kernels
+ * for those calls too.  WKV_SCORE_SINGLE_READ selects the
  * single-read kernel instead where it applies (16-bit inputs, at most 128 softmax rows per KV head,
  * no normalisers handed over; ignored elsewhere): every key slice stays on chip between the
  * statistics phase and the score phase and workgroups exchange the row statistics through the
  * workspace.  On MI355X that exchange costs more than the second read it saves, so this is an
- * option for measurements, not the default.  WKV_SCORE_TWO_PASS states the default explicitly.
- * Results of the two agree to fp32 rounding of the normalisers.
+ * option for measurements, not the default.
+ * Results of all three agree to fp32 rounding of logits and normalisers.
  * WKV_DEBUG_WAIT_GIVES_UP makes every cross-workgroup wait of the
  * single-read kernel give up at once, which exercises its fall-back: the kernel exits normally,
  * raises a word in the workspace, and the two-pass kernels enqueued behind it (which return at

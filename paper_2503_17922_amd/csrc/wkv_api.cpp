@@ -196,7 +196,7 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
   hipError_t e;
 #define WKV_MARK(i) if (ev && (e = hipEventRecord(ev[i], stream)) != hipSuccess) return hip_fail(e, "event record");
   WKV_MARK(0)
-  if (!ev && !rp.use && whole_call_in_one(pr.shape, n_groups, gamma)) {
+  if (!ev && !rp.use && !(problem->flags & WKV_SCORE_TWO_PASS) && whole_call_in_one(pr.shape, n_groups, gamma)) {
     e = launch_short(pr.shape, pr.bp, gk, gp, lp, n_groups, gamma, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);
     return e == hipSuccess ? WKV_OK : hip_fail(e, "short call launch");
   }

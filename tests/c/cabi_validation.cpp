@@ -70,6 +70,20 @@ int main() {
   EXPECT(wkv_compress_groups(&P.pr, 2, 2, qg, nullptr, kg, kl, kl, ol, ol, idev, idev, idev, dev, ws2, nullptr) == WKV_OK);
   EXPECT(wkv_index_jaccard(&P.pr, 4, idev, idev, fdev, nullptr) == WKV_OK);
   EXPECT(wkv_stub_launches > before);
+  // ---- a short call: one launch, or by the two score passes (one launcher) where the caller asks for them -----------
+  Prob Q(2, 500, 8, 2, 128, 8, 8, 8, 6, WKV_BF16);
+  const size_t wsq = wkv_workspace_bytes(&Q.pr, 1);
+  char *base = (char *)dev;
+  const void *kq[2] = {base, base + (1 << 20)}; void *oq[2] = {base + (2 << 20), base + (3 << 20)};
+  int32_t *iq = (int32_t *)(base + (4 << 20));
+  auto launches = [&]() {
+    const int had = wkv_stub_launches;
+    EXPECT(wkv_compress_group(&Q.pr, 2, base + (5 << 20), nullptr, kq, kq, oq, oq, iq, iq, iq, base + (6 << 20), wsq, nullptr) == WKV_OK);
+    return wkv_stub_launches - had;
+  };
+  EXPECT(launches() == 1);
+  Q.pr.flags = WKV_SCORE_TWO_PASS;
+  EXPECT(launches() == 2);
   before = wkv_stub_launches;
   EXPECT(wkv_score(&P.pr, nullptr, dev, nullptr, fdev, dev, ws1, nullptr) == WKV_ERR_INVALID_ARG);
   EXPECT(wkv_score(&P.pr, (char *)dev + 2, dev, nullptr, fdev, dev, ws1, nullptr) == WKV_ERR_INVALID_ARG);

@@ -82,6 +82,20 @@ def test_normalisers_handed_over(dtype, d, L, device):
     assert torch.equal(st.tok_idx, own.tok_idx) and torch.equal(st.v_out[3], own.v_out[3])
 
 
+@pytest.mark.parametrize("dtype,d,L", [("bf16", 128, 500), ("f16", 64, 1000), ("f32", 64, 700)])
+def test_the_two_passes_where_they_are_asked_for(dtype, d, L, device):
+    w = _w(dtype=dtype, head_dim=d, seq_len=[L, 300], win=[16, 8], top_p=[8, 8], k_windows=[6, 6])
+    st = P.DeviceState(w, device); st.compress()
+    asked = P.DeviceState(w, device, flags=W.WKV_SCORE_TWO_PASS); asked.compress()
+    (_, s_short), (_, s_asked) = batched_intermediates(st), batched_intermediates(asked)
+    _, s, *_ = asked.stages(0)                                # the stage calls run the same passes: the same bits
+    for b, n in enumerate(w.seq_len):
+        nw = -(-(n - w.w_obs) // w.win[b])
+        assert np.array_equal(s_asked[0, b, :, :nw], s[b, :, :nw].cpu().numpy())
+        np.testing.assert_allclose(s_short[0, b, :, :nw], s_asked[0, b, :, :nw], rtol=2e-5, atol=1e-12)
+    assert torch.equal(st.tok_idx, asked.tok_idx) and torch.equal(st.k_out[1], asked.k_out[1])
+
+
 def test_strides(device):
     # caches and queries in token-major order, outputs spread out: the rows of the contiguous call
     w = _w(dtype="f16", seq_len=[400, 311], win=[8, 24], top_p=[8, 12], k_windows=[6, 3])
