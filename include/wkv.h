@@ -235,7 +235,8 @@ wkv_status wkv_compress_group(const wkv_problem *problem, int32_t gamma, const v
 
 /*
  * The whole path (Eq. 1-4, selection, sharing, gather) for n_groups layer groups of gamma
- * layers each, batched so that every stage is one launch over all groups.
+ * layers each, batched so that every stage is one launch over all groups; selection and gather of a
+ * small call are one launch, and a call over short prompts is one launch altogether.
  *   q_obs_groups   host array [n_groups] of device pointers: q_obs of each group's first layer
  *   lse_obs_groups NULL, or host array [n_groups] of device pointers: lse_obs of each group's
  *                  first layer as described at wkv_score (all groups or none)
@@ -252,7 +253,8 @@ wkv_status wkv_compress_group(const wkv_problem *problem, int32_t gamma, const v
  *   n_keep_out     device int32 [n_groups, batch, n_kv_heads]
  * Results equal those of the four stage calls run group by group, except that the fp32
  * summation order of the softmax normalisers depends on how a launch splits the keys over
- * workgroups: token scores can differ in their last bits, hence selections only between windows
+ * workgroups, and that a call over short prompts takes exponentials against other references: token
+ * scores can differ in their last bits, hence selections only between windows
  * whose scores agree to fp32 rounding.
  * n_groups <= WKV_MAX_GROUPS, n_groups*gamma <= WKV_MAX_LAYERS.
  */
@@ -274,7 +276,9 @@ wkv_status wkv_compress_groups(const wkv_problem *problem, int32_t n_groups, int
  *                 pass (Eq. 1; 0 with lse_obs_groups; with WKV_SCORE_SINGLE_READ the single-read
  *                 kernel, which then covers Eq. 1-2), the score pass (Eq. 1-2, and Eq. 3-4 where it
  *                 pools its own windows), the selection (2.2.1, and Eq. 3-4 otherwise) and
- *                 the shared-index gather (2.2.2).
+ *                 the shared-index gather (2.2.2).  The one launch of a call over short prompts is
+ *                 reported as the score pass, the other stages as 0; with WKV_SCORE_TWO_PASS such a
+ *                 call has the stages of the others.
  */
 #define WKV_N_STAGES 4
 wkv_status wkv_compress_groups_profiled(const wkv_problem *problem, int32_t n_groups, int32_t gamma,

@@ -195,11 +195,15 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
   hipStream_t stream = (hipStream_t)hip_stream;
   hipError_t e;
 #define WKV_MARK(i) if (ev && (e = hipEventRecord(ev[i], stream)) != hipSuccess) return hip_fail(e, "event record");
-  WKV_MARK(0)
-  if (!ev && !rp.use && !(problem->flags & WKV_SCORE_TWO_PASS) && whole_call_in_one(pr.shape, n_groups, gamma)) {
+  if (!rp.use && !(problem->flags & WKV_SCORE_TWO_PASS) && whole_call_in_one(pr.shape, n_groups, gamma)) {
+    // (timed, too: the passes could select differently between near ties.  The events that are left out make the other stages read 0.)
+    WKV_MARK(1)
     e = launch_short(pr.shape, pr.bp, gk, gp, lp, n_groups, gamma, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);
-    return e == hipSuccess ? WKV_OK : hip_fail(e, "short call launch");
+    if (e != hipSuccess) return hip_fail(e, "short call launch");
+    WKV_MARK(2) WKV_MARK(4)
+    return WKV_OK;
   }
+  WKV_MARK(0)
   // The score kernel pools its own windows (Eq. 3-4 on the scores still in LDS) and only the window
   // scores reach memory.
   float *s_pool = rp.pools ? ws.s : nullptr;

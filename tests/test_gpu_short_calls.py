@@ -96,6 +96,24 @@ def test_the_two_passes_where_they_are_asked_for(dtype, d, L, device):
     assert torch.equal(st.tok_idx, asked.tok_idx) and torch.equal(st.k_out[1], asked.k_out[1])
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("handed_over", [False, True])
+def test_profiled_call_gives_the_same_results(dtype, d, handed_over, device):
+    w = _w(dtype=dtype, head_dim=d, n_groups=2, seq_len=[500, 300], win=[16, 8], top_p=[8, 8], k_windows=[6, 6])
+    ref, st = P.DeviceState(w, device), P.DeviceState(w, device)
+    lse = [st.oracle_lse(g) for g in range(2)] if handed_over else None
+    ref.compress(lse=lse)
+    ms = W.CompressCall(st.problem, w.n_groups, w.gamma, st.q, lse, st.k, st.v, st.k_out, st.v_out, st.win_idx, st.tok_idx, st.n_keep,
+                        st.workspace).profiled()
+    assert 0.0 < ms[1] < 50.0 and ms[0] == ms[2] == ms[3] == 0.0, ms
+    (_, want), (_, got) = batched_intermediates(ref), batched_intermediates(st)
+    for b, n in enumerate(w.seq_len):
+        nw = -(-(n - w.w_obs) // w.win[b])
+        assert np.array_equal(got[:, b, :, :nw], want[:, b, :, :nw])          # the same launch: the same bits
+    for a, b in zip((st.win_idx, st.tok_idx, st.n_keep, *st.k_out, *st.v_out), (ref.win_idx, ref.tok_idx, ref.n_keep, *ref.k_out, *ref.v_out)):
+        assert torch.equal(a, b)
+
+
 def test_strides(device):
     # caches and queries in token-major order, outputs spread out: the rows of the contiguous call
     w = _w(dtype="f16", seq_len=[400, 311], win=[8, 24], top_p=[8, 12], k_windows=[6, 3])
