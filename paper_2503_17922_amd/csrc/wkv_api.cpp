@@ -132,6 +132,30 @@ wkv_status wkv_gather_group(const wkv_problem *problem, int32_t n_layers, const 
   return e == hipSuccess ? WKV_OK : hip_fail(e, "wkv_gather_group launch");
 }
 
+// Does an output lie in the memory of the queries or of the normalisers?  Behind the passes it may: they have read both before a row or an index
+// is written.  In one launch some workgroups write while others still read.
+static bool outputs_over_queries(const Shape &s, int32_t n_groups, int32_t gamma, const GroupPtrs &gp, const LayerPtrs &lp, const int32_t *win_idx,
+                                 const int32_t *tok_idx, const int32_t *n_keep) {
+  const uint64_t rows = (uint64_t)n_groups * s.B * s.Hkv;
+  auto span = [&](uint64_t b, uint64_t sb, uint64_t h, uint64_t sh, uint64_t t, uint64_t st) {
+    return ((b - 1) * sb + (h - 1) * sh + (t - 1) * st + s.d) * elem_bytes(s.dtype);
+  };
+  const uint64_t q_bytes = span(s.B, s.q_sb, s.Hq, s.q_sh, s.w_obs, s.q_st), out_bytes = span(s.B, s.o_sb, s.Hkv, s.o_sh, s.nkeep_max, s.o_st);
+  const uint64_t lse_bytes = (uint64_t)s.B * s.Hq * s.w_obs * 4;
+  auto meets_inputs = [&](const void *out, uint64_t bytes) {
+    const uintptr_t from = (uintptr_t)out, to = from + bytes;
+    for (int32_t g = 0; g < n_groups; ++g) {
+      const uintptr_t q = (uintptr_t)gp.q[g], lse = (uintptr_t)gp.lse[g];
+      if (from < q + q_bytes && q < to) return true;
+      if (lse && from < lse + lse_bytes && lse < to) return true;
+    }
+    return false;
+  };
+  bool found = meets_inputs(win_idx, rows * s.k_max * 4) || meets_inputs(tok_idx, rows * s.nkeep_max * 4) || meets_inputs(n_keep, rows * 4);
+  for (int32_t l = 0; !found && l < n_groups * gamma; ++l) found = meets_inputs(lp.k_out[l], out_bytes) || meets_inputs(lp.v_out[l], out_bytes);
+  return found;
+}
+
 static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, int32_t gamma,
                                 const void *const *q_obs_groups, const float *const *lse_obs_groups,
                                 const int32_t *k_windows_groups, const void *const *k_layers,
@@ -195,7 +219,8 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
   hipStream_t stream = (hipStream_t)hip_stream;
   hipError_t e;
 #define WKV_MARK(i) if (ev && (e = hipEventRecord(ev[i], stream)) != hipSuccess) return hip_fail(e, "event record");
-  if (!rp.use && !(problem->flags & WKV_SCORE_TWO_PASS) && whole_call_in_one(pr.shape, n_groups, gamma)) {
+  if (!rp.use && !(problem->flags & WKV_SCORE_TWO_PASS) && whole_call_in_one(pr.shape, n_groups, gamma) &&
+      !outputs_over_queries(pr.shape, n_groups, gamma, gp, lp, win_idx_out, tok_idx_out, n_keep_out)) {
     // (timed, too: the passes could select differently between near ties.  The events that are left out make the other stages read 0.)
     WKV_MARK(1)
     e = launch_short(pr.shape, pr.bp, gk, gp, lp, n_groups, gamma, ws.s, win_idx_out, tok_idx_out, n_keep_out, stream);

@@ -84,6 +84,26 @@ int main() {
   EXPECT(launches() == 1);
   Q.pr.flags = WKV_SCORE_TWO_PASS;
   EXPECT(launches() == 2);
+  // outputs in the memory of the queries or the normalisers are written when the passes have read those; beside it they are as any others
+  Q.pr.flags = 0;
+  const int64_t q_bytes = 2 * 8 * 8 * 128 * 2, out_bytes = 2 * 2 * 56 * 128 * 2;
+  void *const v_out = oq[1];
+  auto with = [&](char *q, const float *lse, char *out, char *idx) {
+    oq[1] = out;
+    const int had = wkv_stub_launches;
+    EXPECT(wkv_compress_group(&Q.pr, 2, q, lse, kq, kq, oq, oq, iq, (int32_t *)idx, iq, base + (6 << 20), wsq, nullptr) == WKV_OK);
+    oq[1] = v_out;
+    return wkv_stub_launches - had;
+  };
+  char *const q = base + (5 << 20), *const lse = base + (7 << 20), *const apart = (char *)v_out;
+  EXPECT(with(q, nullptr, q + q_bytes, (char *)iq) == 1);
+  EXPECT(with(q, nullptr, q + q_bytes - 16, (char *)iq) == 2);
+  EXPECT(with(q, nullptr, q - out_bytes, (char *)iq) == 1);
+  EXPECT(with(q, nullptr, q - out_bytes + 16, (char *)iq) == 2);
+  EXPECT(with(q, (const float *)lse, apart, (char *)iq) == 1);
+  EXPECT(with(q, (const float *)lse, lse, (char *)iq) == 2);
+  EXPECT(with(q, (const float *)lse, apart, lse + 2 * 8 * 8 * 4 - 4) == 2);
+  EXPECT(with(q, (const float *)lse, apart, lse + 2 * 8 * 8 * 4) == 1);
   before = wkv_stub_launches;
   EXPECT(wkv_score(&P.pr, nullptr, dev, nullptr, fdev, dev, ws1, nullptr) == WKV_ERR_INVALID_ARG);
   EXPECT(wkv_score(&P.pr, (char *)dev + 2, dev, nullptr, fdev, dev, ws1, nullptr) == WKV_ERR_INVALID_ARG);

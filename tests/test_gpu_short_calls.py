@@ -114,6 +114,21 @@ def test_profiled_call_gives_the_same_results(dtype, d, handed_over, device):
         assert torch.equal(a, b)
 
 
+def test_outputs_in_the_memory_of_the_queries(device):
+    # the last layer's compact values take the place of the queries
+    w = _w(n_q_heads=16, w_obs=16, seq_len=[500], win=[16], top_p=[8])
+    ref = P.DeviceState(w, device); ref.compress()
+    st = P.DeviceState(w, device)
+    room = torch.empty(max(st.q[0].numel(), st.v_out[1].numel()), dtype=torch.bfloat16, device=device)
+    q, out = room[:st.q[0].numel()].view_as(st.q[0]), room[:st.v_out[1].numel()].view_as(st.v_out[1])
+    for _ in range(20):
+        q.copy_(st.q[0])
+        st.q[0], st.v_out[1], given = q, out, st.q[0]
+        st.compress()
+        st.q[0] = given
+        assert torch.equal(st.tok_idx, ref.tok_idx) and torch.equal(out, ref.v_out[1]) and torch.equal(st.k_out[0], ref.k_out[0])
+
+
 def test_strides(device):
     # caches and queries in token-major order, outputs spread out: the rows of the contiguous call
     w = _w(dtype="f16", seq_len=[400, 311], win=[8, 24], top_p=[8, 12], k_windows=[6, 3])
