@@ -1,5 +1,5 @@
 """GPU parity of short calls in one launch: sizes around the tiles, the key tiles of a wave, the row tiles and the limits of the rule, every type,
-masks, strides, budgets of their own, handed-over normalisers and keys that weigh nothing."""
+masks, strides, budgets of their own, handed-over normalisers, keys that weigh nothing, the flag that keeps such calls on the passes, the profiled call."""
 import numpy as np
 import pytest
 import torch
@@ -27,11 +27,12 @@ def test_lengths(dtype, d, L, device):
     run_and_check(_w(dtype=dtype, head_dim=d, seq_len=[L], k_windows=[min(nw, 9)]), device)
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f16", 128), ("f16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("L", [450, 900])
 @pytest.mark.parametrize("q_heads,w_obs", [(2, 1), (2, 16), (2, 17), (6, 11), (8, 16), (10, 13), (14, 16), (8, 32), (10, 26)])
-def test_row_counts(dtype, d, q_heads, w_obs, device):
-    # 1 to 130 rows a KV head
-    run_and_check(_w(dtype=dtype, head_dim=d, n_q_heads=q_heads, w_obs=w_obs, seq_len=[450, w_obs], win=[24, 8], top_p=[12, 8], k_windows=[5, 0]), device)
+def test_row_counts(dtype, d, L, q_heads, w_obs, device):
+    # 1 to 130 rows a KV head, four and eight key tiles a wave: every kernel that the rule can choose, and both sides of its lines
+    run_and_check(_w(dtype=dtype, head_dim=d, n_q_heads=q_heads, w_obs=w_obs, seq_len=[L, w_obs], win=[24, 8], top_p=[12, 8], k_windows=[5, 0]), device)
 
 
 @pytest.mark.parametrize("kw", [
