@@ -313,8 +313,9 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
 // has in a range of 128 rows, and waits for memory once; the arithmetic of both is one piece of code, and the heads' numbers are
 // divided by multiplication.  Such a layer with its merge 11.3 us with one block requested ahead of the one in hand (the compiler
 // put the request of the second behind the arrival of the first), 10.1 us so; eleven sequences of mixed lengths, 28q/4kv heads, f16, a layer
-// 16.6 and 14.8 us; 64 sequences 169 and 167.  Ranges of 64 rows, one block a wave: 10.9, 14.7 and 167 us.  Three waves a SIMD: with
-// four, the registers of two blocks spill.  Ranges of a block a wave without a state before it, a lane's rows by one multiplication each, the caches'
+// 16.6 and 14.8 us; 64 sequences 169 and 167.  Ranges of 64 rows, one block without a state for each of four waves, against the
+// present kernels: one sequence 8.53 -> 9.07, two 11.06 -> 11.65, the eleven 14.24 -> 14.21.  Two blocks and a state take 102 to 125 registers with 128 channels and up to four heads (four waves a SIMD), 134 to 162 with more (three), one block without a
+// state 56 to 60 (eight).  Ranges of a block a wave without a state before it, a lane's rows by one multiplication each, the caches'
 // addresses while the row count is under way; here and in the merge offsets of 32 bits into the partial results: one sequence of 4128 rows through 32
 // layers 309 -> 298 us, of 20000 rows 22.0 -> 20.6 a layer, three of 4128 14.4 -> 13.7, fp32 with four 21.3 -> 20.8.
 // The value of lane N of each 16-lane DPP row, in all its lanes.
@@ -673,14 +674,13 @@ static void launch_partial_g(const DecodeShape &s, dim3 grid, const void *q, con
   hipLaunchKernelGGL(KERNEL, grid, dim3(NT), 0, stream, s, (const E *)q, (const E *)kc, (const E *)vc, n_valid, part)
   if constexpr (sizeof(T) == 2) {   // bf16 / fp16: scores on the matrix pipe
     constexpr bool F16 = !__is_same(T, uint16_t);
-    // Ranges of 128 rows by eight waves with a block each instead of four with two: half the arithmetic in a row, twice the states to
-    // merge; the device holds 512 such workgroups, 768 of four waves.  With 128 channels and up to four heads it pays for one sequence and where many of
-    // the workgroups find no rows, as in batches of mixed lengths, which the host cannot tell from equal ones.  us a layer with four / eight
-    // waves (with one block ahead): 32q/8kv heads, one sequence of 4128 rows 9.18 / 8.97 (10.35), 6000 10.55 / 10.68 (12.13); three of 1000 to 3000 rows 11.28 / 10.25
-    // (13.05), four of 500 to 3000 11.41 / 10.23 (13.17); 32q/32kv, six of 100 to 700 12.50 / 11.94 (14.72).  It loses where more than 512 have rows: two of 4128
-    // 11.55 / 11.76 (13.59), three 13.85 / 14.97 (15.52); eight of 1000 rows, 512 workgroups, 11.15 / 11.05 (12.51).  64 channels: one of 4128 rows 8.19 / 8.08, two 9.02 /
-    // 9.29, three mixed 9.27 / 9.55, 32q/32kv six mixed 9.47 / 9.65.  Six heads and more: 12q/2kv 7.82 / 8.12, eleven mixed sequences with 28q/4kv 14.5 /
-    // 16.0, 64q/8kv heads of 64 channels 13.4 / 14.9.
+    // Ranges of 128 rows by eight waves with a block each instead of four with two: half the arithmetic in a row, no state before the block, twice the
+    // states to merge; the device holds 1024 workgroups of either kind (four waves of five heads and more: 768).  us a layer with four / eight waves,
+    // 128 channels: 32q/8kv heads, one sequence of 4128 rows 8.77 / 8.52, 6000 10.15 / 10.19, two of 4128 11.26 / 11.02, three 13.59 / 13.30, eight of 1000 10.90 / 10.74; three of
+    // 1000 to 3000 11.04 / 11.25, four of 500 to 3000 11.01 / 11.23; 32q/16kv, one of 4128 10.70 / 10.51; 32q/32kv, six of 100 to 700 10.68 / 10.75.  The line is from kernels
+    // whose single block had a state, for which more heads and 64 channels lost by eight waves.  On these: 40q/8kv, one of 4128 9.22 / 8.88; 12q/2kv, eleven mixed 11.67 / 11.50;
+    // 28q/4kv, eleven mixed 14.23 / 15.27; 64q/8kv, one of 4128 9.97 / 9.58, three of 1000 to 3000 13.02 / 11.49, eight of 1000 12.35 / 11.80; 64 channels, 32q/8kv, one of 4128 7.82 /
+    // 7.75, two 8.88 / 8.64, three of 1000 to 3000 9.15 / 8.84; 64q/8kv, three of 1000 to 3000 10.90 / 9.44.
     constexpr bool WIDE = D == 128 && G <= 4;
     if constexpr (WIDE)
       if (s.chunk <= WIDE_THREADS / 64 * 16 && stream_level < 2) {

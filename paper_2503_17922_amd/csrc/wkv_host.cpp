@@ -356,11 +356,13 @@ wkv_status validate_decode(const wkv_decode_shape *p, Decode *out) {
   s.c1 = (float)(scale * 1.4426950408889634074);
   s.sb = p->cache_stride_b; s.sh = p->cache_stride_h; s.st = p->cache_stride_t;
   s.heads_magic = division_magic(s.B * s.Hkv); s.kv_magic = division_magic(s.Hkv);
-  // Key ranges: about 1536 workgroups if every cache were full (six per compute unit; n_valid is not known
+  // Key ranges: about 1536 workgroups if every cache were full (one and a half times what the device holds with 128 channels and up to four heads; n_valid is not known
   // here, and in a batch of mixed lengths a good part of them finds nothing to do), of at least 128 rows (two
   // blocks for each of four waves, or one for each of eight: with half of that the fixed cost and the merge outweigh the shorter chain),
-  // multiples of 64 rows (a block for each of four waves).  Against 1024, 1280 and 2016 workgroups on 80 mixed batches of 2 to 64 (up to 1000, 4000 or 32000 rows, the
-  // shortest an eighth of the longest; 4, 8 and 32 KV heads): 6 %, 3 % slower and 1 % faster than 1536 in the mean; equal lengths the same.
+  // multiples of 64 rows (a block for each of four waves).  us a layer of 32q/8kv heads with 1024 / 1536 / 2016 workgroups: one sequence of 20000 rows
+  // 21.8 / 20.7 / 20.7, five of 3000 16.1 / 15.2 / 15.0, 16 of 4128 50.5 / 48.4 / 49.9, 64 of 4128 165.0 / 166.4 / 166.5; mixed batches, the shortest an eighth of the longest: 8 up to
+  // 4000 19.3 / 15.9 / 15.9, 24 up to 4000 48.4 / 44.7 / 40.1, 64 up to 2000 65.6 / 59.3 / 59.4; 4 KV heads, 16 up to 32000 106 / 97 / 86; 32 KV heads, 8 up to 16000 244 / 185 / 164;
+  // 28q/4kv, eleven 16.2 / 14.4 / 14.4.
   const int64_t rows = (int64_t)s.B * s.Hkv;
   constexpr int64_t total = 1536;
   static_assert(total * 8 * (128 + 2) * (int64_t)sizeof(float) <= WKV_DECODE_STATIC_SCRATCH_BYTES,

@@ -211,7 +211,8 @@ inline bool selects_and_gathers(const Shape &s, int32_t n_groups, int32_t gamma)
 }
 
 // The whole call in one launch?  Every workgroup scores a whole row by itself (wkv_short.hip), which takes the place of the two passes where a row
-// is short, and as many workgroups as (row, tensor) pairs do so side by side: one a compute unit.
+// is short, and as many workgroups as (row, tensor) pairs do so side by side: one a compute unit.  (t_stride + w_obs is the room of the caches: a short
+// prompt in caches with room for more than the rule takes goes by the passes.)
 constexpr int32_t SHORT_WORKGROUPS = 256;
 // Key tiles of 16 that a wave of eight holds, at most, by the row tiles of 16 (1, 2, 4 or 8): four are 512 keys.  0: not in one launch.  16-bit types take what
 // fits the registers; all of it gains, 16 to 128 rows a KV head, 200 to 1000 keys: 0.48 to 0.84 of the time of the passes with the merged selection
