@@ -219,7 +219,7 @@ static wkv_status compress_impl(const wkv_problem *problem, int32_t n_groups, in
   hipStream_t stream = (hipStream_t)hip_stream;
   hipError_t e;
 #define WKV_MARK(i) if (ev && (e = hipEventRecord(ev[i], stream)) != hipSuccess) return hip_fail(e, "event record");
-  if (!rp.use && !(problem->flags & WKV_SCORE_TWO_PASS) && whole_call_in_one(pr.shape, n_groups, gamma) &&
+  if (!rp.use && !(problem->flags & WKV_SCORE_TWO_PASS) && whole_call_in_one(pr.shape, pr.bp, n_groups, gamma, lse_obs_groups != nullptr) &&
       !outputs_over_queries(pr.shape, n_groups, gamma, gp, lp, win_idx_out, tok_idx_out, n_keep_out)) {
     // (timed, too: the passes could select differently between near ties.  The events that are left out make the other stages read 0.)
     WKV_MARK(1)

@@ -218,15 +218,25 @@ constexpr int32_t SHORT_WORKGROUPS = 256;
 // fits the registers; all of it gains, 16 to 128 rows a KV head, 200 to 1000 keys: 0.48 to 0.84 of the time of the passes with the merged selection
 // and gather, 1, 2, 4 and 8 sequences alike.  fp32 is a matrix product of 1/16 the rate, done by every workgroup: 16 rows of 64 channels 0.50 to 0.77,
 // 32 rows 0.64, 16 rows of 128 channels 0.61; 32 rows of 1000 keys would take 1.39, 64 rows of 512 keys 1.24, 32 rows of 128 channels 1.27.
-constexpr int32_t short_key_tiles(int32_t d, int32_t esize, int32_t row_tiles) {
+// With handed-over normalisers (given) there is one pass less to replace: 0.75 to 0.91 of the time of the launches (medians of some 20 calls each) where it is taken; it
+// would be 1.10 with 16-bit types, 64 channels, 33 to 64 rows of 1024 keys, 1.08 and 1.14 with 65 to 128 rows of 64 and 128 channels, 1.04 with 128 channels, 17 to
+// 32 rows of 1024 keys; fp32, 64 channels, 16 rows of 1024 keys 1.10, 32 rows 1.01, 128 channels 1.02.
+constexpr int32_t short_key_tiles(int32_t d, int32_t esize, int32_t row_tiles, bool given = false) {
+  if (given) return esize == 4 ? (d == 64 && row_tiles == 1 ? 4 : 0) : row_tiles == 1 || (d == 64 && row_tiles == 2) ? 8 : row_tiles <= 4 ? 4 : 0;
   if (esize == 4) return row_tiles == 1 ? (d == 64 ? 8 : 4) : d == 64 && row_tiles == 2 ? 4 : 0;
   return row_tiles <= 2 || (d == 64 && row_tiles == 4) ? 8 : 4;
 }
 inline int32_t short_row_tiles(const Shape &s) { return s.M <= 16 ? 1 : s.M <= 32 ? 2 : s.M <= 64 ? 4 : s.M <= 128 ? 8 : 0; }
-inline bool whole_call_in_one(const Shape &s, int32_t n_groups, int32_t gamma) {
+// Windows of more than 64 tokens have their tokens ranked by a loop over the window, one token a thread and then the next; every workgroup of a row does it here, those of
+// the score pass share it.  In sequences of more than SHORT_TOKENS, two tokens a thread, that makes 1.05 of the time of the passes, 1.31 with handed-over
+// normalisers (all other calls 0.72 and 0.86; up to that 1.01 and 1.05 at most).
+constexpr int32_t SHORT_TOKENS = 512;
+inline bool whole_call_in_one(const Shape &s, const BatchParams &bp, int32_t n_groups, int32_t gamma, bool given) {
   const int32_t tiles = short_row_tiles(s);
-  return tiles > 0 && s.t_stride + s.w_obs <= 128 * short_key_tiles(s.d, (int32_t)elem_bytes(s.dtype), tiles) && selects_and_gathers(s, n_groups, gamma) &&
-         2 * n_groups * gamma * s.B * s.Hkv <= SHORT_WORKGROUPS;
+  bool in = tiles > 0 && s.t_stride + s.w_obs <= 128 * short_key_tiles(s.d, (int32_t)elem_bytes(s.dtype), tiles, given) && selects_and_gathers(s, n_groups, gamma) &&
+            2 * n_groups * gamma * s.B * s.Hkv <= SHORT_WORKGROUPS;
+  for (int32_t b = 0; in && b < s.B; ++b) in = bp.seq[b].win <= 64 || bp.seq[b].L - s.w_obs <= SHORT_TOKENS;
+  return in;
 }
 
 // Workgroups over the rows of a compact cache, two pieces of `rows` rows each, `apart` pieces from one to the other; the ones from

@@ -20,6 +20,7 @@
 namespace wkv {
 
 constexpr int SHORT_THREADS = 512, SHORT_WAVES = SHORT_THREADS / 64;
+static_assert(SHORT_TOKENS == SHORT_THREADS, "a token a thread");
 
 struct ShortScore {
   const void *q[SMALL_GROUPS];

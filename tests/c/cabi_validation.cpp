@@ -104,6 +104,28 @@ int main() {
   EXPECT(with(q, (const float *)lse, lse, (char *)iq) == 2);
   EXPECT(with(q, (const float *)lse, apart, lse + 2 * 8 * 8 * 4 - 4) == 2);
   EXPECT(with(q, (const float *)lse, apart, lse + 2 * 8 * 8 * 4) == 1);
+  // ---- which short calls are one launch: with handed-over normalisers fewer, long windows only in short sequences ---------------
+  auto one = [&](int L, int heads, int kv, int d, int w_obs, int win, int dtype, bool given) {
+    Prob R(1, L, heads, kv, d, w_obs, win, win, 1, dtype);
+    const int had = wkv_stub_launches;
+    EXPECT(wkv_compress_group(&R.pr, 2, q, given ? (const float *)lse : nullptr, kq, kq, oq, oq, iq, iq, iq, base + (64 << 20), wkv_workspace_bytes(&R.pr, 1), nullptr) == WKV_OK);
+    return wkv_stub_launches - had == 1;
+  };
+  const int rows_of[5] = {16, 32, 64, 128, 136};              // by one query head of two a KV head; tokens at most: all, with normalisers
+  const int tokens[2][2][5][2] = {{{{1024, 1024}, {1024, 1024}, {1024, 512}, {512, 0}, {0, 0}}, {{1024, 1024}, {1024, 512}, {512, 512}, {512, 0}, {0, 0}}},
+                                  {{{1024, 512}, {512, 0}, {0, 0}, {0, 0}, {0, 0}}, {{512, 0}, {0, 0}, {0, 0}, {0, 0}, {0, 0}}}};
+  for (int f32 = 0; f32 < 2; ++f32)
+    for (int wide = 0; wide < 2; ++wide)
+      for (int r = 0; r < 5; ++r)
+        for (int given = 0; given < 2; ++given)
+          for (int L : {400, 512, 513, 1024, 1025})
+            for (int dtype : {WKV_F32, WKV_BF16, WKV_F16})
+              if ((dtype == WKV_F32) == (f32 == 1))
+                EXPECT(one(L, 4, 2, wide ? 128 : 64, rows_of[r] / 2, 8, dtype, given) == (L <= tokens[f32][wide][r][given]));
+  for (int given = 0; given < 2; ++given) {
+    EXPECT(one(1000, 4, 2, 64, 8, 64, WKV_BF16, given));
+    EXPECT(one(512 + 8, 4, 2, 64, 8, 65, WKV_BF16, given) && !one(513 + 8, 4, 2, 64, 8, 65, WKV_BF16, given));
+  }
   before = wkv_stub_launches;
   EXPECT(wkv_score(&P.pr, nullptr, dev, nullptr, fdev, dev, ws1, nullptr) == WKV_ERR_INVALID_ARG);
   EXPECT(wkv_score(&P.pr, (char *)dev + 2, dev, nullptr, fdev, dev, ws1, nullptr) == WKV_ERR_INVALID_ARG);

@@ -40,6 +40,8 @@ def test_row_counts(dtype, d, L, q_heads, w_obs, device):
     dict(n_groups=2, gamma=4, n_kv_heads=2, seq_len=[290 - 30 * b for b in range(8)], win=[16, 8] * 4, top_p=[5, 8] * 4, k_windows=[4] * 8),     # 256 pairs
     dict(n_groups=1, gamma=3, n_q_heads=86, n_kv_heads=43, seq_len=[200]),                             # 258: in several launches
     dict(seq_len=[900, 700], win=[128, 1], top_p=[100, 1], k_windows=[3, 300], w_obs=16),              # the largest and the smallest windows
+    dict(seq_len=[528, 900], win=[128, 1], top_p=[100, 1], k_windows=[3, 300], w_obs=16),              # a token a thread ranked: in one launch
+    dict(seq_len=[529, 900], win=[65, 64], top_p=[40, 64], k_windows=[3, 3], w_obs=16),
 ])
 def test_calls(kw, device):
     run_and_check(_w(**kw), device)
@@ -72,9 +74,10 @@ def _budgets(w, device):
         assert not ref.v_out[l][b, h, n:].any() and bool((st.k_out[l][b, h, n:] == 7.0).all())
 
 
-@pytest.mark.parametrize("dtype,d,L", [("bf16", 128, 500), ("f16", 64, 1000), ("f32", 64, 700)])
-def test_normalisers_handed_over(dtype, d, L, device):
-    w = _w(dtype=dtype, head_dim=d, n_groups=2, seq_len=[L], win=[16], top_p=[8])
+@pytest.mark.parametrize("dtype,d,L", [("bf16", 128, 500), ("f16", 64, 1000), ("f32", 64, 700), ("f32", 64, 400)])
+@pytest.mark.parametrize("w_obs", [8, 32])
+def test_normalisers_handed_over(dtype, d, L, w_obs, device):
+    w = _w(dtype=dtype, head_dim=d, n_groups=2, w_obs=w_obs, seq_len=[L], win=[16], top_p=[8])
     st = P.DeviceState(w, device); st.compress(lse=[st.oracle_lse(g) for g in range(2)])
     _, s_given = batched_intermediates(st)
     own = P.DeviceState(w, device); own.compress()
