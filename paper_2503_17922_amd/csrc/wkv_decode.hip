@@ -314,8 +314,9 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(DecodeShape
 // divided by multiplication.  Such a layer with its merge 11.3 us with one block requested ahead of the one in hand (the compiler
 // put the request of the second behind the arrival of the first), 10.1 us so; eleven sequences of mixed lengths, 28q/4kv heads, f16, a layer
 // 16.6 and 14.8 us; 64 sequences 169 and 167.  Ranges of 64 rows, one block without a state for each of four waves, against the
-// present kernels: one sequence 8.53 -> 9.07, two 11.06 -> 11.65, the eleven 14.24 -> 14.21.  Two blocks and a state take 102 to 125 registers with 128 channels and up to four heads (four waves a SIMD), 134 to 162 with more (three), one block without a
-// state 56 to 60 (eight).  Ranges of a block a wave without a state before it, a lane's rows by one multiplication each, the caches'
+// present kernels: one sequence 8.53 -> 9.07, two 11.06 -> 11.65, the eleven 14.24 -> 14.21.  Two blocks and a state take 102 to 125 registers with
+// 128 channels and up to four heads (four waves a SIMD), 134 to 162 with more (three), one block without a state 56 to 60 (eight).
+// Ranges of a block a wave without a state before it, a lane's rows by one multiplication each, the caches'
 // addresses while the row count is under way; here and in the merge offsets of 32 bits into the partial results: one sequence of 4128 rows through 32
 // layers 309 -> 298 us, of 20000 rows 22.0 -> 20.6 a layer, three of 4128 14.4 -> 13.7, fp32 with four 21.3 -> 20.8.
 // The value of lane N of each 16-lane DPP row, in all its lanes.
